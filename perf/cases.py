@@ -132,22 +132,48 @@ def _index_list(ids, off, cap=None):
     return binding.IndexList(buf.cuda(), torch.tensor(off, dtype=torch.int32).cuda())
 
 
-def prepare(case, seed):
-    torch.cuda.set_device(0)
+def _inputs(case, seed):
+    """Everything that is drawn for a case: plain tensors on the GPU (the lists on the CPU)."""
     s, B, L, kind = SHAPES[case["shape"]], case["batch"], case["seq"], case["kind"]
     gen = torch.Generator(device="cuda").manual_seed(seed)
     gen_cpu = torch.Generator().manual_seed(seed)
-    st = dict(kind=kind, B=B, L=L, turn=0)
     if kind == "saliency":
-        lay = Layer.from_shape(s, 1, 1)  # (a context for the calls; max_batch and max_seq below)
-        cfg = binding.LayerCfg(s.hidden, s.n_heads, s.n_kv_heads, s.head_dim, s.ffn, B, L, B * L, lay.cfg.dtype, s.rms_eps, s.rope_theta)
-        lay.close()
         ids, _, _ = _candidates(case, gen_cpu)
         ids = ids.cuda()
         old = torch.randn(B * L, s.dq, device="cuda", generator=gen)
         new = old + 0.02 * torch.randn(B * L, s.dq, device="cuda", generator=gen)
         new[ids] = torch.randn(ids.numel(), s.dq, device="cuda", generator=gen)
-        st.update(ctx=binding.Context(cfg), old=old.to(torch_dtype(s.dtype)), new=new.to(torch_dtype(s.dtype)),
+        return dict(old=old.to(torch_dtype(s.dtype)), new=new.to(torch_dtype(s.dtype)))
+    d = dict(weights=[_weights(s, gen, case.get("bias", False)) for _ in range(case.get("layers", 1))])
+    x0 = _hidden(s, B, L, gen)
+    d["x"] = [x0]
+    if kind == "dense":
+        return d
+    ids, moved, off = _candidates(case, gen_cpu)
+    x1 = x0.clone()
+    at = moved.cuda()
+    x1[at] = torch.randn(at.numel(), s.hidden, device="cuda", generator=gen).to(x0.dtype)
+    d["x"].append(x1)
+    d.update(ids=ids, moved=moved, off=off)
+    if kind == "loop":
+        # one token per sequence has just been decoded (a moved one); the rest is carried
+        starts = [0]
+        for _, m in _per_seq(case)[0]:
+            starts.append(starts[-1] + m)
+        d["decoded"] = moved[torch.tensor(starts[:-1])]
+    return d
+
+
+def prepare(case, seed):
+    torch.cuda.set_device(0)
+    s, B, L, kind = SHAPES[case["shape"]], case["batch"], case["seq"], case["kind"]
+    d = _inputs(case, seed)
+    st = dict(kind=kind, B=B, L=L, turn=0)
+    if kind == "saliency":
+        lay = Layer.from_shape(s, 1, 1)  # (a context for the calls; max_batch and max_seq below)
+        cfg = binding.LayerCfg(s.hidden, s.n_heads, s.n_kv_heads, s.head_dim, s.ffn, B, L, B * L, lay.cfg.dtype, s.rms_eps, s.rope_theta)
+        lay.close()
+        st.update(ctx=binding.Context(cfg), old=d["old"], new=d["new"],
                   cos=torch.zeros(B * L, device="cuda"), flag=torch.zeros(B * L, dtype=torch.uint8, device="cuda"),
                   out=binding.IndexList.empty(B * L, B))
         return st
@@ -158,35 +184,23 @@ def prepare(case, seed):
     else:
         stack = Stack(s, n_layers, B, L, keep_lse=case.get("approx") == 2)
         layers, st["stack"] = stack.layers, stack
-    for lay in layers:
-        lay.set_device_weights(_weights(s, gen, case.get("bias", False)))
-    x0 = _hidden(s, B, L, gen)
-    st["x"] = [x0.view(B, L, -1)]
+    for lay, w in zip(layers, d["weights"]):
+        lay.set_device_weights(w)
+    st["x"] = [x.view(B, L, -1) for x in d["x"]]
     if kind == "dense":
         return st
-    ids, moved, off = _candidates(case, gen_cpu)
-    moved = moved.cuda()
-    x1 = x0.clone()
-    x1[moved] = torch.randn(moved.numel(), s.hidden, device="cuda", generator=gen).to(x0.dtype)
-    st["x"].append(x1.view(B, L, -1))
     # the dense step before: it fills the caches
     if "layer" in st:
         st["layer"].full_step(st["x"][0])
-        st["idx"] = _index_list(ids, off)
+        st["idx"] = _index_list(d["ids"], d["off"])
         st["layer"].idx_out = binding.IndexList.empty(st["idx"].cap, B)
     else:
         st["stack"].full_step(st["x"][0])
         if kind == "stack":
-            st["idx"] = _index_list(ids, off)
+            st["idx"] = _index_list(d["ids"], d["off"])
         else:
-            # one token per sequence has just been decoded (a moved one); the rest is carried
-            counts, _ = _per_seq(case)
-            dec, at = [], 0
-            for _, m in counts:
-                dec.append(int(moved[at]))
-                at += m
-            st["decoded"] = _index_list(torch.tensor(dec), list(range(B + 1)))
-            st["carry"] = _index_list(ids, off, cap=B * L)
+            st["decoded"] = _index_list(d["decoded"], list(range(B + 1)))
+            st["carry"] = _index_list(d["ids"], d["off"], cap=B * L)
             st["cand"] = binding.IndexList.empty(B * L, B)
             st["sched"] = binding.Schedule(1, 4, L - min(RESP, L // 2), case["approx"], TAU)
     return st
@@ -219,6 +233,118 @@ def run(st):
         return dict(caches=_caches(st["stack"].layers), cos=st["stack"].cos.view(-1)[:n], offsets=[o.offsets for o in outs])
     out = st["layer"].layer_step(x, st["idx"], TAU)
     return dict(caches=_caches([st["layer"]]), cos=st["layer"].cos[:st["idx"].cap], idx=out.idx, offsets=out.offsets)
+
+
+# ---- the same pass in 64 bits: plain torch, nothing rounded in between ------------------------------------
+
+def _norm64(x, g, eps):
+    return x / torch.sqrt((x * x).mean(-1, keepdim=True) + eps) * g
+
+
+def _heads64(s, x, w, b, n_heads, rows, L, rotate):
+    y = x @ w.t()
+    if b is not None:
+        y = y + b
+    y = y.view(-1, n_heads, s.head_dim)
+    if rotate:
+        half = s.head_dim // 2
+        freq = s.rope_theta ** (-2.0 * torch.arange(half, dtype=torch.float64, device="cuda") / s.head_dim)
+        a = ((rows % L).double()[:, None] * freq)[:, None, :]
+        lo, hi = y[..., :half], y[..., half:]
+        y = torch.cat([lo * a.cos() - hi * a.sin(), hi * a.cos() + lo * a.sin()], -1)
+    return y
+
+
+def _attend64(s, q, rows, k, v, L):
+    """Attention rows of the queries at tokens `rows` over k, v [B*L, Hkv, dh] of their sequences."""
+    out = torch.empty(rows.numel(), s.n_heads, s.head_dim, dtype=torch.float64, device="cuda")
+    g = s.n_heads // s.n_kv_heads
+    for b in torch.unique(rows // L).tolist():
+        at = (rows // L == b).nonzero().view(-1)
+        kb, vb = k[b * L:(b + 1) * L], v[b * L:(b + 1) * L]
+        for h in range(s.n_kv_heads):
+            p = torch.softmax(q[at, h * g:(h + 1) * g].reshape(-1, s.head_dim) @ kb[:, h].t() / math.sqrt(s.head_dim), -1)
+            out[at, h * g:(h + 1) * g] = (p @ vb[:, h]).view(-1, g, s.head_dim)
+    return out.view(rows.numel(), -1)
+
+
+def _layer64(s, w, c, x, rows, L, window=None):
+    """One layer over the tokens `rows` (updates the caches c); returns their cosines and the tokens below tau.
+    window: also update the contexts of these tokens through the changed values of `rows`."""
+    n = _norm64(x[rows], w["g_attn"], s.rms_eps)
+    q = _heads64(s, n, w["wq"], w.get("bq"), s.n_heads, rows, L, True)
+    v = _heads64(s, n, w["wv"], w.get("bv"), s.n_kv_heads, rows, L, False)
+    dv = torch.zeros_like(c["v"])
+    dv[rows] = v - c["v"][rows]
+    c["k"][rows] = _heads64(s, n, w["wk"], w.get("bk"), s.n_kv_heads, rows, L, True)
+    c["v"][rows] = v
+    exact_rows = _attend64(s, q, rows, c["k"], c["v"], L)
+    toks, new = rows, exact_rows
+    if window is not None:
+        toks = window
+        qa = _heads64(s, _norm64(x[toks], w["g_attn"], s.rms_eps), w["wq"], w.get("bq"), s.n_heads, toks, L, True)
+        full = c["c"].clone()
+        full[toks] += _attend64(s, qa, toks, c["k"], dv, L)
+        full[rows] = exact_rows
+        new = full[toks]
+    old = c["c"][toks]
+    cos = (new * old).sum(-1) / (new.norm(dim=-1).clamp_min(1e-8) * old.norm(dim=-1).clamp_min(1e-8))
+    c["c"][toks] = new
+    return cos, toks[cos < TAU]
+
+
+def _ffn64(s, w, c, x, rows):
+    h = x[rows] + c["c"][rows] @ w["wo"].t()
+    f = _norm64(h, w["g_ffn"], s.rms_eps)
+    c["out"][rows] = h + (torch.nn.functional.silu(f @ w["w_gate"].t()) * (f @ w["w_up"].t())) @ w["w_down"].t()
+
+
+def exact(case, seed):
+    if case.get("approx") == 2:
+        return None  # (the carried normalisers make this form's result depend on the steps before)
+    torch.cuda.set_device(0)
+    s, B, L, kind = SHAPES[case["shape"]], case["batch"], case["seq"], case["kind"]
+    d = _inputs(case, seed)
+    if kind == "saliency":
+        a, b = d["new"].double(), d["old"].double()
+        return dict(cos=(a * b).sum(-1) / (a.norm(dim=-1) * b.norm(dim=-1)), flag=None, idx=None, offsets=None)
+    T, n_layers = B * L, case.get("layers", 1)
+    W = [{k: v.double() for k, v in w.items()} for w in d["weights"]]
+    X = [x.double() for x in d["x"]]
+    def zeros(*sh):
+        return torch.zeros(T, *sh, dtype=torch.float64, device="cuda")
+    C = [dict(k=zeros(s.n_kv_heads, s.head_dim), v=zeros(s.n_kv_heads, s.head_dim), c=zeros(s.dq), out=zeros(s.hidden)) for _ in W]
+    every = torch.arange(T, device="cuda")
+    x = X[0]
+    for w, c in zip(W, C):
+        _layer64(s, w, c, x, every, L)
+        _ffn64(s, w, c, x, every)
+        x = c["out"]
+    cos = None
+    def step(x, rows, window=None):
+        for w, c in zip(W, C):
+            cs, rows = _layer64(s, w, c, x, rows, L, window)
+            _ffn64(s, w, c, x, rows)
+            x = c["out"]
+        return cs, rows
+    if kind == "loop":
+        carry, dec, lo = d["ids"].cuda(), d["decoded"].cuda(), L - min(RESP, L // 2)
+        for t in range(4, 8):
+            win = every if t % 4 == 0 else every[every % L >= lo]
+            rows = torch.unique(torch.cat([carry, dec]))
+            rows = rows if t % 4 == 0 else rows[rows % L >= lo]
+            _, carry = step(X[(t + 1) % 2], rows, win if case["approx"] else None)
+    elif kind != "dense":
+        cos, _ = step(X[1], d["ids"].cuda())
+    caches = [dict(k=c["k"].view(B, L, s.n_kv_heads, -1), v=c["v"].view(B, L, s.n_kv_heads, -1), c=c["c"].view(B, L, -1),
+                   out=c["out"].view(B, L, -1)) for c in C]
+    if kind == "dense":
+        return caches
+    if kind == "loop":
+        return dict(caches=caches, carry=None, cand=None)
+    if kind == "stack":
+        return dict(caches=caches, cos=None, offsets=[None] * n_layers)
+    return dict(caches=caches, cos=cos, idx=None, offsets=None)
 
 
 # ---- what a pass cannot do without ----------------------------------------------------------------------
