@@ -30,6 +30,8 @@
 // MFMA.  v_mfma_f32_32x32x16_bf16: lane l supplies 8 consecutive k of row (l%32) for A and of
 // column (l%32) for B at k offset 8*(l/32); the accumulator block holds
 //   row = 8*(r/4) + 4*(l/32) + (r%4),  col = l%32   in register r of lane l.
+// The 256-row tiles of the ring loop use v_mfma_f32_16x16x32_bf16 with the operands exchanged, so that
+// a lane's results are eight neighbouring columns of one row (gemm_bf16_ring.h).
 //
 // Tile walk.  The row count lives on the device; the grid is sized from the list capacity and each
 // workgroup walks the existing tiles in a grouped order, remapped so that neighbouring tiles run on
@@ -338,6 +340,62 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
     using RingFull = Ring<NMAT, NB, BN, 4>;
     constexpr int NWC = RingFull::NWC;
     static_assert(Epi::INTERLEAVE == 0 && SH::A_LD == 8 && NMAT * SH::B_LD == NWC, "ring shapes");
+    // Epilogue of one tile: this lane has rows j0 + 16 i (i < 8) and columns c0 + 32 g .. + 7 (g < NB), in
+    // acc[t][i][2 g] and [2 g + 1].
+    auto ring_epilogue = [&](floatx4 (&acc)[NMAT][8][2 * NB], int j0, int c0) {
+      if constexpr (SPLIT) {
+        float *pz = split.part + (size_t)z * split.split_stride + c0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int j = j0 + 16 * i;
+          if (j < M) {
+            float *r = pz + (size_t)j * split.N;
+#pragma unroll
+            for (int c = 0; c < 2 * NB; ++c) *reinterpret_cast<floatx4 *>(r + (c / 2) * 32 + (c % 2) * 4) = acc[0][i][c];
+          }
+        }
+      } else if constexpr (Epi::PRELOAD) {
+        // what row block i + 1 reads is requested before block i is written: a wave's memory operations
+        // complete in order, so a load behind stores would wait for all of them
+        int rowv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int j = j0 + 16 * i;
+          rowv[i] = (rows.idx && j < M) ? rows.idx[j] : j;
+        }
+        floatx4 pre[2][2 * NB];
+        auto load = [&](int i) {
+          const int j = j0 + 16 * i;
+          if (j < M) {
+#pragma unroll
+            for (int c = 0; c < 2 * NB; ++c) pre[i & 1][c] = epi.load4(j, c0 + (c / 2) * 32 + (c % 2) * 4);
+          }
+        };
+        load(0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          if (i + 1 < 8) load(i + 1);
+          if (j0 + 16 * i < M) {
+#pragma unroll
+            for (int g = 0; g < NB; ++g)
+              epi.store8(rowv[i], c0 + 32 * g, acc[0][i][2 * g], acc[0][i][2 * g + 1], pre[i & 1][2 * g], pre[i & 1][2 * g + 1]);
+          }
+          __builtin_amdgcn_sched_barrier(0);  // (a row block at a time: more of them at once spill)
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          int j = j0 + 16 * i;
+          asm volatile("" : "+v"(j));  // (addresses of all row blocks at once spill)
+          if (j < M) {
+#pragma unroll
+            for (int g = 0; g < NB; ++g)
+              epi.store8(j, c0 + 32 * g, acc[0][i][2 * g], acc[0][i][2 * g + 1], acc[NMAT - 1][i][2 * g], acc[NMAT - 1][i][2 * g + 1]);
+          }
+          __builtin_amdgcn_sched_barrier(0);  // (a row block at a time: more of them at once spill)
+        }
+      }
+    };
     auto ring_sources = [&](int tm, int tn, RingSrc &src) {
       const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
       // Lane offsets are 32 bits.  Without a gather list the descriptor starts at the tile's first
@@ -368,7 +426,8 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
         // a copy's rows lie in one matrix: segment ends are multiples of 8
         const bool in1 = nu >= seg.n_end[0], in2 = nu >= seg.n_end[1];
         const void *base = t == 1 ? (const void *)W2 : in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0];
-        const int nl = nu + r8 - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0);
+        // row in its matrix: the rows of a group of 32 (matrices start at multiples of 32) are permuted
+        const int nl = nu - (nrow0 & 31) + ring_wperm((nrow0 & 31) + r8) - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0);
         src.srd_w[c] = make_srd(base, 0xfffffff0u);
         src.vw[c] = (uint32_t)((((size_t)(nl / WPANEL) * (ldw / BK) + kbeg / BK) * (WPANEL * BK) + (nl % WPANEL) * BK + csrc * 8) * 2);
       }
@@ -380,20 +439,22 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
     ring_sources(tm, tn, src);
     RingFull::fill(src, lds0, wave);
     bool all_landed = false;
-    const unsigned char *rd_a = smem_raw + (wm0 + l32) * ROWB, *rd_w = smem_raw + (wn0 + l32) * ROWB;
+    const int l16 = lane % 16, lq = lane / 16;
+    const unsigned char *rd_a = smem_raw + (wm0 + l16) * ROWB, *rd_w = smem_raw + (wn0 + l16) * ROWB;
+    int rd_off16[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) rd_off16[kk] = (((4 * kk + lq) ^ ((l16 >> 1) & 7)) * 16);
     for (;;) {
       const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
-      floatx16 acc[NMAT][MB][NB];
+      floatx4 acc[NMAT][8][2 * NB];
 #pragma unroll
       for (int t = 0; t < NMAT; ++t)
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-          for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[t][i][j][e] = 0.f;
+          for (int j = 0; j < 2 * NB; ++j) acc[t][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
       auto run_ring = [&](auto mbv_c) {
-        Ring<NMAT, NB, BN, decltype(mbv_c)::value>::tile(acc, lds0, wave, src, rd_a, rd_w, rd_off, KT, all_landed);
+        Ring<NMAT, NB, BN, decltype(mbv_c)::value>::tile(acc, lds0, wave, src, rd_a, rd_w, rd_off16, KT, all_landed);
       };
       // 32-row blocks of this wave that hold rows (wave-uniform)
       const int mbv = (M - (m0 + wm0) + 31) / 32;
@@ -408,7 +469,7 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
         ring_sources(tmn, tnn, src);
         RingFull::fill(src, lds0, wave);
       }
-      epilogue(acc, m0, n0, tn);
+      ring_epilogue(acc, m0 + wm0 + l16, n0 + wn0 + 8 * lq);
       if (!more) break;
       p = pn; tm = tmn; tn = tnn;
       all_landed = true;

@@ -55,30 +55,47 @@ struct RingSrc {
   uint32_t va[8], vw[8];
 };
 
-// The loop for one wave tile of 128 rows x (32 NMAT NB) columns: NMAT x NB column blocks of 32, block
-// c = t * NB + j reads weight-tile rows (t * BN + wn0 + 32 j ...).  Four column blocks (a 256-row
+// Matrix instruction and operand order.  v_mfma_f32_16x16x32_bf16 with the WEIGHTS as its first operand:
+// lane l holds activation row l % 16 of a block and, in its four registers, the columns 4 * (l / 16) ..
+// + 3 -- a row's results come in vectors, not one column per lane.  Two neighbouring 16-column blocks
+// share a group of 32 columns whose weight rows are permuted on their way into LDS (ring_wperm), so
+// that the lane's two blocks hold columns 8 * (l / 16) .. + 7 of the group: a 16-byte store of bf16, or
+// two of fp32.  The 16x16 form also does the same products with less power than the 32x32 one, and
+// the matrix clock is power-bound: operands in registers, all CUs busy, random values: 1.85 against
+// 1.75 PFLOP/s.  Together with the vector epilogues, against 32x32x16 instructions whose results were
+// stored a column per lane: dense layer of 20480 rows 7565 -> 7248 us, of 1024 rows 484 -> 465 us, sparse
+// step of about 2000 rows 913 -> 880 us.
+//
+// The loop for one wave tile of 128 rows x (32 NMAT NB) columns: NMAT x NB column groups of 32, group
+// g = t * NB + j reads weight-tile rows (t * BN + wn0 + 32 j ...).  Four column groups (a 256-row
 // weight tile, 256 x 256 or 256 x (128+128) outputs) or two (128 weight rows: 256 x 128 or
 // 256 x (64+64)); the weight half of a slice then fills half of its slot.
 // MBV = 32-row blocks of this wave that hold rows (4 in a full tile).  In a row tile with fewer than
 // 256 rows a wave multiplies only those, down to none: copies, waits and barriers are the same for
 // every wave, so such a tile costs about what its copies cost (leaving out the A copies of the empty
 // row groups as well was measured: no faster).
+
+// weight row (inside its panel of 32) that row x of a group of 32 LDS rows holds
+__device__ __forceinline__ int ring_wperm(int x) { return ((x >> 2) & 3) * 8 + (x >> 4) * 4 + (x & 3); }
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+
 template <int NMAT, int NB, int BN, int MBV> struct Ring {
-  static constexpr int NCB = NMAT * NB;  // column blocks per wave
+  static constexpr int NCB = NMAT * NB;  // column groups per wave
   static constexpr int NWC = 2 * NCB;    // weight copies per wave and slice
-  static constexpr int PS = 4 * NCB;     // products per K step
-  static constexpr int QH = 2 * PS;      // product slots per half slice
-  static constexpr int RD = 4 + NCB;     // operand reads per K step
-  static constexpr int RPS = (3 * RD + QH - 1) / QH;  // reads per product slot in the first half
-  static_assert(NCB == 4 || NCB == 2, "four or two column blocks per wave");
+  static constexpr int NC = 2 * NCB;     // 16-column blocks per wave
+  static constexpr int PS = 8 * NC;      // products per K step of 32 = per half slice
+  static constexpr int RD = 8 + NC;      // operand reads per K step
+  static constexpr int RSP = PS / 2 >= 2 * RD ? 2 : 1;  // products between two operand reads
+  static_assert(NCB == 4 || NCB == 2, "four or two column groups per wave");
   static constexpr int ROW = 128, A_STEP = 128, W_STEP = 4096;  // bytes per tile row; K walk per slice
 
-  static __device__ __forceinline__ int w_row(int c) { return ((c / NB) * BN + (c % NB) * 32) * ROW; }
+  static __device__ __forceinline__ int w_row(int c) { return (((c / 2) / NB) * BN + ((c / 2) % NB) * 32 + (c % 2) * 16) * ROW; }
   static __device__ __forceinline__ int nxt(int s, int d) { const int t = s + d; return t >= RING_SLOTS ? t - RING_SLOTS : t; }
-  // read x of a K step: A block x (x < 4) or column block x - 4; product p of a K step: row block
-  // p / NCB, column block p % NCB
-  static __device__ constexpr bool has_read(int x) { return x < 4 ? x < MBV : MBV > 0; }
-  static __device__ constexpr bool has_prod(int p) { return p / NCB < MBV; }
+  // read x of a K step: activation block x (x < 8) or column block x - 8; product p of a K step: row
+  // block p / NC, column block p % NC
+  static __device__ constexpr bool has_read(int x) { return x < 8 ? x < 2 * MBV : MBV > 0; }
+  static __device__ constexpr bool has_prod(int p) { return p / NC < 2 * MBV; }
 
   // Fills the ring for a tile: A(0) W(0) A(1) W(1) A(2) into slots 0..4.  The slots must be free
   // (every wave past the middle barrier of the previous tile's last slice).
@@ -103,10 +120,9 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
   //                   the first slice alone; wave-uniform
   //   rd_a / rd_w     this lane's operand-read addresses inside a slot (slot 0), without the chunk swizzle
   //   rd_off[s]       swizzled chunk offset of K step s
-  template <typename Acc>
-  static __device__ __forceinline__ void tile(Acc &acc, uint32_t lds0, int wave, const RingSrc &src,
+  static __device__ __forceinline__ void tile(floatx4 (&acc)[NMAT][8][2 * NB], uint32_t lds0, int wave, const RingSrc &src,
                                               const unsigned char *rd_a, const unsigned char *rd_w,
-                                              const int (&rd_off)[4], int KT, bool all_landed) {
+                                              const int (&rd_off)[2], int KT, bool all_landed) {
     const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
     auto copy_a = [&](int i, int kt, int slot) {
       dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + (uint32_t)slot * RING_SLOT + i * 4096u);
@@ -119,20 +135,27 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    bf16x8 af[4][4], bfr[4][NCB];  // [K step][32-row block], [K step][column block]
+    bf16x8 af[2][8], bfr[2][NC];  // [K step][16-row block], [K step][16-column block]
     auto read = [&](int st, int x, const unsigned char *sa, const unsigned char *sb) {
-      if (x < 4) af[st][x] = *reinterpret_cast<const bf16x8 *>(sa + x * 32 * ROW + rd_off[st]);
-      else bfr[st][x - 4] = *reinterpret_cast<const bf16x8 *>(sb + w_row(x - 4) + rd_off[st]);
+      if (x < 8) af[st][x] = *reinterpret_cast<const bf16x8 *>(sa + x * 16 * ROW + rd_off[st]);
+      else bfr[st][x - 8] = *reinterpret_cast<const bf16x8 *>(sb + w_row(x - 8) + rd_off[st]);
     };
     auto prod = [&](int st, int p) {
-      const int i = p / NCB, c = p % NCB;
-      acc[c / NB][i][c % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[st][i], bfr[st][c], acc[c / NB][i][c % NB], 0, 0, 0);
+      const int i = p / NC, c = p % NC;
+      auto &a = acc[c / (2 * NB)][i][c % (2 * NB)];
+      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[st][c], af[st][i], a, 0, 0, 0);
     };
+    // read r of the other K step goes behind product RSP * r
+    auto read_due = [](int q) { return q % RSP == 0 && q / RSP < RD; };
+    // slot of A(kt); W(kt) is in the next one.  (Hidden from the optimiser: with a known start the first
+    // slice's operand addresses lie past the reach of an LDS offset, are computed once per kernel, and are
+    // then reloaded from scratch memory in every tile, each reload waiting for all copies in flight.)
+    int slot_a = 0;
+    asm volatile("" : "+s"(slot_a));
 #pragma unroll
     for (int x = 0; x < RD; ++x)
-      if (has_read(x)) read(0, x, rd_a, rd_w + RING_SLOT);
+      if (has_read(x)) read(0, x, rd_a + (uint32_t)slot_a * RING_SLOT, rd_w + (uint32_t)(slot_a + 1) * RING_SLOT);
 
-    int slot_a = 0;  // slot of A(kt); W(kt) is in the next one
     auto slice = [&](int kt, auto first_c, auto m1_c, auto m2_c) {
       // FIRST: slice 0 (A(2) is already on its way); M1 / M2: slices kt+1 / kt+2 exist.  The last
       // slice keeps its barrier: past it every wave has read the tile's last operands out of the
@@ -141,25 +164,21 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       constexpr bool CA = !FIRST && M2;
       const int slot_w = nxt(slot_a, 1), slot_a1 = nxt(slot_a, 2), slot_w1 = nxt(slot_a, 3), slot_a2 = nxt(slot_a, 4);
       const unsigned char *sa = rd_a + (uint32_t)slot_a * RING_SLOT, *sb = rd_w + (uint32_t)slot_w * RING_SLOT;
-      // First half: products of K steps 0 and 1; the operand reads of steps 1..3 behind the first
-      // products (RPS per product); the 8 copies of A(kt+2) into the slot W(kt-1) left, evenly.
-      // In the instruction order (sched_group_barrier: product, reads, copy) the scheduler left alone
-      // would fetch each operand right before its use and bunch the copies.
-      auto copy_a_due = [](int q) { return (q + 1) % (QH / 8) == 0; };
+      // First half: products of K step 0; the operand reads of step 1 between the first of them; the 8
+      // copies of A(kt+2) into the slot W(kt-1) left, evenly.  In the instruction order
+      // (sched_group_barrier: product, read, copy) the scheduler left alone would fetch each operand
+      // right before its use and bunch the copies.
+      auto copy_a_due = [](int q) { return (q + 1) % (PS / 8) == 0; };
 #pragma unroll
-      for (int q = 0; q < QH; ++q) {
-#pragma unroll
-        for (int r = q * RPS; r < (q + 1) * RPS && r < 3 * RD; ++r)
-          if (has_read(r % RD)) read(1 + r / RD, r % RD, sa, sb);
-        if (CA && copy_a_due(q)) copy_a((q + 1) / (QH / 8) - 1, kt + 2, slot_a2);
-        if (has_prod(q % PS)) prod(q / PS, q % PS);
+      for (int q = 0; q < PS; ++q) {
+        if (read_due(q) && has_read(q / RSP)) read(1, q / RSP, sa, sb);
+        if (CA && copy_a_due(q)) copy_a((q + 1) / (PS / 8) - 1, kt + 2, slot_a2);
+        if (has_prod(q)) prod(0, q);
       }
 #pragma unroll
-      for (int q = 0; q < QH; ++q) {
-        if (has_prod(q % PS)) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-#pragma unroll
-        for (int r = q * RPS; r < (q + 1) * RPS && r < 3 * RD; ++r)
-          if (has_read(r % RD)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      for (int q = 0; q < PS; ++q) {
+        if (has_prod(q)) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (read_due(q) && has_read(q / RSP)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         if (CA && copy_a_due(q)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
       }
       // Middle: slice kt+1 has landed (the copies of A(kt+2) behind it may still be in flight), and
@@ -171,20 +190,20 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       wait_lgkmcnt0();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      // Second half: products of K steps 2 and 3, the copies of W(kt+2) into the slot A(kt) left, the
-      // operands of step 0 of slice kt+1 (behind the products of step 3).
+      // Second half: products of K step 1, the copies of W(kt+2) into the slot A(kt) left, the
+      // operands of step 0 of slice kt+1.
       const unsigned char *sa1 = rd_a + (uint32_t)slot_a1 * RING_SLOT, *sb1 = rd_w + (uint32_t)slot_w1 * RING_SLOT;
-      auto copy_w_due = [](int q) { return (q + 1) % (QH / NWC) == 0; };
+      auto copy_w_due = [](int q) { return (q + 1) % (PS / NWC) == 0; };
 #pragma unroll
-      for (int q = 0; q < QH; ++q) {
-        if (M1 && q >= PS && q - PS < RD && has_read(q - PS)) read(0, q - PS, sa1, sb1);
-        if (M2 && copy_w_due(q)) copy_w((q + 1) / (QH / NWC) - 1, kt + 2, slot_a);
-        if (has_prod(q % PS)) prod(2 + q / PS, q % PS);
+      for (int q = 0; q < PS; ++q) {
+        if (M1 && read_due(q) && has_read(q / RSP)) read(0, q / RSP, sa1, sb1);
+        if (M2 && copy_w_due(q)) copy_w((q + 1) / (PS / NWC) - 1, kt + 2, slot_a);
+        if (has_prod(q)) prod(1, q);
       }
 #pragma unroll
-      for (int q = 0; q < QH; ++q) {
-        if (has_prod(q % PS)) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (M1 && q >= PS && q - PS < RD && has_read(q - PS)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      for (int q = 0; q < PS; ++q) {
+        if (has_prod(q)) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (M1 && read_due(q) && has_read(q / RSP)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         if (M2 && copy_w_due(q)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
       }
       slot_a = slot_a1;
