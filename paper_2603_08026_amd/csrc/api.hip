@@ -39,6 +39,7 @@ struct dyllm_ctx {
   void *fs;        // [R, d]        RMSNorm(h)
   void *act;       // [R, F]        silu(gate)*up
   int32_t *status; // device status word
+  int32_t *plan;   // four words of the last GEMM's plan, for the row kernel behind it
   int32_t *scan;   // words of the chained compaction kernel; all zero between calls
   float *rope;     // [max_seq, dh/2, 2]
   // optional per-stage timing (dyllm_profile_begin / _end)
@@ -200,9 +201,9 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
   seg.w[0] = w->wq; seg.w[1] = w->wk; seg.w[2] = w->wv;
   seg.n_end[0] = ctx->dq; seg.n_end[1] = ctx->dq + ctx->dkv; seg.n_end[2] = ctx->dq + 2 * ctx->dkv;
   const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
-                                     ctx->part_o, ctx->part_elems, s);
+                                     ctx->part_o, ctx->part_elems, ctx->plan, s);
   prof_mark(ctx, ST_GEMM_QKV, s);
-  launch_qkv_finalize(dt(ctx), ctx->part_o, splits, (size_t)rows.cap * seg.n_end[2], ctx->rope, rows, L,
+  launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rows, L,
                       c.n_heads, c.n_kv_heads, c.head_dim, w->bq, w->bk, w->bv, q_out, cache->k,
                       cache->v, nullptr, 0, nullptr, 0, nullptr, 0, s);
   prof_mark(ctx, ST_ROPE_SCATTER, s);
@@ -239,16 +240,16 @@ int enqueue_ffn(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, con
                 Rows rows, void *out_cache, size_t n_tokens, hipStream_t s) {
   const dyllm_layer_cfg &c = ctx->cfg;
   const Splits splits = launch_gemm_raw(dt(ctx), GemmA{c_all, rows.idx, ctx->dq, n_tokens}, rows, ctx->dq,
-                                     wseg_one(w->wo, c.hidden), ctx->part_o, ctx->part_elems, s);
+                                     wseg_one(w->wo, c.hidden), ctx->part_o, ctx->part_elems, ctx->plan, s);
   prof_mark(ctx, ST_GEMM_OPROJ, s);
-  launch_oproj_finalize(dt(ctx), ctx->part_o, splits, (size_t)rows.cap * c.hidden, x, w->g_ffn, rows,
+  launch_oproj_finalize(dt(ctx), ctx->part_o, splits, x, w->g_ffn, rows,
                         c.hidden, c.rms_eps, ctx->hs, ctx->fs, s);
   prof_mark(ctx, ST_NORM_FFN, s);
   launch_gemm_swiglu(dt(ctx), GemmA{ctx->fs, nullptr, c.hidden}, rows, c.hidden, c.ffn_dim, w->w_gate,
-                     w->w_up, ctx->act, ctx->part_o, ctx->part_elems, s);
+                     w->w_up, ctx->act, s);
   prof_mark(ctx, ST_GEMM_SWIGLU, s);
   launch_gemm_down(dt(ctx), GemmA{ctx->act, nullptr, c.ffn_dim}, rows, c.ffn_dim, c.hidden, w->w_down,
-                   ctx->hs, out_cache, ctx->part_o, ctx->part_elems, s);
+                   ctx->hs, out_cache, ctx->part_o, ctx->part_elems, ctx->plan, s);
   prof_mark(ctx, ST_GEMM_DOWN, s);
   return check_launch(ctx, "salient ffn");
 }
@@ -354,8 +355,8 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   launch_gather_rmsnorm(dt(ctx), x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, s);
   {
     const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, all, c.hidden,
-                                       wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, s);
-    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, (size_t)all.cap * ctx->dq, ctx->rope, all, L, c.n_heads,
+                                       wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s);
+    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, all, L, c.n_heads,
                         0, c.head_dim, w->bq, nullptr, nullptr, ctx->qs, nullptr, nullptr, nullptr, by_token,
                         nullptr, 0, nullptr, 0, s);
   }
@@ -366,10 +367,10 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     seg.w[0] = w->wk; seg.w[1] = w->wv; seg.w[2] = w->wv;
     seg.n_end[0] = ctx->dkv; seg.n_end[1] = 2 * ctx->dkv; seg.n_end[2] = 2 * ctx->dkv;
     const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->fs, nullptr, c.hidden}, rin, c.hidden, seg,
-                                       ctx->part_o, ctx->part_elems, s);
+                                       ctx->part_o, ctx->part_elems, ctx->plan, s);
     // value residual: by token into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
     // entry next to a compact copy of the new keys (reused normalisers: only candidates are scored)
-    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, (size_t)rin.cap * 2 * ctx->dkv, ctx->rope, rin, L, 0,
+    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rin, L, 0,
                         c.n_kv_heads, c.head_dim, nullptr, w->bk, w->bv, nullptr, cache->k, cache->v,
                         cached_norm ? ctx->dc : ctx->dv_full, 0, cached_norm ? ctx->ksal : nullptr,
                         cached_norm, ctx->pos, win.lo, s);  // also marks the step's candidates in the token -> entry map
@@ -508,7 +509,7 @@ int dyllm_create(const dyllm_layer_cfg *cfg, dyllm_ctx **out) {
   ctx->part_elems = l.part_elems;
   ctx->cosb = (float *)(b + l.cosb); ctx->flag = (uint8_t *)(b + l.flag);
   ctx->hs = (float *)(b + l.hs); ctx->fs = b + l.fs; ctx->act = b + l.act;
-  ctx->status = (int32_t *)(b + l.status); ctx->rope = (float *)(b + l.rope);
+  ctx->status = (int32_t *)(b + l.status); ctx->plan = ctx->status + 8; ctx->rope = (float *)(b + l.rope);
   ctx->dv_full = b + l.dv_full; ctx->dc = b + l.dc; ctx->csal = b + l.csal; ctx->pos = (int32_t *)(b + l.pos);
   ctx->win_idx = (int32_t *)(b + l.win_idx); ctx->win_off = (int32_t *)(b + l.win_off);
   ctx->ksal = b + l.ksal; ctx->scan = (int32_t *)(b + l.scan);

@@ -35,9 +35,9 @@
 //
 // Tile walk.  The row count lives on the device; the grid is sized from the list capacity and each
 // workgroup walks the existing tiles in a grouped order, remapped so that neighbouring tiles run on
-// one XCD (workgroup i is dispatched to XCD i % 8) and share A / weight tiles in its L2.  A launch
-// covers a window of list rows [row_lo, row_hi), so that a launcher can give a short last row tile
-// to another tile shape in a launch of its own.
+// one XCD (workgroup i is dispatched to XCD i % 8) and share A / weight tiles in its L2.  gemm_tiles
+// covers a window of list rows [row_lo, row_hi), so that a short last row tile can go to another tile
+// shape.
 //
 // Epilogues.  A wave's loads and stores complete in order, and a wave of the 256-row shapes is alone
 // on its SIMD: a load issued behind stores (a residual, a register reloaded from scratch memory)
@@ -47,6 +47,7 @@
 #pragma once
 #include <type_traits>
 #include "gemm_epilogues.h"
+#include "gemm_plan.h"
 #include "kernels.h"
 
 namespace dy {
@@ -100,22 +101,40 @@ struct SplitStore {  // part != nullptr: raw fp32 tile part[z][j][n] instead of 
   int N;
 };
 
-// SPLIT: the tile goes to the raw fp32 result part[z][j][n] (split.part) instead of through the
+// Operands of one GEMM, as the kernels take them.
+struct GemmArgs {
+  const bf16_t *A;
+  const int32_t *gather;
+  int lda;
+  Rows rows;
+  int N;
+  WSeg seg;
+  const bf16_t *W2;
+  int K;
+  float *part;  // raw result part[z][j][n], split stride = existing rows * N
+};
+
+// The tiles of list rows [row_lo, min(count, row_hi)) (row_lo is a multiple of BM) with `splitk` K splits,
+// those with numbers first, first + step, ... .  Splits are cut in whole K slices and may differ by one.
+// SPLIT: the tile goes to the raw fp32 result part[z][j][n] instead of through the
 // fused epilogue.  A compile-time switch: with both forms behind a run-time branch the compiler
 // moves the accumulators out of the accumulation registers ahead of the branch, where they do not
 // fit, and the epilogue's stores each wait for a reload from scratch memory.
 template <typename SH, typename Epi, bool SPLIT>
-__global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__ A,
-                                                   const int32_t *__restrict__ gather, int lda,
-                                                   Rows rows, int N, WSeg seg,
-                                                   const bf16_t *__restrict__ W2, int ldw, int kchunk,
-                                                   int group_m, Epi epi, SplitStore split,
-                                                   int row_lo, int row_hi) {
-  extern __shared__ __align__(1024) unsigned char smem_raw[];
+__device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, int row_lo, int row_hi, int splitk,
+                                           int first, int step, unsigned char *smem_raw) {
   constexpr int BM = SH::BM, BN = SH::BN, MB = SH::MB, NB = SH::NB, NMAT = SH::NMAT, NS = SH::NS, NW = SH::NW;
+  constexpr int group_m = 4;
+  const bf16_t *const A = ga.A;
+  const int32_t *const gather = ga.gather;
+  const bf16_t *const W2 = ga.W2;
+  const int lda = ga.lda, N = ga.N, ldw = ga.K;
+  const Rows rows = ga.rows;
+  const WSeg &seg = ga.seg;
 
-  // rows [row_lo, min(count, row_hi)) of the list are this launch's; row_lo is a multiple of BM
-  const int M = min(rows.count ? min(*rows.count, rows.cap) : rows.cap, row_hi);
+  const int M_all = rows.count ? min(*rows.count, rows.cap) : rows.cap;
+  const int M = min(M_all, row_hi);
+  const SplitStore split{ga.part, (size_t)M_all * N, N};
   const int tm_lo = row_lo / BM;
   const int m_rel = max(M - tm_lo * BM, 0);
   const int tiles_m = (m_rel + BM - 1) / BM, tiles_n = N / BN;
@@ -123,9 +142,7 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
   const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave-uniform, kept scalar
   const int wm0 = (wave / SH::WAVES_N) * SH::WM, wn0 = (wave % SH::WAVES_N) * SH::WN;
   const int l32 = lane % 32, lhi = lane / 32;
-  const int z = blockIdx.y;  // K split
-  const int kbeg = z * kchunk;
-  const int KT = kchunk / BK;
+  const int KS = ldw / BK;  // K slices
   const uint32_t lds0 = lds_offset_of(smem_raw);
 
   // copy mapping of this lane inside an 8-row block: tile row r8, chunk position p, source chunk c
@@ -142,36 +159,51 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
   // so that the tiles it runs at one time share operands in its L2) and, after those, its share of
   // the tiles of a last row tile that holds fewer than BM rows: those cost a fraction of a full tile
   // (see the partial loop below) and fill the end of every XCD's schedule instead of one XCD's.
+  // With K splits the list of full tiles is the order above once per split, and so is that of the partial
+  // ones: an XCD's run then mostly holds tiles of one split, which read the same part of K.
   const int has_tail = (m_rel % BM != 0) ? 1 : 0;
   const int rows_full = tiles_m - has_tail;
   const int n_full = rows_full * tiles_n, n_part = has_tail * tiles_n;
-  const int fx = (n_full + N_XCD - 1) / N_XCD, px = (n_part + N_XCD - 1) / N_XCD;
-  const int total_pad = (fx + px) * N_XCD;
+  const int fx = (n_full * splitk + N_XCD - 1) / N_XCD, px = (n_part * splitk + N_XCD - 1) / N_XCD;
+  const int total_all = (fx + px) * N_XCD;
 
-  // tile (tm, tn) of position p in that order; false for the padding positions (uniform for the
-  // workgroup)
-  auto tile_at = [&](int p, int &tm, int &tn) -> bool {
+  // Divisions are products with a reciprocal: for whole x below 2^21, (x + 1/2) / d lies at least 1 / (2 d)
+  // from the next whole number, more than the product's rounding (an integer division is a chain of some
+  // thirty instructions, eight of them in a row at the start of every tile).
+  auto quot = [](int x, float inv) -> int { return __builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * inv)); };
+  const int gsz = group_m * tiles_n;
+  const float inv_full = __builtin_amdgcn_rcpf((float)n_full), inv_part = __builtin_amdgcn_rcpf((float)n_part),
+              inv_gsz = __builtin_amdgcn_rcpf((float)gsz);
+  // K slices of a split: the first k_rem splits have one more than the others
+  const int k_base = splitk > 1 ? quot(KS, __builtin_amdgcn_rcpf((float)splitk)) : KS, k_rem = KS - k_base * splitk;
+  auto k_first = [&](int z) -> int { return z * k_base + min(z, k_rem); };
+
+  // tile (tm, tn) and K split z of position p in that order; false for the padding positions (uniform
+  // for the workgroup)
+  auto tile_at = [&](int p, int &tm, int &tn, int &z) -> bool {
     const int xcd = p % N_XCD, q = p / N_XCD;
     if (q < fx) {
-      const int logical = xcd * fx + q;
-      if (logical >= n_full) return false;
-      const int gsz = group_m * tiles_n;
-      const int g = logical / gsz, r = logical % gsz;
+      int logical = xcd * fx + q;
+      if (logical >= n_full * splitk) return false;
+      z = splitk > 1 ? quot(logical, inv_full) : 0;
+      logical -= z * n_full;
+      const int g = quot(logical, inv_gsz), r = logical - g * gsz;
       const int gm = min(group_m, rows_full - g * group_m);
-      tm = g * group_m + r % gm;
-      tn = r / gm;
+      tn = quot(r, __builtin_amdgcn_rcpf((float)gm));
+      tm = g * group_m + r - tn * gm;
     } else {
       const int lp = xcd * px + (q - fx);
-      if (lp >= n_part) return false;
+      if (lp >= n_part * splitk) return false;
+      z = splitk > 1 ? quot(lp, inv_part) : 0;
       tm = tiles_m - 1;
-      tn = lp;
+      tn = lp - z * n_part;
     }
     return true;
   };
 
   // Epilogue of one tile: the accumulators of this wave go through the fused epilogue (or, for a K
   // split, into the raw partial result).
-  auto epilogue = [&](floatx16 (&acc)[NMAT][MB][NB], int m0, int n0, int tn) {
+  auto epilogue = [&](floatx16 (&acc)[NMAT][MB][NB], int m0, int n0, int tn, int z) {
     if constexpr (Epi::INTERLEAVE == 48) {
       // 32 x 96 wave tile = columns [0,48) of matrix 0 (gate) and [48,96) of matrix 1 (up): gate
       // column c pairs with tile column c + 48, which lane (c%32) ^ 16 holds one or two blocks on
@@ -342,7 +374,7 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
     static_assert(Epi::INTERLEAVE == 0 && SH::A_LD == 8 && NMAT * SH::B_LD == NWC, "ring shapes");
     // Epilogue of one tile: this lane has rows j0 + 16 i (i < 8) and columns c0 + 32 g .. + 7 (g < NB), in
     // acc[t][i][2 g] and [2 g + 1].
-    auto ring_epilogue = [&](floatx4 (&acc)[NMAT][8][2 * NB], int j0, int c0) {
+    auto ring_epilogue = [&](floatx4 (&acc)[NMAT][8][2 * NB], int j0, int c0, int z) {
       if constexpr (SPLIT) {
         float *pz = split.part + (size_t)z * split.split_stride + c0;
 #pragma unroll
@@ -396,7 +428,8 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
         }
       }
     };
-    auto ring_sources = [&](int tm, int tn, RingSrc &src) {
+    auto ring_sources = [&](int tm, int tn, int z, RingSrc &src) {
+      const int kbeg = k_first(z) * BK;
       const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
       // Lane offsets are 32 bits.  Without a gather list the descriptor starts at the tile's first
       // row, so the offsets stay below 256 rows; with one they are taken from the start of the
@@ -426,17 +459,17 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
         // a copy's rows lie in one matrix: segment ends are multiples of 8
         const bool in1 = nu >= seg.n_end[0], in2 = nu >= seg.n_end[1];
         const void *base = t == 1 ? (const void *)W2 : in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0];
-        // row in its matrix: the rows of a group of 32 (matrices start at multiples of 32) are permuted
-        const int nl = nu - (nrow0 & 31) + ring_wperm((nrow0 & 31) + r8) - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0);
-        src.srd_w[c] = make_srd(base, 0xfffffff0u);
-        src.vw[c] = (uint32_t)((((size_t)(nl / WPANEL) * (ldw / BK) + kbeg / BK) * (WPANEL * BK) + (nl % WPANEL) * BK + csrc * 8) * 2);
+        const int np = (nu - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0)) / WPANEL;  // panel in its matrix
+        src.srd_w[c] = make_srd((const bf16_t *)base + ((size_t)np * KS + kbeg / BK) * (WPANEL * BK), 0xfffffff0u);
       }
+      // (the rows of a panel are permuted; the copies of a wave all start at the same row of their panels)
+      src.vw = (uint32_t)((ring_wperm((wave & 3) * 8 + r8) * BK + csrc * 8) * 2);
     };
-    int tm = 0, tn = 0, p = blockIdx.x;
-    while (p < total_pad && !tile_at(p, tm, tn)) p += gridDim.x;
-    if (p >= total_pad) return;
+    int tm = 0, tn = 0, z = 0, p = first;
+    while (p < total_all && !tile_at(p, tm, tn, z)) p += step;
+    if (p >= total_all) return;
     RingSrc src;
-    ring_sources(tm, tn, src);
+    ring_sources(tm, tn, z, src);
     RingFull::fill(src, lds0, wave);
     bool all_landed = false;
     const int l16 = lane % 16, lq = lane / 16;
@@ -446,6 +479,7 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
     for (int kk = 0; kk < 2; ++kk) rd_off16[kk] = (((4 * kk + lq) ^ ((l16 >> 1) & 7)) * 16);
     for (;;) {
       const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
+      const int KT = k_base + (z < k_rem ? 1 : 0);
       floatx4 acc[NMAT][8][2 * NB];
 #pragma unroll
       for (int t = 0; t < NMAT; ++t)
@@ -462,25 +496,26 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
       else if (mbv == 2) run_ring(std::integral_constant<int, 2>{});
       else if (mbv == 1) run_ring(std::integral_constant<int, 1>{});
       else run_ring(std::integral_constant<int, 0>{});
-      int pn = p + gridDim.x, tmn = 0, tnn = 0;
-      while (pn < total_pad && !tile_at(pn, tmn, tnn)) pn += gridDim.x;
-      const bool more = pn < total_pad;
+      int pn = p + step, tmn = 0, tnn = 0, zn = 0;
+      while (pn < total_all && !tile_at(pn, tmn, tnn, zn)) pn += step;
+      const bool more = pn < total_all;
       if (more) {
-        ring_sources(tmn, tnn, src);
+        ring_sources(tmn, tnn, zn, src);
         RingFull::fill(src, lds0, wave);
       }
-      ring_epilogue(acc, m0 + wm0 + l16, n0 + wn0 + 8 * lq);
+      ring_epilogue(acc, m0 + wm0 + l16, n0 + wn0 + 8 * lq, z);
       if (!more) break;
-      p = pn; tm = tmn; tn = tnn;
+      p = pn; tm = tmn; tn = tnn; z = zn;
       all_landed = true;
     }
     return;
   }
 
-  for (int p = blockIdx.x; p < total_pad; p += gridDim.x) {
-    int tm, tn;
-    if (!tile_at(p, tm, tn)) continue;
+  for (int p = first; p < total_all; p += step) {
+    int tm, tn, z;
+    if (!tile_at(p, tm, tn, z)) continue;
     const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
+    const int kbeg = k_first(z) * BK, KT = k_base + (z < k_rem ? 1 : 0);
 
     // per-lane global sources of the copies it issues every slice
     const bf16_t *ap[SH::A_LD];
@@ -736,7 +771,58 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(const bf16_t *__restrict__
     }
     }
 
-    epilogue(acc, m0, n0, tn);
+    epilogue(acc, m0, n0, tn, z);
+  }
+}
+
+// One tile shape, chosen by the launcher.
+template <typename SH, typename Epi, bool SPLIT>
+__global__ __launch_bounds__(SH::NT) void k_gemm_bf16(GemmArgs ga, Epi epi, int splitk) {
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
+  gemm_tiles<SH, Epi, SPLIT>(ga, epi, 0, 0x7fffffff, splitk, blockIdx.x, gridDim.x, smem_raw);
+}
+
+// The 256-row tiles (and the weight-streaming tiles of a short last row tile, or of a list with few
+// rows), by the plan that fits the rows that exist (gemm_plan.h).  One workgroup per CU.
+//   Kind::Epi      fused epilogue of the 256-row tiles; Kind::FUSED / RAW: which of its forms exist
+//   Kind::X, L     tile shapes; Kind::stream(...) runs the weight-streaming tiles
+// planned: the plan was made on the host (the count is known there).  plan_out (optional): the splits,
+// for the row kernels (Splits::dev).
+template <typename Kind>
+__global__ __launch_bounds__(256) void k_gemm_planned(GemmArgs ga, typename Kind::Epi epi, PlanArgs pa, GemmPlan pl,
+                                                      int planned, int32_t *plan_out) {
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
+  const int M = ga.rows.count ? min(*ga.rows.count, ga.rows.cap) : ga.rows.cap;
+  if (!planned) pl = plan_on_device(pa, M);
+  if (plan_out && blockIdx.x == 0 && threadIdx.x == 0) {
+    plan_out[0] = pl.sk;
+    plan_out[1] = pl.row_hi;
+    plan_out[2] = pl.sk_tail;
+    plan_out[3] = (Kind::FUSED && pl.sk == 1) ? pl.row_hi : 0;  // rows whose results are in place
+  }
+  const int first = blockIdx.x, step = gridDim.x;
+  if (pl.row_hi > 0) {
+    if (Kind::RAW && (!Kind::FUSED || pl.sk > 1)) {
+      if constexpr (Kind::RAW) {
+        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, true>(ga, epi, 0, pl.row_hi, pl.sk, first, step, smem_raw);
+        else gemm_tiles<typename Kind::L, typename Kind::Epi, true>(ga, epi, 0, pl.row_hi, pl.sk, first, step, smem_raw);
+      }
+    } else {
+      if constexpr (Kind::FUSED) {
+        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, false>(ga, epi, 0, pl.row_hi, 1, first, step, smem_raw);
+        else gemm_tiles<typename Kind::L, typename Kind::Epi, false>(ga, epi, 0, pl.row_hi, 1, first, step, smem_raw);
+      }
+    }
+  }
+  if (pl.row_hi < M) Kind::stream(ga, epi, pl.row_hi, pl.sk_tail, first, step, smem_raw);
+}
+
+template <typename Kind> void set_lds_once_planned() {
+  static bool done = false;
+  if (!done) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_planned<Kind>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, RING_SLOTS * (int)RING_SLOT);
+    done = true;
   }
 }
 

@@ -48,11 +48,12 @@ constexpr int RING_MIN_SLICES = 3;
 
 // Sources of a wave's copies for one tile:
 //   srd_a / va[i]   descriptor and lane offsets of its 8 A copies (8 tile rows each)
-//   srd_w[c] / vw[c] the same for its weight copies (8 for a 256-row weight tile, 4 for a 128-row one;
-//                   a copy's 8 rows lie in one weight matrix)
+//   srd_w[c] / vw   the same for its weight copies (8 for a 256-row weight tile, 4 for a 128-row one): a
+//                   copy's 8 rows lie in one weight panel, where its descriptor starts, so that one lane
+//                   offset serves them all
 struct RingSrc {
   __amdgpu_buffer_rsrc_t srd_a, srd_w[8];
-  uint32_t va[8], vw[8];
+  uint32_t va[8], vw;
 };
 
 // Matrix instruction and operand order.  v_mfma_f32_16x16x32_bf16 with the WEIGHTS as its first operand:
@@ -109,7 +110,7 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
         for (int i = 0; i < 8; ++i) dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + h * RING_SLOT + i * 4096u);
       } else {
 #pragma unroll
-        for (int c = 0; c < NWC; ++c) dma16_buf(src.srd_w[c], src.vw[c], (uint32_t)kt * W_STEP, lds_w + h * RING_SLOT + c * 4096u);
+        for (int c = 0; c < NWC; ++c) dma16_buf(src.srd_w[c], src.vw, (uint32_t)kt * W_STEP, lds_w + h * RING_SLOT + c * 4096u);
       }
     }
   }
@@ -128,7 +129,7 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + (uint32_t)slot * RING_SLOT + i * 4096u);
     };
     auto copy_w = [&](int c, int kt, int slot) {
-      dma16_buf(src.srd_w[c], src.vw[c], (uint32_t)kt * W_STEP, lds_w + (uint32_t)slot * RING_SLOT + c * 4096u);
+      dma16_buf(src.srd_w[c], src.vw, (uint32_t)kt * W_STEP, lds_w + (uint32_t)slot * RING_SLOT + c * 4096u);
     };
     if (all_landed) wait_vmcnt<0>();
     else wait_vmcnt<16 + NWC>();  // slice 0 has landed (this wave's part); the rest of the fill is behind it

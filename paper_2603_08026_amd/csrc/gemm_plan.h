@@ -1,0 +1,124 @@
+// Launch plans of the bf16 GEMMs with 256-row tiles, made from the number of rows that EXIST.
+//
+// The row count of a list lives on the device, and a list's capacity says little about it: a generation
+// loop carries lists of B*L entries of which a few percent are used.  A plan made from the capacity then
+// takes the shapes of a dense step for a few hundred rows (one request batch of 8 x 1024 tokens, 330
+// salient rows: 32 tiles of the down projection on 256 CUs, 201 us against 55 us with a K split; two layers and four
+// steps of that loop 4080 -> 2424 us).
+// So the kernel makes its own plan once it has read the count: every candidate is priced by one lane of
+// a wave, the cheapest wins, and the row kernels that follow read the chosen split back from four words
+// of device memory.  Where the host knows the count (dense steps) it evaluates the same function and
+// passes the plan in.
+#pragma once
+#include <type_traits>
+#include "common.h"
+
+namespace dy {
+namespace mm {
+
+// A plan: rows [0, row_hi) of the list in 256-row tiles (xl: 256 columns wide, else 128) with sk K splits;
+// the rows from row_hi on in 128-row weight-streaming tiles with sk_tail K splits.
+struct GemmPlan { int xl, sk, row_hi, sk_tail; };
+
+// What plans are made from.  N output columns, K; and for the kind of GEMM:
+//   tiles_l / tiles_x  column tiles of the 256 x 128 / 256 x 256 shape; tiles_x = 0: it does not divide N
+//   w_cols             weight rows per output column (2 for gate|up)
+//   stream_cols        columns of the weight-streaming tiles; 0: not to be used
+//   split_ok           K splits (and a streamed tail that is split) may be used: a row kernel sums them
+//   split_free         a raw result is written and read back whatever the split (q|k|v, out-projection);
+//                      otherwise a split or a streamed tail costs a sum kernel
+//   part_elems         fp32 elements of the buffer of raw results
+//   cus, inv_cus       CUs of an XCD
+struct PlanArgs {
+  int N, K, tiles_l, tiles_x, w_cols, stream_cols, split_ok, split_free;
+  long part_elems;
+  float cus, inv_cus;
+};
+
+constexpr int PLAN_BK = 64, PLAN_XCD = 8;
+constexpr int STREAM_ROWS = 128;     // rows that one weight-streaming tile holds
+constexpr int PLAN_MIN_SLICES = 8;   // K slices every split keeps (the ring loop needs 3)
+constexpr int PLAN_MAX_SPLIT = 16;
+constexpr int PLAN_CANDIDATES = 4 * PLAN_MAX_SPLIT;  // {128, 256 columns} x {last row tile padded, streamed} x splits
+
+// K splits of the weight-streaming tiles: about one workgroup per CU
+__host__ __device__ inline int stream_split(const PlanArgs &a, int M) {
+  const int tiles = a.N / a.stream_cols;
+  int s = 1;
+  while (tiles * s < 192 && s < 8 && (a.K / PLAN_BK) / (s * 2) >= 4) s *= 2;
+  while (s > 1 && (long)s * M * a.N > a.part_elems) s /= 2;
+  return a.split_ok ? s : 1;
+}
+
+// Price of candidate c in microseconds, or a huge value if it cannot be taken.  The constants are
+// fitted to the measured times of every candidate at 18 row counts from 140 to 3000 for seven GEMMs of
+// two layer shapes (126 points, weights cold): the candidate with the least price is on average 0.2 %,
+// at worst 5 %, slower than the fastest one.  What they say:
+//   - a CU takes 51 us for the K loop of a 256 x 128 tile over K = 4096 and 1.31 times that for a
+//     256 x 256 one, and 6.9 or 13.8 us per tile for what surrounds the loop;
+//   - an XCD's CUs take its positions of the tile order in turn (gemm_tiles): full tiles first, then the
+//     tiles of a last row tile with fewer than 256 rows, which cost a fraction of a full one (they
+//     still walk all of K with their copies) and first fill the slots the full tiles leave;
+//   - weights arrive at 4 TB/s whatever the tiles do, at 5.3 TB/s in the streaming tiles;
+//   - every K split moves its fp32 sums once more, written and read.
+__host__ __device__ inline float plan_price(const PlanArgs &a, int M, int c) {
+  const int sk = c % PLAN_MAX_SPLIT + 1, xl = (c / PLAN_MAX_SPLIT) & 1, streamed = c / (2 * PLAN_MAX_SPLIT);
+  const int tail = M % 256;
+  bool ok = xl ? a.tiles_x != 0 : true;
+  if (sk > 1) ok = ok && a.split_ok && a.K / PLAN_BK >= PLAN_MIN_SLICES * sk && (long)sk * M * a.N <= a.part_elems;
+  if (streamed) ok = ok && a.stream_cols && tail > 0 && tail <= STREAM_ROWS && M >= 256;
+  const int tiles = (xl ? a.tiles_x : a.tiles_l) * sk;
+  const int full = (M / 256 * tiles + PLAN_XCD - 1) / PLAN_XCD, part = (tail && !streamed) ? (tiles + PLAN_XCD - 1) / PLAN_XCD : 0;
+  // (counts are whole numbers far below 2^20: the products with the reciprocal round to the right side)
+  const float rounds = ceilf((float)full * a.inv_cus - 1e-4f), slack = rounds * a.cus - (float)full;
+  const float more = fmaxf(ceilf(((float)part - slack) * a.inv_cus - 1e-4f), 0.f);  // rounds of partial tiles alone
+  const float f = fminf(fmaxf(0.31f + 0.125f * (float)((tail + 31) / 32), 0.385f), 1.0f);
+  const float per_split = 1.0f / (float)sk;
+  const float loop = 51.3f / 4096.0f * (float)a.K * (xl ? 1.31f : 1.0f) * per_split;
+  const float w_bytes = (float)a.N * (float)a.w_cols * (float)a.K * 2.0f;
+  float t = fmaxf((rounds + f * more) * loop + (rounds + more) * (xl ? 13.8f : 6.9f), w_bytes * (1.0f / 4.04e6f));
+  const float sums = 1.29e-6f * (float)M * (float)a.N;
+  if (a.split_free) t += sums * (float)(sk - 1);
+  else if (a.split_ok && (sk > 1 || streamed)) t += sums * (float)sk + 4.0f;
+  if (streamed) t += 2.3f + w_bytes * (1.0f / 5.26e6f);
+  return ok ? t : 3e30f;
+}
+
+__host__ __device__ inline GemmPlan plan_of(const PlanArgs &a, int M, int c) {
+  const int streamed = c / (2 * PLAN_MAX_SPLIT);
+  return GemmPlan{(c / PLAN_MAX_SPLIT) & 1, c % PLAN_MAX_SPLIT + 1, streamed ? M - M % 256 : M, streamed ? stream_split(a, M) : 1};
+}
+
+inline GemmPlan plan_on_host(const PlanArgs &a, int M) {
+  if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M)};
+  int best = 0;
+  float best_t = 1e30f;
+  for (int c = 0; c < PLAN_CANDIDATES; ++c) {
+    const float t = plan_price(a, M, c);
+    if (t < best_t) { best_t = t; best = c; }
+  }
+  return plan_of(a, M, best);
+}
+
+// one wave (all 64 lanes active); the result is uniform
+__device__ __forceinline__ GemmPlan plan_on_device(const PlanArgs &a, int M) {
+  static_assert(PLAN_CANDIDATES == WAVE, "a candidate per lane");
+  if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M)};
+  // least price with its candidate in the low six bits (prices are positive: they order like their bits)
+  const int lane = threadIdx.x % WAVE;
+  uint32_t k = (__float_as_uint(plan_price(a, M, lane)) & ~63u) | (uint32_t)lane;
+  auto dpp = [](uint32_t v, auto ctrl) -> uint32_t {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, decltype(ctrl)::value, 0xf, 0xf, false);
+  };
+  k = min(k, dpp(k, std::integral_constant<int, 0xb1>{}));   // quad_perm 1,0,3,2
+  k = min(k, dpp(k, std::integral_constant<int, 0x4e>{}));   // quad_perm 2,3,0,1
+  k = min(k, dpp(k, std::integral_constant<int, 0x141>{}));  // row_half_mirror
+  k = min(k, dpp(k, std::integral_constant<int, 0x140>{}));  // row_mirror: every lane has its row's least
+  const uint32_t r0 = __builtin_amdgcn_readlane(k, 0), r1 = __builtin_amdgcn_readlane(k, 16),
+                 r2 = __builtin_amdgcn_readlane(k, 32), r3 = __builtin_amdgcn_readlane(k, 48);
+  const int who = (int)(min(min(r0, r1), min(r2, r3)) & 63u);
+  return plan_of(a, M, who);
+}
+
+}  // namespace mm
+}  // namespace dy

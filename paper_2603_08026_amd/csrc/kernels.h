@@ -16,10 +16,18 @@ struct Rows {
 };
 
 // K splits of a raw GEMM result: the rows below tail_from hold n partial sums each, the rows from
-// tail_from on (a short last row tile that a launch of its own computed) n_tail.
+// tail_from on (a short last row tile in tiles of another shape) n_tail.  The split stride is the number of
+// rows that exist times the row length.  dev: the plan was made on the device, which left
+// {n, tail_from, n_tail, done_to} there; the members are then ignored.
 struct Splits {
   int n = 1, tail_from = 0x7fffffff, n_tail = 1;
   int done_to = 0;  // down projection: rows below it need no sum kernel (the GEMM's own epilogue wrote them)
+  const int32_t *dev = nullptr;
+  __device__ Splits resolved() const {
+    Splits r = *this;
+    if (dev) { r.n = dev[0]; r.tail_from = dev[1]; r.n_tail = dev[2]; r.done_to = dev[3]; }
+    return r;
+  }
   __host__ __device__ int of(int j) const { return j < tail_from ? n : n_tail; }
 };
 
@@ -38,18 +46,18 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
 // dv_out (optional, [T, Hkv*dh] T-typed): value residual new - cached of the rows, taken before the merge
 // entry_of (optional, [T] int32): entry_of[row_j] = j + 1, the map from a token to its list entry, written
 // for the rows at positions >= entry_lo of their sequence only
-void launch_qkv_finalize(DType t, const float *part, Splits splits, size_t split_stride,
+void launch_qkv_finalize(DType t, const float *part, Splits splits,
                          const float *rope_tab, Rows rows, int L, int H, int Hkv, int dh,
                          const void *bq, const void *bk, const void *bv, void *q_out, void *k_cache,
                          void *v_cache, void *dv_out, int q_by_token, void *ksal_out, int dv_by_entry,
                          int32_t *entry_of, int entry_lo, hipStream_t s);
 // out-projection: h[j] = x[row_j] + sum of splits (fp32 [cap,d]); f[j] = RMSNorm(h[j]) * gain (T-typed)
-void launch_oproj_finalize(DType t, const float *part, Splits splits, size_t split_stride, const void *x,
+void launch_oproj_finalize(DType t, const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
                            hipStream_t s);
 // down projection after a K split: out_cache[row_j] = h[j] + sum of splits, for the rows from
 // splits.done_to on (the rows below it were written by the GEMM's own epilogue)
-void launch_down_finalize(DType t, const float *part, Splits splits, size_t split_stride, const float *h,
+void launch_down_finalize(DType t, const float *part, Splits splits, const float *h,
                           Rows rows, int d, void *out_cache, hipStream_t s);
 // cosine of c_new[j] vs c_cache[row_j], flag = cos < tau, optional commit of the new row.
 void launch_saliency(DType t, const void *c_new, void *c_cache, Rows rows, int D, float tau,
@@ -134,20 +142,18 @@ inline WSeg wseg_one(const void *w, int N) {
   s.n_end[0] = s.n_end[1] = s.n_end[2] = N;
   return s;
 }
-// raw GEMM: part[z][j][n] = sum over K split z of A[j,:] * W[n,:] (fp32, split stride cap*N);
-// returns the numbers of splits used (>= 1), chosen from the capacity, N and K.
+// raw GEMM: part[z][j][n] = sum over K split z of A[j,:] * W[n,:] (fp32, split stride rows*N);
+// returns the numbers of splits used (>= 1), chosen from the rows that exist, N and K (on the device, in
+// the four words `plan`, when their number is known there alone).
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
-                    hipStream_t s);
+                       int32_t *plan, hipStream_t s);
 // up: act[j,:] = silu(A w_gate^T) * (A w_up^T), T-typed out [cap, N]
-// `scratch` holds the raw gate|up result in the weight-streaming regime (then a row kernel applies
-// the SwiGLU); otherwise the epilogue is fused.
 void launch_gemm_swiglu(DType t, GemmA A, Rows rows, int K, int N, const void *w_gate,
-                        const void *w_up, void *act, float *scratch, size_t scratch_elems,
-                        hipStream_t s);
+                        const void *w_up, void *act, hipStream_t s);
 // down: out_cache[row_j,:] = h[j,:] + A[j,:] * w_down^T, T-typed scatter into [T, N]; `scratch`
-// holds K-split partials when the launcher decides to split.
+// holds K-split partials when K is split; plan: as for launch_gemm_raw.
 void launch_gemm_down(DType t, GemmA A, Rows rows, int K, int N, const void *w_down, const float *h,
-                      void *out_cache, float *scratch, size_t scratch_elems, hipStream_t s);
+                      void *out_cache, float *scratch, size_t scratch_elems, int32_t *plan, hipStream_t s);
 
 // row-major [n_out, n_in] (2-byte elements; n_out % 32 == 0, n_in % 64 == 0) -> weight panels of the bf16 GEMMs
 void launch_pack_weight(const void *src, int n_out, int n_in, void *dst, hipStream_t s);

@@ -60,15 +60,17 @@ __global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
 // h[j] = x[row_j] + sum_z part[z][j] (kept in fp32 for the second residual), f[j] = RMSNorm(h[j]) * gain
 template <typename T>
 __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__ part, Splits splits_of,
-                                                        size_t split_stride, const T *__restrict__ x,
+                                                        const T *__restrict__ x,
                                                         const T *__restrict__ gain, Rows rows, int d,
                                                         float eps, float *__restrict__ h,
                                                         T *__restrict__ f) {
   __shared__ float red[RB / WAVE];
   const int n = row_count(rows), nv = d / 4;
+  const Splits sp = splits_of.resolved();
+  const size_t split_stride = (size_t)n * d;
   for (int j = blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
-    const int splits = splits_of.of(j);
+    const int splits = sp.of(j);
     const T *xr = x + (size_t)r * d;
     float *hr = h + (size_t)j * d;
     float ss = 0.f;
@@ -110,13 +112,14 @@ __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__
 // ---- down-projection tail after a K split  [Alg. 3: FFN second half + cache commit] ---------------
 template <typename T>
 __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ part, Splits splits_of,
-                                                       size_t split_stride, const float *__restrict__ h,
+                                                       const float *__restrict__ h,
                                                        Rows rows, int d, T *__restrict__ out) {
   const int n = row_count(rows), nv = d / 4;
-  for (int j = splits_of.done_to + blockIdx.x; j < n; j += gridDim.x) {
+  const Splits sp = splits_of.resolved();
+  const size_t split_stride = (size_t)n * d;
+  for (int j = sp.done_to + blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
-    const int splits = splits_of.of(j);
-    if (splits == 0) continue;  // the row's result is in place already (its GEMM had no K split)
+    const int splits = sp.of(j);
     T *orow = out + (size_t)r * d;
     for (int v = threadIdx.x; v < nv; v += RB) {
       float4 a = *reinterpret_cast<const float4 *>(h + (size_t)j * d + v * 4);
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ 
 // pairs of one head (two float4 of the raw result, two float4 of the table).
 template <typename T>
 __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ part, Splits splits_of,
-                                                      size_t split_stride, const float *__restrict__ tab,
+                                                      const float *__restrict__ tab,
                                                       Rows rows, int L, int H, int Hkv, int dh,
                                                       const T *__restrict__ bq, const T *__restrict__ bk,
                                                       const T *__restrict__ bv, T *__restrict__ q_out,
@@ -148,9 +151,11 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
   const int half = dh / 2, dq = H * dh, dkv = Hkv * dh, ld = dq + 2 * dkv;
   const int per_head = half / 4;  // items of 4 pairs per head
   const int qk_items = (H + Hkv) * per_head, v_items = dkv / 4;
+  const Splits sp = splits_of.resolved();
+  const size_t split_stride = (size_t)n * ld;
   for (int j = blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
-    const int splits = splits_of.of(j);
+    const int splits = sp.of(j);
     const int pos = r % L;
     // token -> its list entry (0 = not in the list), for the tokens at positions >= entry_lo only
     if (entry_of && threadIdx.x == 0 && pos >= entry_lo) entry_of[r] = j + 1;
@@ -376,30 +381,31 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
   }
 }
 
-void launch_oproj_finalize(DType t, const float *part, Splits splits, size_t split_stride, const void *x,
+void launch_oproj_finalize(DType t, const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
                            hipStream_t s) {
   if (rows.cap <= 0) return;
   if (t == F32)
-    k_oproj_finalize<float><<<row_grid(rows.cap), RB, 0, s>>>(part, splits, split_stride, (const float *)x,
+    k_oproj_finalize<float><<<row_grid(rows.cap), RB, 0, s>>>(part, splits, (const float *)x,
                                                               (const float *)gain, rows, d, eps, h, (float *)f);
   else
-    k_oproj_finalize<bf16_t><<<row_grid(rows.cap), RB, 0, s>>>(part, splits, split_stride, (const bf16_t *)x,
+    k_oproj_finalize<bf16_t><<<row_grid(rows.cap), RB, 0, s>>>(part, splits, (const bf16_t *)x,
                                                                (const bf16_t *)gain, rows, d, eps, h,
                                                                (bf16_t *)f);
 }
 
-void launch_down_finalize(DType t, const float *part, Splits splits, size_t split_stride, const float *h,
+void launch_down_finalize(DType t, const float *part, Splits splits, const float *h,
                           Rows rows, int d, void *out_cache, hipStream_t s) {
-  if (rows.cap <= 0 || splits.done_to >= rows.cap) return;
-  const int g = row_grid(rows.cap - splits.done_to);
+  const int done = splits.dev ? 0 : splits.done_to;
+  if (rows.cap <= 0 || done >= rows.cap) return;
+  const int g = row_grid(rows.cap - done);
   if (t == F32)
-    k_down_finalize<float><<<g, RB, 0, s>>>(part, splits, split_stride, h, rows, d, (float *)out_cache);
+    k_down_finalize<float><<<g, RB, 0, s>>>(part, splits, h, rows, d, (float *)out_cache);
   else
-    k_down_finalize<bf16_t><<<g, RB, 0, s>>>(part, splits, split_stride, h, rows, d, (bf16_t *)out_cache);
+    k_down_finalize<bf16_t><<<g, RB, 0, s>>>(part, splits, h, rows, d, (bf16_t *)out_cache);
 }
 
-void launch_qkv_finalize(DType t, const float *part, Splits splits, size_t split_stride,
+void launch_qkv_finalize(DType t, const float *part, Splits splits,
                          const float *rope_tab, Rows rows, int L, int H, int Hkv, int dh,
                          const void *bq, const void *bk, const void *bv, void *q_out, void *k_cache,
                          void *v_cache, void *dv_out, int q_by_token, void *ksal_out, int dv_by_entry,
@@ -407,12 +413,12 @@ void launch_qkv_finalize(DType t, const float *part, Splits splits, size_t split
   if (rows.cap <= 0) return;
   if (t == F32)
     k_qkv_finalize<float><<<row_grid(rows.cap), RB, 0, s>>>(
-        part, splits, split_stride, rope_tab, rows, L, H, Hkv, dh, (const float *)bq, (const float *)bk,
+        part, splits, rope_tab, rows, L, H, Hkv, dh, (const float *)bq, (const float *)bk,
         (const float *)bv, (float *)q_out, (float *)k_cache, (float *)v_cache, (float *)dv_out, q_by_token,
         (float *)ksal_out, dv_by_entry, entry_of, entry_lo);
   else
     k_qkv_finalize<bf16_t><<<row_grid(rows.cap), RB, 0, s>>>(
-        part, splits, split_stride, rope_tab, rows, L, H, Hkv, dh, (const bf16_t *)bq, (const bf16_t *)bk,
+        part, splits, rope_tab, rows, L, H, Hkv, dh, (const bf16_t *)bq, (const bf16_t *)bk,
         (const bf16_t *)bv, (bf16_t *)q_out, (bf16_t *)k_cache, (bf16_t *)v_cache, (bf16_t *)dv_out, q_by_token,
         (bf16_t *)ksal_out, dv_by_entry, entry_of, entry_lo);
 }
