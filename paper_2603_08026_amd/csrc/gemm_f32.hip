@@ -1,8 +1,7 @@
 // Salient-row GEMMs for the fp32 storage type: C[j,n] = sum_k A[row_j,k] * W[n,k] with fused
-// epilogues.  64x64 output tile per workgroup, K staged through LDS in slices of 16, 4x4 outputs
-// per thread, plain fp32 FMAs (the fp32 path is the accuracy reference of the library; the bf16
-// path has MFMA kernels of its own).  The row count lives on the device: the grid is sized for the
-// list's capacity and each workgroup loops over the tiles that exist.
+// epilogues, on the fp32 matrix instructions (fp32 products and sums; the fp32 path is the accuracy
+// reference of the library).  The row count lives on the device: the grid is sized for the list's
+// capacity and each workgroup loops over the tiles that exist.
 #include "gemm_epilogues.h"
 #include "kernels.h"
 
@@ -10,114 +9,145 @@ namespace dy {
 
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 16;
+constexpr int KSTEP = 64;  // K elements of a wave's step
 
-template <typename T, typename Epi>
-__global__ __launch_bounds__(256) void k_gemm_f32(const T *__restrict__ A, const int32_t *gather,
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+
+// Tile of 16 MT rows x 16 NT columns per workgroup; its four waves take K steps of 64 in turn (wave w the
+// steps w, w + 4, ...) and their sums are added through LDS in the order of the waves.  A lane loads four
+// neighbouring k of row l % 16 of a block (k = 4 (l / 16) .. + 3 of every 16) straight into registers, 16
+// bytes at a time and all of a step at once, and the four are the k of four v_mfma_f32_16x16x4_f32: the
+// order in which k is summed does not matter as long as both operands agree.  Weights are the first
+// operand, so that a lane's four results are neighbouring columns of one row (row l % 16, columns
+// 4 (l / 16) .. + 3).  fp32 products and sums throughout.
+template <typename Epi, int MT, int NT>
+__global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, const int32_t *gather,
                                                    int lda, Rows rows, int K, int N, WSeg seg,
-                                                   const T *__restrict__ W2, Epi epi) {
-  __shared__ float As[TK][TM + 4];
-  __shared__ float Bs[TK][TN + 4];
-  __shared__ float B2s[Epi::DUAL ? TK : 1][TN + 4];
+                                                   const float *__restrict__ W2, Epi epi) {
+  constexpr int TM = 16 * MT, TN = 16 * NT, NMAT = Epi::DUAL ? 2 : 1;
+  __shared__ floatx4 part[3][NMAT * MT * NT][64];
 
   const int M = rows.count ? min(*rows.count, rows.cap) : rows.cap;
   const int tiles_n = N / TN, tiles_m = (M + TM - 1) / TM;
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int lr = tid / 4, lk = (tid % 4) * 4;  // load mapping: row lr of the tile, k offset lk..lk+3
+  const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+  const int l16 = lane % 16, lq = lane / 16;
 
   for (int tile = blockIdx.x; tile < tiles_m * tiles_n; tile += gridDim.x) {
     const int tm = tile / tiles_n, tn = tile % tiles_n;
     const int m0 = tm * TM, n0 = tn * TN;
-    // A row of this thread's load slot
-    const int jm = m0 + lr;
-    const T *arow = nullptr;
-    if (jm < M) arow = A + (size_t)(gather ? gather[jm] : jm) * lda;
-    // weight row of this thread's load slot, looked up in the stacked weight matrices
-    const int nw = n0 + lr;
-    const bool in1 = nw >= seg.n_end[0], in2 = nw >= seg.n_end[1];
-    const int seg_start = in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0;
-    const T *wrow = (const T *)(in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0]) + (size_t)(nw - seg_start) * K;
-    const T *w2row = Epi::DUAL ? W2 + (size_t)(n0 + lr) * K : nullptr;
-
-    float acc[4][4], acc2[4][4];
+    const float *ap[MT], *wp[NMAT][NT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = acc2[i][j] = 0.f;
-
-    for (int k0 = 0; k0 < K; k0 += TK) {
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        As[lk + i][lr] = arow ? to_f<T>(arow[k0 + lk + i]) : 0.f;
-        Bs[lk + i][lr] = to_f<T>(wrow[k0 + lk + i]);
-        if (Epi::DUAL) B2s[lk + i][lr] = to_f<T>(w2row[k0 + lk + i]);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int kk = 0; kk < TK; ++kk) {
-        float a[4], b[4], b2[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-        if (Epi::DUAL) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) b2[j] = B2s[kk][tx * 4 + j];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            acc[i][j] += a[i] * b[j];
-            if (Epi::DUAL) acc2[i][j] += a[i] * b2[j];
-          }
-      }
+    for (int i = 0; i < MT; ++i) {
+      const int j = min(m0 + 16 * i + l16, M - 1);  // rows past the end are clamped; their results are never stored
+      ap[i] = A + (size_t)(gather ? gather[j] : j) * lda + 4 * lq;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int j = m0 + ty * 4 + i;
-      if (j < M) {
-        const int row = rows.idx ? rows.idx[j] : j;
+    for (int c = 0; c < NT; ++c) {
+      const int n = n0 + 16 * c + l16;  // looked up in the stacked weight matrices
+      const bool in1 = n >= seg.n_end[0], in2 = n >= seg.n_end[1];
+      const int start = in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0;
+      wp[0][c] = (const float *)(in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0]) + (size_t)(n - start) * K + 4 * lq;
+      if (NMAT == 2) wp[NMAT - 1][c] = W2 + (size_t)n * K + 4 * lq;
+    }
+    floatx4 acc[NMAT][MT][NT];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) epi(j, row, n0 + tx * 4 + jj, acc[i][jj], acc2[i][jj]);
+    for (int t = 0; t < NMAT; ++t)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int c = 0; c < NT; ++c) acc[t][i][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    for (int k0 = wave * KSTEP; k0 < K; k0 += 4 * KSTEP) {  // K is a multiple of KSTEP
+      floatx4 a[KSTEP / 16][MT], w[KSTEP / 16][NMAT][NT];
+#pragma unroll
+      for (int s = 0; s < KSTEP / 16; ++s) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) a[s][i] = *reinterpret_cast<const floatx4 *>(ap[i] + k0 + 16 * s);
+#pragma unroll
+        for (int t = 0; t < NMAT; ++t)
+#pragma unroll
+          for (int c = 0; c < NT; ++c) w[s][t][c] = *reinterpret_cast<const floatx4 *>(wp[t][c] + k0 + 16 * s);
+      }
+#pragma unroll
+      for (int s = 0; s < KSTEP / 16; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < NMAT; ++t)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+              for (int c = 0; c < NT; ++c)
+                acc[t][i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][t][c][e], a[s][i][e], acc[t][i][c], 0, 0, 0);
+    }
+
+    __syncthreads();  // the sums of the previous tile have been read
+    if (wave > 0) {
+#pragma unroll
+      for (int t = 0; t < NMAT; ++t)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int c = 0; c < NT; ++c) part[wave - 1][(t * MT + i) * NT + c][lane] = acc[t][i][c];
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const int j = m0 + 16 * i + l16;
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+          floatx4 v[NMAT];
+#pragma unroll
+          for (int t = 0; t < NMAT; ++t) {
+            v[t] = acc[t][i][c];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) v[t] += part[q][(t * MT + i) * NT + c][lane];
+          }
+          if (j < M) {
+            const int row = rows.idx ? rows.idx[j] : j;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) epi(j, row, n0 + 16 * c + 4 * lq + e, v[0][e], v[NMAT - 1][e]);
+          }
+        }
       }
     }
   }
 }
 
-inline int gemm_grid(int cap, int N) {
-  long t = (long)((cap + TM - 1) / TM) * (N / TN);
-  if (t < 1) t = 1;
-  return (int)(t > 4096 ? 4096 : t);
+template <typename Epi, int MT, int NT>
+void launch(GemmA A, Rows rows, int K, int N, WSeg seg, const void *w2, Epi epi, hipStream_t s) {
+  const long t = (long)((rows.cap + 16 * MT - 1) / (16 * MT)) * (N / (16 * NT));
+  k_gemm_f32<Epi, MT, NT><<<(int)(t > 4096 ? 4096 : t), 256, 0, s>>>((const float *)A.a, A.gather, A.lda, rows, K, N, seg,
+                                                                     (const float *)w2, epi);
 }
 
-template <typename T, typename Epi>
+// 16 x 16 tiles while those of a full list number at most two per CU: a few rows are bound by the latency
+// of one round of loads, and small tiles put the whole of a short K in flight at once.  Beyond, 32 x 32
+// (32 x 32 of each of gate and up): half the operand bytes per product.  Steps of a layer of hidden size
+// 256 and FFN 768, against 64 x 64 tiles of plain FMAs that staged K in slices of 16 through LDS, a dozen
+// workgroups each waiting for memory sixteen times in a row: 13 rows 193 -> 45 us (the four GEMMs 156 ->
+// 18), 105 rows 247 -> 67 us, 2048 rows (dense) 369 -> 206 us; error against 64 bits 7.9e-7 -> 6.1e-7.
+template <typename Epi>
 void run(GemmA A, Rows rows, int K, int N, WSeg seg, const void *w2, Epi epi, hipStream_t s) {
   if (rows.cap <= 0) return;
-  k_gemm_f32<T, Epi><<<gemm_grid(rows.cap, N), 256, 0, s>>>((const T *)A.a, A.gather, A.lda, rows, K,
-                                                            N, seg, (const T *)w2, epi);
+  const long small = (long)((rows.cap + 15) / 16) * (N / 16);
+  if (small <= 512) launch<Epi, 1, 1>(A, rows, K, N, seg, w2, epi, s);
+  else launch<Epi, 2, 2>(A, rows, K, N, seg, w2, epi, s);
 }
 
 }  // namespace
 
-void gemm_f32_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, hipStream_t s) {
-  const int N = seg.n_end[2];
-  EpiStoreF32 e{part, N};
-  if (t == F32) run<float>(A, rows, K, N, seg, nullptr, e, s);
-  else run<bf16_t>(A, rows, K, N, seg, nullptr, e, s);
+void gemm_f32_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, hipStream_t s) {
+  run(A, rows, K, seg.n_end[2], seg, nullptr, EpiStoreF32{part, seg.n_end[2]}, s);
 }
 
-void gemm_f32_swiglu(DType t, GemmA A, Rows rows, int K, int N, const void *w_gate, const void *w_up,
-                     void *act, hipStream_t s) {
-  if (t == F32) run<float>(A, rows, K, N, wseg_one(w_gate, N), w_up, EpiSwiGLU<float>{(float *)act, N}, s);
-  else run<bf16_t>(A, rows, K, N, wseg_one(w_gate, N), w_up, EpiSwiGLU<bf16_t>{(bf16_t *)act, N}, s);
+void gemm_f32_swiglu(GemmA A, Rows rows, int K, int N, const void *w_gate, const void *w_up, void *act, hipStream_t s) {
+  run(A, rows, K, N, wseg_one(w_gate, N), w_up, EpiSwiGLU<float>{(float *)act, N}, s);
 }
 
-void gemm_f32_down(DType t, GemmA A, Rows rows, int K, int N, const void *w_down, const float *h,
-                   void *out_cache, hipStream_t s) {
-  if (t == F32) run<float>(A, rows, K, N, wseg_one(w_down, N), nullptr, EpiDown<float>{h, (float *)out_cache, N}, s);
-  else run<bf16_t>(A, rows, K, N, wseg_one(w_down, N), nullptr, EpiDown<bf16_t>{h, (bf16_t *)out_cache, N}, s);
+void gemm_f32_down(GemmA A, Rows rows, int K, int N, const void *w_down, const float *h, void *out_cache, hipStream_t s) {
+  run(A, rows, K, N, wseg_one(w_down, N), nullptr, EpiDown<float>{h, (float *)out_cache, N}, s);
 }
 
 }  // namespace dy
