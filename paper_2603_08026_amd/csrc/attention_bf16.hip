@@ -394,7 +394,6 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   constexpr int DH = T::DH, NW = T::NW, WK = T::WK, BQ = T::BQ, TK = T::TK, ROWB = T::ROWB, NS = T::NS,
                 DB = T::DB, KK = T::KK, LPW = T::LPW;
   extern __shared__ __align__(1024) unsigned char smem_raw[];
-  __shared__ int tile_info[4];
 
   const int tid = threadIdx.x, lane = tid % WAVE;
   const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
@@ -402,8 +401,8 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   const int wq = wave / WK, wk = wave % WK;
   int tile, kvh, split;
   if (!attn_work_item_grouped(a, q_tiles, &tile, &kvh, &split)) return;  // uniform
-  if (tid == 0) find_tile_grouped(a, BQ, tile, tile_info);
-  __syncthreads();
+  int tile_info[4];
+  find_tile_grouped(a, BQ, tile, tile_info);
   const int b = tile_info[0];
   if (b < 0) return;  // uniform: no such tile
   const int nq = tile_info[3];  // (row, head of the group) pairs in this tile

@@ -360,24 +360,33 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int n) {
   if (i < n) p[i] = v;
 }
 
-inline int row_grid(int cap) { return cap < 1 ? 1 : (cap > 8192 ? 8192 : cap); }
+// Workgroups of a row kernel.  Where the count is on the device the capacity may be far above it, and
+// workgroups without a row are not free (8192 of 1024 threads each for 330 rows: k_qkv_finalize 12.7 us);
+// 1024 of them are two per CU, resident at once, and take further rows in turn.
+constexpr int GRID_KNOWN = 8192, GRID_LISTED = 1024;
+inline int row_grid(const Rows &rows, int cap) {
+  const int most = rows.count ? GRID_LISTED : GRID_KNOWN;
+  return cap < 1 ? 1 : (cap > most ? most : cap);
+}
+inline int row_grid(const Rows &rows) { return row_grid(rows, rows.cap); }
 
 }  // namespace
 
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
                            void *out, hipStream_t s) {
   if (rows.cap <= 0) return;
-  const int grid = rows.cap < 1 ? 1 : (rows.cap > 32768 ? 32768 : rows.cap);
+  const int most = rows.count ? 4 * GRID_LISTED : 32768;  // (a quarter of the threads per workgroup)
+  const int grid = rows.cap > most ? most : rows.cap;
   if (t == F32) {
     if (d / 4 <= 256 * KEEP)
       k_gather_rmsnorm<float, 256><<<grid, 256, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out);
     else
-      k_gather_rmsnorm<float, RB><<<row_grid(rows.cap), RB, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out);
+      k_gather_rmsnorm<float, RB><<<row_grid(rows), RB, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out);
   } else {
     if (d / 8 <= 256 * KEEP)
       k_gather_rmsnorm<bf16_t, 256><<<grid, 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out);
     else
-      k_gather_rmsnorm<bf16_t, RB><<<row_grid(rows.cap), RB, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out);
+      k_gather_rmsnorm<bf16_t, RB><<<row_grid(rows), RB, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out);
   }
 }
 
@@ -386,10 +395,10 @@ void launch_oproj_finalize(DType t, const float *part, Splits splits, const void
                            hipStream_t s) {
   if (rows.cap <= 0) return;
   if (t == F32)
-    k_oproj_finalize<float><<<row_grid(rows.cap), RB, 0, s>>>(part, splits, (const float *)x,
+    k_oproj_finalize<float><<<row_grid(rows), RB, 0, s>>>(part, splits, (const float *)x,
                                                               (const float *)gain, rows, d, eps, h, (float *)f);
   else
-    k_oproj_finalize<bf16_t><<<row_grid(rows.cap), RB, 0, s>>>(part, splits, (const bf16_t *)x,
+    k_oproj_finalize<bf16_t><<<row_grid(rows), RB, 0, s>>>(part, splits, (const bf16_t *)x,
                                                                (const bf16_t *)gain, rows, d, eps, h,
                                                                (bf16_t *)f);
 }
@@ -398,7 +407,7 @@ void launch_down_finalize(DType t, const float *part, Splits splits, const float
                           Rows rows, int d, void *out_cache, hipStream_t s) {
   const int done = splits.dev ? 0 : splits.done_to;
   if (rows.cap <= 0 || done >= rows.cap) return;
-  const int g = row_grid(rows.cap - done);
+  const int g = row_grid(rows, rows.cap - done);
   if (t == F32)
     k_down_finalize<float><<<g, RB, 0, s>>>(part, splits, h, rows, d, (float *)out_cache);
   else
@@ -412,12 +421,12 @@ void launch_qkv_finalize(DType t, const float *part, Splits splits,
                          int32_t *entry_of, int entry_lo, hipStream_t s) {
   if (rows.cap <= 0) return;
   if (t == F32)
-    k_qkv_finalize<float><<<row_grid(rows.cap), RB, 0, s>>>(
+    k_qkv_finalize<float><<<row_grid(rows), RB, 0, s>>>(
         part, splits, rope_tab, rows, L, H, Hkv, dh, (const float *)bq, (const float *)bk,
         (const float *)bv, (float *)q_out, (float *)k_cache, (float *)v_cache, (float *)dv_out, q_by_token,
         (float *)ksal_out, dv_by_entry, entry_of, entry_lo);
   else
-    k_qkv_finalize<bf16_t><<<row_grid(rows.cap), RB, 0, s>>>(
+    k_qkv_finalize<bf16_t><<<row_grid(rows), RB, 0, s>>>(
         part, splits, rope_tab, rows, L, H, Hkv, dh, (const bf16_t *)bq, (const bf16_t *)bk,
         (const bf16_t *)bv, (bf16_t *)q_out, (bf16_t *)k_cache, (bf16_t *)v_cache, (bf16_t *)dv_out, q_by_token,
         (bf16_t *)ksal_out, dv_by_entry, entry_of, entry_lo);
@@ -611,8 +620,8 @@ void launch_mark_flags(Rows rows, int T, int L, int lo, uint8_t *flag, hipStream
 
 void launch_clear_rows(DType t, Rows rows, void *dv, int dkv, hipStream_t s) {
   if (rows.cap <= 0) return;
-  if (t == F32) k_clear_rows<float><<<row_grid(rows.cap), 256, 0, s>>>(rows, (float *)dv, dkv);
-  else k_clear_rows<bf16_t><<<row_grid(rows.cap), 256, 0, s>>>(rows, (bf16_t *)dv, dkv);
+  if (t == F32) k_clear_rows<float><<<row_grid(rows), 256, 0, s>>>(rows, (float *)dv, dkv);
+  else k_clear_rows<bf16_t><<<row_grid(rows), 256, 0, s>>>(rows, (bf16_t *)dv, dkv);
 }
 
 // Row-major [n_out, n_in] matrix of 2-byte elements -> the panel layout the bf16 GEMMs read
