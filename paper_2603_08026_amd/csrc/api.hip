@@ -424,6 +424,12 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
 int enqueue_merge(dyllm_ctx *ctx, const dyllm_index_list *a, const dyllm_index_list *b, int B, int L,
                   int pos_lo, dyllm_index_list *out, hipStream_t s) {
   const int T = B * L;
+  if (T <= MERGE_TOKENS) {
+    const Rows none{nullptr, nullptr, 0};
+    launch_merge_compact(a ? rows_of(a, B) : none, b ? rows_of(b, B) : none, pos_lo, ctx->flag, B, L, out->idx,
+                         out->offsets, out->cap, ctx->status, ctx->scan, s);
+    return check_launch(ctx, "list merge");
+  }
   launch_fill_i32((int32_t *)ctx->flag, 0, (T + 3) / 4, s);
   if (a) launch_mark_flags(rows_of(a, B), T, L, pos_lo, ctx->flag, s);
   if (b) launch_mark_flags(rows_of(b, B), T, L, pos_lo, ctx->flag, s);

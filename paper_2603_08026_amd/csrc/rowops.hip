@@ -271,6 +271,15 @@ __global__ __launch_bounds__(SAL_NT) void k_saliency(const T *__restrict__ c_new
 // FROM_PARTS: the flags do not exist yet; a thread first takes the cosine of each of its entries from
 // the per-head sums the attention kernel left (cos_part [n, H, 4]: <new, old>, |new|^2, |old|^2), writes
 // cos_out and the flag, and then counts and places the flags it wrote itself.
+// FROM_LISTS: the flags do not exist yet either; a workgroup marks the tokens of its own chunk that are in
+// one of two lists (any order, ids outside [0, B*L) and positions below pos_lo ignored) and goes on with
+// the flags it wrote itself.  Every workgroup reads both lists, so this is for a moderate number of tokens.
+struct ListPair {
+  Rows a, b;  // count == nullptr and cap == 0: no such list
+  uint8_t *flag_out;
+  int pos_lo;
+};
+enum CompactFrom { FROM_FLAGS, FROM_COS, FROM_LISTS };
 struct CosParts {
   const float *part;
   float *cos_out;
@@ -279,11 +288,14 @@ struct CosParts {
   float tau;
 };
 
-template <bool FROM_PARTS>
+template <CompactFrom FROM>
 __global__ __launch_bounds__(CB) void k_compact(const uint8_t *__restrict__ flag, Rows rows, int B, int L,
                                                  int chunk, int32_t *out_idx, int32_t *out_off, int out_cap,
-                                                 int32_t *status, int overflow_code, int32_t *scan, CosParts cp) {
+                                                 int32_t *status, int overflow_code, int32_t *scan, CosParts cp, ListPair lp) {
+  constexpr bool FROM_PARTS = FROM == FROM_COS;
+  uint8_t *const own_flags = FROM == FROM_LISTS ? lp.flag_out : cp.flag_out;
   __shared__ int wave_cnt[CB / WAVE];
+  __shared__ uint8_t mark[FROM == FROM_LISTS ? CB : 1];
   __shared__ int s_bid, s_last;
   const int tid = threadIdx.x, lane = tid % WAVE, w = tid / WAVE;
   const int n = row_count(rows);
@@ -296,7 +308,24 @@ __global__ __launch_bounds__(CB) void k_compact(const uint8_t *__restrict__ flag
   for (int start = lo; start < hi; start += CB) {
     const int j = start + tid;
     bool f = false;
-    if (j < hi) {
+    if constexpr (FROM == FROM_LISTS) {
+      mark[tid] = 0;
+      __syncthreads();
+      auto mark_list = [&](const Rows &l) {
+        const int m = row_count(l);
+        for (int i = tid; i < m; i += CB) {
+          const int r = l.idx[i];
+          if (r >= start && r < min(hi, start + CB) && r % L >= lp.pos_lo) mark[r - start] = 1;
+        }
+      };
+      mark_list(lp.a);
+      mark_list(lp.b);
+      __syncthreads();
+      if (j < hi) {
+        f = mark[tid] != 0;
+        lp.flag_out[j] = f ? 1 : 0;
+      }
+    } else if (j < hi) {
       if constexpr (FROM_PARTS) {
         const float4 *p = reinterpret_cast<const float4 *>(cp.part) + (size_t)j * cp.H;
         float dot = 0.f, na = 0.f, nb = 0.f;
@@ -339,9 +368,9 @@ __global__ __launch_bounds__(CB) void k_compact(const uint8_t *__restrict__ flag
 #pragma unroll
   for (int i = 0; i < CB / WAVE; ++i) before += wave_cnt[i];
   __syncthreads();
-  if constexpr (FROM_PARTS) wait_vmcnt<0>();  // this thread's flag stores have reached the L2
-  const int total = compact_range<CB>(FROM_PARTS ? cp.flag_out : flag, rows, lo, hi, before, B, L, out_idx, out_off,
-                                      out_cap, FROM_PARTS, wave_cnt);
+  if constexpr (FROM != FROM_FLAGS) wait_vmcnt<0>();  // this thread's flag stores have reached the L2
+  const int total = compact_range<CB>(FROM != FROM_FLAGS ? own_flags : flag, rows, lo, hi, before, B, L, out_idx, out_off,
+                                      out_cap, FROM != FROM_FLAGS, wave_cnt);
   // the workgroup that holds the end of the list (workgroup 0 of an empty one) writes the tail
   if ((lo < hi && hi == n) || (n == 0 && bid == 0))
     compact_tail<CB>(rows, n, total, B, L, out_off, out_cap, status, overflow_code);
@@ -453,7 +482,7 @@ void launch_compact(const uint8_t *flag, Rows rows, int B, int L, int32_t *out_i
   int chunk = (cap + G - 1) / G;
   chunk = ((chunk + CB - 1) / CB) * CB;
   if (chunk < CB) chunk = CB;
-  k_compact<false><<<G, CB, 0, s>>>(flag, rows, B, L, chunk, out_idx, out_offsets, out_cap, status, -6, scan, CosParts{});
+  k_compact<FROM_FLAGS><<<G, CB, 0, s>>>(flag, rows, B, L, chunk, out_idx, out_offsets, out_cap, status, -6, scan, CosParts{}, ListPair{});
 }
 
 void launch_cos_compact(const float *cos_part, int H, float tau, float *cos_out, uint8_t *flag_out, Rows rows,
@@ -465,8 +494,15 @@ void launch_cos_compact(const float *cos_part, int H, float tau, float *cos_out,
   int chunk = (cap + G - 1) / G;
   chunk = ((chunk + CB - 1) / CB) * CB;
   if (chunk < CB) chunk = CB;
-  k_compact<true><<<G, CB, 0, s>>>(flag_out, rows, B, L, chunk, out_idx, out_offsets, out_cap, status, -6, scan,
-                                   CosParts{cos_part, cos_out, flag_out, H, tau});
+  k_compact<FROM_COS><<<G, CB, 0, s>>>(flag_out, rows, B, L, chunk, out_idx, out_offsets, out_cap, status, -6, scan,
+                                       CosParts{cos_part, cos_out, flag_out, H, tau}, ListPair{});
+}
+
+void launch_merge_compact(Rows a, Rows b, int pos_lo, uint8_t *flag_out, int B, int L, int32_t *out_idx,
+                          int32_t *out_offsets, int out_cap, int32_t *status, int32_t *scan, hipStream_t s) {
+  const int T = B * L, G = (T + CB - 1) / CB;  // (T <= MERGE_TOKENS: a chunk is one sweep of the workgroup)
+  k_compact<FROM_LISTS><<<G, CB, 0, s>>>(flag_out, Rows{nullptr, nullptr, T}, B, L, CB, out_idx, out_offsets, out_cap,
+                                         status, -6, scan, CosParts{}, ListPair{a, b, flag_out, pos_lo});
 }
 
 // ---- approximate context update of the non-salient rows  [Sec. 3.3; Alg. 3 lines C <- ..., cosine] --

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import assert_close, oracle_cfg, rand_rows, rand_weights
+from tests.helpers import assert_close, oracle_cfg, rand_rows, rand_weights
 from oracle import dyllm_oracle as O
 from paper_2603_08026_amd.layer import Layer, to_device, to_host
 from synth import workload as W
