@@ -80,12 +80,12 @@ void launch_cos_compact(const float *cos_part, int H, float tau, float *cos_out,
 
 // The union of two lists (any order; ids outside [0, B*L) and positions below pos_lo ignored; a list with
 // cap 0 is none) in one launch: flags of all tokens to flag_out, the flagged tokens compacted as by
-// launch_compact.  B*L <= MERGE_TOKENS: every workgroup of 256 tokens reads both lists, which for full
-// lists of 32768 entries is as long as the four launches this replaces (clear, mark twice, compact: 19.5 us;
-// for lists of a few hundred entries it saves about 6 us: loop of four steps over 8 x 1024 tokens 2334 -> 2310).
+// launch_compact.  B*L <= MERGE_TOKENS: every workgroup of 256 tokens reads both lists.  Against the four
+// launches this replaces (clear, mark twice, compact: 15.8 us): two lists of 80 entries 8.3 us; two full ones
+// 14.6 us at 8192 tokens, 40.7 us at 32768, so the line lies where full lists still gain.
 void launch_merge_compact(Rows a, Rows b, int pos_lo, uint8_t *flag_out, int B, int L, int32_t *out_idx,
                           int32_t *out_offsets, int out_cap, int32_t *status, int32_t *scan, hipStream_t s);
-constexpr int MERGE_TOKENS = 32768;
+constexpr int MERGE_TOKENS = 8192;
 
 // ---- attention ---------------------------------------------------------------------------------
 struct AttnArgs {

@@ -13,7 +13,7 @@ from paper_2603_08026_amd.layer import Layer
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,L", [(1, 1), (1, 255), (2, 128), (1, 257), (3, 300), (2, 16384), (1, 32769)])
+@pytest.mark.parametrize("B,L", [(1, 1), (1, 255), (2, 128), (1, 257), (3, 300), (2, 4096), (1, 8193)])
 def test_union_in_one_launch_and_in_four(B, L):
     print("merge lists", B, L, flush=True)
     lay = Layer.from_shape(small_shape("bf16"), B, L)
