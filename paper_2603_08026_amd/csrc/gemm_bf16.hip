@@ -47,7 +47,7 @@ int cu_count() {
 
 // The ring loop addresses its operands with a scalar base and 32-bit byte offsets per lane.  The base
 // of the activation operand moves with the tile unless rows are gathered: a gathered operand, and
-// each weight matrix, must span less than 4 GiB, and a copy's 8 weight rows must lie in one matrix;
+// each weight matrix, must span less than 4 GiB, and a group of permuted weight rows must lie in one matrix;
 // otherwise the eight-wave 256 x 128 shapes run.  (Every K split of the plans keeps at least 8
 // slices; the loop needs 3.)
 // DYLLM_GEMM_NO_RING=1 in the environment takes the fallback for every call (diagnostics and tests).
@@ -58,7 +58,7 @@ bool ring_ok(const GemmA &A, int K, const WSeg &seg, int n_rows_w) {
   if (A.gather && (A.a_rows == 0 || A.a_rows * (size_t)A.lda * 2 >= lim)) return false;
   if ((size_t)A.lda * 2 * 256 >= lim) return false;
   if ((size_t)n_rows_w * (size_t)K * 2 >= lim) return false;
-  if (seg.n_end[0] % 8 || seg.n_end[1] % 8) return false;
+  if (!ring_groups_ok(seg.n_end[0], seg.n_end[1])) return false;
   return K / BK >= RING_MIN_SLICES;
 }
 

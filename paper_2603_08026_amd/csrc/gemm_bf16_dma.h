@@ -456,7 +456,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
         const int t = c / SH::B_LD, i = c % SH::B_LD;
         const int nrow0 = (i * NW + wave) * 8;  // first of the copy's 8 tile rows (wave-uniform)
         const int nu = n0 + nrow0;
-        // a copy's rows lie in one matrix: segment ends are multiples of 8
+        // the 32 permuted rows of a panel lie in one matrix: its ends are multiples of 32 (ring_groups_ok)
         const bool in1 = nu >= seg.n_end[0], in2 = nu >= seg.n_end[1];
         const void *base = t == 1 ? (const void *)W2 : in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0];
         const int np = (nu - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0)) / WPANEL;  // panel in its matrix
