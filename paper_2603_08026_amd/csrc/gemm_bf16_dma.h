@@ -30,8 +30,8 @@
 // MFMA.  v_mfma_f32_32x32x16_bf16: lane l supplies 8 consecutive k of row (l%32) for A and of
 // column (l%32) for B at k offset 8*(l/32); the accumulator block holds
 //   row = 8*(r/4) + 4*(l/32) + (r%4),  col = l%32   in register r of lane l.
-// The 256-row tiles of the ring loop use v_mfma_f32_16x16x32_bf16 with the operands exchanged, so that
-// a lane's results are eight neighbouring columns of one row (gemm_bf16_ring.h).
+// The 256-row tiles of the ring loop use v_mfma_f32_16x16x32_bf16 with a permuted order of the weight rows,
+// so that neighbouring lanes hold neighbouring runs of columns of one row (gemm_bf16_ring.h).
 //
 // Tile walk.  The row count lives on the device; the grid is sized from the list capacity and each
 // workgroup walks the existing tiles in a grouped order, remapped so that neighbouring tiles run on
@@ -114,6 +114,15 @@ struct GemmArgs {
   float *part;  // raw result part[z][j][n], split stride = existing rows * N
 };
 
+// This lane's number, hidden from the optimiser and computed anew at every call.  What follows from it at the ends
+// of a tile would otherwise be computed once per kernel, kept across the slice loops of every shape in it, which have
+// no registers for that, and reloaded from scratch memory behind the copies in flight.
+__device__ __forceinline__ int own_lane() {
+  uint32_t all = ~0u;
+  asm volatile("" : "+s"(all));
+  return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+}
+
 // The tiles of list rows [row_lo, min(count, row_hi)) (row_lo is a multiple of BM) with `splitk` K splits,
 // those with numbers first, first + step, ... .  Splits are cut in whole K slices and may differ by one.
 // SPLIT: the tile goes to the raw fp32 result part[z][j][n] instead of through the
@@ -138,8 +147,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
   const int tm_lo = row_lo / BM;
   const int m_rel = max(M - tm_lo * BM, 0);
   const int tiles_m = (m_rel + BM - 1) / BM, tiles_n = N / BN;
-  const int tid = threadIdx.x, lane = tid % WAVE;
-  const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);  // wave-uniform, kept scalar
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);  // wave-uniform, kept scalar
+  const int lane = own_lane(), tid = wave * WAVE + lane;
   const int wm0 = (wave / SH::WAVES_N) * SH::WM, wn0 = (wave % SH::WAVES_N) * SH::WN;
   const int l32 = lane % 32, lhi = lane / 32;
   const int KS = ldw / BK;  // K slices
@@ -171,9 +180,11 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
   // from the next whole number, more than the product's rounding (an integer division is a chain of some
   // thirty instructions, eight of them in a row at the start of every tile).
   auto quot = [](int x, float inv) -> int { return __builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * inv)); };
+  auto inverse = [](int d) -> float {  // kept scalar
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, __builtin_amdgcn_rcpf((float)d))));
+  };
   const int gsz = group_m * tiles_n;
-  const float inv_full = __builtin_amdgcn_rcpf((float)n_full), inv_part = __builtin_amdgcn_rcpf((float)n_part),
-              inv_gsz = __builtin_amdgcn_rcpf((float)gsz);
+  const float inv_full = inverse(n_full), inv_part = inverse(n_part), inv_gsz = inverse(gsz);
   // K slices of a split: the first k_rem splits have one more than the others
   const int k_base = splitk > 1 ? quot(KS, __builtin_amdgcn_rcpf((float)splitk)) : KS, k_rem = KS - k_base * splitk;
   auto k_first = [&](int z) -> int { return z * k_base + min(z, k_rem); };
@@ -372,58 +383,81 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     using RingFull = Ring<NMAT, NB, BN, 4>;
     constexpr int NWC = RingFull::NWC;
     static_assert(Epi::INTERLEAVE == 0 && SH::A_LD == 8 && NMAT * SH::B_LD == NWC, "ring shapes");
-    // Epilogue of one tile: this lane has rows j0 + 16 i (i < 8) and columns c0 + 32 g .. + 7 (g < NB), in
-    // acc[t][i][2 g] and [2 g + 1].
-    auto ring_epilogue = [&](floatx4 (&acc)[NMAT][8][2 * NB], int j0, int c0, int z) {
+    // Epilogue of one tile whose wave rows start at rbase and columns at cbase (both wave-uniform): this lane has
+    // row rbase + 16 i + 4 lq + e in element e of acc[t][i][..], column cbase + 16 G q + G l16 + h in block G q + h
+    // (gemm_bf16_ring.h).  Row-ordered operands are addressed through buffer descriptors that end with the last
+    // row: what lies past it is neither read nor written, without a branch per row (a branch around a load makes
+    // the compiler wait for the load where the paths meet: 38000 instead of 14000 cycles for the down epilogue).
+    constexpr int G = RingFull::G, NQ = 2 * NB / G;
+    auto ring_epilogue = [&](auto &acc, int rbase, int cbase, int z) {
+      constexpr int MI = sizeof(acc[0]) / sizeof(acc[0][0]);  // 16-row blocks
+      const int ln = own_lane(), l16 = ln % 16, lq = ln / 16;
+      // rows of block i on; descriptor of rows [16 i, ..) of a [., N] operand of esz bytes per element
+      auto left = [&](int i) -> int { return __builtin_amdgcn_readfirstlane(min(max(M - rbase - 16 * i, 0), 16)); };
+      auto block = [&](const void *p, int i, int esz) {
+        return make_srd((const char *)p + ((size_t)(rbase + 16 * i) * N + cbase) * esz, left(i) ? (uint32_t)(left(i) * N - cbase) * esz : 0);
+      };
+      uint32_t lane_row[4];  // element offsets of this lane's four rows in a block
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lane_row[e] = (uint32_t)(4 * lq + e) * N + G * l16;
       if constexpr (SPLIT) {
-        float *pz = split.part + (size_t)z * split.split_stride + c0;
+        static_assert(!SPLIT || G == 4, "16-byte raw stores");
+        const float *pz = split.part + (size_t)z * split.split_stride;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int j = j0 + 16 * i;
-          if (j < M) {
-            float *r = pz + (size_t)j * split.N;
+        for (int i = 0; i < MI; ++i) {
+          const auto part = block(pz, i, 4);
 #pragma unroll
-            for (int c = 0; c < 2 * NB; ++c) *reinterpret_cast<floatx4 *>(r + (c / 2) * 32 + (c % 2) * 4) = acc[0][i][c];
-          }
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+              store_buf(floatx4{acc[0][i][G * q][e], acc[0][i][G * q + 1][e], acc[0][i][G * q + 2][e], acc[0][i][G * q + 3][e]},
+                        part, lane_row[e] * 4u + 64 * G * q);
         }
       } else if constexpr (Epi::PRELOAD) {
         // what row block i + 1 reads is requested before block i is written: a wave's memory operations
         // complete in order, so a load behind stores would wait for all of them
-        int rowv[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int j = j0 + 16 * i;
-          rowv[i] = (rows.idx && j < M) ? rows.idx[j] : j;
-        }
-        floatx4 pre[2][2 * NB];
+        floatx4 pre[2][4][NQ];
+        int row[2][4];
         auto load = [&](int i) {
-          const int j = j0 + 16 * i;
-          if (j < M) {
+          const auto res = block(epi.h, i, 4);
+          const auto list = make_srd(rows.idx + (rows.idx ? rbase + 16 * i : 0), rows.idx ? left(i) * 4u : 0);
 #pragma unroll
-            for (int c = 0; c < 2 * NB; ++c) pre[i & 1][c] = epi.load4(j, c0 + (c / 2) * 32 + (c % 2) * 4);
+          for (int e = 0; e < 4; ++e) {
+            row[i & 1][e] = __builtin_amdgcn_raw_buffer_load_b32(list, lq * 16 + e * 4, 0, 0);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) pre[i & 1][e][q] = load_buf(res, lane_row[e] * 4u + 64 * G * q);
           }
         };
         load(0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          if (i + 1 < 8) load(i + 1);
-          if (j0 + 16 * i < M) {
+        for (int i = 0; i < MI; ++i) {
+          if (i + 1 < MI) load(i + 1);
 #pragma unroll
-            for (int g = 0; g < NB; ++g)
-              epi.store8(rowv[i], c0 + 32 * g, acc[0][i][2 * g], acc[0][i][2 * g + 1], pre[i & 1][2 * g], pre[i & 1][2 * g + 1]);
+          for (int e = 0; e < 4; ++e) {
+            const int r = 4 * lq + e;
+            if (r < left(i)) {
+#pragma unroll
+              for (int q = 0; q < NQ; ++q) {
+                const floatx4 a = {acc[0][i][G * q][e], acc[0][i][G * q + 1][e], acc[0][i][G * q + 2][e], acc[0][i][G * q + 3][e]};
+                epi.store4(rows.idx ? row[i & 1][e] : rbase + 16 * i + r, cbase + 16 * G * q + G * l16, a, pre[i & 1][e][q]);
+              }
+            }
           }
           __builtin_amdgcn_sched_barrier(0);  // (a row block at a time: more of them at once spill)
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          int j = j0 + 16 * i;
-          asm volatile("" : "+v"(j));  // (addresses of all row blocks at once spill)
-          if (j < M) {
+        for (int i = 0; i < MI; ++i) {
+          const auto act = block(epi.act, i, 2);
 #pragma unroll
-            for (int g = 0; g < NB; ++g)
-              epi.store8(j, c0 + 32 * g, acc[0][i][2 * g], acc[0][i][2 * g + 1], acc[NMAT - 1][i][2 * g], acc[NMAT - 1][i][2 * g + 1]);
-          }
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+              float v[G];
+#pragma unroll
+              for (int h = 0; h < G; ++h) v[h] = epi.product(acc[0][i][G * q + h][e], acc[NMAT - 1][i][G * q + h][e]);
+              store_buf(v, act, lane_row[e] * 2u + 32 * G * q);
+            }
           __builtin_amdgcn_sched_barrier(0);  // (a row block at a time: more of them at once spill)
         }
       }
@@ -431,6 +465,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     auto ring_sources = [&](int tm, int tn, int z, RingSrc &src) {
       const int kbeg = k_first(z) * BK;
       const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
+      const int ln = own_lane(), r8 = ln / 8, csrc = (ln % 8) ^ (((wave & 1) << 2) | (r8 >> 1));  // as above
       // Lane offsets are 32 bits.  Without a gather list the descriptor starts at the tile's first
       // row, so the offsets stay below 256 rows; with one they are taken from the start of the
       // operand (the launcher checks that it spans less than 4 GiB).
@@ -454,16 +489,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
 #pragma unroll
       for (int c = 0; c < NWC; ++c) {
         const int t = c / SH::B_LD, i = c % SH::B_LD;
-        const int nrow0 = (i * NW + wave) * 8;  // first of the copy's 8 tile rows (wave-uniform)
-        const int nu = n0 + nrow0;
-        // the 32 permuted rows of a panel lie in one matrix: its ends are multiples of 32 (ring_groups_ok)
+        // the copy's 8 tile rows hold every G-th weight row from nu on (wave-uniform): rows of one panel, and
+        // so of one matrix, whose ends are multiples of 16 G (ring_groups_ok)
+        const int nu = n0 + RingFull::weight_row(i, wave);
         const bool in1 = nu >= seg.n_end[0], in2 = nu >= seg.n_end[1];
         const void *base = t == 1 ? (const void *)W2 : in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0];
-        const int np = (nu - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0)) / WPANEL;  // panel in its matrix
-        src.srd_w[c] = make_srd((const bf16_t *)base + ((size_t)np * KS + kbeg / BK) * (WPANEL * BK), 0xfffffff0u);
+        const int nl = nu - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0);  // row in its matrix
+        src.srd_w[c] = make_srd((const bf16_t *)base + ((size_t)(nl / WPANEL) * KS + kbeg / BK) * (WPANEL * BK) + (nl % WPANEL) * BK, 0xfffffff0u);
       }
-      // (the rows of a panel are permuted; the copies of a wave all start at the same row of their panels)
-      src.vw = (uint32_t)((ring_wperm((wave & 3) * 8 + r8) * BK + csrc * 8) * 2);
+      src.vw = (uint32_t)((G * r8 * BK + csrc * 8) * 2);
     };
     int tm = 0, tn = 0, z = 0, p = first;
     while (p < total_all && !tile_at(p, tm, tn, z)) p += step;
@@ -472,40 +506,38 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     ring_sources(tm, tn, z, src);
     RingFull::fill(src, lds0, wave);
     bool all_landed = false;
-    const int l16 = lane % 16, lq = lane / 16;
-    const unsigned char *rd_a = smem_raw + (wm0 + l16) * ROWB, *rd_w = smem_raw + (wn0 + l16) * ROWB;
-    int rd_off16[2];
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) rd_off16[kk] = (((4 * kk + lq) ^ ((l16 >> 1) & 7)) * 16);
-    for (;;) {
-      const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
+    // The whole of a tile for MBV 32-row blocks of this wave that hold rows, epilogue included: where the paths for
+    // the block counts met before the epilogue, the 256 accumulators of the fused 256 x 256 tile were moved between
+    // registers, and through scratch memory, at the end of every tile.  Returns whether another tile follows.
+    auto run_tile = [&](auto mbv_c) -> bool {
+      constexpr int MBV = decltype(mbv_c)::value, MI = 2 * MBV;
       const int KT = k_base + (z < k_rem ? 1 : 0);
-      floatx4 acc[NMAT][8][2 * NB];
+      const int rbase = (tm_lo + tm) * BM + wm0, cbase = tn * BN + wn0, z_now = z;
+      const int ln = own_lane(), l16 = ln % 16, lq = ln / 16;
+      const unsigned char *rd_a = smem_raw + (wm0 + l16) * ROWB, *rd_w = smem_raw + (wn0 + l16) * ROWB;
+      int rd_off16[2];
 #pragma unroll
-      for (int t = 0; t < NMAT; ++t)
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int j = 0; j < 2 * NB; ++j) acc[t][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-      auto run_ring = [&](auto mbv_c) {
-        Ring<NMAT, NB, BN, decltype(mbv_c)::value>::tile(acc, lds0, wave, src, rd_a, rd_w, rd_off16, KT, all_landed);
-      };
-      // 32-row blocks of this wave that hold rows (wave-uniform)
-      const int mbv = (M - (m0 + wm0) + 31) / 32;
-      if (mbv >= 3) run_ring(std::integral_constant<int, 4>{});
-      else if (mbv == 2) run_ring(std::integral_constant<int, 2>{});
-      else if (mbv == 1) run_ring(std::integral_constant<int, 1>{});
-      else run_ring(std::integral_constant<int, 0>{});
-      int pn = p + step, tmn = 0, tnn = 0, zn = 0;
-      while (pn < total_all && !tile_at(pn, tmn, tnn, zn)) pn += step;
-      const bool more = pn < total_all;
+      for (int kk = 0; kk < 2; ++kk) rd_off16[kk] = (((4 * kk + lq) ^ ((l16 >> 1) & 7)) * 16);
+      floatx4 acc[NMAT][MI ? MI : 1][2 * NB];
+      Ring<NMAT, NB, BN, MBV>::tile(acc, lds0, wave, src, rd_a, rd_w, rd_off16, KT, all_landed);
+      p += step;
+      while (p < total_all && !tile_at(p, tm, tn, z)) p += step;
+      const bool more = p < total_all;
       if (more) {
-        ring_sources(tmn, tnn, zn, src);
+        ring_sources(tm, tn, z, src);
         RingFull::fill(src, lds0, wave);
       }
-      ring_epilogue(acc, m0 + wm0 + l16, n0 + wn0 + 8 * lq, z);
+      if constexpr (MBV > 0) ring_epilogue(acc, rbase, cbase, z_now);
+      return more;
+    };
+    for (;;) {
+      const int mbv = (M - ((tm_lo + tm) * BM + wm0) + 31) / 32;  // wave-uniform
+      bool more;
+      if (mbv >= 3) more = run_tile(std::integral_constant<int, 4>{});
+      else if (mbv == 2) more = run_tile(std::integral_constant<int, 2>{});
+      else if (mbv == 1) more = run_tile(std::integral_constant<int, 1>{});
+      else more = run_tile(std::integral_constant<int, 0>{});
       if (!more) break;
-      p = pn; tm = tmn; tn = tnn; z = zn;
       all_landed = true;
     }
     return;

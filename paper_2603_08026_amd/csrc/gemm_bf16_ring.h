@@ -42,6 +42,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_srd(const void *p, uint32
   return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)bytes, 0x00020000);
 }
 
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t uintx4;
+typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t uintx2;
+
+// four floats, or two / four floats as bf16, at byte offset `off` of a buffer
+__device__ __forceinline__ floatx4 load_buf(__amdgpu_buffer_rsrc_t srd, uint32_t off) {
+  return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(srd, off, 0, 0));
+}
+__device__ __forceinline__ void store_buf(floatx4 v, __amdgpu_buffer_rsrc_t srd, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), srd, off, 0, 0);
+}
+__device__ __forceinline__ void store_buf(const float (&v)[2], __amdgpu_buffer_rsrc_t srd, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b32(pack_bf16(v[0], v[1]), srd, off, 0, 0);
+}
+__device__ __forceinline__ void store_buf(const float (&v)[4], __amdgpu_buffer_rsrc_t srd, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b64(uintx2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])}, srd, off, 0, 0);
+}
+
 constexpr uint32_t RING_SLOT = 32768;
 constexpr int RING_SLOTS = 5;
 constexpr int RING_MIN_SLICES = 3;
@@ -49,23 +67,23 @@ constexpr int RING_MIN_SLICES = 3;
 // Sources of a wave's copies for one tile:
 //   srd_a / va[i]   descriptor and lane offsets of its 8 A copies (8 tile rows each)
 //   srd_w[c] / vw   the same for its weight copies (8 for a 256-row weight tile, 4 for a 128-row one): a
-//                   copy's 8 rows lie in one weight panel, where its descriptor starts, so that one lane
-//                   offset serves them all
+//                   copy's 8 rows lie in one weight panel; the descriptor starts at the first of them, so that
+//                   one lane offset serves all copies
 struct RingSrc {
   __amdgpu_buffer_rsrc_t srd_a, srd_w[8];
   uint32_t va[8], vw;
 };
 
-// Matrix instruction and operand order.  v_mfma_f32_16x16x32_bf16 with the WEIGHTS as its first operand:
-// lane l holds activation row l % 16 of a block and, in its four registers, the columns 4 * (l / 16) ..
-// + 3 -- a row's results come in vectors, not one column per lane.  Two neighbouring 16-column blocks
-// share a group of 32 columns whose weight rows are permuted on their way into LDS (ring_wperm), so
-// that the lane's two blocks hold columns 8 * (l / 16) .. + 7 of the group: a 16-byte store of bf16, or
-// two of fp32.  The 16x16 form also does the same products with less power than the 32x32 one, and
-// the matrix clock is power-bound: operands in registers, all CUs busy, random values: 1.85 against
-// 1.75 PFLOP/s.  Together with the vector epilogues, against 32x32x16 instructions whose results were
-// stored a column per lane: dense layer of 20480 rows 7565 -> 7248 us, of 1024 rows 484 -> 465 us, sparse
-// step of about 2000 rows 913 -> 880 us.
+// Matrix instruction and column order.  v_mfma_f32_16x16x32_bf16: element e of lane l's four registers is
+// activation row 4 * (l / 16) + e and column l % 16 of its 16 x 16 block.  The weight rows of G blocks (four, or
+// two where a wave has two of a matrix) are permuted on their way into LDS so that lane l % 16 of the G blocks holds
+// columns G * (l % 16) .. + G - 1 of the 16 G: its results of a row are one store (16 bytes of fp32; 8 or 4 of bf16), and the 16
+// lanes after one another fill 256 (128, 64) bytes of the row.  The copy and store path takes four lanes at a time, and they
+// have to lie next to each other: with the weights as FIRST operand, where a lane holds eight columns but
+// neighbouring lanes different rows, a 16-byte store of a wave took 64 cycles instead of 16, and the raw store of a
+// 256 x 128 tile 7700 cycles instead of 3400.
+// The 16x16 form does the same products with less power than the 32x32 one, and the matrix clock is power-bound:
+// operands in registers, all CUs busy, random values: 1.85 against 1.75 PFLOP/s.
 //
 // The loop for one wave tile of 128 rows x (32 NMAT NB) columns: NMAT x NB column groups of 32, group
 // g = t * NB + j reads weight-tile rows (t * BN + wn0 + 32 j ...).  Four column groups (a 256-row
@@ -76,11 +94,6 @@ struct RingSrc {
 // every wave, so such a tile costs about what its copies cost (leaving out the A copies of the empty
 // row groups as well was measured: no faster).
 
-// weight row (inside its panel of 32) that row x of a group of 32 LDS rows holds
-__device__ __forceinline__ int ring_wperm(int x) { return ((x >> 2) & 3) * 8 + (x >> 4) * 4 + (x & 3); }
-
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
 template <int NMAT, int NB, int BN, int MBV> struct Ring {
   static constexpr int NCB = NMAT * NB;  // column groups per wave
   static constexpr int NWC = 2 * NCB;    // weight copies per wave and slice
@@ -89,6 +102,14 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
   static constexpr int RD = 8 + NC;      // operand reads per K step
   static constexpr int RSP = PS / 2 >= 2 * RD ? 2 : 1;  // products between two operand reads
   static_assert(NCB == 4 || NCB == 2, "four or two column groups per wave");
+  // 16-column blocks whose columns alternate: row x of a group of 16 G LDS rows holds weight row
+  // G (x % 16) + x / 16 of the group, so that lane l16 of the G blocks has columns G l16 .. + G - 1
+  static constexpr int G = NB >= 2 ? 4 : 2;
+  // weight row (from the tile's first column on) in LDS rows (4 i + wave) * 8 of a matrix; the row r8 after it
+  // holds weight row weight_row + G r8
+  static __device__ __forceinline__ int weight_row(int i, int wave) {
+    return G == 4 ? (i / 2) * 64 + (wave & 1) * 32 + (i & 1) * 2 + (wave >> 1) : i * 32 + (wave & 1) * 16 + (wave >> 1);
+  }
   static constexpr int ROW = 128, A_STEP = 128, W_STEP = 4096;  // bytes per tile row; K walk per slice
 
   static __device__ __forceinline__ int w_row(int c) { return (((c / 2) / NB) * BN + ((c / 2) % NB) * 32 + (c % 2) * 16) * ROW; }
@@ -115,13 +136,15 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
     }
   }
 
-  // One tile: acc += A tile x W tile over KT >= 3 slices; the ring has been filled (fill).
+  // One tile: acc[matrix][16-row block][16-column block] = A tile x W tile over KT >= 3 slices; the ring has been
+  // filled (fill).
   //   all_landed      wait for everything this wave has in flight (a fill issued before the previous
   //                   tile's epilogue, whose own loads and stores are counted with it) instead of for
   //                   the first slice alone; wave-uniform
   //   rd_a / rd_w     this lane's operand-read addresses inside a slot (slot 0), without the chunk swizzle
   //   rd_off[s]       swizzled chunk offset of K step s
-  static __device__ __forceinline__ void tile(floatx4 (&acc)[NMAT][8][2 * NB], uint32_t lds0, int wave, const RingSrc &src,
+  template <typename Acc>
+  static __device__ __forceinline__ void tile(Acc &acc, uint32_t lds0, int wave, const RingSrc &src,
                                               const unsigned char *rd_a, const unsigned char *rd_w,
                                               const int (&rd_off)[2], int KT, bool all_landed) {
     const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
@@ -141,10 +164,11 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       if (x < 8) af[st][x] = *reinterpret_cast<const bf16x8 *>(sa + x * 16 * ROW + rd_off[st]);
       else bfr[st][x - 8] = *reinterpret_cast<const bf16x8 *>(sb + w_row(x - 8) + rd_off[st]);
     };
-    auto prod = [&](int st, int p) {
+    auto prod = [&](int st, int p, bool zero) {
       const int i = p / NC, c = p % NC;
       auto &a = acc[c / (2 * NB)][i][c % (2 * NB)];
-      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[st][c], af[st][i], a, 0, 0, 0);
+      const floatx4 sum = zero ? floatx4{0.f, 0.f, 0.f, 0.f} : a;  // (the first products of a tile start from zero)
+      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[st][i], bfr[st][c], sum, 0, 0, 0);
     };
     // read r of the other K step goes behind product RSP * r
     auto read_due = [](int q) { return q % RSP == 0 && q / RSP < RD; };
@@ -174,7 +198,7 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       for (int q = 0; q < PS; ++q) {
         if (read_due(q) && has_read(q / RSP)) read(1, q / RSP, sa, sb);
         if (CA && copy_a_due(q)) copy_a((q + 1) / (PS / 8) - 1, kt + 2, slot_a2);
-        if (has_prod(q)) prod(0, q);
+        if (has_prod(q)) prod(0, q, FIRST);
       }
 #pragma unroll
       for (int q = 0; q < PS; ++q) {
@@ -199,7 +223,7 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       for (int q = 0; q < PS; ++q) {
         if (M1 && read_due(q) && has_read(q / RSP)) read(0, q / RSP, sa1, sb1);
         if (M2 && copy_w_due(q)) copy_w((q + 1) / (PS / NWC) - 1, kt + 2, slot_a);
-        if (has_prod(q)) prod(1, q);
+        if (has_prod(q)) prod(1, q, false);
       }
 #pragma unroll
       for (int q = 0; q < PS; ++q) {

@@ -29,14 +29,6 @@ template <typename T> __device__ __forceinline__ float silu_for(float x) {
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float epi_f4;  // four neighbouring columns
 
-// eight neighbouring bf16 columns (16 bytes)
-__device__ __forceinline__ void store8_bf16(bf16_t *p, const float (&v)[8]) {
-  uint4 w;
-  w.x = pack_bf16(v[0], v[1]); w.y = pack_bf16(v[2], v[3]);
-  w.z = pack_bf16(v[4], v[5]); w.w = pack_bf16(v[6], v[7]);
-  *reinterpret_cast<uint4 *>(p) = w;
-}
-
 struct EpiStoreF32 {
   static constexpr bool DUAL = false;
   static constexpr int INTERLEAVE = 0;
@@ -65,13 +57,7 @@ template <typename T> struct EpiSwiGLU {
     const float s = silu_for<T>(gate);
     act[(size_t)j * N + n] = from_f<T>(s * up);
   }
-  // columns n .. n+7 of row j (bf16)
-  __device__ __forceinline__ void store8(int j, int n, epi_f4 g0, epi_f4 g1, epi_f4 u0, epi_f4 u1) const {
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { v[e] = silu_for<T>(g0[e]) * u0[e]; v[4 + e] = silu_for<T>(g1[e]) * u1[e]; }
-    store8_bf16((bf16_t *)act + (size_t)j * N + n, v);
-  }
+  __device__ __forceinline__ float product(float gate, float up) const { return silu_for<T>(gate) * up; }
   __device__ __forceinline__ int ld() const { return N; }
   __device__ __forceinline__ uint32_t lane_bytes(int lhi, int l32) const {
     return ((uint32_t)(4 * lhi) * N + l32) * (uint32_t)sizeof(T);
@@ -99,13 +85,10 @@ template <typename T> struct EpiDown {
   __device__ __forceinline__ void operator()(int j, int row, int n, float acc, float) const {
     store(row, n, acc, load(j, n));
   }
-  __device__ __forceinline__ epi_f4 load4(int j, int n) const { return *reinterpret_cast<const epi_f4 *>(h + (size_t)j * N + n); }
-  // columns n .. n+7 of row `row` (bf16)
-  __device__ __forceinline__ void store8(int row, int n, epi_f4 a0, epi_f4 a1, epi_f4 h0, epi_f4 h1) const {
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { v[e] = h0[e] + a0[e]; v[4 + e] = h1[e] + a1[e]; }
-    store8_bf16((bf16_t *)out + (size_t)row * N + n, v);
+  // columns n .. n+3 of row `row` (bf16)
+  __device__ __forceinline__ void store4(int row, int n, epi_f4 acc, epi_f4 hv) const {
+    *reinterpret_cast<uint2 *>((bf16_t *)out + (size_t)row * N + n) =
+        uint2{pack_bf16(hv[0] + acc[0], hv[1] + acc[1]), pack_bf16(hv[2] + acc[2], hv[3] + acc[3])};
   }
   __device__ __forceinline__ int ld() const { return N; }
   __device__ __forceinline__ uint32_t lane_bytes(int lhi, int l32) const {

@@ -103,7 +103,7 @@ inline GemmPlan plan_on_host(const PlanArgs &a, int M) {
 // The ring loop's weight copies have one lane offset for all of a tile: the rows they gather lie in one group of
 // RING_GROUP weight rows, and so must lie in one matrix.  (Ends of the stacked matrices; every head size the library
 // accepts is a multiple of 64.)
-constexpr int RING_GROUP = 32;
+constexpr int RING_GROUP = 64;
 inline bool ring_groups_ok(int end0, int end1) { return end0 % RING_GROUP == 0 && end1 % RING_GROUP == 0; }
 
 // one wave (all 64 lanes active); the result is uniform
