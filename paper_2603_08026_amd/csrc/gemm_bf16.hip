@@ -112,9 +112,9 @@ struct RawKind {  // q|k|v, out-projection: fp32 result, a row kernel follows
   typedef XLargeS X;
   typedef LargeS L;
   static constexpr bool FUSED = false, RAW = true;
-  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int row_lo, int sk, int first, int step, unsigned char *sm) {
-    if (ga.N % SkinnyW96::BN == 0) gemm_tiles<SkinnyW96, Epi, true>(ga, e, row_lo, INT_MAX, sk, first, step, sm);
-    else gemm_tiles<SkinnyN64, Epi, true>(ga, e, row_lo, INT_MAX, sk, first, step, sm);
+  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
+    if (ga.N % SkinnyW96::BN == 0) gemm_tiles<SkinnyW96, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
+    else gemm_tiles<SkinnyN64, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
   }
 };
 struct DownKind {  // residual + scatter in the epilogue, or fp32 sums of a K split
@@ -122,8 +122,8 @@ struct DownKind {  // residual + scatter in the epilogue, or fp32 sums of a K sp
   typedef XLargeS X;
   typedef LargeS L;
   static constexpr bool FUSED = true, RAW = true;
-  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int row_lo, int sk, int first, int step, unsigned char *sm) {
-    gemm_tiles<SkinnyN64, Epi, true>(ga, e, row_lo, INT_MAX, sk, first, step, sm);
+  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
+    gemm_tiles<SkinnyN64, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
   }
 };
 // weight streaming of gate|up: tiles of HALF gate + HALF up columns, SwiGLU in registers, no raw result
@@ -141,10 +141,10 @@ struct SwigluKind {
   typedef XLargeD X;
   typedef LargeD L;
   static constexpr bool FUSED = true, RAW = false;
-  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int row_lo, int, int first, int step, unsigned char *sm) {
+  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int, const Walk &w) {
     const GemmArgs h = halves_args(ga);
-    if (ga.N % 48 == 0) gemm_tiles<SkinnyW96, EpiSwiGLUHalves<bf16_t, 48>, false>(h, EpiSwiGLUHalves<bf16_t, 48>{e.act, ga.N}, row_lo, INT_MAX, 1, first, step, sm);
-    else gemm_tiles<SkinnyH128, EpiSwiGLUHalves<bf16_t, 64>, false>(h, EpiSwiGLUHalves<bf16_t, 64>{e.act, ga.N}, row_lo, INT_MAX, 1, first, step, sm);
+    if (ga.N % 48 == 0) gemm_tiles<SkinnyW96, EpiSwiGLUHalves<bf16_t, 48>, false>(h, EpiSwiGLUHalves<bf16_t, 48>{e.act, ga.N}, M, row_lo, INT_MAX, 1, w);
+    else gemm_tiles<SkinnyH128, EpiSwiGLUHalves<bf16_t, 64>, false>(h, EpiSwiGLUHalves<bf16_t, 64>{e.act, ga.N}, M, row_lo, INT_MAX, 1, w);
   }
 };
 

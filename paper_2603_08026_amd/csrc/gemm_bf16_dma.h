@@ -123,15 +123,29 @@ __device__ __forceinline__ int own_lane() {
   return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
 }
 
-// The tiles of list rows [row_lo, min(count, row_hi)) (row_lo is a multiple of BM) with `splitk` K splits,
-// those with numbers first, first + step, ... .  Splits are cut in whole K slices and may differ by one.
+// How a workgroup walks the tiles: the first one's number and the distance to the next; the wave's number (scalar)
+// and the LDS.  (Read off the thread's number once per kernel: a later shape's use of it would keep a register across
+// the loop of an earlier one.)
+struct Walk {
+  int first, step, wave;
+  unsigned char *smem;
+};
+__device__ __forceinline__ Walk walk_of(unsigned char *smem) {
+  return Walk{(int)blockIdx.x, (int)gridDim.x, (int)__builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), smem};
+}
+
+// Rows of a list that exist
+__device__ __forceinline__ int rows_that_exist(const Rows &rows) { return rows.count ? min(*rows.count, rows.cap) : rows.cap; }
+
+// The tiles of rows [row_lo, min(M_all, row_hi)) of a list of M_all rows (row_lo is a multiple of BM) with `splitk` K splits,
+// those that `walk` names.  Splits are cut in whole K slices and may differ by one.
 // SPLIT: the tile goes to the raw fp32 result part[z][j][n] instead of through the
 // fused epilogue.  A compile-time switch: with both forms behind a run-time branch the compiler
 // moves the accumulators out of the accumulation registers ahead of the branch, where they do not
 // fit, and the epilogue's stores each wait for a reload from scratch memory.
 template <typename SH, typename Epi, bool SPLIT>
-__device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, int row_lo, int row_hi, int splitk,
-                                           int first, int step, unsigned char *smem_raw) {
+__device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, int M_all, int row_lo, int row_hi, int splitk,
+                                           const Walk &walk) {
   constexpr int BM = SH::BM, BN = SH::BN, MB = SH::MB, NB = SH::NB, NMAT = SH::NMAT, NS = SH::NS, NW = SH::NW;
   constexpr int group_m = 4;
   const bf16_t *const A = ga.A;
@@ -141,13 +155,13 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
   const Rows rows = ga.rows;
   const WSeg &seg = ga.seg;
 
-  const int M_all = rows.count ? min(*rows.count, rows.cap) : rows.cap;
   const int M = min(M_all, row_hi);
   const SplitStore split{ga.part, (size_t)M_all * N, N};
   const int tm_lo = row_lo / BM;
   const int m_rel = max(M - tm_lo * BM, 0);
   const int tiles_m = (m_rel + BM - 1) / BM, tiles_n = N / BN;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);  // wave-uniform, kept scalar
+  const int first = walk.first, step = walk.step, wave = walk.wave;
+  unsigned char *const smem_raw = walk.smem;
   const int lane = own_lane(), tid = wave * WAVE + lane;
   const int wm0 = (wave / SH::WAVES_N) * SH::WM, wn0 = (wave % SH::WAVES_N) * SH::WN;
   const int l32 = lane % 32, lhi = lane / 32;
@@ -486,16 +500,22 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) src.va[i] = (uint32_t)(((size_t)srow[i] * lda + kbeg + csrc * 8) * 2);
+      // The matrices' addresses and ends are fetched together and selected from: left to itself the compiler fetches
+      // each descriptor's address from the kernel arguments when it knows which one it is, one wait after the other
+      // (eight of them in the 256 x 256 tile).
+      const void *w[4] = {seg.w[0], seg.w[1], seg.w[2], W2};
+      int n_end[2] = {seg.n_end[0], seg.n_end[1]};
+      asm volatile("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[2]), "+s"(w[3]), "+s"(n_end[0]), "+s"(n_end[1]));
 #pragma unroll
-      for (int c = 0; c < NWC; ++c) {
-        const int t = c / SH::B_LD, i = c % SH::B_LD;
+      for (int d = 0; d < RingFull::ND; ++d) {
+        const int c = d * (NWC / RingFull::ND), t = c / SH::B_LD, i = c % SH::B_LD;
         // the copy's 8 tile rows hold every G-th weight row from nu on (wave-uniform): rows of one panel, and
         // so of one matrix, whose ends are multiples of 16 G (ring_groups_ok)
         const int nu = n0 + RingFull::weight_row(i, wave);
-        const bool in1 = nu >= seg.n_end[0], in2 = nu >= seg.n_end[1];
-        const void *base = t == 1 ? (const void *)W2 : in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0];
-        const int nl = nu - (t == 1 ? 0 : in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0);  // row in its matrix
-        src.srd_w[c] = make_srd((const bf16_t *)base + ((size_t)(nl / WPANEL) * KS + kbeg / BK) * (WPANEL * BK) + (nl % WPANEL) * BK, 0xfffffff0u);
+        const bool in1 = nu >= n_end[0], in2 = nu >= n_end[1];
+        const void *base = t == 1 ? w[3] : in2 ? w[2] : in1 ? w[1] : w[0];
+        const int nl = nu - (t == 1 ? 0 : in2 ? n_end[1] : in1 ? n_end[0] : 0);  // row in its matrix
+        src.srd_w[d] = make_srd((const bf16_t *)base + ((size_t)(nl / WPANEL) * KS + kbeg / BK) * (WPANEL * BK) + (nl % WPANEL) * BK, 0xfffffff0u);
       }
       src.vw = (uint32_t)((G * r8 * BK + csrc * 8) * 2);
     };
@@ -811,7 +831,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
 template <typename SH, typename Epi, bool SPLIT>
 __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(GemmArgs ga, Epi epi, int splitk) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
-  gemm_tiles<SH, Epi, SPLIT>(ga, epi, 0, 0x7fffffff, splitk, blockIdx.x, gridDim.x, smem_raw);
+  gemm_tiles<SH, Epi, SPLIT>(ga, epi, rows_that_exist(ga.rows), 0, 0x7fffffff, splitk, walk_of(smem_raw));
 }
 
 // The 256-row tiles (and the weight-streaming tiles of a short last row tile, or of a list with few
@@ -824,7 +844,8 @@ template <typename Kind>
 __global__ __launch_bounds__(256) void k_gemm_planned(GemmArgs ga, typename Kind::Epi epi, PlanArgs pa, GemmPlan pl,
                                                       int planned, int32_t *plan_out) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
-  const int M = ga.rows.count ? min(*ga.rows.count, ga.rows.cap) : ga.rows.cap;
+  const Walk walk = walk_of(smem_raw);
+  const int M = rows_that_exist(ga.rows);
   if (!planned) pl = plan_on_device(pa, M);
   if (plan_out && blockIdx.x == 0 && threadIdx.x == 0) {
     plan_out[0] = pl.sk;
@@ -832,21 +853,20 @@ __global__ __launch_bounds__(256) void k_gemm_planned(GemmArgs ga, typename Kind
     plan_out[2] = pl.sk_tail;
     plan_out[3] = (Kind::FUSED && pl.sk == 1) ? pl.row_hi : 0;  // rows whose results are in place
   }
-  const int first = blockIdx.x, step = gridDim.x;
   if (pl.row_hi > 0) {
     if (Kind::RAW && (!Kind::FUSED || pl.sk > 1)) {
       if constexpr (Kind::RAW) {
-        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, true>(ga, epi, 0, pl.row_hi, pl.sk, first, step, smem_raw);
-        else gemm_tiles<typename Kind::L, typename Kind::Epi, true>(ga, epi, 0, pl.row_hi, pl.sk, first, step, smem_raw);
+        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, true>(ga, epi, M, 0, pl.row_hi, pl.sk, walk);
+        else gemm_tiles<typename Kind::L, typename Kind::Epi, true>(ga, epi, M, 0, pl.row_hi, pl.sk, walk);
       }
     } else {
       if constexpr (Kind::FUSED) {
-        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, false>(ga, epi, 0, pl.row_hi, 1, first, step, smem_raw);
-        else gemm_tiles<typename Kind::L, typename Kind::Epi, false>(ga, epi, 0, pl.row_hi, 1, first, step, smem_raw);
+        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, false>(ga, epi, M, 0, pl.row_hi, 1, walk);
+        else gemm_tiles<typename Kind::L, typename Kind::Epi, false>(ga, epi, M, 0, pl.row_hi, 1, walk);
       }
     }
   }
-  if (pl.row_hi < M) Kind::stream(ga, epi, pl.row_hi, pl.sk_tail, first, step, smem_raw);
+  if (pl.row_hi < M) Kind::stream(ga, epi, M, pl.row_hi, pl.sk_tail, walk);
 }
 
 template <typename Kind> void set_lds_once_planned() {

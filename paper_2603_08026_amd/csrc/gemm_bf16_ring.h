@@ -66,11 +66,12 @@ constexpr int RING_MIN_SLICES = 3;
 
 // Sources of a wave's copies for one tile:
 //   srd_a / va[i]   descriptor and lane offsets of its 8 A copies (8 tile rows each)
-//   srd_w[c] / vw   the same for its weight copies (8 for a 256-row weight tile, 4 for a 128-row one): a
+//   srd_w[d] / vw   the same for its weight copies (8 for a 256-row weight tile, 4 for a 128-row one): a
 //                   copy's 8 rows lie in one weight panel; the descriptor starts at the first of them, so that
-//                   one lane offset serves all copies
+//                   one lane offset serves all copies, and with G = 4 also at the first of the next copy's,
+//                   which lie two weight rows on
 struct RingSrc {
-  __amdgpu_buffer_rsrc_t srd_a, srd_w[8];
+  __amdgpu_buffer_rsrc_t srd_a, srd_w[4];
   uint32_t va[8], vw;
 };
 
@@ -112,6 +113,11 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
   }
   static constexpr int ROW = 128, A_STEP = 128, W_STEP = 4096;  // bytes per tile row; K walk per slice
 
+  static constexpr int ND = G == 4 ? NWC / 2 : NWC;  // descriptors
+  static __device__ __forceinline__ void copy_w(const RingSrc &src, int c, uint32_t kt, uint32_t lds_addr) {
+    dma16_buf(src.srd_w[c * ND / NWC], src.vw, kt * W_STEP + (G == 4 && c % 2 ? 2 * ROW : 0), lds_addr);
+  }
+
   static __device__ __forceinline__ int w_row(int c) { return (((c / 2) / NB) * BN + ((c / 2) % NB) * 32 + (c % 2) * 16) * ROW; }
   static __device__ __forceinline__ int nxt(int s, int d) { const int t = s + d; return t >= RING_SLOTS ? t - RING_SLOTS : t; }
   // read x of a K step: activation block x (x < 8) or column block x - 8; product p of a K step: row
@@ -131,7 +137,7 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
         for (int i = 0; i < 8; ++i) dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + h * RING_SLOT + i * 4096u);
       } else {
 #pragma unroll
-        for (int c = 0; c < NWC; ++c) dma16_buf(src.srd_w[c], src.vw, (uint32_t)kt * W_STEP, lds_w + h * RING_SLOT + c * 4096u);
+        for (int c = 0; c < NWC; ++c) copy_w(src, c, kt, lds_w + h * RING_SLOT + c * 4096u);
       }
     }
   }
@@ -150,9 +156,6 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
     const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
     auto copy_a = [&](int i, int kt, int slot) {
       dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + (uint32_t)slot * RING_SLOT + i * 4096u);
-    };
-    auto copy_w = [&](int c, int kt, int slot) {
-      dma16_buf(src.srd_w[c], src.vw, (uint32_t)kt * W_STEP, lds_w + (uint32_t)slot * RING_SLOT + c * 4096u);
     };
     if (all_landed) wait_vmcnt<0>();
     else wait_vmcnt<16 + NWC>();  // slice 0 has landed (this wave's part); the rest of the fill is behind it
@@ -222,7 +225,7 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
 #pragma unroll
       for (int q = 0; q < PS; ++q) {
         if (M1 && read_due(q) && has_read(q / RSP)) read(0, q / RSP, sa1, sb1);
-        if (M2 && copy_w_due(q)) copy_w((q + 1) / (PS / NWC) - 1, kt + 2, slot_a);
+        if (M2 && copy_w_due(q)) copy_w(src, (q + 1) / (PS / NWC) - 1, kt + 2, lds_w + (uint32_t)slot_a * RING_SLOT + ((q + 1) / (PS / NWC) - 1) * 4096u);
         if (has_prod(q)) prod(1, q, false);
       }
 #pragma unroll

@@ -111,7 +111,7 @@ __device__ __forceinline__ GemmPlan plan_on_device(const PlanArgs &a, int M) {
   static_assert(PLAN_CANDIDATES == WAVE, "a candidate per lane");
   if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M)};
   // least price with its candidate in the low six bits (prices are positive: they order like their bits)
-  const int lane = threadIdx.x % WAVE;
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
   uint32_t k = (__float_as_uint(plan_price(a, M, lane)) & ~63u) | (uint32_t)lane;
   auto dpp = [](uint32_t v, auto ctrl) -> uint32_t {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, decltype(ctrl)::value, 0xf, 0xf, false);
