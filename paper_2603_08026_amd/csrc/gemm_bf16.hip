@@ -25,6 +25,7 @@ typedef Shape<256, 256, 2, 2, false, 2> XLargeS;
 typedef Shape<256, 128, 2, 2, true, 2> XLargeD;
 typedef Shape<256, 128, 2, 2, false, 2> LargeS;
 typedef Shape<256, 64, 2, 2, true, 2> LargeD;
+static_assert(LargeS::BN == 128 && XLargeS::BN == 256 && LargeD::BN == 64 && XLargeD::BN == 128, "columns that the plans count in");
 typedef Shape<256, 128, 4, 2, false, 2> LargeS8;  // eight waves, two LDS stages
 typedef Shape<256, 64, 4, 2, true, 2> LargeD8;
 typedef Shape<128, 64, 4, 2, false, 4> SkinnyS;
@@ -76,15 +77,8 @@ void run_tiles(const GemmArgs &ga, Epi epi, int splitk, hipStream_t s) {
 
 int ring_grid() { return std::max(N_XCD, cu_count() / N_XCD * N_XCD); }
 
-PlanArgs plan_args(int N, int K, int tiles_l, int tiles_x) {
-  const float cus = (float)(ring_grid() / N_XCD);
-  return PlanArgs{N, K, tiles_l, tiles_x, 1, 0, 0, 0, 0, cus, 1.0f / cus};
-}
-
-// Is the plan made on the host?  When the count is known here; and for a list of up to 256 entries, one row
-// tile whatever its count: the same shapes serve, and the device's own plan costs about 1 us (a step of
-// 166 candidates: 219 us planned on the device, 216 us here; 128 and fewer entries are streamed).
-bool plan_known(const Rows &rows) { return rows.count == nullptr || rows.cap <= 256; }
+int cus_of_xcd() { return ring_grid() / N_XCD; }
+bool plan_known(const Rows &rows) { return mm::plan_known(rows.count != nullptr, rows.cap); }
 
 // GEMM of `rows` in 256-row tiles by a plan: made here (returned in *pl), or on the device, which leaves
 // the splits in plan_dev
@@ -162,10 +156,7 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
   const EpiStoreF32 e{part, N};
   const bool w96 = N % SkinnyW96::BN == 0, ring = ring_ok(A, K, seg, N);
-  PlanArgs pa = plan_args(N, K, N / LargeS::BN, ring && N % XLargeS::BN == 0 ? N / XLargeS::BN : 0);
-  pa.stream_cols = w96 ? SkinnyW96::BN : SkinnyN64::BN;
-  pa.split_ok = pa.split_free = 1;
-  pa.part_elems = (long)part_elems;
+  PlanArgs pa = raw_plan_args(N, K, part_elems, ring, cus_of_xcd());
   if (rows.cap <= STREAM_ROWS) {
     out.n = stream_split(pa, rows.cap);
     if (w96) run_tiles<SkinnyW96, true>(ga, e, out.n, s);
@@ -195,9 +186,7 @@ void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const vo
   } else if (!ring_ok(A, K, seg, N)) {
     run_tiles<LargeD8, false>(ga, e, 1, s);
   } else {
-    PlanArgs pa = plan_args(N, K, N / LargeD::BN, N % XLargeD::BN == 0 ? N / XLargeD::BN : 0);
-    pa.w_cols = 2;
-    pa.stream_cols = streamable ? (N % 48 == 0 ? 48 : 64) : 0;
+    const PlanArgs pa = swiglu_plan_args(N, K, cus_of_xcd());
     GemmPlan pl;
     run_planned<SwigluKind>(ga, e, pa, &pl, nullptr, s);
   }
@@ -210,10 +199,7 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
   const WSeg seg = wseg_one(wd, N);
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
   const bool ring = ring_ok(A, K, seg, N);
-  PlanArgs pa = plan_args(N, K, N / LargeS::BN, ring && N % XLargeS::BN == 0 ? N / XLargeS::BN : 0);
-  pa.stream_cols = SkinnyN64::BN;
-  pa.split_ok = 1;
-  pa.part_elems = (long)part_elems;
+  PlanArgs pa = down_plan_args(N, K, part_elems, ring, cus_of_xcd());
   Splits sp;
   if (rows.cap <= STREAM_ROWS) {
     sp.n = stream_split(pa, rows.cap);
@@ -231,12 +217,7 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
     }
     run_tiles<LargeS8, true>(ga, e, sp.n, s);
   } else {
-    // A plan that splits K needs the sum kernel after it, which costs a launch (about 4 us) where the
-    // device then decides against a split.  A list of up to SUM_CAP entries whose full length is best
-    // done without one gets neither; longer lists are seldom full.
-    constexpr int SUM_CAP = 4096;
-    const GemmPlan full = plan_on_host(pa, rows.cap);
-    const bool sums = full.sk > 1 || full.row_hi < rows.cap || (!plan_known(rows) && rows.cap > SUM_CAP);
+    const bool sums = down_has_sums(pa, rows.cap, plan_known(rows));
     if (!sums) pa.split_ok = pa.stream_cols = 0;
     GemmPlan pl;
     run_planned<DownKind>(ga, e, pa, &pl, plan_dev, s);

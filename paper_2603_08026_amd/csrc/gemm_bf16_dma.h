@@ -162,7 +162,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
   const int tiles_m = (m_rel + BM - 1) / BM, tiles_n = N / BN;
   const int first = walk.first, step = walk.step, wave = walk.wave;
   unsigned char *const smem_raw = walk.smem;
-  const int lane = own_lane(), tid = wave * WAVE + lane;
+  const int lane = own_lane();
   const int wm0 = (wave / SH::WAVES_N) * SH::WM, wn0 = (wave % SH::WAVES_N) * SH::WN;
   const int l32 = lane % 32, lhi = lane / 32;
   const int KS = ldw / BK;  // K slices

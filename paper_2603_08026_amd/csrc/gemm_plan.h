@@ -100,6 +100,48 @@ inline GemmPlan plan_on_host(const PlanArgs &a, int M) {
   return plan_of(a, M, best);
 }
 
+// What the launchers of the three kinds of GEMM make their plans from.  ring: the ring loop's shapes can be taken
+// (ring_ok); part_elems: elements of the buffer of raw results; cus: CUs of an XCD
+inline PlanArgs plan_args(int N, int K, int bn_l, bool wide_ok, int cus) {
+  return PlanArgs{N, K, N / bn_l, wide_ok && N % (2 * bn_l) == 0 ? N / (2 * bn_l) : 0, 1, 0, 0, 0, 0, (float)cus, 1.0f / (float)cus};
+}
+// q|k|v, out-projection: fp32 result, a row kernel follows
+inline PlanArgs raw_plan_args(int N, int K, size_t part_elems, bool ring, int cus) {
+  PlanArgs a = plan_args(N, K, 128, ring, cus);
+  a.stream_cols = N % 96 == 0 ? 96 : 64;
+  a.split_ok = a.split_free = 1;
+  a.part_elems = (long)part_elems;
+  return a;
+}
+// gate|up: SwiGLU in the epilogue
+inline PlanArgs swiglu_plan_args(int N, int K, int cus) {
+  PlanArgs a = plan_args(N, K, 64, true, cus);
+  a.w_cols = 2;
+  a.stream_cols = N % 48 == 0 ? 48 : N % 64 == 0 ? 64 : 0;
+  return a;
+}
+// down projection: residual and scatter in the epilogue, or fp32 sums of a K split
+inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int cus) {
+  PlanArgs a = plan_args(N, K, 128, ring, cus);
+  a.stream_cols = 64;
+  a.split_ok = 1;
+  a.part_elems = (long)part_elems;
+  return a;
+}
+// Is the plan made on the host?  When the count is known here; and for a list of up to 256 entries, one row
+// tile whatever its count: the same shapes serve, and the device's own plan costs 0.5 to 1 us of a GEMM.
+inline bool plan_known(bool count_on_device, int cap) { return !count_on_device || cap <= 256; }
+// Does the down projection get a sum kernel behind it, and so a plan that may split K or stream a last row tile?
+// The kernel costs a launch (about 4 us) where the device then decides against a split.  A list of up to SUM_CAP
+// entries whose full length is best done without one gets neither.  That spares the launch where such a list is
+// full, and is the one place where the capacity still decides: with 4096 columns over K = 12288 it holds for
+// capacities from 2561 to 4096, where few rows then run unsplit (330 rows 161 us by the prices below, 56 us split).
+constexpr int SUM_CAP = 4096;
+inline bool down_has_sums(const PlanArgs &a, int cap, bool known) {
+  const GemmPlan full = plan_on_host(a, cap);
+  return full.sk > 1 || full.row_hi < cap || (!known && cap > SUM_CAP);
+}
+
 // The ring loop's weight copies have one lane offset for all of a tile: the rows they gather lie in one group of
 // RING_GROUP weight rows, and so must lie in one matrix.  (Ends of the stacked matrices; every head size the library
 // accepts is a multiple of 64.)

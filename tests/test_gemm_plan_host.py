@@ -1,16 +1,33 @@
-"""The bf16 GEMMs' launch rules (gemm_plan.h), compiled for the host: no GPU needed."""
+"""The bf16 GEMMs' launch rules (gemm_plan.h), compiled for the host: no GPU needed.  What the GPU tests of the
+planned GEMMs say that their cases run is checked here against the rules, so that a change of the prices cannot
+quietly empty those cases."""
 import ctypes as C
-import os
 import subprocess
 
 import pytest
 
 from paper_2603_08026_amd import build
+from synth import workload as W
+from tests.test_gpu_planned_gemm import NO_SUMS_CAP, REGIMES, SHAPE
 
 SOURCE = r"""
 #include "%s/gemm_plan.h"
 using namespace dy::mm;
 extern "C" int groups_ok(int end0, int end1) { return ring_groups_ok(end0, end1); }
+// kind 0: raw result, 1: gate|up, 2: down; the plan of a list with `count` of `cap` entries (cap < 0: count known on
+// the host) -> columns of the row tiles (0: weight-streaming tiles alone), splits, rows in row tiles, splits behind them,
+// planned on the device, sum kernel
+extern "C" void plan(int kind, int N, int K, long part_elems, int count, int cap, int *out) {
+  PlanArgs a = kind == 0 ? raw_plan_args(N, K, part_elems, true, 32) : kind == 1 ? swiglu_plan_args(N, K, 32)
+                                                                                : down_plan_args(N, K, part_elems, true, 32);
+  const bool known = plan_known(cap >= 0, cap < 0 ? count : cap);
+  const int c = cap < 0 ? count : cap;
+  out[5] = kind == 0 ? 1 : kind == 2 ? down_has_sums(a, c, known) : 0;
+  if (kind == 2 && !out[5]) a.split_ok = a.stream_cols = 0;
+  const GemmPlan p = plan_on_host(a, known ? c : count);
+  out[0] = p.row_hi == 0 ? 0 : p.xl ? 256 : 128;
+  out[1] = p.sk; out[2] = p.row_hi; out[3] = p.sk_tail; out[4] = !known;
+}
 """
 
 
@@ -26,6 +43,17 @@ def lib(tmp_path_factory):
     return C.CDLL(so)
 
 
+class Plan:
+    def __init__(self, lib, shape, gemm, count, cap, tokens):
+        d, dq, dkv, f = shape.hidden, shape.dq, shape.dkv, shape.ffn
+        kind, n, k = {"qkv": (0, dq + 2 * dkv, d), "oproj": (0, d, dq), "gate_up": (1, f, d), "down": (2, d, f)}[gemm]
+        part = max(16 * min(tokens, 2048) * dq, tokens * max(dq + 2 * dkv, d))  # the context's fp32 scratch
+        out = (C.c_int * 6)()
+        lib.plan(kind, n, k, C.c_long(part), count, cap, out)
+        self.cols, self.splits, self.tiled_rows, self.tail_splits, self.on_device, self.sums = out
+        self.streams_tail = 0 < self.tiled_rows < count
+
+
 @pytest.mark.parametrize("end", [8, 16, 24, 40, 4096 + 8, 4096 + 16])
 def test_matrix_ends_inside_a_group_of_permuted_rows_are_not_for_the_ring_loop(lib, end):
     assert not lib.groups_ok(end, 8192)
@@ -36,3 +64,48 @@ def test_matrix_ends_inside_a_group_of_permuted_rows_are_not_for_the_ring_loop(l
 def test_ends_of_the_stacked_projections_are(lib, dq, dkv):
     assert lib.groups_ok(dq, dq + dkv)
     assert lib.groups_ok(dkv, 2 * dkv)
+
+
+@pytest.mark.parametrize("case", range(len(REGIMES)))
+def test_cases_of_the_gpu_test_run_the_plans_they_name(lib, case):
+    shape, count, cap, plans = REGIMES[case]
+    tokens = 4200 if cap > 2200 else 2200
+    for gemm, want in plans.items():
+        p = Plan(lib, shape, gemm, count, cap, tokens)
+        assert p.on_device and (gemm != "down" or p.sums)
+        assert (p.cols, p.splits, p.tiled_rows, p.tail_splits) == want, gemm
+
+
+@pytest.mark.parametrize("count", [1, 128, 129, 330, 640])
+def test_capacities_around_the_range_without_a_sum_kernel(lib, count):
+    for cap, sums in ((1000, True), (NO_SUMS_CAP, False), (4200, True)):
+        p = Plan(lib, SHAPE, "down", count, cap, 4200)
+        assert p.on_device and bool(p.sums) == sums
+        if not sums:
+            assert p.splits == 1 and p.tiled_rows == count  # no split and no streamed rows, however few they are
+        elif count <= 128:
+            assert p.tiled_rows == 0 and p.tail_splits > 1  # weight-streaming tiles alone
+        else:
+            assert p.splits == 3
+
+
+# rows, capacity, FFN width of test_gpu_kernels.py's test of a short last row tile (4096 hidden, 32 over 16 heads) ->
+# the GEMMs that hand the rows behind the full tiles to the weight-streaming tiles, with how many splits
+@pytest.mark.parametrize("count,cap,ffn,streamed", [
+    (2075, 2075, 4096, {"qkv": 2, "oproj": 4, "gate_up": 1}), (2060, 2075, 4096, {"qkv": 2, "oproj": 4, "gate_up": 1}),
+    (1990, 2075, 4096, {}), (1819, 1819, 12288, {}), (1800, 1819, 12288, {})])
+def test_streamed_rows_of_a_short_last_row_tile(lib, count, cap, ffn, streamed):
+    shape = W.LayerShape(hidden=4096, n_heads=32, n_kv_heads=16, head_dim=128, ffn=ffn, dtype="bf16")
+    for gemm in ("qkv", "oproj", "gate_up", "down"):
+        p = Plan(lib, shape, gemm, count, cap, 2200)
+        assert p.streams_tail == (gemm in streamed), gemm
+        assert not p.streams_tail or p.tail_splits == streamed[gemm], gemm
+
+
+@pytest.mark.parametrize("count,cap,cols,streams", [(32668, 32768, 128, False), (16411, 16411, 256, True),
+                                                    (16400, 16411, 256, True), (9000, 16411, 256, False)])
+def test_plans_of_the_many_row_cases(lib, count, cap, cols, streams):
+    shape = W.LayerShape(hidden=1024, n_heads=4, n_kv_heads=2, head_dim=128, ffn=512, dtype="bf16")
+    p = Plan(lib, shape, "qkv", count, cap, 32768 if cap > 17600 else 17600)
+    assert p.streams_tail == streams and p.splits == 1 and p.tail_splits == 1
+    assert p.cols == cols

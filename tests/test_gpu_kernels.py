@@ -388,12 +388,11 @@ def test_four_wave_256x256_tiles_with_short_k_and_stacked_weights(hidden, heads,
 def test_short_last_row_tile_streamed_in_a_launch_of_its_own(M, cap, ffn):
     """Widths at which eight full 256-row tiles fill the chip's 256 CUs exactly (q|k|v 8192, out-projection
     and gate|up 4096 columns over K = 4096), so that the 27 rows of a ninth row tile would open a round of their own:
-    the launchers hand rows 2048.. to the weight-streaming tiles in a second launch, whose K split
-    differs from the first one's.  With fewer rows than the capacity that launch has fewer rows than
-    planned (2060) or none, and the first one a partial tile of its own (1990).  The down projection
-    does the same: with 4096 FFN columns its full tiles go through the fused epilogue and only the streamed
-    rows have partial sums; with 12288 (7 row tiles + 27 rows) the full tiles have a K split of their own,
-    and the sum kernel takes a different number of partial results on either side of row 1792."""
+    rows 2048.. go to the weight-streaming tiles, whose K split (2 for q|k|v, 4 for the out-projection) differs from the
+    row tiles' (none).  With fewer rows than the capacity there are fewer streamed rows (2060) or none and a partial row
+    tile (1990).  The down projection's plans for these counts stream nothing: without a K split at 4096 FFN columns,
+    split in two at 12288 (1819 and 1800 rows, where the other GEMMs stream nothing either).  The plans are checked in
+    test_gemm_plan_host.py; streamed rows of the down projection are in test_gpu_planned_gemm.py."""
     _say("streamed last row tile", M, cap)
     dtype = "bf16"
     s = W.LayerShape(hidden=4096, n_heads=32, n_kv_heads=16, head_dim=128, ffn=ffn, dtype=dtype, rope_theta=10000.0)
@@ -434,12 +433,11 @@ def test_short_last_row_tile_streamed_in_a_launch_of_its_own(M, cap, ffn):
 @pytest.mark.parametrize("B,L,M,cap,bias", [(16, 2048, 32668, 32768, True), (16, 1100, 16411, 16411, True),
                                               (16, 1100, 16400, 16411, False), (16, 1100, 9000, 16411, True)])
 def test_qkv_refresh_with_128_wide_heads_at_many_rows(B, L, M, cap, bias):
-    """bf16 with 128-wide heads and enough rows for 256 x 256 tiles (grouped-query shape: 4 query
-    heads, 2 key/value heads, so a column tile holds q heads, or a k and a v head pair), with and without
-    biases.  Cases: a last row tile of 156 rows inside the same launch; 16384 + 27 rows, where the 27 go
-    to the weight-streaming tiles with a K split of their own; fewer rows than the capacity, so that
-    the second launch has 16 rows, or none and the first one a partial tile.  Rows outside the list
-    keep their cached keys and values bit for bit."""
+    """bf16 with 128-wide heads and many rows (grouped-query shape: 4 query heads, 2 key/value heads, so a column tile
+    holds q heads, or a k and a v head pair), with and without biases.  Cases: a last row tile of 156 rows beside full
+    256 x 128 tiles; 16384 + 27 rows, where the 27 go to the weight-streaming tiles behind 256 x 256 ones; fewer rows than
+    the capacity, so that 16 rows are streamed, or none and the last row tile is a partial one.  Rows outside the list
+    keep their cached keys and values bit for bit.  The plans are checked in test_gemm_plan_host.py."""
     _say("q/k/v refresh, 128-wide heads, many rows", B, L, M, cap)
     dtype = "bf16"
     s = W.LayerShape(hidden=1024, n_heads=4, n_kv_heads=2, head_dim=128, ffn=512, dtype=dtype, rope_theta=10000.0)
