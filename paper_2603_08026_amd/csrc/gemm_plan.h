@@ -132,14 +132,18 @@ inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int c
 // tile whatever its count: the same shapes serve, and the device's own plan costs 0.5 to 1 us of a GEMM.
 inline bool plan_known(bool count_on_device, int cap) { return !count_on_device || cap <= 256; }
 // Does the down projection get a sum kernel behind it, and so a plan that may split K or stream a last row tile?
-// The kernel costs a launch (about 4 us) where the device then decides against a split.  A list of up to SUM_CAP
-// entries whose full length is best done without one gets neither.  That spares the launch where such a list is
-// full, and is the one place where the capacity still decides: with 4096 columns over K = 12288 it holds for
-// capacities from 2561 to 4096, where few rows then run unsplit (330 rows 161 us by the prices below, 56 us split).
+// Always where the plan for the full length wants it.  Where the device may find fewer rows, also if the list is long
+// (SUM_CAP) or K is: a few rows without a split take the whole K loop of one row tile, against the sum kernel's
+// launch of about 4 us where it then finds nothing to do.  The line is at ten such launches (K = 3200 and longer).
+// FFN half at hidden 4096, FFN 12288, lists of 3000 without / with the sum kernel: 40 rows 215 / 92 us, 330 rows
+// 274 / 172 us; a full list of 2600 777 / 783 us.  At hidden 1024, FFN 1664, 330 rows would gain 6 us and a full list
+// lose 4 of 86.
 constexpr int SUM_CAP = 4096;
+constexpr float SUM_LOOP_US = 40.0f;
+inline float loop_us(int K) { return 51.3f / 4096.0f * (float)K; }  // K loop of a 256 x 128 tile (plan_price)
 inline bool down_has_sums(const PlanArgs &a, int cap, bool known) {
   const GemmPlan full = plan_on_host(a, cap);
-  return full.sk > 1 || full.row_hi < cap || (!known && cap > SUM_CAP);
+  return full.sk > 1 || full.row_hi < cap || (!known && (cap > SUM_CAP || loop_us(a.K) >= SUM_LOOP_US));
 }
 
 // The ring loop's weight copies have one lane offset for all of a tile: the rows they gather lie in one group of

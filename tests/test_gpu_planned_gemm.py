@@ -16,7 +16,7 @@ from synth import workload as W
 pytestmark = pytest.mark.gpu
 
 SHAPE = W.LayerShape(hidden=1024, n_heads=8, n_kv_heads=2, head_dim=128, ffn=1664, dtype="bf16")
-NO_SUMS_CAP = 2600  # full, the list would not split the down projection's K: no sum kernel, no split for any count
+NO_SUMS_CAP = 2600  # full, the list would not split the down projection's (short) K: no sum kernel, no split for any count
 WIDE = W.LayerShape(hidden=4096, n_heads=32, n_kv_heads=16, head_dim=128, ffn=12288, dtype="bf16")
 SHORT_K = W.LayerShape(hidden=4096, n_heads=32, n_kv_heads=8, head_dim=128, ffn=2048, dtype="bf16")
 
@@ -32,6 +32,8 @@ REGIMES = [
     (SHORT_K, 4129, 4200, {"down": (256, 1, 4096, 4)}),
     # ... and finished in all rows: the sum kernel finds nothing to do
     (SHAPE, 2600, 4200, {"down": (128, 1, 2600, 1)}),
+    # a few rows in a list that needs no split when it is full
+    (WIDE, 330, 3000, {"down": (128, 4, 330, 1)}),
 ]
 
 
