@@ -29,10 +29,11 @@ struct GemmPlan { int xl, sk, row_hi, sk_tail; };
 //                      otherwise a split or a streamed tail costs a sum kernel
 //   part_elems         fp32 elements of the buffer of raw results
 //   cus, inv_cus       CUs of an XCD
+//   stream_us          price of a streamed last row tile
 struct PlanArgs {
   int N, K, tiles_l, tiles_x, w_cols, stream_cols, split_ok, split_free;
   long part_elems;
-  float cus, inv_cus;
+  float cus, inv_cus, stream_us;
 };
 
 constexpr int PLAN_BK = 64, PLAN_XCD = 8;
@@ -51,15 +52,16 @@ __host__ __device__ inline int stream_split(const PlanArgs &a, int M) {
 }
 
 // Price of candidate c in microseconds, or a huge value if it cannot be taken.  The constants are
-// fitted to the measured times of every candidate at 18 row counts from 140 to 3000 for seven GEMMs of
-// two layer shapes (126 points, weights cold): the candidate with the least price is on average 0.2 %,
-// at worst 5 %, slower than the fastest one.  What they say:
+// fitted to measured times of seven GEMMs of two layer shapes (hidden 4096 and 3584).  Every candidate was then timed
+// for 23 GEMMs of six layer shapes (hidden 256 to 4096) at 14 row counts from 140 to 5000: the candidate with the least
+// price is on average 0.25 % slower than the fastest one, at worst 11 % (322 points, weights of 16 copies in turn:
+// profiles/gemm_plan_candidates.md).  What they say:
 //   - a CU takes 51 us for the K loop of a 256 x 128 tile over K = 4096 and 1.31 times that for a
 //     256 x 256 one, and 6.9 or 13.8 us per tile for what surrounds the loop;
 //   - an XCD's CUs take its positions of the tile order in turn (gemm_tiles): full tiles first, then the
 //     tiles of a last row tile with fewer than 256 rows, which cost a fraction of a full one (they
 //     still walk all of K with their copies) and first fill the slots the full tiles leave;
-//   - weights arrive at 4 TB/s whatever the tiles do, at 5.3 TB/s in the streaming tiles;
+//   - weights arrive at 4 TB/s whatever the tiles do; in the streaming tiles as with_stream_price says;
 //   - every K split moves its fp32 sums once more, written and read.
 __host__ __device__ inline float plan_price(const PlanArgs &a, int M, int c) {
   const int sk = c % PLAN_MAX_SPLIT + 1, xl = (c / PLAN_MAX_SPLIT) & 1, streamed = c / (2 * PLAN_MAX_SPLIT);
@@ -80,7 +82,7 @@ __host__ __device__ inline float plan_price(const PlanArgs &a, int M, int c) {
   const float sums = 1.29e-6f * (float)M * (float)a.N;
   if (a.split_free) t += sums * (float)(sk - 1);
   else if (a.split_ok && (sk > 1 || streamed)) t += sums * (float)sk + 4.0f;
-  if (streamed) t += 2.3f + w_bytes * (1.0f / 5.26e6f);
+  if (streamed) t += a.stream_us;
   return ok ? t : 3e30f;
 }
 
@@ -103,7 +105,16 @@ inline GemmPlan plan_on_host(const PlanArgs &a, int M) {
 // What the launchers of the three kinds of GEMM make their plans from.  ring: the ring loop's shapes can be taken
 // (ring_ok); part_elems: elements of the buffer of raw results; cus: CUs of an XCD
 inline PlanArgs plan_args(int N, int K, int bn_l, bool wide_ok, int cus) {
-  return PlanArgs{N, K, N / bn_l, wide_ok && N % (2 * bn_l) == 0 ? N / (2 * bn_l) : 0, 1, 0, 0, 0, 0, (float)cus, 1.0f / (float)cus};
+  return PlanArgs{N, K, N / bn_l, wide_ok && N % (2 * bn_l) == 0 ? N / (2 * bn_l) : 0, 1, 0, 0, 0, 0, (float)cus, 1.0f / (float)cus, 0.0f};
+}
+// The streaming tiles read the weights once, at 5.3 TB/s together and at most 34.5 GB/s each (gate|up has no K
+// split: with 88 tiles of 5632 columns over K = 2048 a streamed last row tile takes 18 us, not the 11 of the rate of
+// all CUs)
+inline PlanArgs with_stream_price(PlanArgs a) {
+  if (!a.stream_cols) return a;
+  const float w_bytes = (float)a.N * (float)a.w_cols * (float)a.K * 2.0f, tiles = (float)(a.N / a.stream_cols * stream_split(a, 1));
+  a.stream_us = 2.3f + fmaxf(w_bytes * (1.0f / 5.26e6f), w_bytes / tiles * (1.0f / 34.5e3f));
+  return a;
 }
 // q|k|v, out-projection: fp32 result, a row kernel follows
 inline PlanArgs raw_plan_args(int N, int K, size_t part_elems, bool ring, int cus) {
@@ -111,14 +122,14 @@ inline PlanArgs raw_plan_args(int N, int K, size_t part_elems, bool ring, int cu
   a.stream_cols = N % 96 == 0 ? 96 : 64;
   a.split_ok = a.split_free = 1;
   a.part_elems = (long)part_elems;
-  return a;
+  return with_stream_price(a);
 }
 // gate|up: SwiGLU in the epilogue
 inline PlanArgs swiglu_plan_args(int N, int K, int cus) {
   PlanArgs a = plan_args(N, K, 64, true, cus);
   a.w_cols = 2;
   a.stream_cols = N % 48 == 0 ? 48 : N % 64 == 0 ? 64 : 0;
-  return a;
+  return with_stream_price(a);
 }
 // down projection: residual and scatter in the epilogue, or fp32 sums of a K split
 inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int cus) {
@@ -126,7 +137,7 @@ inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int c
   a.stream_cols = 64;
   a.split_ok = 1;
   a.part_elems = (long)part_elems;
-  return a;
+  return with_stream_price(a);
 }
 // Is the plan made on the host?  When the count is known here; and for a list of up to 256 entries, one row
 // tile whatever its count: the same shapes serve, and the device's own plan costs 0.5 to 1 us of a GEMM.
