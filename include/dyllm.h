@@ -16,7 +16,10 @@
  *  - Tensors are dense row-major (the weight matrices of bf16 contexts excepted:
  *    see dyllm_layer_weights).  A "token id" is b*L + i for position i of
  *    sequence b; T = B*L.  Element type is the context's dtype (fp32 or bf16)
- *    unless a parameter says otherwise.
+ *    unless a parameter says otherwise.  Tensors are expected to start at a
+ *    multiple of 16 bytes, as allocators return them (not checked): kernels read
+ *    and write up to 16 bytes of a row at a time.  Index lists, offsets and
+ *    flags need their element's alignment only.
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    Calls only enqueue work on it: no device synchronisation, no device-to-host
  *    copy.  Row counts stay on the device (offsets[B]).

@@ -33,9 +33,9 @@
 // The 256-row tiles of the ring loop use v_mfma_f32_16x16x32_bf16 with a permuted order of the weight rows,
 // so that neighbouring lanes hold neighbouring runs of columns of one row (gemm_bf16_ring.h).
 //
-// Tile walk.  The row count lives on the device; the grid is sized from the list capacity and each
-// workgroup walks the existing tiles in a grouped order, remapped so that neighbouring tiles run on
-// one XCD (workgroup i is dispatched to XCD i % 8) and share A / weight tiles in its L2.  gemm_tiles
+// Tile walk.  The row count lives on the device; the grid is one workgroup per CU (k_gemm_planned) or sized
+// from the list capacity (k_gemm_bf16), and each workgroup walks the existing tiles in a grouped order, remapped so
+// that neighbouring tiles run on one XCD (workgroup i is dispatched to XCD i % 8) and share A / weight tiles in its L2.  gemm_tiles
 // covers a window of list rows [row_lo, row_hi), so that a short last row tile can go to another tile
 // shape.
 //

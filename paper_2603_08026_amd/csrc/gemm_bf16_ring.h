@@ -12,7 +12,7 @@
 // barrier per slice, in its middle: by then a wave has the operands of the whole slice in registers
 // (128 of them), so the two slots of slice kt are free; W(kt+2) is copied into one during the second
 // half of slice kt and A(kt+3) into the other during the first half of slice kt+1 -- one copy after
-// every fourth matrix instruction, all the time -- and the eight newest copies stay in flight across
+// every eighth matrix instruction (every fourth for the A half beside a 128-row weight tile), all the time -- and the eight newest copies stay in flight across
 // the barrier (s_waitcnt vmcnt(8) and a raw s_barrier: __syncthreads would wait for all of them).
 //
 // The copies are buffer loads with LDS destination: a scalar descriptor per source matrix, a 32-bit
@@ -176,8 +176,8 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
     // read r of the other K step goes behind product RSP * r
     auto read_due = [](int q) { return q % RSP == 0 && q / RSP < RD; };
     // slot of A(kt); W(kt) is in the next one.  (Hidden from the optimiser: with a known start the first
-    // slice's operand addresses lie past the reach of an LDS offset, are computed once per kernel, and are
-    // then reloaded from scratch memory in every tile, each reload waiting for all copies in flight.)
+    // slice's operand addresses lie past the reach of an LDS offset and are computed once per kernel, which
+    // has no registers to keep them.)
     int slot_a = 0;
     asm volatile("" : "+s"(slot_a));
 #pragma unroll

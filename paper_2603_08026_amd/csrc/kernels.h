@@ -82,7 +82,9 @@ void launch_cos_compact(const float *cos_part, int H, float tau, float *cos_out,
 // cap 0 is none) in one launch: flags of all tokens to flag_out, the flagged tokens compacted as by
 // launch_compact.  B*L <= MERGE_TOKENS: every workgroup of 256 tokens reads both lists.  Against the four
 // launches this replaces (clear, mark twice, compact: 15.8 us): two lists of 80 entries 8.3 us; two full ones
-// 14.6 us at 8192 tokens, 40.7 us at 32768, so the line lies where full lists still gain.
+// 14.6 us at 8192 tokens, 40.7 us at 32768.  Every workgroup reads both lists whole, so the time grows with their
+// length: the line is the largest of the measured sizes at which even full lists gain.  Short lists, which are the
+// usual ones, would gain beyond it.
 void launch_merge_compact(Rows a, Rows b, int pos_lo, uint8_t *flag_out, int B, int L, int32_t *out_idx,
                           int32_t *out_offsets, int out_cap, int32_t *status, int32_t *scan, hipStream_t s);
 constexpr int MERGE_TOKENS = 8192;

@@ -390,8 +390,10 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int n) {
 }
 
 // Workgroups of a row kernel.  Where the count is on the device the capacity may be far above it, and
-// workgroups without a row are not free (8192 of 1024 threads each for 330 rows: k_qkv_finalize 12.7 us);
-// 1024 of them are two per CU, resident at once, and take further rows in turn.
+// workgroups without a row are not free (8192 of 1024 threads each for 330 rows: k_qkv_finalize 12.7 us, with
+// 1024 of them 11.3 us).  Of the 1024-thread ones 512 are resident at once (two per CU); they take further rows in
+// turn.  Full lists lose nothing by it: q/k/v stage at hidden 256 / 4096, 20480 listed rows, 96 -> 85 / 1937 -> 1820 us
+// together with what the GEMMs gained.
 constexpr int GRID_KNOWN = 8192, GRID_LISTED = 1024;
 inline int row_grid(const Rows &rows, int cap) {
   const int most = rows.count ? GRID_LISTED : GRID_KNOWN;
