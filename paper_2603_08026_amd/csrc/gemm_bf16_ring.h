@@ -12,8 +12,9 @@
 // barrier per slice, in its middle: by then a wave has the operands of the whole slice in registers
 // (128 of them), so the two slots of slice kt are free; W(kt+2) is copied into one during the second
 // half of slice kt and A(kt+3) into the other during the first half of slice kt+1 -- one copy after
-// every eighth matrix instruction (every fourth for the A half beside a 128-row weight tile), all the time -- and the eight newest copies stay in flight across
-// the barrier (s_waitcnt vmcnt(8) and a raw s_barrier: __syncthreads would wait for all of them).
+// every eighth matrix instruction (every fourth for the A half beside a 128-row weight tile), all the
+// time -- and the eight newest copies stay in flight across the barrier (s_waitcnt vmcnt(8) and a raw
+// s_barrier: __syncthreads would wait for all of them).
 //
 // The copies are buffer loads with LDS destination: a scalar descriptor per source matrix, a 32-bit
 // byte offset per lane that is fixed for the tile, and the K walk as a scalar offset, so a copy costs
@@ -76,13 +77,13 @@ struct RingSrc {
 };
 
 // Matrix instruction and column order.  v_mfma_f32_16x16x32_bf16: element e of lane l's four registers is
-// activation row 4 * (l / 16) + e and column l % 16 of its 16 x 16 block.  The weight rows of G blocks (four, or
-// two where a wave has two of a matrix) are permuted on their way into LDS so that lane l % 16 of the G blocks holds
-// columns G * (l % 16) .. + G - 1 of the 16 G: its results of a row are one store (16 bytes of fp32; 8 or 4 of bf16), and the 16
-// lanes after one another fill 256 (128, 64) bytes of the row.  The copy and store path takes four lanes at a time, and they
-// have to lie next to each other: with the weights as FIRST operand, where a lane holds eight columns but
-// neighbouring lanes different rows, a 16-byte store of a wave took 64 cycles instead of 16, and the raw store of a
-// 256 x 128 tile 7700 cycles instead of 3400.
+// activation row 4 * (l / 16) + e and column l % 16 of its 16 x 16 block.  The weight rows of G blocks (four,
+// or two where a wave has two of a matrix) are permuted on their way into LDS so that lane l % 16 of the G
+// blocks holds columns G * (l % 16) .. + G - 1 of the 16 G: its results of a row are one store (16 bytes of
+// fp32; 8 or 4 of bf16), and those of the 16 lanes fill 256 (128, 64) bytes of the row.  The store path takes
+// four lanes at a time, and they have to lie next to each other: with the weights as FIRST operand, where a lane
+// holds eight columns but neighbouring lanes different rows, a 16-byte store of a wave took 64 cycles instead
+// of 16, and the raw store of a 256 x 128 tile 7700 cycles instead of 3400.
 // The 16x16 form does the same products with less power than the 32x32 one, and the matrix clock is power-bound:
 // operands in registers, all CUs busy, random values: 1.85 against 1.75 PFLOP/s.
 //

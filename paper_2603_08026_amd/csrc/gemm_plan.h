@@ -54,8 +54,8 @@ __host__ __device__ inline int stream_split(const PlanArgs &a, int M) {
 // Price of candidate c in microseconds, or a huge value if it cannot be taken.  The constants are
 // fitted to measured times of seven GEMMs of two layer shapes (hidden 4096 and 3584).  Every candidate was then timed
 // for 23 GEMMs of six layer shapes (hidden 256 to 4096) at 14 row counts from 140 to 5000: the candidate with the least
-// price is on average 0.25 % slower than the fastest one, at worst 11 % (322 points, weights of 16 copies in turn:
-// profiles/gemm_plan_candidates.md).  What they say:
+// price is on average 0.25 % slower than the fastest one, at worst 11 % (322 points, weights of up to 16 copies in
+// turn).  What they say:
 //   - a CU takes 51 us for the K loop of a 256 x 128 tile over K = 4096 and 1.31 times that for a
 //     256 x 256 one, and 6.9 or 13.8 us per tile for what surrounds the loop;
 //   - an XCD's CUs take its positions of the tile order in turn (gemm_tiles): full tiles first, then the
