@@ -103,7 +103,7 @@ __device__ __forceinline__ void block_sum3(float &a, float &b, float &c, float *
 __device__ __forceinline__ void dma16(const void *g, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                :
-               : "s"(lds_base), "v"(g)
+               : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(g)
                : "memory", "m0");
 }
 

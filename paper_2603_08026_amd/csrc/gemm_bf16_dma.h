@@ -81,8 +81,9 @@ template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, bool DUAL_, int NS_> str
   static constexpr int B_LD = BN / (8 * NW);
   static constexpr int LPS = A_LD + NMAT * B_LD;  // copies per wave and slice
   static constexpr int A_BYTES = BM * ROWB, W_BYTES = NMAT * BN * ROWB;
-  // four waves on a 256-row tile with 256 or 128 weight rows: the five-slot ring loop
-  static constexpr bool RING = NW == 4 && BM == 256 && (NMAT * BN == 256 || NMAT * BN == 128) && NS == 2;
+  // four waves on a tile of up to 256 rows with 256, 192 or 128 weight rows: the five-slot ring loop
+  static constexpr bool RING = NW == 4 && BM == 256 && NS == 2;
+  static constexpr int RING_ROWS = 16 * WAVES_M;  // a ring tile's rows are a multiple of this
   static constexpr size_t LDS_BYTES = RING ? (size_t)RING_SLOTS * RING_SLOT : (size_t)NS * (A_BYTES + W_BYTES);
   // shapes with three or more stages (weight streaming) run the loop pipelined over slices
   static constexpr bool PIPE = NS >= 3;
@@ -138,18 +139,32 @@ __device__ __forceinline__ Walk walk_of(unsigned char *smem) {
 __device__ __forceinline__ int rows_that_exist(const Rows &rows) { return rows.count ? min(*rows.count, rows.cap) : rows.cap; }
 
 // The tiles of rows [row_lo, min(M_all, row_hi)) of a list of M_all rows (row_lo is a multiple of BM) with `splitk` K splits,
-// those that `walk` names.  Splits are cut in whole K slices and may differ by one.
+// those that `walk` names.  Ring shapes: tiles of `ring_rows` rows (a multiple of RING_ROWS, at most BM), row_lo = 0.  Splits are cut in whole K slices and may differ by one.
 // SPLIT: the tile goes to the raw fp32 result part[z][j][n] instead of through the
 // fused epilogue.  A compile-time switch: with both forms behind a run-time branch the compiler
 // moves the accumulators out of the accumulation registers ahead of the branch, where they do not
 // fit, and the epilogue's stores each wait for a reload from scratch memory.
+// f(MI) for the number of 16-row blocks per wave of a tile, of at most MAX: every count has a path of its own
+template <int MAX, typename F> __device__ __forceinline__ bool with_blocks(int mi, F &&f) {
+  if constexpr (MAX > 4) {
+    if (mi == 8) return f(std::integral_constant<int, 8>{});
+    if (mi == 7) return f(std::integral_constant<int, 7>{});
+    if (mi == 6) return f(std::integral_constant<int, 6>{});
+    if (mi == 5) return f(std::integral_constant<int, 5>{});
+  }
+  if (mi == 4) return f(std::integral_constant<int, 4>{});
+  if (mi == 3) return f(std::integral_constant<int, 3>{});
+  if (mi == 2) return f(std::integral_constant<int, 2>{});
+  return f(std::integral_constant<int, 1>{});
+}
+
 template <typename SH, typename Epi, bool SPLIT>
 __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, int M_all, int row_lo, int row_hi, int splitk,
-                                           const Walk &walk) {
+                                           const Walk &walk, int ring_rows = SH::BM) {
   constexpr int BM = SH::BM, BN = SH::BN, MB = SH::MB, NB = SH::NB, NMAT = SH::NMAT, NS = SH::NS, NW = SH::NW;
   constexpr int group_m = 4;
   const bf16_t *const A = ga.A;
-  const int32_t *const gather = ga.gather;
+  const int32_t *const gather = Epi::GATHER ? ga.gather : nullptr;
   const bf16_t *const W2 = ga.W2;
   const int lda = ga.lda, N = ga.N, ldw = ga.K;
   const Rows rows = ga.rows;
@@ -157,9 +172,17 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
 
   const int M = min(M_all, row_hi);
   const SplitStore split{ga.part, (size_t)M_all * N, N};
-  const int tm_lo = row_lo / BM;
+  const int bm = SH::RING ? ring_rows : BM;
+  const int tm_lo = SH::RING ? 0 : row_lo / BM;
   const int m_rel = max(M - tm_lo * BM, 0);
-  const int tiles_m = (m_rel + BM - 1) / BM, tiles_n = N / BN;
+  // (ring tiles: list lengths are below 2^30 and a quotient's product with 1/bm may round either way)
+  int tiles_m = (m_rel + BM - 1) / BM;
+  if (SH::RING && bm != BM) {
+    tiles_m = __builtin_amdgcn_readfirstlane((int)((float)m_rel * __builtin_amdgcn_rcpf((float)bm)));
+    while (tiles_m * bm < m_rel) ++tiles_m;
+    while (tiles_m > 0 && (tiles_m - 1) * bm >= m_rel) --tiles_m;
+  }
+  const int tiles_n = N / BN;
   const int first = walk.first, step = walk.step, wave = walk.wave;
   unsigned char *const smem_raw = walk.smem;
   const int lane = own_lane();
@@ -184,7 +207,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
   // (see the partial loop below) and fill the end of every XCD's schedule instead of one XCD's.
   // With K splits the list of full tiles is the order above once per split, and so is that of the partial
   // ones: an XCD's run then mostly holds tiles of one split, which read the same part of K.
-  const int has_tail = (m_rel % BM != 0) ? 1 : 0;
+  const int has_tail = tiles_m * bm != m_rel ? 1 : 0;
   const int rows_full = tiles_m - has_tail;
   const int n_full = rows_full * tiles_n, n_part = has_tail * tiles_n;
   const int fx = (n_full * splitk + N_XCD - 1) / N_XCD, px = (n_part * splitk + N_XCD - 1) / N_XCD;
@@ -394,11 +417,13 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     // Four-wave ring shapes.  The workgroup walks its tiles itself (the launcher starts one per CU),
     // and the ring is refilled for the next tile before the epilogue of the current one, so that
     // the first slices of a tile land while the previous tile's results are written.
-    using RingFull = Ring<NMAT, NB, BN, 4>;
+    constexpr int WR = SH::WAVES_M, RR = SH::RING_ROWS, MAX_MI = BM / RR;
+    using RingFull = Ring<NMAT, NB, BN, WR, MAX_MI>;
     constexpr int NWC = RingFull::NWC;
     static_assert(Epi::INTERLEAVE == 0 && SH::A_LD == 8 && NMAT * SH::B_LD == NWC, "ring shapes");
-    // Epilogue of one tile whose wave rows start at rbase and columns at cbase (both wave-uniform): this lane has
-    // row rbase + 16 i + 4 lq + e in element e of acc[t][i][..], column cbase + 16 G q + G l16 + h in block G q + h
+    const int wr = wave / SH::WAVES_N;  // wave row
+    // Epilogue of one tile whose first row of this wave is rbase and first column cbase (both wave-uniform): this lane has
+    // row rbase + RR i + 4 lq + e in element e of acc[t][i][..], column cbase + 16 G q + G l16 + h in block G q + h
     // (gemm_bf16_ring.h).  Row-ordered operands are addressed through buffer descriptors that end with the last
     // row: what lies past it is neither read nor written, without a branch per row (a branch around a load makes
     // the compiler wait for the load where the paths meet: 38000 instead of 14000 cycles for the down epilogue).
@@ -406,10 +431,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     auto ring_epilogue = [&](auto &acc, int rbase, int cbase, int z) {
       constexpr int MI = sizeof(acc[0]) / sizeof(acc[0][0]);  // 16-row blocks
       const int ln = own_lane(), l16 = ln % 16, lq = ln / 16;
-      // rows of block i on; descriptor of rows [16 i, ..) of a [., N] operand of esz bytes per element
-      auto left = [&](int i) -> int { return __builtin_amdgcn_readfirstlane(min(max(M - rbase - 16 * i, 0), 16)); };
+      // rows of block i that exist; descriptor of its rows of a [., N] operand of esz bytes per element
+      auto left = [&](int i) -> int { return __builtin_amdgcn_readfirstlane(min(max(M - rbase - RR * i, 0), 16)); };
       auto block = [&](const void *p, int i, int esz) {
-        return make_srd((const char *)p + ((size_t)(rbase + 16 * i) * N + cbase) * esz, left(i) ? (uint32_t)(left(i) * N - cbase) * esz : 0);
+        return make_srd((const char *)p + ((size_t)(rbase + RR * i) * N + cbase) * esz, left(i) ? (uint32_t)(left(i) * N - cbase) * esz : 0);
       };
       uint32_t lane_row[4];  // element offsets of this lane's four rows in a block
 #pragma unroll
@@ -434,7 +459,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
         int row[2][4];
         auto load = [&](int i) {
           const auto res = block(epi.h, i, 4);
-          const auto list = make_srd(rows.idx + (rows.idx ? rbase + 16 * i : 0), rows.idx ? left(i) * 4u : 0);
+          const auto list = make_srd(rows.idx + (rows.idx ? rbase + RR * i : 0), rows.idx ? left(i) * 4u : 0);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             row[i & 1][e] = __builtin_amdgcn_raw_buffer_load_b32(list, lq * 16 + e * 4, 0, 0);
@@ -453,7 +478,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
 #pragma unroll
               for (int q = 0; q < NQ; ++q) {
                 const floatx4 a = {acc[0][i][G * q][e], acc[0][i][G * q + 1][e], acc[0][i][G * q + 2][e], acc[0][i][G * q + 3][e]};
-                epi.store4(rows.idx ? row[i & 1][e] : rbase + 16 * i + r, cbase + 16 * G * q + G * l16, a, pre[i & 1][e][q]);
+                epi.store4(rows.idx ? row[i & 1][e] : rbase + RR * i + r, cbase + 16 * G * q + G * l16, a, pre[i & 1][e][q]);
               }
             }
           }
@@ -478,7 +503,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     };
     auto ring_sources = [&](int tm, int tn, int z, RingSrc &src) {
       const int kbeg = k_first(z) * BK;
-      const int m0 = (tm_lo + tm) * BM, n0 = tn * BN;
+      const int m0 = tm * bm, n0 = tn * BN;
       const int ln = own_lane(), r8 = ln / 8, csrc = (ln % 8) ^ (((wave & 1) << 2) | (r8 >> 1));  // as above
       // Lane offsets are 32 bits.  Without a gather list the descriptor starts at the tile's first
       // row, so the offsets stay below 256 rows; with one they are taken from the start of the
@@ -499,7 +524,11 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
         for (int i = 0; i < 8; ++i) srow[i] -= m0;
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) src.va[i] = (uint32_t)(((size_t)srow[i] * lda + kbeg + csrc * 8) * 2);
+      for (int i = 0; i < 8; ++i) {
+        uint32_t at = (uint32_t)srow[i] * (uint32_t)(lda * 2);
+        asm volatile("" : "+v"(at));  // (a fused multiply-add has a 64-bit result: a second register per offset)
+        src.va[i] = at + (uint32_t)(kbeg + csrc * 8) * 2u;
+      }
       // The matrices' addresses and ends are fetched together and selected from: left to itself the compiler fetches
       // each descriptor's address from the kernel arguments when it knows which one it is, one wait after the other
       // (eight of them in the 256 x 256 tile).
@@ -519,47 +548,48 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
       }
       src.vw = (uint32_t)((G * r8 * BK + csrc * 8) * 2);
     };
+    // 16-row blocks per wave of row tile t
+    auto blocks_of = [&](int t) -> int { return (min(bm, M - t * bm) + RR - 1) / RR; };
     int tm = 0, tn = 0, z = 0, p = first;
-    while (p < total_all && !tile_at(p, tm, tn, z)) p += step;
-    if (p >= total_all) return;
-    RingSrc src;
-    ring_sources(tm, tn, z, src);
-    RingFull::fill(src, lds0, wave);
-    bool all_landed = false;
-    // The whole of a tile for MBV 32-row blocks of this wave that hold rows, epilogue included: where the paths for
-    // the block counts met before the epilogue, the 256 accumulators of the fused 256 x 256 tile were moved between
-    // registers, and through scratch memory, at the end of every tile.  Returns whether another tile follows.
-    auto run_tile = [&](auto mbv_c) -> bool {
-      constexpr int MBV = decltype(mbv_c)::value, MI = 2 * MBV;
-      const int KT = k_base + (z < k_rem ? 1 : 0);
-      const int rbase = (tm_lo + tm) * BM + wm0, cbase = tn * BN + wn0, z_now = z;
-      const int ln = own_lane(), l16 = ln % 16, lq = ln / 16;
-      const unsigned char *rd_a = smem_raw + (wm0 + l16) * ROWB, *rd_w = smem_raw + (wn0 + l16) * ROWB;
-      int rd_off16[2];
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) rd_off16[kk] = (((4 * kk + lq) ^ ((l16 >> 1) & 7)) * 16);
-      floatx4 acc[NMAT][MI ? MI : 1][2 * NB];
-      Ring<NMAT, NB, BN, MBV>::tile(acc, lds0, wave, src, rd_a, rd_w, rd_off16, KT, all_landed);
-      p += step;
+    auto find = [&]() -> bool {  // the workgroup's tile at p or behind it
       while (p < total_all && !tile_at(p, tm, tn, z)) p += step;
-      const bool more = p < total_all;
-      if (more) {
-        ring_sources(tm, tn, z, src);
-        RingFull::fill(src, lds0, wave);
-      }
-      if constexpr (MBV > 0) ring_epilogue(acc, rbase, cbase, z_now);
-      return more;
+      return p < total_all;
     };
-    for (;;) {
-      const int mbv = (M - ((tm_lo + tm) * BM + wm0) + 31) / 32;  // wave-uniform
-      bool more;
-      if (mbv >= 3) more = run_tile(std::integral_constant<int, 4>{});
-      else if (mbv == 2) more = run_tile(std::integral_constant<int, 2>{});
-      else if (mbv == 1) more = run_tile(std::integral_constant<int, 1>{});
-      else more = run_tile(std::integral_constant<int, 0>{});
-      if (!more) break;
-      all_landed = true;
-    }
+    // Consecutive tiles with MI 16-row blocks of each wave, from the one at p on; returns whether there is another tile.
+    // Everything about these tiles is in their own loop, epilogue included, and nothing but the tile's number passes
+    // from one path to another (the first tile of a path fills the ring anew: only a last row tile changes the path).
+    // Where the paths shared a loop, the sources of the copies, and where they met before the epilogue the
+    // accumulators, went through other registers and scratch memory at the end of every tile.
+    auto run_tiles_of = [&](auto mi_c) -> bool {
+      constexpr int MI = decltype(mi_c)::value;
+      using R = Ring<NMAT, NB, BN, WR, MI>;
+      uint32_t lds_at = lds0;
+      asm volatile("" : "+s"(lds_at));  // (what follows from it is computed here, not once for all paths and kept)
+      RingSrc src;
+      ring_sources(tm, tn, z, src);
+      R::fill(src, lds_at, wave, k_base + (z < k_rem ? 1 : 0));
+      for (bool all_landed = false;; all_landed = true) {
+        const int KT = k_base + (z < k_rem ? 1 : 0);
+        const int rbase = tm * bm + 16 * wr, cbase = tn * BN + wn0, z_now = z;
+        const int ln = own_lane(), l16 = ln % 16, lq = ln / 16;
+        const unsigned char *rd_a = smem_raw + (16 * wr + l16) * ROWB, *rd_w = smem_raw + (wn0 + l16) * ROWB;
+        int rd_off16[2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) rd_off16[kk] = (((4 * kk + lq) ^ ((l16 >> 1) & 7)) * 16);
+        floatx4 acc[NMAT][MI][2 * NB];
+        R::tile(acc, lds_at, wave, src, rd_a, rd_w, rd_off16, KT, all_landed);
+        p += step;
+        const bool more = find(), same = more && blocks_of(tm) == MI;
+        if (same) {
+          ring_sources(tm, tn, z, src);
+          R::fill(src, lds_at, wave, k_base + (z < k_rem ? 1 : 0));
+        }
+        ring_epilogue(acc, rbase, cbase, z_now);
+        if (!same) return more;
+      }
+    };
+    bool more = find();
+    while (more) more = with_blocks<MAX_MI>(blocks_of(tm), run_tiles_of);
     return;
   }
 
@@ -846,7 +876,10 @@ __global__ __launch_bounds__(256) void k_gemm_planned(GemmArgs ga, typename Kind
   extern __shared__ __align__(1024) unsigned char smem_raw[];
   const Walk walk = walk_of(smem_raw);
   const int M = rows_that_exist(ga.rows);
-  if (!planned) pl = plan_on_device(pa, M);
+  if (!planned) {
+    pl = plan_on_device(pa, M, walk.wave, (uint32_t *)smem_raw);
+    __syncthreads();  // (the words are read before anything is copied over them)
+  }
   if (plan_out && blockIdx.x == 0 && threadIdx.x == 0) {
     plan_out[0] = pl.sk;
     plan_out[1] = pl.row_hi;
@@ -856,13 +889,15 @@ __global__ __launch_bounds__(256) void k_gemm_planned(GemmArgs ga, typename Kind
   if (pl.row_hi > 0) {
     if (Kind::RAW && (!Kind::FUSED || pl.sk > 1)) {
       if constexpr (Kind::RAW) {
-        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, true>(ga, epi, M, 0, pl.row_hi, pl.sk, walk);
-        else gemm_tiles<typename Kind::L, typename Kind::Epi, true>(ga, epi, M, 0, pl.row_hi, pl.sk, walk);
+        if (pl.xl == PLAN_X) gemm_tiles<typename Kind::X, typename Kind::Epi, true>(ga, epi, M, 0, pl.row_hi, pl.sk, walk, pl.bm);
+        else if (pl.xl == PLAN_L) gemm_tiles<typename Kind::L, typename Kind::Epi, true>(ga, epi, M, 0, pl.row_hi, pl.sk, walk, pl.bm);
+        else if constexpr (!std::is_void<typename Kind::W>::value) gemm_tiles<typename Kind::W, typename Kind::Epi, true>(ga, epi, M, 0, pl.row_hi, pl.sk, walk, pl.bm);
       }
     } else {
       if constexpr (Kind::FUSED) {
-        if (pl.xl) gemm_tiles<typename Kind::X, typename Kind::Epi, false>(ga, epi, M, 0, pl.row_hi, 1, walk);
-        else gemm_tiles<typename Kind::L, typename Kind::Epi, false>(ga, epi, M, 0, pl.row_hi, 1, walk);
+        if (pl.xl == PLAN_X) gemm_tiles<typename Kind::X, typename Kind::Epi, false>(ga, epi, M, 0, pl.row_hi, 1, walk, pl.bm);
+        else if (pl.xl == PLAN_L) gemm_tiles<typename Kind::L, typename Kind::Epi, false>(ga, epi, M, 0, pl.row_hi, 1, walk, pl.bm);
+        else if constexpr (!std::is_void<typename Kind::W>::value) gemm_tiles<typename Kind::W, typename Kind::Epi, false>(ga, epi, M, 0, pl.row_hi, 1, walk, pl.bm);
       }
     }
   }

@@ -1,0 +1,57 @@
+// bf16 down projection with the residual and the scatter in its epilogue, or fp32 sums for a row kernel.
+#include "gemm_bf16_launch.h"
+
+namespace dy {
+
+namespace {
+
+struct DownKind {  // residual + scatter in the epilogue, or fp32 sums of a K split
+  typedef EpiDown<bf16_t> Epi;
+  typedef XLargeS X;
+  typedef LargeS L;
+  typedef void W;
+  static constexpr bool FUSED = true, RAW = true;
+  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
+    gemm_tiles<SkinnyN64, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
+  }
+};
+
+}  // namespace
+
+void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const float *h, void *out,
+                    float *part, size_t part_elems, int32_t *plan_dev, hipStream_t s) {
+  if (rows.cap <= 0) return;
+  const EpiDown<bf16_t> e{h, (bf16_t *)out, N};
+  const WSeg seg = wseg_one(wd, N);
+  const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
+  const bool ring = ring_ok(A, K, seg, N);
+  PlanArgs pa = down_plan_args(N, K, part_elems, ring, cus_of_xcd());
+  Splits sp;
+  if (rows.cap <= STREAM_ROWS) {
+    sp.n = stream_split(pa, rows.cap);
+    if (sp.n == 1) {
+      run_tiles<SkinnyS, false>(ga, e, 1, s);
+      return;
+    }
+    run_tiles<SkinnyS, true>(ga, e, sp.n, s);
+  } else if (!ring) {
+    pa.stream_cols = 0;
+    sp.n = plan_of(pa, rows.cap, first_on_host(pa, rows.cap)).sk;
+    if (sp.n == 1) {
+      run_tiles<LargeS8, false>(ga, e, 1, s);
+      return;
+    }
+    run_tiles<LargeS8, true>(ga, e, sp.n, s);
+  } else {
+    const bool known = plan_known(rows), sums = known || down_has_sums(pa, rows.cap, false);
+    if (!sums) pa.split_ok = pa.stream_cols = 0;
+    if (known) pa.sum_us = 4.0f;
+    GemmPlan pl;
+    run_planned<DownKind>(ga, e, pa, &pl, plan_dev, s);
+    if (!sums || (known && pl.sk == 1 && pl.row_hi == rows.cap)) return;
+    sp = splits_of(ga, pl, true, plan_dev);
+  }
+  launch_down_finalize(BF16, part, sp, h, rows, N, out, s);
+}
+
+}  // namespace dy

@@ -1,8 +1,8 @@
-// Slice loop of the 256-row bf16 GEMM tiles with four waves (one per SIMD; 128 x 128 outputs each
-// for the 256 x 256 tile, 128 x 64 for the 256 x 128 tile; the accumulators in the second register
-// file) and a ring of five 32 KB LDS slots.
+// Slice loop of the bf16 GEMM tiles with four waves (one per SIMD; the accumulators in the second register
+// file) and 160 KB of LDS as a ring of slices: whole slices where three or more fit (tile_slices), else halves
+// of slices in five 32 KB slots (tile_halves).
 //
-// Why a ring.  A K slice of the tile is 64 KB (A tile 32 KB + weight tile 32 KB), and two whole
+// Why a ring of halves in the 256 x 256 tile.  A K slice of the tile is 64 KB (A tile 32 KB + weight tile 32 KB), and two whole
 // slices are all that fit beside nothing else in the 160 KB of LDS.  With two stages, the copies of
 // slice kt+2 can only be issued once slice kt has been read out, and must have landed before slice
 // kt+1 is read out: the copy path runs empty before every barrier and is asked for a whole slice in a
@@ -12,8 +12,7 @@
 // barrier per slice, in its middle: by then a wave has the operands of the whole slice in registers
 // (128 of them), so the two slots of slice kt are free; W(kt+2) is copied into one during the second
 // half of slice kt and A(kt+3) into the other during the first half of slice kt+1 -- one copy after
-// every eighth matrix instruction (every fourth for the A half beside a 128-row weight tile), all the
-// time -- and the eight newest copies stay in flight across the barrier (s_waitcnt vmcnt(8) and a raw
+// every eighth matrix instruction, all the time -- and the eight newest copies stay in flight across the barrier (s_waitcnt vmcnt(8) and a raw
 // s_barrier: __syncthreads would wait for all of them).
 //
 // The copies are buffer loads with LDS destination: a scalar descriptor per source matrix, a 32-bit
@@ -64,15 +63,16 @@ __device__ __forceinline__ void store_buf(const float (&v)[4], __amdgpu_buffer_r
 constexpr uint32_t RING_SLOT = 32768;
 constexpr int RING_SLOTS = 5;
 constexpr int RING_MIN_SLICES = 3;
+constexpr int RING_MAX_WSRC = 6;
 
 // Sources of a wave's copies for one tile:
-//   srd_a / va[i]   descriptor and lane offsets of its 8 A copies (8 tile rows each)
-//   srd_w[d] / vw   the same for its weight copies (8 for a 256-row weight tile, 4 for a 128-row one): a
+//   srd_a / va[i]   descriptor and lane offsets of its A copies (8 tile rows each; as many as the tile's height needs)
+//   srd_w[d] / vw   the same for its weight copies (8, 6 or 4 for 256, 192 or 128 weight rows): a
 //                   copy's 8 rows lie in one weight panel; the descriptor starts at the first of them, so that
 //                   one lane offset serves all copies, and with G = 4 also at the first of the next copy's,
 //                   which lie two weight rows on
 struct RingSrc {
-  __amdgpu_buffer_rsrc_t srd_a, srd_w[4];
+  __amdgpu_buffer_rsrc_t srd_a, srd_w[RING_MAX_WSRC];
   uint32_t va[8], vw;
 };
 
@@ -87,26 +87,30 @@ struct RingSrc {
 // The 16x16 form does the same products with less power than the 32x32 one, and the matrix clock is power-bound:
 // operands in registers, all CUs busy, random values: 1.85 against 1.75 PFLOP/s.
 //
-// The loop for one wave tile of 128 rows x (32 NMAT NB) columns: NMAT x NB column groups of 32, group
-// g = t * NB + j reads weight-tile rows (t * BN + wn0 + 32 j ...).  Four column groups (a 256-row
-// weight tile, 256 x 256 or 256 x (128+128) outputs) or two (128 weight rows: 256 x 128 or
-// 256 x (64+64)); the weight half of a slice then fills half of its slot.
-// MBV = 32-row blocks of this wave that hold rows (4 in a full tile).  In a row tile with fewer than
-// 256 rows a wave multiplies only those, down to none: copies, waits and barriers are the same for
-// every wave, so such a tile costs about what its copies cost (leaving out the A copies of the empty
-// row groups as well was measured: no faster).
+// Tile heights.  A tile holds any number of rows up to 16 MI WR (WR wave rows, MI 16-row blocks of each), and everything a
+// slice costs follows MI: its A copies, operand reads and products.  The blocks of 16 rows are dealt to the wave rows in
+// turn (block i of wave row w holds rows 16 (WR i + w) .. + 15 of the tile), so that every wave of a tile with few rows has
+// its share of them.  MI is the same for all waves, chosen per tile (gemm_bf16_dma.h).
+//
+// The loop for one wave: NMAT x NB column groups of 32, group g = t * NB + j reads weight-tile rows (t * BN + wn0 + 32 j ...).
+// Wave grid 2 x 2: four column groups of a wave (a 256-row weight tile: 256 x 256 or 256 x (128+128) outputs) or two (128
+// weight rows); wave grid 4 x 1: six groups, all 192 weight rows of the tile.  The halves of a slice fill as much of
+// their slots as they need.
 
-template <int NMAT, int NB, int BN, int MBV> struct Ring {
+template <int NMAT, int NB, int BN, int WR, int MI> struct Ring {
   static constexpr int NCB = NMAT * NB;  // column groups per wave
-  static constexpr int NWC = 2 * NCB;    // weight copies per wave and slice
   static constexpr int NC = 2 * NCB;     // 16-column blocks per wave
-  static constexpr int PS = 8 * NC;      // products per K step of 32 = per half slice
-  static constexpr int RD = 8 + NC;      // operand reads per K step
-  static constexpr int RSP = PS / 2 >= 2 * RD ? 2 : 1;  // products between two operand reads
-  static_assert(NCB == 4 || NCB == 2, "four or two column groups per wave");
+  static constexpr int AC = WR * MI / 2;        // activation copies per wave and slice (32 tile rows each)
+  static constexpr int NWC = NMAT * BN / 32;    // weight copies per wave and slice
+  static constexpr int PS = MI * NC;     // products per K step of 32 = per half slice
+  static constexpr int RD = MI + NC;     // operand reads per K step
+  // products between two operand reads, and reads at a time where there are fewer products than reads
+  static constexpr int RSP = PS / 2 >= 2 * RD ? 2 : 1, RPP = (RD + PS - 1) / PS;
+  static_assert((WR == 2 && (NWC == 8 || NWC == 4) && MI <= 8) || (WR == 4 && NWC == 6 && MI <= 4), "tile shapes of the ring");
+  static_assert(AC >= 1 && AC <= 8 && PS % AC == 0 && PS % NWC == 0, "copies are spread evenly over the products");
   // 16-column blocks whose columns alternate: row x of a group of 16 G LDS rows holds weight row
   // G (x % 16) + x / 16 of the group, so that lane l16 of the G blocks has columns G l16 .. + G - 1
-  static constexpr int G = NB >= 2 ? 4 : 2;
+  static constexpr int G = (2 * NB) % 4 == 0 ? 4 : 2;
   // weight row (from the tile's first column on) in LDS rows (4 i + wave) * 8 of a matrix; the row r8 after it
   // holds weight row weight_row + G r8
   static __device__ __forceinline__ int weight_row(int i, int wave) {
@@ -115,36 +119,57 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
   static constexpr int ROW = 128, A_STEP = 128, W_STEP = 4096;  // bytes per tile row; K walk per slice
 
   static constexpr int ND = G == 4 ? NWC / 2 : NWC;  // descriptors
+  static_assert(ND <= RING_MAX_WSRC, "descriptors of the weight copies");
   static __device__ __forceinline__ void copy_w(const RingSrc &src, int c, uint32_t kt, uint32_t lds_addr) {
     dma16_buf(src.srd_w[c * ND / NWC], src.vw, kt * W_STEP + (G == 4 && c % 2 ? 2 * ROW : 0), lds_addr);
   }
 
   static __device__ __forceinline__ int w_row(int c) { return (((c / 2) / NB) * BN + ((c / 2) % NB) * 32 + (c % 2) * 16) * ROW; }
   static __device__ __forceinline__ int nxt(int s, int d) { const int t = s + d; return t >= RING_SLOTS ? t - RING_SLOTS : t; }
-  // read x of a K step: activation block x (x < 8) or column block x - 8; product p of a K step: row
-  // block p / NC, column block p % NC
-  static __device__ constexpr bool has_read(int x) { return x < 8 ? x < 2 * MBV : MBV > 0; }
-  static __device__ constexpr bool has_prod(int p) { return p / NC < 2 * MBV; }
 
-  // Fills the ring for a tile: A(0) W(0) A(1) W(1) A(2) into slots 0..4.  The slots must be free
-  // (every wave past the middle barrier of the previous tile's last slice).
-  static __device__ __forceinline__ void fill(const RingSrc &src, uint32_t lds0, int wave) {
-    const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
+  // Whole slices that fit beside each other where a slice is small enough for three of them (0: the ring of half
+  // slices).  CPS copies of a wave fill CPS * 4 KB.
+  static constexpr int CPS = AC + NWC;
+  static __host__ __device__ constexpr int stages_of(int cps) {
+    const int n = (int)(RING_SLOTS * RING_SLOT / 4096) / cps;
+    return n < 3 ? 0 : n > 5 ? 5 : n;
+  }
+  static constexpr int STAGES = stages_of(CPS);
+
+  // Fills the ring for a tile of KT slices.  The ring must be free (every wave past the middle barrier of the previous
+  // tile's last slice).
+  //   half slices: A(0) W(0) A(1) W(1) A(2) into slots 0..4;  whole slices: slice s into stage s, as many as there are
+  static __device__ __forceinline__ void fill(const RingSrc &src, uint32_t lds0, int wave, int KT) {
+    // (hidden from the optimiser: the copies' LDS addresses are sums of it and a constant, which are otherwise all
+    // computed once per kernel and kept, forty of them, at the cost of vector registers for their spills)
+    uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
+    asm volatile("" : "+s"(lds_w));
+    if constexpr (STAGES > 0) {
+      const int n = min(STAGES, KT);
+      for (int st = 0; st < n; ++st) {
+        const uint32_t to = lds_w + (uint32_t)st * (CPS * 4096u);
 #pragma unroll
-    for (int h = 0; h < RING_SLOTS; ++h) {
-      const int kt = h / 2;
-      if (h % 2 == 0) {
+        for (int i = 0; i < AC; ++i) dma16_buf(src.srd_a, src.va[i], (uint32_t)st * A_STEP, to + i * 4096u);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + h * RING_SLOT + i * 4096u);
-      } else {
+        for (int c = 0; c < NWC; ++c) copy_w(src, c, st, to + (AC + c) * 4096u);
+      }
+    } else {
 #pragma unroll
-        for (int c = 0; c < NWC; ++c) copy_w(src, c, kt, lds_w + h * RING_SLOT + c * 4096u);
+      for (int h = 0; h < RING_SLOTS; ++h) {
+        const int kt = h / 2;
+        if (h % 2 == 0) {
+#pragma unroll
+          for (int i = 0; i < AC; ++i) dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + h * RING_SLOT + i * 4096u);
+        } else {
+#pragma unroll
+          for (int c = 0; c < NWC; ++c) copy_w(src, c, kt, lds_w + h * RING_SLOT + c * 4096u);
+        }
       }
     }
   }
 
   // One tile: acc[matrix][16-row block][16-column block] = A tile x W tile over KT >= 3 slices; the ring has been
-  // filled (fill).
+  // filled (fill with AC copies).
   //   all_landed      wait for everything this wave has in flight (a fill issued before the previous
   //                   tile's epilogue, whose own loads and stores are counted with it) instead of for
   //                   the first slice alone; wave-uniform
@@ -154,36 +179,152 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
   static __device__ __forceinline__ void tile(Acc &acc, uint32_t lds0, int wave, const RingSrc &src,
                                               const unsigned char *rd_a, const unsigned char *rd_w,
                                               const int (&rd_off)[2], int KT, bool all_landed) {
+    if constexpr (STAGES > 0) tile_slices(acc, lds0, wave, src, rd_a, rd_w, rd_off, KT, all_landed);
+    else tile_halves(acc, lds0, wave, src, rd_a, rd_w, rd_off, KT, all_landed);
+  }
+
+  // Reads of the other K step that go behind product q of a half slice: [first_read(q), first_read(q + 1))
+  static __device__ __forceinline__ constexpr int first_read(int q) {
+    const int r = RPP > 1 ? q * RPP : (q + RSP - 1) / RSP;
+    return r < RD ? r : RD;
+  }
+
+  // Small tiles: STAGES whole slices, slice kt in stage kt % STAGES.  Where a few rows meet a whole weight matrix the
+  // weights come from HBM, and the ring of half slices leaves a weight copy half a slice to one slice of time to
+  // arrive, less than the memory's latency once a slice takes 0.6 us; here it has STAGES - 1.5 to STAGES - 1.  The
+  // stage of slice kt is free past the barrier in the middle of slice kt: W(kt + STAGES) follows in its second half,
+  // A(kt + STAGES) in the first half of slice kt + 1.  Against halves in the same tiles (16 GEMMs, 140 to 5000 rows):
+  // 128 columns and 32 / 64 / 128 / 256 rows 0.56 / 0.66 / 0.79 / 0.92 of the time, 256 columns and 64 / 128 / 160 rows
+  // 0.78 / 0.85 / 0.89, 192 columns and 64 / 128 / 192 rows 0.79 / 0.88 / 0.92.
+  template <typename Acc>
+  static __device__ __forceinline__ void tile_slices(Acc &acc, uint32_t lds0, int wave, const RingSrc &src,
+                                                     const unsigned char *rd_a, const unsigned char *rd_w,
+                                                     const int (&rd_off)[2], int KT, bool all_landed) {
+    constexpr int S = STAGES > 0 ? STAGES : 1;
+    constexpr uint32_t STAGE = CPS * 4096u, A_BYTES = AC * 4096u;
+    static_assert((S - 1) * CPS < 64, "vmcnt immediate");
     const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
-    auto copy_a = [&](int i, int kt, int slot) {
-      dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + (uint32_t)slot * RING_SLOT + i * 4096u);
+    // wait for all but the newest n slices (n known to be at most S - 1)
+    auto wait_but = [](int n) {
+      if (S > 4 && n >= 4) wait_vmcnt<(S > 4 ? 4 : 0) * CPS>();
+      else if (S > 3 && n >= 3) wait_vmcnt<(S > 3 ? 3 : 0) * CPS>();
+      else if (n >= 2) wait_vmcnt<2 * CPS>();
+      else if (n == 1) wait_vmcnt<CPS>();
+      else wait_vmcnt<0>();
     };
     if (all_landed) wait_vmcnt<0>();
-    else wait_vmcnt<16 + NWC>();  // slice 0 has landed (this wave's part); the rest of the fill is behind it
+    else wait_but(min(S, KT) - 1);  // slice 0 has landed (this wave's part)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    bf16x8 af[2][8], bfr[2][NC];  // [K step][16-row block], [K step][16-column block]
-    auto read = [&](int st, int x, const unsigned char *sa, const unsigned char *sb) {
-      if (x < 8) af[st][x] = *reinterpret_cast<const bf16x8 *>(sa + x * 16 * ROW + rd_off[st]);
-      else bfr[st][x - 8] = *reinterpret_cast<const bf16x8 *>(sb + w_row(x - 8) + rd_off[st]);
+    bf16x8 af[2][MI], bfr[2][NC];  // [K step][16-row block], [K step][16-column block]
+    auto read = [&](int st, int x, uint32_t stage) {
+      if (x < MI) af[st][x] = *reinterpret_cast<const bf16x8 *>(rd_a + stage + x * (16 * WR) * ROW + rd_off[st]);
+      else bfr[st][x - MI] = *reinterpret_cast<const bf16x8 *>(rd_w + stage + A_BYTES + w_row(x - MI) + rd_off[st]);
     };
-    auto prod = [&](int st, int p, bool zero) {
+    auto prod = [&](int st, int p, bool zero) {  // product p of a K step: row block p / NC, column block p % NC
       const int i = p / NC, c = p % NC;
       auto &a = acc[c / (2 * NB)][i][c % (2 * NB)];
       const floatx4 sum = zero ? floatx4{0.f, 0.f, 0.f, 0.f} : a;  // (the first products of a tile start from zero)
       a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[st][i], bfr[st][c], sum, 0, 0, 0);
     };
-    // read r of the other K step goes behind product RSP * r
-    auto read_due = [](int q) { return q % RSP == 0 && q / RSP < RD; };
+    uint32_t cur = 0;  // stage of slice kt (byte offset; hidden from the optimiser as in tile_halves)
+    asm volatile("" : "+s"(cur));
+#pragma unroll
+    for (int x = 0; x < RD; ++x) read(0, x, cur);
+
+    // CA: A(kt - 1 + S) is copied; CW: W(kt + S) is.  MORE: slice kt + 1 exists.
+    auto slice = [&](int kt, auto first_c, auto ca_c, auto cw_c, bool more) {
+      constexpr bool FIRST = decltype(first_c)::value, CA = decltype(ca_c)::value, CW = decltype(cw_c)::value;
+      const uint32_t nxt = cur + STAGE >= S * STAGE ? 0 : cur + STAGE, prv = cur ? cur - STAGE : (S - 1) * STAGE;
+      auto copy_a_due = [](int q) { return (q + 1) % (PS / AC) == 0; };
+#pragma unroll
+      for (int q = 0; q < PS; ++q) {
+#pragma unroll
+        for (int r = first_read(q); r < first_read(q + 1); ++r) read(1, r, cur);
+        if (CA && copy_a_due(q)) {
+          const int i = (q + 1) / (PS / AC) - 1;
+          dma16_buf(src.srd_a, src.va[i], (uint32_t)(kt - 1 + S) * A_STEP, lds_w + prv + i * 4096u);
+        }
+        prod(0, q, FIRST);
+      }
+#pragma unroll
+      for (int q = 0; q < PS; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (first_read(q + 1) > first_read(q)) __builtin_amdgcn_sched_group_barrier(0x100, RPP, 0);
+        if (CA && copy_a_due(q)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+      }
+      // Middle: slice kt+1 has landed, and with the barrier everyone's part of it; everyone has read slice kt.
+      if (CA || CW) wait_vmcnt<(S - 2) * CPS>();
+      else wait_but(KT - 2 - kt);
+      wait_lgkmcnt0();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      auto copy_w_due = [](int q) { return (q + 1) % (PS / NWC) == 0; };
+#pragma unroll
+      for (int q = 0; q < PS; ++q) {
+        if (more) {
+#pragma unroll
+          for (int r = first_read(q); r < first_read(q + 1); ++r) read(0, r, nxt);
+        }
+        if (CW && copy_w_due(q)) copy_w(src, (q + 1) / (PS / NWC) - 1, kt + S, lds_w + cur + A_BYTES + ((q + 1) / (PS / NWC) - 1) * 4096u);
+        prod(1, q, false);
+      }
+#pragma unroll
+      for (int q = 0; q < PS; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (more && first_read(q + 1) > first_read(q)) __builtin_amdgcn_sched_group_barrier(0x100, RPP, 0);
+        if (CW && copy_w_due(q)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+      }
+      cur = nxt;
+    };
+    constexpr auto yes = std::true_type{};
+    constexpr auto no = std::false_type{};
+    int kt = 1;
+    if (KT > S) {
+      slice(0, yes, no, yes, true);
+      for (; kt + S < KT; ++kt) slice(kt, no, yes, yes, true);
+      slice(kt, no, yes, no, true);
+      ++kt;
+    } else {
+      slice(0, yes, no, no, true);
+    }
+    for (; kt + 1 < KT; ++kt) slice(kt, no, no, no, true);
+    slice(kt, no, no, no, false);
+  }
+
+  // Large tiles: five slots of half slices (see the head of this file).
+  template <typename Acc>
+  static __device__ __forceinline__ void tile_halves(Acc &acc, uint32_t lds0, int wave, const RingSrc &src,
+                                              const unsigned char *rd_a, const unsigned char *rd_w,
+                                              const int (&rd_off)[2], int KT, bool all_landed) {
+    const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
+    auto copy_a = [&](int i, int kt, int slot) {
+      dma16_buf(src.srd_a, src.va[i], (uint32_t)kt * A_STEP, lds_w + (uint32_t)slot * RING_SLOT + i * 4096u);
+    };
+    if (all_landed) wait_vmcnt<0>();
+    else wait_vmcnt<2 * AC + NWC>();  // slice 0 has landed (this wave's part); the rest of the fill is behind it
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    bf16x8 af[2][MI], bfr[2][NC];  // [K step][16-row block], [K step][16-column block]
+    auto read = [&](int st, int x, const unsigned char *sa, const unsigned char *sb) {
+      if (x < MI) af[st][x] = *reinterpret_cast<const bf16x8 *>(sa + x * (16 * WR) * ROW + rd_off[st]);
+      else bfr[st][x - MI] = *reinterpret_cast<const bf16x8 *>(sb + w_row(x - MI) + rd_off[st]);
+    };
+    auto prod = [&](int st, int p, bool zero) {  // product p of a K step: row block p / NC, column block p % NC
+      const int i = p / NC, c = p % NC;
+      auto &a = acc[c / (2 * NB)][i][c % (2 * NB)];
+      const floatx4 sum = zero ? floatx4{0.f, 0.f, 0.f, 0.f} : a;  // (the first products of a tile start from zero)
+      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[st][i], bfr[st][c], sum, 0, 0, 0);
+    };
     // slot of A(kt); W(kt) is in the next one.  (Hidden from the optimiser: with a known start the first
     // slice's operand addresses lie past the reach of an LDS offset and are computed once per kernel, which
     // has no registers to keep them.)
     int slot_a = 0;
     asm volatile("" : "+s"(slot_a));
 #pragma unroll
-    for (int x = 0; x < RD; ++x)
-      if (has_read(x)) read(0, x, rd_a + (uint32_t)slot_a * RING_SLOT, rd_w + (uint32_t)(slot_a + 1) * RING_SLOT);
+    for (int x = 0; x < RD; ++x) read(0, x, rd_a + (uint32_t)slot_a * RING_SLOT, rd_w + (uint32_t)(slot_a + 1) * RING_SLOT);
 
     auto slice = [&](int kt, auto first_c, auto m1_c, auto m2_c) {
       // FIRST: slice 0 (A(2) is already on its way); M1 / M2: slices kt+1 / kt+2 exist.  The last
@@ -193,27 +334,28 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       constexpr bool CA = !FIRST && M2;
       const int slot_w = nxt(slot_a, 1), slot_a1 = nxt(slot_a, 2), slot_w1 = nxt(slot_a, 3), slot_a2 = nxt(slot_a, 4);
       const unsigned char *sa = rd_a + (uint32_t)slot_a * RING_SLOT, *sb = rd_w + (uint32_t)slot_w * RING_SLOT;
-      // First half: products of K step 0; the operand reads of step 1 between the first of them; the 8
+      // First half: products of K step 0; the operand reads of step 1 between the first of them; the
       // copies of A(kt+2) into the slot W(kt-1) left, evenly.  In the instruction order
       // (sched_group_barrier: product, read, copy) the scheduler left alone would fetch each operand
       // right before its use and bunch the copies.
-      auto copy_a_due = [](int q) { return (q + 1) % (PS / 8) == 0; };
+      auto copy_a_due = [](int q) { return (q + 1) % (PS / AC) == 0; };
 #pragma unroll
       for (int q = 0; q < PS; ++q) {
-        if (read_due(q) && has_read(q / RSP)) read(1, q / RSP, sa, sb);
-        if (CA && copy_a_due(q)) copy_a((q + 1) / (PS / 8) - 1, kt + 2, slot_a2);
-        if (has_prod(q)) prod(0, q, FIRST);
+#pragma unroll
+        for (int r = first_read(q); r < first_read(q + 1); ++r) read(1, r, sa, sb);
+        if (CA && copy_a_due(q)) copy_a((q + 1) / (PS / AC) - 1, kt + 2, slot_a2);
+        prod(0, q, FIRST);
       }
 #pragma unroll
       for (int q = 0; q < PS; ++q) {
-        if (has_prod(q)) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (read_due(q) && has_read(q / RSP)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (first_read(q + 1) > first_read(q)) __builtin_amdgcn_sched_group_barrier(0x100, RPP, 0);
         if (CA && copy_a_due(q)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
       }
       // Middle: slice kt+1 has landed (the copies of A(kt+2) behind it may still be in flight), and
       // with the barrier everyone's part of it; everyone has read slice kt out of its slots.
       if (M1) {
-        if (M2) wait_vmcnt<8>();
+        if (M2) wait_vmcnt<AC>();
         else wait_vmcnt<0>();
       }
       wait_lgkmcnt0();
@@ -225,14 +367,17 @@ template <int NMAT, int NB, int BN, int MBV> struct Ring {
       auto copy_w_due = [](int q) { return (q + 1) % (PS / NWC) == 0; };
 #pragma unroll
       for (int q = 0; q < PS; ++q) {
-        if (M1 && read_due(q) && has_read(q / RSP)) read(0, q / RSP, sa1, sb1);
+        if (M1) {
+#pragma unroll
+          for (int r = first_read(q); r < first_read(q + 1); ++r) read(0, r, sa1, sb1);
+        }
         if (M2 && copy_w_due(q)) copy_w(src, (q + 1) / (PS / NWC) - 1, kt + 2, lds_w + (uint32_t)slot_a * RING_SLOT + ((q + 1) / (PS / NWC) - 1) * 4096u);
-        if (has_prod(q)) prod(1, q, false);
+        prod(1, q, false);
       }
 #pragma unroll
       for (int q = 0; q < PS; ++q) {
-        if (has_prod(q)) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (M1 && read_due(q) && has_read(q / RSP)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (M1 && first_read(q + 1) > first_read(q)) __builtin_amdgcn_sched_group_barrier(0x100, RPP, 0);
         if (M2 && copy_w_due(q)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
       }
       slot_a = slot_a1;

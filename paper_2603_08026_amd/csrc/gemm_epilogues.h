@@ -31,6 +31,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float epi_f4;  // fo
 
 struct EpiStoreF32 {
   static constexpr bool DUAL = false;
+  static constexpr bool GATHER = true;  // the activation rows may be gathered
   static constexpr int INTERLEAVE = 0;
   static constexpr bool PRELOAD = false;
   float *out;
@@ -48,6 +49,7 @@ struct EpiStoreF32 {
 
 template <typename T> struct EpiSwiGLU {
   static constexpr bool DUAL = true;
+  static constexpr bool GATHER = false;  // the activation rows may be gathered
   static constexpr int INTERLEAVE = 0;
   static constexpr bool PRELOAD = false;
   T *act;  // [cap, N]
@@ -70,6 +72,7 @@ template <typename T> struct EpiSwiGLU {
 
 template <typename T> struct EpiDown {
   static constexpr bool DUAL = false;
+  static constexpr bool GATHER = false;  // the activation rows may be gathered
   static constexpr int INTERLEAVE = 0;
   // The residual is read before the result is written.  h and out may alias as far as the compiler
   // knows, so element by element every load would wait for the store before it; the kernel instead
@@ -108,6 +111,7 @@ template <typename T> struct EpiDown {
 
 template <typename T, int HALF> struct EpiSwiGLUHalves {
   static constexpr bool DUAL = false;
+  static constexpr bool GATHER = false;  // the activation rows may be gathered
   static constexpr int INTERLEAVE = HALF;  // 48 (96-column tiles) or 64 (128-column tiles)
   static constexpr bool PRELOAD = false;
   T *act;  // [cap, F]

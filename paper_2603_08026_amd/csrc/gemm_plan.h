@@ -1,4 +1,4 @@
-// Launch plans of the bf16 GEMMs with 256-row tiles, made from the number of rows that EXIST.
+// Launch plans of the bf16 GEMMs in row tiles, made from the number of rows that EXIST.
 //
 // The row count of a list lives on the device, and a list's capacity says little about it: a generation
 // loop carries lists of B*L entries of which a few percent are used.  A plan made from the capacity then
@@ -6,9 +6,14 @@
 // salient rows: 32 tiles of the down projection on 256 CUs, 201 us against 55 us with a K split; two layers and four
 // steps of that loop 4080 -> 2424 us).
 // So the kernel makes its own plan once it has read the count: every candidate is priced by one lane of
-// a wave, the cheapest wins, and the row kernels that follow read the chosen split back from four words
-// of device memory.  Where the host knows the count (dense steps) it evaluates the same function and
+// a workgroup, the cheapest wins, and the row kernels that follow read the chosen split back from four words
+// of device memory.  Where the host knows the count (dense steps) it evaluates the same functions and
 // passes the plan in.
+//
+// Two sets of candidates.  The first has tiles of 256 rows (plan_price).  The second has tiles of any height
+// that is a multiple of 32 (64) rows, and tiles of 192 columns (tile_price): rows divided evenly over their tiles
+// leave no thin last one, and 256 CUs are filled by what divides the matrix into about as many pieces -- 330 rows
+// are 256 tiles of 192 x 192, not 192 tiles of 256 x 256 of which half hold 74 rows.
 #pragma once
 #include <type_traits>
 #include "common.h"
@@ -16,12 +21,13 @@
 namespace dy {
 namespace mm {
 
-// A plan: rows [0, row_hi) of the list in 256-row tiles (xl: 256 columns wide, else 128) with sk K splits;
+// A plan: rows [0, row_hi) of the list in tiles of bm rows (xl: 1: 256 columns wide, 2: 192, 0: 128) with sk K splits;
 // the rows from row_hi on in 128-row weight-streaming tiles with sk_tail K splits.
-struct GemmPlan { int xl, sk, row_hi, sk_tail; };
+struct GemmPlan { int xl, sk, row_hi, sk_tail, bm; };
+constexpr int PLAN_L = 0, PLAN_X = 1, PLAN_W = 2;  // GemmPlan::xl
 
 // What plans are made from.  N output columns, K; and for the kind of GEMM:
-//   tiles_l / tiles_x  column tiles of the 256 x 128 / 256 x 256 shape; tiles_x = 0: it does not divide N
+//   tiles_l / _x / _w  column tiles of 128 / 256 / 192 columns; tiles_x, tiles_w = 0: they do not divide N
 //   w_cols             weight rows per output column (2 for gate|up)
 //   stream_cols        columns of the weight-streaming tiles; 0: not to be used
 //   split_ok           K splits (and a streamed tail that is split) may be used: a row kernel sums them
@@ -30,10 +36,12 @@ struct GemmPlan { int xl, sk, row_hi, sk_tail; };
 //   part_elems         fp32 elements of the buffer of raw results
 //   cus, inv_cus       CUs of an XCD
 //   stream_us          price of a streamed last row tile
+//   sum_us             what a sum kernel costs that would not be launched without a split (down projection with a plan
+//                      made on the host)
 struct PlanArgs {
-  int N, K, tiles_l, tiles_x, w_cols, stream_cols, split_ok, split_free;
+  int N, K, tiles_l, tiles_x, w_cols, stream_cols, split_ok, split_free, tiles_w;
   long part_elems;
-  float cus, inv_cus, stream_us;
+  float cus, inv_cus, stream_us, sum_us;
 };
 
 constexpr int PLAN_BK = 64, PLAN_XCD = 8;
@@ -88,24 +96,105 @@ __host__ __device__ inline float plan_price(const PlanArgs &a, int M, int c) {
 
 __host__ __device__ inline GemmPlan plan_of(const PlanArgs &a, int M, int c) {
   const int streamed = c / (2 * PLAN_MAX_SPLIT);
-  return GemmPlan{(c / PLAN_MAX_SPLIT) & 1, c % PLAN_MAX_SPLIT + 1, streamed ? M - M % 256 : M, streamed ? stream_split(a, M) : 1};
+  return GemmPlan{(c / PLAN_MAX_SPLIT) & 1, c % PLAN_MAX_SPLIT + 1, streamed ? M - M % 256 : M, streamed ? stream_split(a, M) : 1, 256};
 }
 
-inline GemmPlan plan_on_host(const PlanArgs &a, int M) {
-  if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M)};
+// Price in microseconds of M rows in tiles of `mi` units of 32 (192 columns: 64) rows with sk K splits, or a huge value.
+// Fitted to 8287 times: 16 GEMMs of four layer shapes (hidden 512 to 4096) at 18 row counts from 140 to 5000, every
+// shape, height and up to ten splits, weights of up to 16 copies in turn.  The candidate with the least price is on
+// average 1.0 % slower than the fastest of all (worst 18 %); the least time itself is 2 to 34 % below that of the best
+// 256-row tiles.
+//   - a K slice costs a fixed part (waits, the weight copies) and one per unit of rows; from five (three) units on
+//     256 (192) columns are bound by their products
+//   - tiles at the same time slow each other down: a chip that is half empty is 11 % faster per tile
+//   - the weights' stream and the tiles' own time overlap, not entirely; a raw result is written at 10 TB/s beside it
+__host__ __device__ inline float tile_price(const PlanArgs &a, int M, int shape, int mi, int sk) {
+  const bool l = shape == PLAN_L, x = shape == PLAN_X;
+  const int cols = l ? a.tiles_l : x ? a.tiles_x : a.tiles_w, unit = l || x ? 32 : 64, bm = mi * unit;
+  const bool raw = a.split_free || sk > 1;
+  bool ok = cols != 0 && bm <= 256;
+  if (sk > 1) ok = ok && a.split_ok && a.K / PLAN_BK >= PLAN_MIN_SLICES * sk && (long)sk * M * a.N <= a.part_elems;
+  const int full = M / bm, tail = M - full * bm;
+  const float fx = (float)((full * cols * sk + PLAN_XCD - 1) / PLAN_XCD), px = tail ? (float)((cols * sk + PLAN_XCD - 1) / PLAN_XCD) : 0.0f;
+  const float rounds = ceilf(fx * a.inv_cus - 1e-4f), more = fmaxf(ceilf((px - (rounds * a.cus - fx)) * a.inv_cus - 1e-4f), 0.0f);
+  const float slices = (float)a.K * (1.0f / PLAN_BK) / (float)sk;
+  auto tile_us = [&](float m) -> float {
+    const float s = l ? 0.261f + 0.0488f * m : x ? fmaxf(0.532f + 0.0557f * m, 0.287f + 0.1124f * m) : fmaxf(0.429f + 0.104f * m, 0.196f + 0.195f * m);
+    const float o = l ? 1.96f + 0.50f * m : x ? 1.48f + 0.80f * m : 2.45f + 0.94f * m;
+    return slices * s + o;
+  };
+  const float empty = 1.0f - fminf((fx + px) * a.inv_cus / fmaxf(rounds + more, 1.0f), 1.0f);
+  const float t = (rounds * tile_us((float)mi) + more * tile_us((float)((tail + unit - 1) / unit))) * (1.0f - 0.22f * empty);
+  const float w = (float)a.N * (float)a.w_cols * (float)a.K * 2.0f * (1.0f / 4.03e6f);
+  const float hi = fmaxf(t, w), lo = fminf(t, w);
+  float us = 1.8f + hi + 0.26f * lo * (lo / hi) * (lo / hi);
+  const float mn = 1e-6f * (float)M * (float)a.N;
+  if (raw) us += 0.384f * mn * (float)sk;
+  else if (a.w_cols == 1) us *= 1.08f;  // (the down projection's own epilogue: residual and scatter)
+  if (a.split_free) us += 1.58f * mn * (float)(sk - 1);
+  else if (sk > 1) us += 1.58f * mn * (float)sk + a.sum_us;
+  return ok ? us : 3e30f;
+}
+
+// Candidate c of the second set for one shape: heights of 1 to 8 units x 8 splits
+constexpr int TILE_CANDIDATES = 64;
+__host__ __device__ inline int tile_split(int c) {  // 1 2 3 4 5 6 8 12
+  const int i = c % 8;
+  return i < 6 ? i + 1 : i == 6 ? 8 : 12;
+}
+__host__ __device__ inline int tile_units(int c) { return c / 8 + 1; }
+
+// The first set's choice in tiles of the best height, height h (units - 1)
+__host__ __device__ inline float first_price(const PlanArgs &a, const GemmPlan &p, int M, int h) {
+  const float us = tile_price(a, p.row_hi, p.xl, h + 1, p.sk);
+  return p.row_hi < M ? us + a.stream_us : us;
+}
+// Whether a candidate of the second set, with sk splits, takes the place of the first set's choice p: by how much it has
+// to be cheaper.  The prices' error is 8 % (rms), most of it between different numbers of splits, whose sums are
+// another kernel's time; and the longer the list, the less there is to gain (rounds of the chip are many or nearly full).
+__host__ __device__ inline bool takes_over(const PlanArgs &a, int M, const GemmPlan &p, float first, int sk, float second) {
+  const bool same = p.row_hi == M && sk == p.sk, down = a.split_ok && !a.split_free;
+  return second < (M <= 1024 && !down ? 0.97f : same ? 0.95f : 0.85f) * first;
+}
+
+// The first set's choice on the host: candidate number
+inline int first_on_host(const PlanArgs &a, int M) {
   int best = 0;
   float best_t = 1e30f;
   for (int c = 0; c < PLAN_CANDIDATES; ++c) {
     const float t = plan_price(a, M, c);
     if (t < best_t) { best_t = t; best = c; }
   }
-  return plan_of(a, M, best);
+  return best;
+}
+inline GemmPlan plan_on_host(const PlanArgs &a, int M) {
+  if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M), 256};
+  GemmPlan p = plan_of(a, M, first_on_host(a, M));
+  float first = 2e30f, best_t = 1e30f;
+  for (int h = 0; h < 8; ++h) {
+    const float t = first_price(a, p, M, h);
+    if (t < first) { first = t; p.bm = 32 * (h + 1); }
+  }
+  GemmPlan q = p;
+  for (int shape = 0; shape < 3; ++shape) {
+    if (shape == PLAN_X ? !a.tiles_x : shape == PLAN_W && !a.tiles_w) continue;
+    for (int c = 0; c < TILE_CANDIDATES; ++c) {
+      const int sk = tile_split(c), mi = tile_units(c);
+      if (sk > 1 && !a.split_ok) continue;
+      const float t = tile_price(a, M, shape, mi, sk);
+      if (t < best_t) { best_t = t; q = GemmPlan{shape, sk, M, 1, mi * (shape == PLAN_W ? 64 : 32)}; }
+    }
+  }
+  return takes_over(a, M, p, first, q.sk, best_t) ? q : p;
 }
 
 // What the launchers of the three kinds of GEMM make their plans from.  ring: the ring loop's shapes can be taken
 // (ring_ok); part_elems: elements of the buffer of raw results; cus: CUs of an XCD
-inline PlanArgs plan_args(int N, int K, int bn_l, bool wide_ok, int cus) {
-  return PlanArgs{N, K, N / bn_l, wide_ok && N % (2 * bn_l) == 0 ? N / (2 * bn_l) : 0, 1, 0, 0, 0, 0, (float)cus, 1.0f / (float)cus, 0.0f};
+// w_ok: the kind has tiles of 192 columns
+inline PlanArgs plan_args(int N, int K, int bn_l, bool wide_ok, int cus, bool w_ok) {
+  const int bn_w = bn_l / 2 * 3;
+  return PlanArgs{N, K, N / bn_l, wide_ok && N % (2 * bn_l) == 0 ? N / (2 * bn_l) : 0, 1, 0, 0, 0, wide_ok && w_ok && N % bn_w == 0 ? N / bn_w : 0, 0,
+                  (float)cus, 1.0f / (float)cus, 0.0f, 0.0f};
 }
 // The streaming tiles read the weights once, at 5.3 TB/s together and at most 34.5 GB/s each (gate|up has no K
 // split: with 88 tiles of 5632 columns over K = 2048 a streamed last row tile takes 18 us, not the 11 of the rate of
@@ -118,7 +207,7 @@ inline PlanArgs with_stream_price(PlanArgs a) {
 }
 // q|k|v, out-projection: fp32 result, a row kernel follows
 inline PlanArgs raw_plan_args(int N, int K, size_t part_elems, bool ring, int cus) {
-  PlanArgs a = plan_args(N, K, 128, ring, cus);
+  PlanArgs a = plan_args(N, K, 128, ring, cus, true);
   a.stream_cols = N % 96 == 0 ? 96 : 64;
   a.split_ok = a.split_free = 1;
   a.part_elems = (long)part_elems;
@@ -126,14 +215,14 @@ inline PlanArgs raw_plan_args(int N, int K, size_t part_elems, bool ring, int cu
 }
 // gate|up: SwiGLU in the epilogue
 inline PlanArgs swiglu_plan_args(int N, int K, int cus) {
-  PlanArgs a = plan_args(N, K, 64, true, cus);
+  PlanArgs a = plan_args(N, K, 64, true, cus, true);
   a.w_cols = 2;
   a.stream_cols = N % 48 == 0 ? 48 : N % 64 == 0 ? 64 : 0;
   return with_stream_price(a);
 }
 // down projection: residual and scatter in the epilogue, or fp32 sums of a K split
 inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int cus) {
-  PlanArgs a = plan_args(N, K, 128, ring, cus);
+  PlanArgs a = plan_args(N, K, 128, ring, cus, false);
   a.stream_cols = 64;
   a.split_ok = 1;
   a.part_elems = (long)part_elems;
@@ -153,7 +242,7 @@ constexpr int SUM_CAP = 4096;
 constexpr float SUM_LOOP_US = 40.0f;
 inline float loop_us(int K) { return 51.3f / 4096.0f * (float)K; }  // K loop of a 256 x 128 tile (plan_price)
 inline bool down_has_sums(const PlanArgs &a, int cap, bool known) {
-  const GemmPlan full = plan_on_host(a, cap);
+  const GemmPlan full = plan_of(a, cap, first_on_host(a, cap));
   return full.sk > 1 || full.row_hi < cap || (!known && (cap > SUM_CAP || loop_us(a.K) >= SUM_LOOP_US));
 }
 
@@ -163,13 +252,10 @@ inline bool down_has_sums(const PlanArgs &a, int cap, bool known) {
 constexpr int RING_GROUP = 64;
 inline bool ring_groups_ok(int end0, int end1) { return end0 % RING_GROUP == 0 && end1 % RING_GROUP == 0; }
 
-// one wave (all 64 lanes active); the result is uniform
-__device__ __forceinline__ GemmPlan plan_on_device(const PlanArgs &a, int M) {
-  static_assert(PLAN_CANDIDATES == WAVE, "a candidate per lane");
-  if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M)};
-  // least price with its candidate in the low six bits (prices are positive: they order like their bits)
-  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
-  uint32_t k = (__float_as_uint(plan_price(a, M, lane)) & ~63u) | (uint32_t)lane;
+// Least of a positive price over the 64 lanes of a wave, with its lane in the low six bits (positive floats order like
+// their bits); the result is uniform
+__device__ __forceinline__ uint32_t least_of_wave(float price, int lane) {
+  uint32_t k = (__float_as_uint(price) & ~63u) | (uint32_t)lane;
   auto dpp = [](uint32_t v, auto ctrl) -> uint32_t {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, decltype(ctrl)::value, 0xf, 0xf, false);
   };
@@ -179,8 +265,39 @@ __device__ __forceinline__ GemmPlan plan_on_device(const PlanArgs &a, int M) {
   k = min(k, dpp(k, std::integral_constant<int, 0x140>{}));  // row_mirror: every lane has its row's least
   const uint32_t r0 = __builtin_amdgcn_readlane(k, 0), r1 = __builtin_amdgcn_readlane(k, 16),
                  r2 = __builtin_amdgcn_readlane(k, 32), r3 = __builtin_amdgcn_readlane(k, 48);
-  const int who = (int)(min(min(r0, r1), min(r2, r3)) & 63u);
-  return plan_of(a, M, who);
+  return min(min(r0, r1), min(r2, r3));
+}
+
+// A workgroup of four waves (all lanes active): wave 0 prices the first set, waves 1 to 3 a shape of the second each.
+// words: eight words of LDS that nothing else uses yet (the caller's barrier before their reuse).  The result is uniform.
+__device__ __forceinline__ GemmPlan plan_on_device(const PlanArgs &a, int M, int wave, uint32_t *words) {
+  static_assert(PLAN_CANDIDATES == WAVE && TILE_CANDIDATES == WAVE, "a candidate per lane");
+  if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M), 256};
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+  if (wave == 0) {
+    const int c = (int)(least_of_wave(plan_price(a, M, lane), lane) & 63u);
+    const GemmPlan p = plan_of(a, M, c);
+    const uint32_t k = least_of_wave(lane < 8 ? first_price(a, p, M, lane) : 3e30f, lane);
+    if (lane == 0) { words[0] = k; words[4] = (uint32_t)c; }
+  } else {
+    const int shape = wave - 1;
+    const uint32_t k = least_of_wave(tile_price(a, M, shape, tile_units(lane), tile_split(lane)), lane);
+    if (lane == 0) words[wave] = k;
+  }
+  __syncthreads();
+  uint32_t w[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) w[i] = __builtin_amdgcn_readfirstlane(words[i]);
+  GemmPlan p = plan_of(a, M, (int)w[4]);
+  p.bm = 32 * ((int)(w[0] & 63u) + 1);
+  int shape = 0;
+  if (w[2] < w[1]) shape = 1;
+  if (w[3] < w[1 + shape]) shape = 2;
+  const uint32_t k = w[1 + shape];
+  const int c = (int)(k & 63u);
+  if (takes_over(a, M, p, __uint_as_float(w[0] & ~63u), tile_split(c), __uint_as_float(k & ~63u)))
+    p = GemmPlan{shape, tile_split(c), M, 1, tile_units(c) * (shape == PLAN_W ? 64 : 32)};
+  return p;
 }
 
 }  // namespace mm
