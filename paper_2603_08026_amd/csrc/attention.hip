@@ -201,7 +201,7 @@ void attention_plan(DType t, int B, int L, int H, int dh, int cap, int rows_per_
 
 void launch_attention(DType t, const AttnArgs &a, hipStream_t s) {
   if (a.rows.cap <= 0) return;
-  if (t == F32) launch_attention_f32(t, a, s);
+  if (t == F32) launch_attention_f32(a, s);
   else launch_attention_bf16(a, s);
   if (a.splits > 1 && !a.partial) launch_attn_combine(t, a, s);
 }

@@ -164,7 +164,7 @@ __device__ __forceinline__ bool attn_work_item_grouped(const AttnArgs &a, int q_
   return true;
 }
 
-void launch_attention_f32(DType t, const AttnArgs &a, hipStream_t s);
+void launch_attention_f32(const AttnArgs &a, hipStream_t s);
 void launch_attention_bf16(const AttnArgs &a, hipStream_t s);
 void launch_attn_combine(DType t, const AttnArgs &a, hipStream_t s);
 
