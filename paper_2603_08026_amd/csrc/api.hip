@@ -200,8 +200,9 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
   WSeg seg;
   seg.w[0] = w->wq; seg.w[1] = w->wk; seg.w[2] = w->wv;
   seg.n_end[0] = ctx->dq; seg.n_end[1] = ctx->dq + ctx->dkv; seg.n_end[2] = ctx->dq + 2 * ctx->dkv;
+  const DirectCols values{cache->v, w->bv, ctx->dq + ctx->dkv, ctx->dkv};
   const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
-                                     ctx->part_o, ctx->part_elems, ctx->plan, s);
+                                     ctx->part_o, ctx->part_elems, ctx->plan, s, values);
   prof_mark(ctx, ST_GEMM_QKV, s);
   launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rows, L,
                       c.n_heads, c.n_kv_heads, c.head_dim, w->bq, w->bk, w->bv, q_out, cache->k,

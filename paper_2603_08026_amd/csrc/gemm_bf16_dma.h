@@ -442,15 +442,59 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
       if constexpr (SPLIT) {
         static_assert(!SPLIT || G == 4, "16-byte raw stores");
         const float *pz = split.part + (size_t)z * split.split_stride;
+        auto at = [&](int i, int q, int e) {
+          return floatx4{acc[0][i][G * q][e], acc[0][i][G * q + 1][e], acc[0][i][G * q + 2][e], acc[0][i][G * q + 3][e]};
+        };
+        if constexpr (Epi::DIRECT) {
+          // Direct columns (values): a bias and the rounding are all they need, so they skip the raw result: 2 bytes
+          // written per element where 4 were written, read and 2 written by the row kernel.  A run of 64 columns
+          // (16 lanes) is on one side of direct.lo; a tile may be on both.
+          const DirectCols &dc = epi.direct;
+          if (cbase + 64 * NQ > dc.lo) {  // wave-uniform
+            floatx4 bias[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+              uint2 w = {0u, 0u};
+              const int c = cbase + 64 * q - dc.lo;
+              if (dc.bias && c >= 0) w = *reinterpret_cast<const uint2 *>((const bf16_t *)dc.bias + c + 4 * l16);
+              bias[q] = floatx4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
+                                __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
+            }
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+              // (the accumulators are still where they were: without this the compiler moves them out of the second register
+              // file ahead of the branch above, into scratch memory for 58 registers)
+#pragma unroll
+              for (int c = 0; c < 2 * NB; ++c) asm volatile("" : "+a"(acc[0][i][c]));
+#pragma unroll
+              for (int q = 0; q < NQ; ++q) {
+                const int c = cbase + 64 * q - dc.lo;
+                if (c >= 0) {
+                  const auto out = make_srd((const bf16_t *)dc.out + (size_t)(rbase + RR * i) * dc.ld + c, left(i) ? (uint32_t)(left(i) * dc.ld - c) * 2u : 0);
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) {
+                    const floatx4 v = at(i, q, e) + bias[q];
+                    const float o[4] = {v[0], v[1], v[2], v[3]};
+                    store_buf(o, out, ((uint32_t)(4 * lq + e) * dc.ld + 4 * l16) * 2u);
+                  }
+                } else {
+                  const auto part = block(pz, i, 4);
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) store_buf(at(i, q, e), part, lane_row[e] * 4u + 64 * G * q);
+                }
+              }
+              __builtin_amdgcn_sched_barrier(0);  // (a row block at a time: more of them at once spill)
+            }
+            return;
+          }
+        }
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
           const auto part = block(pz, i, 4);
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
-              store_buf(floatx4{acc[0][i][G * q][e], acc[0][i][G * q + 1][e], acc[0][i][G * q + 2][e], acc[0][i][G * q + 3][e]},
-                        part, lane_row[e] * 4u + 64 * G * q);
+            for (int q = 0; q < NQ; ++q) store_buf(at(i, q, e), part, lane_row[e] * 4u + 64 * G * q);
         }
       } else if constexpr (Epi::PRELOAD) {
         // what row block i + 1 reads is requested before block i is written: a wave's memory operations

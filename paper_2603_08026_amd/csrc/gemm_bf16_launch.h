@@ -41,6 +41,8 @@ typedef Shape<128, 64, 4, 1, false, 4> SkinnyN64;  // the same with four waves, 
 typedef Shape<128, 96, 4, 1, false, 4> SkinnyW96;
 typedef Shape<128, 128, 4, 1, false, 4> SkinnyH128;
 
+constexpr int DIRECT_ROWS = 4096;  // rows of a dense step from which its values leave the q|k|v GEMM directly
+
 int cu_count() {
   static int n = 0;
   if (n == 0) {
@@ -106,6 +108,19 @@ Splits splits_of(const GemmArgs &ga, const GemmPlan &pl, bool fused, const int32
   if (!plan_known(ga.rows)) sp.dev = plan_dev;
   return sp;
 }
+
+// q|k|v, out-projection: fp32 result, a row kernel follows
+template <typename E> struct RawKind {
+  typedef E Epi;
+  typedef XLargeS X;
+  typedef LargeS L;
+  typedef WideS W;
+  static constexpr bool FUSED = false, RAW = true;
+  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
+    if (ga.N % SkinnyW96::BN == 0) gemm_tiles<SkinnyW96, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);
+    else gemm_tiles<SkinnyN64, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);
+  }
+};
 
 GemmArgs gemm_args(const GemmA &A, const Rows &rows, int K, const WSeg &seg, const void *w2, float *part) {
   return GemmArgs{(const bf16_t *)A.a, A.gather, A.lda, rows, seg.n_end[2], seg, (const bf16_t *)w2, K, part};

@@ -3,24 +3,12 @@
 
 namespace dy {
 
-namespace {
-
-struct RawKind {  // q|k|v, out-projection: fp32 result, a row kernel follows
-  typedef EpiStoreF32 Epi;
-  typedef XLargeS X;
-  typedef LargeS L;
-  typedef WideS W;
-  static constexpr bool FUSED = false, RAW = true;
-  static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
-    if (ga.N % SkinnyW96::BN == 0) gemm_tiles<SkinnyW96, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
-    else gemm_tiles<SkinnyN64, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
-  }
-};
-
-}  // namespace
+// q|k|v of a dense step of many rows, the values straight into their cache (gemm_bf16_qkv.hip)
+Splits gemm_bf16_qkv(const GemmArgs &ga, float *part, const DirectCols &direct, const PlanArgs &pa, hipStream_t s);
 
 // raw result part[z][j][n]; returns the numbers of K splits (on the device if the count is there)
-Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, hipStream_t s) {
+Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, DirectCols direct,
+                     hipStream_t s) {
   Splits out;
   if (rows.cap <= 0) return out;
   const int N = seg.n_end[2];
@@ -36,7 +24,13 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
   }
   GemmPlan pl;
   if (ring) {
-    run_planned<RawKind>(ga, e, pa, &pl, plan_dev, s);
+    // Dense steps from DIRECT_ROWS rows on: 20480 rows of 12288 columns, GEMM and row kernel together 1835 -> 1735 us.  Lists
+    // stay with the raw result: the kernel is another one than the out-projection's, whose instructions the caches
+    // still hold from layer to layer, and few rows lose more by that than they gain (loop of 8 x 1024 tokens with 330 listed
+    // rows 2119 -> 2149 us a pass, 410 rows of a list 302 -> 306 us a step; 2064 rows 812 -> 808, 5160 rows 1872 -> 1859,
+    // but how many of a list exist is known to the device alone); dense 1024 rows gain nothing (430 us).
+    if (direct.out && !rows.idx && !rows.count && rows.cap >= DIRECT_ROWS) return gemm_bf16_qkv(ga, part, direct, pa, s);
+    run_planned<RawKind<EpiStoreF32>>(ga, e, pa, &pl, plan_dev, s);
     return splits_of(ga, pl, false, plan_dev);
   }
   pa.stream_cols = 0;

@@ -34,6 +34,7 @@ struct EpiStoreF32 {
   static constexpr bool GATHER = true;  // the activation rows may be gathered
   static constexpr int INTERLEAVE = 0;
   static constexpr bool PRELOAD = false;
+  static constexpr bool DIRECT = false;
   float *out;
   int ldo;
   __device__ __forceinline__ void operator()(int j, int row, int n, float acc, float) const {
@@ -45,6 +46,13 @@ struct EpiStoreF32 {
   __device__ __forceinline__ void put(size_t u, uint32_t lb, float acc, float) const {
     *reinterpret_cast<float *>(reinterpret_cast<char *>(out + u) + lb) = acc;
   }
+};
+
+// The same; columns from direct.lo on leave ring tiles as final bf16 rows of direct.out, bias added (gemm_bf16_dma.h).
+// lo is a multiple of 64, or past the last column where there are none; for rows without a list.
+struct EpiStoreDirect : EpiStoreF32 {
+  static constexpr bool DIRECT = true;
+  DirectCols direct;
 };
 
 template <typename T> struct EpiSwiGLU {
@@ -78,6 +86,7 @@ template <typename T> struct EpiDown {
   // knows, so element by element every load would wait for the store before it; the kernel instead
   // loads a block's residuals (load) and then stores the block (store).
   static constexpr bool PRELOAD = true;
+  static constexpr bool DIRECT = false;
   const float *h;  // [cap, N]
   T *out;          // [T, N]
   int N;

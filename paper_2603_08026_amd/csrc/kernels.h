@@ -21,7 +21,7 @@ struct Rows {
 // {n, tail_from, n_tail, done_to} there; the members are then ignored.
 struct Splits {
   int n = 1, tail_from = 0x7fffffff, n_tail = 1;
-  int done_to = 0;  // down projection: rows below it need no sum kernel (the GEMM's own epilogue wrote them)
+  int done_to = 0;  // rows below it were finished by the GEMM's own epilogue: down projection, and the direct columns of q|k|v
   const int32_t *dev = nullptr;
   __device__ Splits resolved() const {
     Splits r = *this;
@@ -153,11 +153,19 @@ inline WSeg wseg_one(const void *w, int N) {
   s.n_end[0] = s.n_end[1] = s.n_end[2] = N;
   return s;
 }
+// Columns of a raw GEMM that need nothing but a bias (the values among q|k|v): column n >= lo of row j is out[row_j, n - lo]
+// (bf16, row length ld).  The returned Splits::done_to says for which rows the GEMM wrote them (it may be none); the
+// row kernel finishes the others from their raw results.
+struct DirectCols {
+  void *out = nullptr;
+  const void *bias = nullptr;
+  int lo = 0x7fffffff, ld = 0;
+};
 // raw GEMM: part[z][j][n] = sum over K split z of A[j,:] * W[n,:] (fp32, split stride rows*N);
 // returns the numbers of splits used (>= 1), chosen from the rows that exist, N and K (on the device, in
 // the four words `plan`, when their number is known there alone).
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
-                       int32_t *plan, hipStream_t s);
+                       int32_t *plan, hipStream_t s, DirectCols direct = DirectCols{});
 // up: act[j,:] = silu(A w_gate^T) * (A w_up^T), T-typed out [cap, N]
 void launch_gemm_swiglu(DType t, GemmA A, Rows rows, int K, int N, const void *w_gate,
                         const void *w_up, void *act, hipStream_t s);

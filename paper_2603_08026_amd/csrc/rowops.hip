@@ -161,7 +161,8 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
     if (entry_of && threadIdx.x == 0 && pos >= entry_lo) entry_of[r] = j + 1;
     const float *src = part + (size_t)j * ld;
     const float *t = tab + (size_t)pos * half * 2;
-    for (int it = threadIdx.x; it < qk_items + v_items; it += RB) {
+    const int items = qk_items + (j < sp.done_to ? 0 : v_items);  // (values that the GEMM has written itself are left out)
+    for (int it = threadIdx.x; it < items; it += RB) {
       if (it < qk_items) {
         const int head = it / per_head, p4 = (it % per_head) * 4;
         const bool isq = head < H;
