@@ -27,7 +27,7 @@ struct dyllm_ctx {
   float *part_o;   // fp32 scratch shared by consecutive stages: raw GEMM results / attention partials
   float *part_ml;
   size_t part_elems;
-  void *dv_full;   // [R, dkv] value residuals of the approximate path; all zero between calls
+  void *dv_full;   // [R, dkv] value residuals of the approximate path; where they lie by token all zero between calls
   void *dc;        // [R, dq] approximate context residual of every token
   void *csal;      // [R, dq] exact context rows of the salient tokens (approximate path)
   int32_t *pos;    // [R] position+1 of a token in the salient list; all zero between calls
@@ -216,7 +216,7 @@ AttnArgs attn_args(dyllm_ctx *ctx, const void *q, const void *k, const void *v, 
   const dyllm_layer_cfg &c = ctx->cfg;
   AttnArgs a;
   a.q = q; a.q_by_token = 0; a.k = k; a.v = v; a.rows = rows; a.offsets = offsets;
-  a.key_offsets = nullptr; a.lse_out = nullptr; a.c_commit = nullptr; a.cos_part = nullptr;
+  a.key_offsets = nullptr; a.key_cap = 0; a.norm_k = nullptr; a.lse_out = nullptr; a.c_commit = nullptr; a.cos_part = nullptr;
   a.B = B; a.L = L; a.H = c.n_heads; a.Hkv = c.n_kv_heads; a.dh = c.head_dim;
   const int rows_per_seq = offsets ? (rows.cap + B - 1) / B : L;
   attention_plan(dt(ctx), B, L, c.n_heads, c.head_dim, rows.cap, rows_per_seq, ctx->part_elems, &a,
@@ -348,6 +348,10 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   const dyllm_layer_cfg &c = ctx->cfg;
   const Rows all = win.rows;
   const Rows rin = rows_of(idx_in, B);
+  // compact: the candidates' new keys and value residuals lie by list entry (ksal and a value buffer), and the attention
+  // over them takes its normalisers from a sweep over all keys; else the residual lies by token in a buffer that is
+  // zero elsewhere, which every key meets
+  const bool compact = !cached_norm && dt(ctx) == BF16 && c.head_dim == 128, by_entry = cached_norm || compact;
   const int by_token = all.idx != nullptr;  // a window keeps q at its token's row, so that both
                                             // attention passes find it from a token id
   int rc;
@@ -370,11 +374,11 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->fs, nullptr, c.hidden}, rin, c.hidden, seg,
                                        ctx->part_o, ctx->part_elems, ctx->plan, s);
     // value residual: by token into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
-    // entry next to a compact copy of the new keys (reused normalisers: only candidates are scored)
+    // entry next to a compact copy of the new keys
     launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rin, L, 0,
                         c.n_kv_heads, c.head_dim, nullptr, w->bk, w->bv, nullptr, cache->k, cache->v,
-                        cached_norm ? ctx->dc : ctx->dv_full, 0, cached_norm ? ctx->ksal : nullptr,
-                        cached_norm, ctx->pos, win.lo, s);  // also marks the step's candidates in the token -> entry map
+                        cached_norm ? ctx->dc : ctx->dv_full, 0, by_entry ? ctx->ksal : nullptr,
+                        by_entry, ctx->pos, win.lo, s);  // also marks the step's candidates in the token -> entry map
   }
   if ((rc = check_launch(ctx, "approx: projections"))) return rc;
   // exact rows of the salient tokens  [Alg. 3: C_sal]; q is stored by token here.  With a cache of
@@ -390,14 +394,19 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   if (!cached_norm) {
     // approximate residual of every token of the step: the full softmax against the merged keys times
     // the value residual, which is zero outside the salient rows  [Alg. 4]
-    AttnArgs a = attn_args(ctx, ctx->qs, cache->k, ctx->dv_full, all, win.offsets, B, L, ctx->dc, 0);
+    AttnArgs a = attn_args(ctx, ctx->qs, compact ? ctx->ksal : cache->k, ctx->dv_full, all, win.offsets, B, L, ctx->dc, 0);
     a.q_by_token = by_token;
+    if (compact) {
+      a.key_offsets = idx_in->offsets;
+      a.key_cap = rin.cap;
+      a.norm_k = cache->k;
+    }
     launch_attention(dt(ctx), a, s);
     if ((rc = check_launch(ctx, "approx: attention"))) return rc;
     // new contexts of the step's tokens, cosine test, commit; then the scratch maps go back to zero
     launch_saliency_approx(dt(ctx), all, ctx->dq, ctx->csal, ctx->dc, ctx->pos, cache->c, tau, cos_out, ctx->flag,
                            nullptr, nullptr, L, s);
-    launch_clear_rows(dt(ctx), rin, ctx->dv_full, ctx->dkv, s);  // the residual buffer goes back to zero
+    if (!compact) launch_clear_rows(dt(ctx), rin, ctx->dv_full, ctx->dkv, s);  // the residual buffer goes back to zero
   } else {
     // Reused normalisers (Sec. 3.3's O(N |A| d) form): every token of the step is scored against the
     // candidates' keys only -- compact rows, sequence b's at [offsets[b], offsets[b+1]) -- and the
@@ -411,6 +420,7 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
                    ctx->part_elems, &a, c.n_heads / c.n_kv_heads);
     a.q_by_token = by_token;
     a.key_offsets = idx_in->offsets;
+    a.key_cap = rin.cap;
     launch_attention(dt(ctx), a, s);
     if ((rc = check_launch(ctx, "approx: attention"))) return rc;
     launch_saliency_approx(dt(ctx), all, ctx->dq, ctx->csal, nullptr, ctx->pos, cache->c, tau, cos_out, ctx->flag,

@@ -131,8 +131,8 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(AttnArgs a, int q_tiles) 
   if (b < 0) return;  // uniform: no such tile
   const int j0 = tile_info[1], nq = tile_info[2];
   const int kvh = h / (a.H / a.Hkv);
-  const int kbase = a.key_offsets ? a.key_offsets[b] : b * a.L;
-  const int Lk = a.key_offsets ? a.key_offsets[b + 1] - kbase : a.L;
+  const int kbase = a.key_offsets ? min(a.key_offsets[b], a.key_cap) : b * a.L;
+  const int Lk = a.key_offsets ? min(a.key_offsets[b + 1], a.key_cap) - kbase : a.L;
   const int k_lo = split * a.chunk, k_hi = min(Lk, k_lo + a.chunk);
   if (k_lo >= k_hi) return;  // uniform
 
@@ -388,7 +388,13 @@ template <int WQ, int WK_> struct DTile {
   static_assert(LPW >= 2 && LPW % 2 == 0, "every wave copies K and V rows");
 };
 
-template <int WQ, int WK_>
+// NORM: keys and values are compact rows (key_offsets) of some of a sequence's tokens only, and the rows of P V are
+// divided by the sum over ALL L keys of the sequence (norm_k): the context update of tokens whose neighbours' values
+// have changed by v [Alg. 4 with the value residual, zero elsewhere, left out].  After the loop over the compact
+// keys a second one sweeps all keys for the sum alone: no V copies and reads, half the products.  8 x 1024 tokens,
+// 32 heads, 330 candidates, against all keys meeting the zero-padded residual: whole sequences and response windows on
+// average 74 -> 63 us a pass (one tile a step of the sweep: 68), and no launch that clears the padded residual.
+template <int WQ, int WK_, bool NORM>
 __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, int q_tiles) {  // two waves per SIMD: 256 registers, no AGPR shuffling
   using T = DTile<WQ, WK_>;
   constexpr int DH = T::DH, NW = T::NW, WK = T::WK, BQ = T::BQ, TK = T::TK, ROWB = T::ROWB, NS = T::NS,
@@ -417,10 +423,12 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
     jq = tile_info[1] + p / grp;
     hq = kvh * grp + p % grp;
   }
-  const int kbase = a.key_offsets ? a.key_offsets[b] : b * a.L;
-  const int Lk = a.key_offsets ? a.key_offsets[b + 1] - kbase : a.L;
-  const int k_lo = split * a.chunk, k_hi = min(Lk, k_lo + a.chunk);
-  if (k_lo >= k_hi) return;  // uniform
+  const int kbase = a.key_offsets ? min(a.key_offsets[b], a.key_cap) : b * a.L;
+  const int Lk = a.key_offsets ? min(a.key_offsets[b + 1], a.key_cap) - kbase : a.L;
+  // (NORM: the splits cut the sweep over all keys; each takes its share of the compact keys, perhaps none)
+  const int k_chunk = NORM ? split_chunk(Lk, a.splits, TK) : a.chunk;
+  const int k_lo = NORM ? min(Lk, split * k_chunk) : split * k_chunk, k_hi = min(Lk, k_lo + k_chunk);
+  if (!NORM && k_lo >= k_hi) return;  // uniform
 
   const size_t kv_stride = (size_t)a.Hkv * DH;
   const bf16_t *kc = (const bf16_t *)a.k + ((size_t)kbase * a.Hkv + kvh) * DH;
@@ -710,6 +718,122 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   }
   pv();  // the last tile's
   }
+  if constexpr (NORM) {
+    if (Lk == 0) {  // uniform: nothing has changed in this sequence, the rows are zero
+      m_run = 0.f;
+      l_run = 1.f;
+    } else {
+      // Sum over all keys of the sequence.  The running reference goes on from the compact keys (which are among them),
+      // and the accumulator follows where it moves.  Two tiles at a time: the scores of the next two and the
+      // exponentials of these overlap, and a barrier, a maximum and their waits serve 32 exponentials of a lane.
+      // Bound by the vector ALU (an exponential, a multiply-add and an addition per score).
+      constexpr int TN = 2 * TK, LPN = LPW;  // keys and copies per wave of a step; a stage holds one
+      const int n_lo = split * a.chunk, n_hi = min(a.L, n_lo + a.chunk), nt = (n_hi - n_lo + TN - 1) / TN;
+      const bf16_t *kn = (const bf16_t *)a.norm_k + (((size_t)b * a.L + n_lo) * a.Hkv + kvh) * DH;
+      const unsigned char *kn_u = uniform_ptr(kn);
+      auto issue_k = [&](int t) {
+        const uint32_t sb = lds0 + (uint32_t)(t % NS) * T::STAGE_BYTES;
+        if (n_lo + (t + 1) * TN <= n_hi) {  // uniform
+#pragma unroll
+          for (int i = 0; i < LPN; ++i) {
+            const unsigned char *base = kn_u + ((size_t)t * TN + (i / (LPN / 2)) * TK) * kv_stride * 2;
+            dma16_s(base, off_k[i % (LPN / 2)], sb + (uint32_t)(i / (LPN / 2)) * T::REGION + (uint32_t)((i % (LPN / 2)) * NW + wave) * 1024u);
+          }
+        } else {  // keys past the end re-read the last one (masked later)
+#pragma unroll
+          for (int i = 0; i < LPN; ++i) {
+            const int row = ((i % (LPN / 2)) * NW + wave) * 4 + r4, key = min(t * TN + (i / (LPN / 2)) * TK + row, n_hi - n_lo - 1);
+            dma16(kn + (size_t)key * kv_stride + (cpos ^ (row & 15)) * 8,
+                  sb + (uint32_t)(i / (LPN / 2)) * T::REGION + (uint32_t)((i % (LPN / 2)) * NW + wave) * 1024u);
+          }
+        }
+      };
+      __syncthreads();  // every wave is done with the compact keys' stages
+#pragma unroll
+      for (int s = 0; s < NS - 1; ++s)
+        if (s < nt) issue_k(s);
+      if (NS - 2 < nt) wait_vmcnt<(NS - 2) * LPN>();  // step 0 has landed (this wave's part)
+      else wait_vmcnt<0>();
+      __syncthreads();
+      const bool idle = wq * 32 >= nq;  // wave-uniform: copies and barriers only
+      floatx16 s_cur[2];
+      auto read_k = [&](bf16x8 (&kf)[KK], int t, int u) {
+        const unsigned char *skp = smem_raw + (size_t)(t % NS) * T::STAGE_BYTES + u * T::REGION + krow * ROWB;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) kf[kk] = *reinterpret_cast<const bf16x8 *>(skp + (((2 * kk + lhi) ^ ksw) * 16));
+      };
+      auto scores = [&](const bf16x8 (&kf)[KK], floatx16 &s) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], s, 0, 0, 0);
+      };
+      if (!idle) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          bf16x8 kf[KK];
+          read_k(kf, 0, u);
+          scores(kf, s_cur[u]);
+        }
+      }
+      float l_lane = 0.f;  // this lane's keys
+      for (int t = 0; t < nt; ++t) {
+        if (t + NS - 2 < nt) wait_vmcnt<(NS - 3) * LPN>();  // step t+1 has landed
+        else wait_vmcnt<0>();
+        __syncthreads();  // ... everyone's part of it; everyone is done with step t-1's stage
+        if (t + NS - 1 < nt) issue_k(t + NS - 1);
+        if (idle) continue;
+        bf16x8 kf0[KK], kf1[KK];  // (after the last step these come from a stage that holds none: the result is dropped)
+        read_k(kf0, t + 1, 0);
+        if (n_lo + (t + 1) * TN > n_hi) {  // wave-uniform: only the last step can hold keys past the end
+          const int key_base = n_lo + t * TN + key_lane;
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if (key_base + u * TK + 8 * (e / 4) + (e % 4) >= n_hi) s_cur[u][e] = -INFINITY;
+        }
+        float m0 = s_cur[0][0], m1 = s_cur[1][0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) {
+          m0 = fmaxf(m0, s_cur[0][e]);
+          m1 = fmaxf(m1, s_cur[1][e]);
+        }
+        float mx = fmaxf(m0, m1) * sc;
+        if (__any(mx > m_run + 8.0f)) {  // rare: the reference moves
+          mx = xhalf_max(mx);
+          const bool need = mx > m_run + 8.0f;
+          const float corr = need ? __builtin_amdgcn_exp2f(m_run - mx) : 1.0f;
+          m_run = need ? mx : m_run;
+          l_lane *= corr;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc_o[db][e] *= corr;
+        }
+        const float neg_ref = (m_run == -INFINITY) ? 0.f : -m_run;
+        read_k(kf1, t + 1, 1);
+        floatx16 s_next[2];
+        scores(kf0, s_next[0]);
+        scores(kf1, s_next[1]);
+        float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 32; ++e) ps[e % 4] += __builtin_amdgcn_exp2f(fmaf(s_cur[e / 16][e % 16], sc, neg_ref));
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // score product
+          if (i < 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // operands of the second tile
+          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // scale + shift of two scores
+          __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);  // their exponentials
+          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // and sums
+        }
+        l_lane += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+        s_cur[0] = s_next[0];
+        s_cur[1] = s_next[1];
+      }
+      l_run = xhalf_sum(l_lane);
+    }
+  }
   __syncthreads();  // every wave is done with the last tile: the stages become merge scratch
 
   // merge the WK wave columns of each query block through LDS
@@ -827,16 +951,16 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   }
 }
 
-template <int WQ, int WK> void launch_dma(const AttnArgs &a, hipStream_t s) {
+template <int WQ, int WK, bool NORM> void launch_dma(const AttnArgs &a, hipStream_t s) {
   using T = DTile<WQ, WK>;
   static bool done = false;
   if (!done) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16_dma<WQ, WK>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16_dma<WQ, WK, NORM>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
     done = true;
   }
   const int q_tiles = max_q_tiles_grouped(a, T::BQ);
-  k_attn_bf16_dma<WQ, WK><<<attn_grid_grouped(a, q_tiles), T::NT, T::LDS_BYTES, s>>>(a, q_tiles);
+  k_attn_bf16_dma<WQ, WK, NORM><<<attn_grid_grouped(a, q_tiles), T::NT, T::LDS_BYTES, s>>>(a, q_tiles);
 }
 
 template <int DH, int WQ, int NW, int QB> void launch_cfg(const AttnArgs &a, hipStream_t s) {
@@ -858,7 +982,11 @@ void launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
   if (a.dh == 128) {
     // 128 query rows: four waves, each with all keys of a 32-key tile (64 KB of LDS: two workgroups
     // per CU, which drift apart and fill each other's stalls); 64 rows: 2 x 2 waves over 64-key tiles
-    if (wide) launch_dma<4, 1>(a, s); else launch_dma<2, 2>(a, s);
+    if (a.norm_k) {
+      if (wide) launch_dma<4, 1, true>(a, s); else launch_dma<2, 2, true>(a, s);
+    } else {
+      if (wide) launch_dma<4, 1, false>(a, s); else launch_dma<2, 2, false>(a, s);
+    }
   } else {
     if (wide) launch_cfg<64, 2, 4, 2>(a, s); else launch_cfg<64, 1, 4, 2>(a, s);
   }

@@ -46,8 +46,8 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
   if (b < 0) return;  // uniform: no such tile
   const int j0 = tile_info[1], nq = tile_info[2];
   const int h = blockIdx.y, kvh = h / (a.H / a.Hkv), split = blockIdx.z;
-  const int kbase = a.key_offsets ? a.key_offsets[b] : b * a.L;
-  const int Lk = a.key_offsets ? a.key_offsets[b + 1] - kbase : a.L;
+  const int kbase = a.key_offsets ? min(a.key_offsets[b], a.key_cap) : b * a.L;
+  const int Lk = a.key_offsets ? min(a.key_offsets[b + 1], a.key_cap) - kbase : a.L;
   const int k_lo = split * a.chunk, k_hi = min(Lk, k_lo + a.chunk);
   if (k_lo >= k_hi) return;  // uniform
 

@@ -95,7 +95,11 @@ struct AttnArgs {
   int q_by_token;
   const void *k, *v;    // [B, L, Hkv, dh] T-typed; with key_offsets: compact rows [*, Hkv, dh]
   const int32_t *key_offsets;  // nullptr, or [B+1]: the keys of sequence b are rows [key_offsets[b],
-                               // key_offsets[b+1]) of k / v (a split past a sequence's last key writes nothing)
+                               // key_offsets[b+1]) of k / v, at most key_cap rows (a split past a sequence's last
+                               // key writes nothing)
+  int key_cap;
+  const void *norm_k;   // nullptr, or (bf16, head_dim 128, with key_offsets) [B, L, Hkv, dh]: the rows are divided by the
+                        // sum over all of these keys, of which the compact ones are a part; `splits` and `chunk` cut them
   float *lse_out;       // nullptr, or [T, H]: the merge kernels store log(sum exp) of every merged row here
   Rows rows;            // token ids of the query rows (idx may be nullptr = identity)
   const int32_t *offsets;  // [B+1] per-sequence offsets into rows, or nullptr = every sequence has L rows

@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256) void k_clear_rows(Rows rows, T *dv, int dkv) {
 struct CachedNorm {
   const float *part_o, *part_ml, *lse;
   const int32_t *key_offsets;
-  int cap, H, dh, chunk, splits, L;
+  int cap, H, dh, chunk, splits, L, key_cap;
 };
 
 template <typename T, bool CACHED>
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(SAL_NT) void k_saliency_approx(Rows win, int D, con
     int ns = 0;  // key splits that hold candidate keys of this token's sequence
     if (CACHED && !p) {
       const int sq = r / cn.L;
-      const int lk = cn.key_offsets[sq + 1] - cn.key_offsets[sq];
+      const int lk = min(cn.key_offsets[sq + 1], cn.key_cap) - min(cn.key_offsets[sq], cn.key_cap);
       ns = (lk + cn.chunk - 1) / cn.chunk;
       ns = ns < cn.splits ? ns : cn.splits;
     }
@@ -633,7 +633,7 @@ void launch_saliency_approx(DType t, Rows win, int D, const void *c_sal, const v
   CachedNorm cn{};
   if (cached)
     cn = CachedNorm{cached->part_o, cached->part_ml, lse, cached->key_offsets, cached->rows.cap,
-                    cached->H, cached->dh, cached->chunk, cached->splits, L};
+                    cached->H, cached->dh, cached->chunk, cached->splits, L, cached->key_cap};
 #define DY_SAL_APPROX(TT, C)                                                                        \
   k_saliency_approx<TT, C><<<grid, SAL_NT, 0, s>>>(win, D, (const TT *)c_sal, (const TT *)dc, pos, \
                                                    (TT *)c_cache, tau, cos_out, flag_out, cn)
