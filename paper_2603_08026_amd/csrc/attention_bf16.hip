@@ -405,10 +405,8 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int l32 = lane % 32, lhi = lane / 32;
   const int wq = wave / WK, wk = wave % WK;
-  int tile, kvh, split;
-  if (!attn_work_item_grouped(a, q_tiles, &tile, &kvh, &split)) return;  // uniform
-  int tile_info[4];
-  find_tile_grouped(a, BQ, tile, tile_info);
+  int kvh = 0, split = 0, tile_info[4];
+  attn_work_item_grouped(a, BQ, q_tiles, &kvh, &split, tile_info);
   const int b = tile_info[0];
   if (b < 0) return;  // uniform: no such tile
   const int nq = tile_info[3];  // (row, head of the group) pairs in this tile

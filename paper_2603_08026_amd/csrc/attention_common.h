@@ -104,64 +104,66 @@ __device__ __forceinline__ int wave_scan(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // last lane of row 1 -> rows 2 and 3
   return x;
 }
-// Tile number -> info[0] = sequence (or -1), info[1] = index of the sequence's first row in the row
-// list, info[2] = first packed row of the tile, info[3] = packed rows in the tile.  Called by every wave
-// with all its lanes; the results are uniform.  A lane counts the tiles of one sequence (64 at a time): one
-// round of loads, where a walk over the sequences waits for each of them in turn.  A list with a large
-// capacity has thousands of workgroups that only find out that their tile does not exist (with the smaller
-// grids of the row kernels: loop of two layers and four steps over 8 x 1024 tokens 2424 -> 2334 us).
-__device__ __forceinline__ void find_tile_grouped(const AttnArgs &a, int BQ, int tile, int (&info)[4]) {
-  const int g = a.H / a.Hkv;
+// Work item of a workgroup of a 1-D launch over (key split, KV head, tile of packed rows), XCD-aware as above.
+// info[0] = sequence (or -1: no item), info[1] = index of the sequence's first row in the row list, info[2] = first packed
+// row of the tile, info[3] = packed rows in the tile.  Called by every wave with all its lanes; the results are
+// uniform.  The items are those of the tiles that exist, not of the q_tiles that the list's capacity allows: each XCD takes
+// an equal share of them, and they come before all workgroups without work.  (Numbered by the capacity, a list of 330
+// entries with room for 8192 had its 256 items in four groups per XCD behind 64 idle workgroups each: 43 us instead of 35
+// for 8 sequences of 1024 tokens, 32 heads.)
+// A lane counts the tiles of one sequence (64 at a time): one round of loads, where a walk over the sequences waits for each
+// of them in turn.
+__device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ, int q_tiles, int *kvh, int *split,
+                                                       int (&info)[4]) {
+  const int g = a.H / a.Hkv, lane = threadIdx.x % WAVE;
   info[0] = -1;
   info[1] = info[2] = info[3] = 0;
-  if (!a.offsets) {
-    const int per = (a.L * g + BQ - 1) / BQ;
-    const int b = tile / per, t = tile % per;
-    if (b < a.B) {
-      info[0] = b;
-      info[1] = b * a.L;
-      info[2] = t * BQ;
-      info[3] = min(BQ, a.L * g - t * BQ);
-    }
-    return;
-  }
-  const int lane = threadIdx.x % WAVE, total = min(a.offsets[a.B], a.rows.cap);
-  int t = tile;
-  for (int b0 = 0; b0 < a.B; b0 += WAVE) {
+  int total = 0, lo = 0, hi = 0, upto = 0, tiles = q_tiles;
+  auto tiles_of = [&](int b0) {  // rows [lo, hi) of this lane's sequence, and the tiles up to and with it
     const int b = b0 + lane;
-    int lo = 0, hi = 0;
+    lo = hi = 0;
     if (b < a.B) {
       lo = min(a.offsets[b], total);
       hi = min(a.offsets[b + 1], total);
     }
-    const int np = (hi - lo) * g, upto = wave_scan((np + BQ - 1) / BQ);
+    upto = wave_scan(((hi - lo) * g + BQ - 1) / BQ);
+    return __builtin_amdgcn_readlane(upto, WAVE - 1);
+  };
+  if (a.offsets) {
+    total = min(a.offsets[a.B], a.rows.cap);
+    tiles = 0;
+    for (int b0 = 0; b0 < a.B; b0 += WAVE) tiles += tiles_of(b0);
+  }
+  const int items = tiles * a.Hkv * a.splits, per_xcd = (items + ATTN_XCD - 1) / ATTN_XCD;
+  const int p = blockIdx.x, w = (p % ATTN_XCD) * per_xcd + p / ATTN_XCD;
+  if (p / ATTN_XCD >= per_xcd || w >= items) return;
+  int t = w % tiles;
+  const int rest = w / tiles;
+  *kvh = rest % a.Hkv;
+  *split = rest / a.Hkv;
+  if (!a.offsets) {
+    const int per = (a.L * g + BQ - 1) / BQ, b = t / per;
+    info[0] = b;
+    info[1] = b * a.L;
+    info[2] = (t % per) * BQ;
+    info[3] = min(BQ, a.L * g - info[2]);
+    return;
+  }
+  for (int b0 = 0; b0 < a.B; b0 += WAVE) {
+    if (a.B > WAVE) tiles_of(b0);  // (else still in the registers)
     const uint64_t past = __ballot(upto > t);  // the sequences at or after the tile's
     if (past) {
-      const int w = __ffsll((unsigned long long)past) - 1;
-      const int n_w = __builtin_amdgcn_readlane(np, w);
-      const int first = t - (__builtin_amdgcn_readlane(upto, w) - (n_w + BQ - 1) / BQ);
-      info[0] = b0 + w;
-      info[1] = __builtin_amdgcn_readlane(lo, w);
+      const int s = __ffsll((unsigned long long)past) - 1;
+      const int n = __builtin_amdgcn_readlane((hi - lo) * g, s);
+      const int first = t - (__builtin_amdgcn_readlane(upto, s) - (n + BQ - 1) / BQ);
+      info[0] = b0 + s;
+      info[1] = __builtin_amdgcn_readlane(lo, s);
       info[2] = first * BQ;
-      info[3] = min(BQ, n_w - first * BQ);
+      info[3] = min(BQ, n - first * BQ);
       return;
     }
     t -= __builtin_amdgcn_readlane(upto, WAVE - 1);
   }
-}
-// Work item of a 1-D launch over (key split, KV head, tile of packed rows), XCD-aware as above.
-__device__ __forceinline__ bool attn_work_item_grouped(const AttnArgs &a, int q_tiles, int *tile, int *kvh,
-                                                       int *split) {
-  const int items = q_tiles * a.Hkv * a.splits;
-  const int per_xcd = (items + ATTN_XCD - 1) / ATTN_XCD;
-  const int p = blockIdx.x;
-  const int w = (p % ATTN_XCD) * per_xcd + p / ATTN_XCD;
-  if (p / ATTN_XCD >= per_xcd || w >= items) return false;
-  *tile = w % q_tiles;
-  const int rest = w / q_tiles;
-  *kvh = rest % a.Hkv;
-  *split = rest / a.Hkv;
-  return true;
 }
 
 void launch_attention_f32(const AttnArgs &a, hipStream_t s);
