@@ -26,11 +26,38 @@ __device__ __forceinline__ int seq_of(int row, int B, int L) {
 // start at or before it.  `coherent` makes the flag reads bypass the per-CU cache (flags written by
 // other workgroups of the same launch).  wave_cnt: LDS scratch of NT/64 ints.  Returns base + the
 // number of flagged entries in [lo, hi).
+// One sweep: entry j = start + thread (j < hi) with its flag f, its token `row` and the sequence sprev of the entry before it
+// (-1: none).  Returns the flagged entries of the sweep.
+template <int NT>
+__device__ __forceinline__ int compact_sweep(bool f, int row, int sprev, bool exists, int base, int B, int L, int32_t *out_idx,
+                                             int32_t *out_off, int out_cap, int *wave_cnt) {
+  const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+  const unsigned long long bal = __ballot(f);
+  const int before = __popcll(bal & ((1ull << lane) - 1ull));
+  if (lane == 0) wave_cnt[w] = __popcll(bal);
+  __syncthreads();
+  int woff = 0, tot = 0;
+#pragma unroll
+  for (int i = 0; i < NT / WAVE; ++i) {
+    const int c = wave_cnt[i];
+    woff += (i < w) ? c : 0;
+    tot += c;
+  }
+  if (exists) {
+    const int p = base + woff + before;  // flagged entries in front of j
+    if (f && p < out_cap) out_idx[p] = row;
+    const int sj = seq_of(row, B, L);
+    for (int b = sprev + 1; b <= sj; ++b) out_off[b] = min(p, out_cap);
+  }
+  __syncthreads();
+  return tot;
+}
+
 template <int NT>
 __device__ __forceinline__ int compact_range(const uint8_t *flag, const Rows &rows, int lo, int hi, int base,
                                              int B, int L, int32_t *out_idx, int32_t *out_off, int out_cap,
                                              bool coherent, int *wave_cnt) {
-  const int tid = threadIdx.x, lane = tid % WAVE, w = tid / WAVE;
+  const int tid = threadIdx.x;
   for (int start = lo; start < hi; start += NT) {
     const int j = start + tid;
     bool f = false;
@@ -42,25 +69,7 @@ __device__ __forceinline__ int compact_range(const uint8_t *flag, const Rows &ro
       row = rows.idx ? rows.idx[j] : j;
       if (j > 0) sprev = seq_of(rows.idx ? rows.idx[j - 1] : j - 1, B, L);
     }
-    const unsigned long long bal = __ballot(f);
-    const int before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wave_cnt[w] = __popcll(bal);
-    __syncthreads();
-    int woff = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < NT / WAVE; ++i) {
-      const int c = wave_cnt[i];
-      woff += (i < w) ? c : 0;
-      tot += c;
-    }
-    if (j < hi) {
-      const int p = base + woff + before;  // flagged entries in front of j
-      if (f && p < out_cap) out_idx[p] = row;
-      const int sj = seq_of(row, B, L);
-      for (int b = sprev + 1; b <= sj; ++b) out_off[b] = min(p, out_cap);
-    }
-    base += tot;
-    __syncthreads();
+    base += compact_sweep<NT>(f, row, sprev, j < hi, base, B, L, out_idx, out_off, out_cap, wave_cnt);
   }
   return base;
 }
