@@ -27,12 +27,12 @@ struct dyllm_ctx {
   float *part_o;   // fp32 scratch shared by consecutive stages: raw GEMM results / attention partials
   float *part_ml;
   size_t part_elems;
-  void *dv_full;   // [R, dkv] value residuals of the approximate path; where they lie by token all zero between calls
+  void *dv_full;   // [R, dkv] value residuals of the approximate path, by token or by sequence; all zero between calls
   void *dc;        // [R, dq] approximate context residual of every token
   void *csal;      // [R, dq] exact context rows of the salient tokens (approximate path)
   int32_t *pos;    // [R] position+1 of a token in the salient list; all zero between calls
   int32_t *win_idx, *win_off;  // [R], [max_batch+1]: the tokens of a response-only step as a list
-  void *ksal;      // [R, dkv] compact copy of the candidates' new key rows (reused-normaliser variant)
+  void *ksal;      // [R, dkv] compact copy of the candidates' new key rows
   float *cosb;     // [R]
   uint8_t *flag;   // [R]
   float *hs;       // [R, d]        x + Wo c (fp32)
@@ -206,7 +206,7 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
   prof_mark(ctx, ST_GEMM_QKV, s);
   launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rows, L,
                       c.n_heads, c.n_kv_heads, c.head_dim, w->bq, w->bk, w->bv, q_out, cache->k,
-                      cache->v, nullptr, 0, nullptr, 0, nullptr, 0, s);
+                      cache->v, 0, nullptr, s);
   prof_mark(ctx, ST_ROPE_SCATTER, s);
   return check_launch(ctx, "qkv refresh");
 }
@@ -348,10 +348,9 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   const dyllm_layer_cfg &c = ctx->cfg;
   const Rows all = win.rows;
   const Rows rin = rows_of(idx_in, B);
-  // compact: the candidates' new keys and value residuals lie by list entry (ksal and a value buffer), and the attention
-  // over them takes its normalisers from a sweep over all keys; else the residual lies by token in a buffer that is
-  // zero elsewhere, which every key meets
-  const bool compact = !cached_norm && dt(ctx) == BF16 && c.head_dim == 128, by_entry = cached_norm || compact;
+  // by_sequence: the candidates' new keys (ksal) and value residuals lie in the form that the share of a sequence's tokens
+  // asks for (compact_form); else the residual lies by token in a buffer that is zero elsewhere, which every key meets
+  const bool by_sequence = !cached_norm && dt(ctx) == BF16 && c.head_dim == 128;
   const int by_token = all.idx != nullptr;  // a window keeps q at its token's row, so that both
                                             // attention passes find it from a token id
   int rc;
@@ -362,8 +361,7 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, all, c.hidden,
                                        wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s);
     launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, all, L, c.n_heads,
-                        0, c.head_dim, w->bq, nullptr, nullptr, ctx->qs, nullptr, nullptr, nullptr, by_token,
-                        nullptr, 0, nullptr, 0, s);
+                        0, c.head_dim, w->bq, nullptr, nullptr, ctx->qs, nullptr, nullptr, by_token, nullptr, s);
   }
   // k, v of the salient tokens: norm, projection, rotation, value residual, merge into the caches
   launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, s);
@@ -373,12 +371,13 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     seg.n_end[0] = ctx->dkv; seg.n_end[1] = 2 * ctx->dkv; seg.n_end[2] = 2 * ctx->dkv;
     const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->fs, nullptr, c.hidden}, rin, c.hidden, seg,
                                        ctx->part_o, ctx->part_elems, ctx->plan, s);
-    // value residual: by token into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
-    // entry next to a compact copy of the new keys
-    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rin, L, 0,
-                        c.n_kv_heads, c.head_dim, nullptr, w->bk, w->bv, nullptr, cache->k, cache->v,
-                        cached_norm ? ctx->dc : ctx->dv_full, 0, by_entry ? ctx->ksal : nullptr,
-                        by_entry, ctx->pos, win.lo, s);  // also marks the step's candidates in the token -> entry map
+    // value residual: by token or by sequence into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
+    // entry; the last two next to a compact copy of the new keys; and the step's candidates in the token -> entry map
+    const CandidateOut cand{cached_norm ? ctx->dc : ctx->dv_full, cached_norm || by_sequence ? ctx->ksal : nullptr,
+                            cached_norm ? DV_BY_ENTRY : by_sequence ? DV_BY_SEQUENCE : DV_BY_TOKEN, idx_in->offsets,
+                            ctx->pos, win.lo};
+    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rin, L, 0, c.n_kv_heads, c.head_dim, nullptr, w->bk, w->bv,
+                        nullptr, cache->k, cache->v, 0, &cand, s);
   }
   if ((rc = check_launch(ctx, "approx: projections"))) return rc;
   // exact rows of the salient tokens  [Alg. 3: C_sal]; q is stored by token here.  With a cache of
@@ -394,19 +393,21 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   if (!cached_norm) {
     // approximate residual of every token of the step: the full softmax against the merged keys times
     // the value residual, which is zero outside the salient rows  [Alg. 4]
-    AttnArgs a = attn_args(ctx, ctx->qs, compact ? ctx->ksal : cache->k, ctx->dv_full, all, win.offsets, B, L, ctx->dc, 0);
+    AttnArgs a = attn_args(ctx, ctx->qs, by_sequence ? ctx->ksal : cache->k, ctx->dv_full, all, win.offsets, B, L, ctx->dc, 0);
     a.q_by_token = by_token;
-    if (compact) {
+    if (by_sequence) {
       a.key_offsets = idx_in->offsets;
       a.key_cap = rin.cap;
       a.norm_k = cache->k;
     }
     launch_attention(dt(ctx), a, s);
     if ((rc = check_launch(ctx, "approx: attention"))) return rc;
-    // new contexts of the step's tokens, cosine test, commit; then the scratch maps go back to zero
+    // new contexts of the step's tokens, cosine test, commit; the scratch maps and the residual buffer go back to zero
+    Residuals residuals;
+    if (by_sequence) residuals = Residuals{ctx->dv_full, idx_in->offsets, rin.cap, L, ctx->dkv};
     launch_saliency_approx(dt(ctx), all, ctx->dq, ctx->csal, ctx->dc, ctx->pos, cache->c, tau, cos_out, ctx->flag,
-                           nullptr, nullptr, L, s);
-    if (!compact) launch_clear_rows(dt(ctx), rin, ctx->dv_full, ctx->dkv, s);  // the residual buffer goes back to zero
+                           nullptr, nullptr, L, residuals, s);
+    if (!by_sequence) launch_clear_rows(dt(ctx), rin, ctx->dv_full, ctx->dkv, s);
   } else {
     // Reused normalisers (Sec. 3.3's O(N |A| d) form): every token of the step is scored against the
     // candidates' keys only -- compact rows, sequence b's at [offsets[b], offsets[b+1]) -- and the
@@ -424,7 +425,7 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     launch_attention(dt(ctx), a, s);
     if ((rc = check_launch(ctx, "approx: attention"))) return rc;
     launch_saliency_approx(dt(ctx), all, ctx->dq, ctx->csal, nullptr, ctx->pos, cache->c, tau, cos_out, ctx->flag,
-                           &a, (const float *)cache->lse, L, s);
+                           &a, (const float *)cache->lse, L, Residuals{}, s);
   }
   launch_compact(ctx->flag, all, B, L, idx_out->idx, idx_out->offsets, idx_out->cap, ctx->status, ctx->scan, s);
   if ((rc = check_launch(ctx, "approx: saliency / compact"))) return rc;

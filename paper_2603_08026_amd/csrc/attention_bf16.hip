@@ -388,12 +388,12 @@ template <int WQ, int WK_> struct DTile {
   static_assert(LPW >= 2 && LPW % 2 == 0, "every wave copies K and V rows");
 };
 
-// NORM: keys and values are compact rows (key_offsets) of some of a sequence's tokens only, and the rows of P V are
-// divided by the sum over ALL L keys of the sequence (norm_k): the context update of tokens whose neighbours' values
-// have changed by v [Alg. 4 with the value residual, zero elsewhere, left out].  After the loop over the compact
-// keys a second one sweeps all keys for the sum alone: no V copies and reads, half the products.  8 x 1024 tokens,
-// 32 heads, 330 candidates, against all keys meeting the zero-padded residual: whole sequences and response windows on
-// average 74 -> 63 us a pass (one tile a step of the sweep: 68), and no launch that clears the padded residual.
+// NORM: the context update of tokens whose neighbours' values have changed by v [Alg. 4], in the form that the number of a
+// sequence's candidates asks for (compact_form).  Many: all keys meet v, which is zero but for the candidates.  Few: keys and
+// values are those of the candidates alone (key_offsets), and the rows of P V are divided by the sum over ALL L keys of
+// the sequence (norm_k).  After the loop over the candidates a second one sweeps all keys for the sum alone: no V copies
+// and reads, half the products.  8 x 1024 tokens, 32 heads, 330 candidates, against all keys meeting the zero-padded
+// residual: whole sequences and response windows on average 74 -> 63 us a pass (one tile a step of the sweep: 68).
 template <int WQ, int WK_, bool NORM>
 __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, int q_tiles) {  // two waves per SIMD: 256 registers, no AGPR shuffling
   using T = DTile<WQ, WK_>;
@@ -421,15 +421,26 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
     jq = tile_info[1] + p / grp;
     hq = kvh * grp + p % grp;
   }
-  const int kbase = a.key_offsets ? min(a.key_offsets[b], a.key_cap) : b * a.L;
-  const int Lk = a.key_offsets ? min(a.key_offsets[b + 1], a.key_cap) - kbase : a.L;
-  // (NORM: the splits cut the sweep over all keys; each takes its share of the compact keys, perhaps none)
-  const int k_chunk = NORM ? split_chunk(Lk, a.splits, TK) : a.chunk;
+  int kbase = b * a.L, Lk = a.L, k_chunk = a.chunk;
+  bool compact = false;  // uniform: the candidates of this sequence alone, then the sweep over all keys
+  if (a.key_offsets) {
+    const int first = min(a.key_offsets[b], a.key_cap), n = min(a.key_offsets[b + 1], a.key_cap) - first;
+    if constexpr (NORM) {
+      compact = compact_form(n, a.L);
+      if (compact) {  // the splits cut the sweep; each takes its share of the compact keys, perhaps none
+        Lk = n;
+        k_chunk = split_chunk(Lk, a.splits, TK);
+      }
+    } else {
+      kbase = first;
+      Lk = n;
+    }
+  }
   const int k_lo = NORM ? min(Lk, split * k_chunk) : split * k_chunk, k_hi = min(Lk, k_lo + k_chunk);
   if (!NORM && k_lo >= k_hi) return;  // uniform
 
   const size_t kv_stride = (size_t)a.Hkv * DH;
-  const bf16_t *kc = (const bf16_t *)a.k + ((size_t)kbase * a.Hkv + kvh) * DH;
+  const bf16_t *kc = (const bf16_t *)(NORM && !compact ? a.norm_k : a.k) + ((size_t)kbase * a.Hkv + kvh) * DH;
   const bf16_t *vc = (const bf16_t *)a.v + ((size_t)kbase * a.Hkv + kvh) * DH;
 
   // query operand: the wave's 32 queries, in registers for the whole key sweep
@@ -716,7 +727,7 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   }
   pv();  // the last tile's
   }
-  if constexpr (NORM) {
+  if (NORM && compact) {
     if (Lk == 0) {  // uniform: nothing has changed in this sequence, the rows are zero
       m_run = 0.f;
       l_run = 1.f;

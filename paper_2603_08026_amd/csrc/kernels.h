@@ -31,6 +31,24 @@ struct Splits {
   __host__ __device__ int of(int j) const { return j < tail_from ? n : n_tail; }
 };
 
+// Candidates of the approximate update of a sequence (bf16, head_dim 128): up to a fifth of its tokens their keys and
+// value residuals lie one after the other, and the normalisers come from a sweep over all keys; from there on the
+// residuals lie by token, zero elsewhere, and every key meets them, which needs no sweep.  The step without its FFN half in
+// one form and the other, 32 heads, us: 8 x 1024 tokens, 10 / 15 / 20 / 25 / 50 / 100 % candidates 575 617 647 678 870 1258
+// against 588 625 646 676 834 1157; 2 x 513 tokens 140 144 150 153 171 232 against 141 144 149 151 166 221; a window of
+// 512 of 2048 positions, 1 / 7.5 / 12.5 / 25 % of the sequence 153 165 174 194 against 159 168 175 192.  The line is decided
+// per sequence, on the device.
+__host__ __device__ inline bool compact_form(int candidates, int L) { return candidates <= L / 5; }
+// Row of candidate r (entry j of its list, which has `cap` entries at most) among the [B*L] rows of both forms.  Inside the
+// sequence's rows whatever the offsets say.
+struct CandidateRow { int row; bool compact; };
+__device__ __forceinline__ CandidateRow candidate_row(const int32_t *offsets, int cap, int L, int r, int j) {
+  const int b = r / L, lo = min(offsets[b], cap);
+  const bool compact = compact_form(min(offsets[b + 1], cap) - lo, L);
+  return CandidateRow{compact ? b * L + min(max(j - lo, 0), L - 1) : r, compact};
+}
+enum DvLayout { DV_NONE, DV_BY_TOKEN, DV_BY_ENTRY, DV_BY_SEQUENCE };
+
 // ---- row kernels (HBM-bound) ------------------------------------------------------------------
 // out[j,:] = RMSNorm(x[row_j,:]) * gain            x: [T,d] T-typed, out: [cap,d] T-typed
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
@@ -40,17 +58,26 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
 //
 // q/k/v: sum of splits + bias, rotary embedding of q and k by the table entry of position
 // (row mod L), q_out[j] (T-typed [cap,dq]; q_out[row_j] when q_by_token), k and v rows scattered into
-// the caches at row_j; dv_out (may be nullptr) takes v - v_cache of those rows before the merge, at
-// row_j or (dv_by_entry) at j; ksal_out (may be nullptr) takes a copy of the rotated k rows at j.
+// the caches at row_j.
 // rope_tab: [max_seq, dh/2, 2] fp32 (cos, sin).  dh is 64 or 128.
-// dv_out (optional, [T, Hkv*dh] T-typed): value residual new - cached of the rows, taken before the merge
-// entry_of (optional, [T] int32): entry_of[row_j] = j + 1, the map from a token to its list entry, written
-// for the rows at positions >= entry_lo of their sequence only
+// What the approximate step keeps of its candidates beside the caches (a kernel of its own: with these in the kernel of
+// every step, q of 8192 rows took 55 instead of 49 us):
+//   dv        v - v_cache of the rows before the merge, at row_j (DV_BY_TOKEN), at j (DV_BY_ENTRY) or at their candidate_row
+//             by `offsets` (DV_BY_SEQUENCE; not for the rows at positions below entry_lo)
+//   k         nullptr, or a copy of the rotated k rows at the same places (DV_BY_SEQUENCE: in the compact form only)
+//   entry_of  [T]: entry_of[row_j] = j + 1, the map from a token to its list entry, written for the rows at positions
+//             >= entry_lo of their sequence only
+struct CandidateOut {
+  void *dv, *k;
+  DvLayout layout;
+  const int32_t *offsets;
+  int32_t *entry_of;
+  int entry_lo;
+};
 void launch_qkv_finalize(DType t, const float *part, Splits splits,
                          const float *rope_tab, Rows rows, int L, int H, int Hkv, int dh,
                          const void *bq, const void *bk, const void *bv, void *q_out, void *k_cache,
-                         void *v_cache, void *dv_out, int q_by_token, void *ksal_out, int dv_by_entry,
-                         int32_t *entry_of, int entry_lo, hipStream_t s);
+                         void *v_cache, int q_by_token, const CandidateOut *cand, hipStream_t s);
 // out-projection: h[j] = x[row_j] + sum of splits (fp32 [cap,d]); f[j] = RMSNorm(h[j]) * gain (T-typed)
 void launch_oproj_finalize(DType t, const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
@@ -98,8 +125,10 @@ struct AttnArgs {
                                // key_offsets[b+1]) of k / v, at most key_cap rows (a split past a sequence's last
                                // key writes nothing)
   int key_cap;
-  const void *norm_k;   // nullptr, or (bf16, head_dim 128, with key_offsets) [B, L, Hkv, dh]: the rows are divided by the
-                        // sum over all of these keys, of which the compact ones are a part; `splits` and `chunk` cut them
+  const void *norm_k;   // nullptr, or (bf16, head_dim 128, with key_offsets) [B, L, Hkv, dh]: the context update of Alg. 4.
+                        // k and v are laid out by sequence then (candidate_row): where compact_form holds the rows are
+                        // divided by the sum over all of these keys, of which the compact ones are a part; elsewhere v
+                        // has a row for every one of these keys.  `splits` and `chunk` cut all L keys
   float *lse_out;       // nullptr, or [T, H]: the merge kernels store log(sum exp) of every merged row here
   Rows rows;            // token ids of the query rows (idx may be nullptr = identity)
   const int32_t *offsets;  // [B+1] per-sequence offsets into rows, or nullptr = every sequence has L rows
@@ -191,10 +220,16 @@ void launch_fill_i32(int32_t *p, int32_t v, int n, hipStream_t s);
 // cos_out[r] (may be nullptr), flag_out[j] = cos < tau.  The residual is dc[j], or (cached != nullptr)
 // sum over the key splits s of part_o[s][j] * exp(m_s - lse[r, h]) from the partials of an attention
 // pass over the compact candidate keys (cached->key_offsets) -- the normalisers are NOT recomputed.
-// Every pos entry that is read non-zero is set back to zero.
+// Every pos entry that is read non-zero is set back to zero, and so is the residual row of that token where the
+// residuals lie by sequence (residuals.dv).
+struct Residuals {
+  void *dv = nullptr;  // [T, dkv] T-typed, rows by candidate_row of the list entry
+  const int32_t *offsets = nullptr;
+  int cap = 0, L = 0, dkv = 0;
+};
 void launch_saliency_approx(DType t, Rows win, int D, const void *c_sal, const void *dc, int32_t *pos,
                             void *c_cache, float tau, float *cos_out, uint8_t *flag_out,
-                            const AttnArgs *cached, const float *lse, int L, hipStream_t s);
+                            const AttnArgs *cached, const float *lse, int L, Residuals residuals, hipStream_t s);
 // idx/off := the tokens at positions [lo, L) of each of the B sequences, as an index list
 void launch_make_window(int B, int L, int lo, int32_t *idx, int32_t *off, hipStream_t s);
 // flag[r] = 1 for every token r < T of the list whose position in its sequence is >= lo

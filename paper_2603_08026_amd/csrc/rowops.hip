@@ -137,15 +137,16 @@ __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ 
 // Half-split pairing: element p of a head couples with element p + dh/2, rotated by the angle
 // pos * theta^(-2p/dh); the table holds (cos, sin) per (pos, p).  A thread handles 4 neighbouring
 // pairs of one head (two float4 of the raw result, two float4 of the table).
-template <typename T>
+// DV: with what the approximate step keeps of its candidates (CandidateOut).
+template <typename T, DvLayout DV>
 __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ part, Splits splits_of,
                                                       const float *__restrict__ tab,
                                                       Rows rows, int L, int H, int Hkv, int dh,
                                                       const T *__restrict__ bq, const T *__restrict__ bk,
                                                       const T *__restrict__ bv, T *__restrict__ q_out,
                                                       T *__restrict__ kc, T *__restrict__ vc,
-                                                      T *__restrict__ dv_out, int q_by_token,
-                                                      T *__restrict__ ksal_out, int dv_by_entry,
+                                                      int q_by_token, T *__restrict__ dv_out, T *__restrict__ k_out,
+                                                      const int32_t *__restrict__ cand_offsets,
                                                       int32_t *__restrict__ entry_of, int entry_lo) {
   const int n = row_count(rows);
   const int half = dh / 2, dq = H * dh, dkv = Hkv * dh, ld = dq + 2 * dkv;
@@ -158,7 +159,15 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
     const int splits = sp.of(j);
     const int pos = r % L;
     // token -> its list entry (0 = not in the list), for the tokens at positions >= entry_lo only
-    if (entry_of && threadIdx.x == 0 && pos >= entry_lo) entry_of[r] = j + 1;
+    if (DV != DV_NONE && threadIdx.x == 0 && pos >= entry_lo) entry_of[r] = j + 1;
+    int cand_row = DV == DV_BY_TOKEN ? r : j;
+    bool dv_here = DV != DV_NONE, k_here = DV == DV_BY_ENTRY;
+    if constexpr (DV == DV_BY_SEQUENCE) {  // (a residual is put back to zero by the token's entry in entry_of)
+      const CandidateRow c = candidate_row(cand_offsets, rows.cap, L, r, j);
+      cand_row = c.row;
+      dv_here = pos >= entry_lo;
+      k_here = c.compact;
+    }
     const float *src = part + (size_t)j * ld;
     const float *t = tab + (size_t)pos * half * 2;
     const int items = qk_items + (j < sp.done_to ? 0 : v_items);  // (values that the GEMM has written itself are left out)
@@ -190,8 +199,7 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
                           from_f<T>(x1.z * t1.x - x2.z * t1.y), from_f<T>(x1.w * t1.z - x2.w * t1.w)};
         const T hi4[4] = {from_f<T>(x2.x * t0.x + x1.x * t0.y), from_f<T>(x2.y * t0.z + x1.y * t0.w),
                           from_f<T>(x2.z * t1.x + x1.z * t1.y), from_f<T>(x2.w * t1.z + x1.w * t1.w)};
-        // (the new key row also goes to a compact copy when the approximate pass scores candidates only)
-        T *ks = (!isq && ksal_out) ? ksal_out + (size_t)j * dkv : nullptr;
+        T *ks = (k_here && !isq) ? k_out + (size_t)cand_row * dkv : nullptr;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           dst[c0 + u] = lo4[u];
@@ -213,8 +221,8 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
         }
         T *vrow = vc + (size_t)r * dkv + c0;
         const T n0 = from_f<T>(x.x), n1 = from_f<T>(x.y), n2 = from_f<T>(x.z), n3 = from_f<T>(x.w);
-        if (dv_out) {  // residual of the stored values, before the merge overwrites the cached row
-          T *d = dv_out + (size_t)(dv_by_entry ? j : r) * dkv + c0;
+        if (dv_here) {  // residual of the stored values, before the merge overwrites the cached row
+          T *d = dv_out + (size_t)cand_row * dkv + c0;
           d[0] = from_f<T>(to_f<T>(n0) - to_f<T>(vrow[0])); d[1] = from_f<T>(to_f<T>(n1) - to_f<T>(vrow[1]));
           d[2] = from_f<T>(to_f<T>(n2) - to_f<T>(vrow[2])); d[3] = from_f<T>(to_f<T>(n3) - to_f<T>(vrow[3]));
         }
@@ -490,19 +498,24 @@ void launch_down_finalize(DType t, const float *part, Splits splits, const float
 void launch_qkv_finalize(DType t, const float *part, Splits splits,
                          const float *rope_tab, Rows rows, int L, int H, int Hkv, int dh,
                          const void *bq, const void *bk, const void *bv, void *q_out, void *k_cache,
-                         void *v_cache, void *dv_out, int q_by_token, void *ksal_out, int dv_by_entry,
-                         int32_t *entry_of, int entry_lo, hipStream_t s) {
+                         void *v_cache, int q_by_token, const CandidateOut *cand, hipStream_t s) {
   if (rows.cap <= 0) return;
-  if (t == F32)
-    k_qkv_finalize<float><<<row_grid(rows), RB, 0, s>>>(
-        part, splits, rope_tab, rows, L, H, Hkv, dh, (const float *)bq, (const float *)bk,
-        (const float *)bv, (float *)q_out, (float *)k_cache, (float *)v_cache, (float *)dv_out, q_by_token,
-        (float *)ksal_out, dv_by_entry, entry_of, entry_lo);
-  else
-    k_qkv_finalize<bf16_t><<<row_grid(rows), RB, 0, s>>>(
-        part, splits, rope_tab, rows, L, H, Hkv, dh, (const bf16_t *)bq, (const bf16_t *)bk,
-        (const bf16_t *)bv, (bf16_t *)q_out, (bf16_t *)k_cache, (bf16_t *)v_cache, (bf16_t *)dv_out, q_by_token,
-        (bf16_t *)ksal_out, dv_by_entry, entry_of, entry_lo);
+  const CandidateOut c = cand ? *cand : CandidateOut{};
+#define DY_QKV_FIN(TT, C)                                                                               \
+  k_qkv_finalize<TT, C><<<row_grid(rows), RB, 0, s>>>(                                                 \
+      part, splits, rope_tab, rows, L, H, Hkv, dh, (const TT *)bq, (const TT *)bk, (const TT *)bv,     \
+      (TT *)q_out, (TT *)k_cache, (TT *)v_cache, q_by_token, (TT *)c.dv, (TT *)c.k, c.offsets, c.entry_of, c.entry_lo)
+  if (t == F32) {
+    if (c.layout == DV_NONE) DY_QKV_FIN(float, DV_NONE);
+    else if (c.layout == DV_BY_TOKEN) DY_QKV_FIN(float, DV_BY_TOKEN);
+    else DY_QKV_FIN(float, DV_BY_ENTRY);
+  } else {
+    if (c.layout == DV_NONE) DY_QKV_FIN(bf16_t, DV_NONE);
+    else if (c.layout == DV_BY_TOKEN) DY_QKV_FIN(bf16_t, DV_BY_TOKEN);
+    else if (c.layout == DV_BY_ENTRY) DY_QKV_FIN(bf16_t, DV_BY_ENTRY);
+    else DY_QKV_FIN(bf16_t, DV_BY_SEQUENCE);
+  }
+#undef DY_QKV_FIN
 }
 
 inline int sal_grid(int cap) { return cap < 1 ? 1 : (cap > 65536 ? 65536 : cap); }
@@ -584,7 +597,8 @@ __global__ __launch_bounds__(SAL_NT) void k_saliency_approx(Rows win, int D, con
                                                              const T *__restrict__ dc,
                                                              int32_t *__restrict__ pos, T *c_cache,
                                                              float tau, float *__restrict__ cos_out,
-                                                             uint8_t *__restrict__ flag_out, CachedNorm cn) {
+                                                             uint8_t *__restrict__ flag_out, CachedNorm cn,
+                                                             Residuals residuals) {
   __shared__ float red[3 * SAL_NT / WAVE];
   constexpr int N = Vec16<T>::N;
   const int nv = D / N;
@@ -647,6 +661,13 @@ __global__ __launch_bounds__(SAL_NT) void k_saliency_approx(Rows win, int D, con
       // workgroup alone reads its entry, and all its threads did so before the barriers of the sum.
       if (p) pos[r] = 0;
     }
+    if (!CACHED && p && residuals.dv) {
+      Vec16<T> zero;
+#pragma unroll
+      for (int e = 0; e < N; ++e) zero.set(e, 0.f);
+      T *dv = (T *)residuals.dv + (size_t)candidate_row(residuals.offsets, residuals.cap, residuals.L, r, p - 1).row * residuals.dkv;
+      for (int v = threadIdx.x; v < residuals.dkv / N; v += SAL_NT) st16(dv + v * N, zero);
+    }
   }
 }
 
@@ -670,7 +691,7 @@ __global__ __launch_bounds__(256) void k_mark_flags(Rows rows, int T, int L, int
 
 void launch_saliency_approx(DType t, Rows win, int D, const void *c_sal, const void *dc, int32_t *pos,
                             void *c_cache, float tau, float *cos_out, uint8_t *flag_out,
-                            const AttnArgs *cached, const float *lse, int L, hipStream_t s) {
+                            const AttnArgs *cached, const float *lse, int L, Residuals residuals, hipStream_t s) {
   if (win.cap <= 0) return;
   const int grid = win.cap > 65536 ? 65536 : win.cap;
   CachedNorm cn{};
@@ -679,7 +700,7 @@ void launch_saliency_approx(DType t, Rows win, int D, const void *c_sal, const v
                     cached->H, cached->dh, cached->chunk, cached->splits, L, cached->key_cap};
 #define DY_SAL_APPROX(TT, C)                                                                        \
   k_saliency_approx<TT, C><<<grid, SAL_NT, 0, s>>>(win, D, (const TT *)c_sal, (const TT *)dc, pos, \
-                                                   (TT *)c_cache, tau, cos_out, flag_out, cn)
+                                                   (TT *)c_cache, tau, cos_out, flag_out, cn, residuals)
   if (t == F32) {
     if (cached) DY_SAL_APPROX(float, true);
     else DY_SAL_APPROX(float, false);
