@@ -150,11 +150,21 @@ __host__ __device__ inline float first_price(const PlanArgs &a, const GemmPlan &
   return p.row_hi < M ? us + a.stream_us : us;
 }
 // Whether a candidate of the second set, with sk splits, takes the place of the first set's choice p: by how much it has
-// to be cheaper.  The prices' error is 8 % (rms), most of it between different numbers of splits, whose sums are
-// another kernel's time; and the longer the list, the less there is to gain (rounds of the chip are many or nearly full).
+// to be cheaper.  The prices' error is 8 % (rms), most of it between different numbers of splits: the sums of many results
+// are priced too high, those of few too low.  Both choices of every GEMM were timed in a step's projections and FFN half, the
+// sum kernels included: 31 row counts from 140 to 2300, eight layer shapes of hidden 512 to 4096, 567 pairs that differ.
+//   - equal splits, and gate|up, which has none: 0.97 up to 1024 rows, 0.95 beyond (0.85 against a streamed last row tile):
+//     gains 301 us in all and loses at most 2 in one place
+//   - the down projection, whose splits cost a sum kernel: 0.85 gains 278 us and loses 10; 0.90 would lose 132
+//   - q|k|v, out-projection: below 2.5e6 results a split less is a gain nearly wherever the price says so; with more of
+//     them 0.88 up to 1024 rows, 0.78 beyond (0.85 against a streamed last row tile): gains 603 us, loses 42, at most 5 in one
+//     place.  0.97 up to 1024 rows and 0.85 beyond gained 501 and lost 141 (step of 256 rows at hidden 4096, q|k|v in one
+//     split against two, 186 against 181 us; 960 rows, the out-projection likewise, 5 us).
 __host__ __device__ inline bool takes_over(const PlanArgs &a, int M, const GemmPlan &p, float first, int sk, float second) {
   const bool same = p.row_hi == M && sk == p.sk, down = a.split_ok && !a.split_free;
-  return second < (M <= 1024 && !down ? 0.97f : same ? 0.95f : 0.85f) * first;
+  float share = M <= 1024 && !down ? 0.97f : same ? 0.95f : 0.85f;
+  if (a.split_free && !same) share = (float)M * (float)a.N < 2.5e6f ? 0.98f : M <= 1024 ? 0.88f : p.row_hi < M ? 0.85f : 0.78f;
+  return second < share * first;
 }
 
 // The first set's choice on the host: candidate number

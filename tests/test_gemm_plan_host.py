@@ -109,3 +109,18 @@ def test_plans_of_the_many_row_cases(lib, count, cap, cols, streams):
     p = Plan(lib, shape, "qkv", count, cap, 32768 if cap > 17600 else 17600)
     assert p.streams_tail == streams and p.splits == 1 and p.tail_splits == 1
     assert p.cols == cols
+
+
+# (hidden, query heads, KV heads, FFN width), GEMM, rows -> columns and K splits of the faster of the two sets' choices, both of
+# which were timed with the sums of their splits
+@pytest.mark.parametrize("dims,gemm,count,cols,splits", [
+    ((4096, 32, 32, 12288), "qkv", 256, 128, 2), ((4096, 32, 32, 12288), "oproj", 960, 128, 2),
+    ((4096, 32, 32, 12288), "oproj", 1024, 128, 2), ((4096, 32, 32, 12288), "oproj", 1500, 256, 2),
+    ((3584, 28, 4, 18944), "oproj", 1000, 128, 2), ((3584, 28, 4, 18944), "qkv", 768, 128, 2),
+    ((4096, 32, 32, 12288), "qkv", 400, 128, 1), ((4096, 32, 32, 12288), "qkv", 512, 128, 1),
+    ((4096, 32, 32, 12288), "oproj", 1100, 128, 1), ((2048, 16, 16, 5632), "oproj", 640, 128, 2),
+    ((1024, 8, 8, 2816), "qkv", 512, 128, 1), ((1024, 8, 8, 2816), "oproj", 1700, 128, 1)])
+def test_plans_of_timed_pairs(lib, dims, gemm, count, cols, splits):
+    d, h, kv, f = dims
+    p = Plan(lib, W.LayerShape(hidden=d, n_heads=h, n_kv_heads=kv, head_dim=128, ffn=f, dtype="bf16"), gemm, count, 6144, 6144)
+    assert (p.cols, p.splits, p.tiled_rows) == (cols, splits, count)
