@@ -71,12 +71,17 @@ __host__ __device__ inline int stream_split(const PlanArgs &a, int M) {
 //     still walk all of K with their copies) and first fill the slots the full tiles leave;
 //   - weights arrive at 4 TB/s whatever the tiles do; in the streaming tiles as with_stream_price says;
 //   - every K split moves its fp32 sums once more, written and read.
+// whether sk K splits may be taken at all (fewer may then as well)
+__host__ __device__ inline bool can_split(const PlanArgs &a, int M, int sk) {
+  return sk == 1 || (a.split_ok && a.K / PLAN_BK >= PLAN_MIN_SLICES * sk && (long)sk * M * a.N <= a.part_elems);
+}
+__host__ __device__ inline bool can_stream(const PlanArgs &a, int M) {
+  return a.stream_cols && M % 256 > 0 && M % 256 <= STREAM_ROWS && M >= 256;
+}
 __host__ __device__ inline float plan_price(const PlanArgs &a, int M, int c) {
   const int sk = c % PLAN_MAX_SPLIT + 1, xl = (c / PLAN_MAX_SPLIT) & 1, streamed = c / (2 * PLAN_MAX_SPLIT);
   const int tail = M % 256;
-  bool ok = xl ? a.tiles_x != 0 : true;
-  if (sk > 1) ok = ok && a.split_ok && a.K / PLAN_BK >= PLAN_MIN_SLICES * sk && (long)sk * M * a.N <= a.part_elems;
-  if (streamed) ok = ok && a.stream_cols && tail > 0 && tail <= STREAM_ROWS && M >= 256;
+  const bool ok = (!xl || a.tiles_x != 0) && can_split(a, M, sk) && (!streamed || can_stream(a, M));
   const int tiles = (xl ? a.tiles_x : a.tiles_l) * sk;
   const int full = (M / 256 * tiles + PLAN_XCD - 1) / PLAN_XCD, part = (tail && !streamed) ? (tiles + PLAN_XCD - 1) / PLAN_XCD : 0;
   // (counts are whole numbers far below 2^20: the products with the reciprocal round to the right side)
@@ -108,32 +113,42 @@ __host__ __device__ inline GemmPlan plan_of(const PlanArgs &a, int M, int c) {
 //     256 (192) columns are bound by their products
 //   - tiles at the same time slow each other down: a chip that is half empty is 11 % faster per tile
 //   - the weights' stream and the tiles' own time overlap, not entirely; a raw result is written at 10 TB/s beside it
-__host__ __device__ inline float tile_price(const PlanArgs &a, int M, int shape, int mi, int sk) {
+// Tiles of one shape and height: whole row tiles, rows of the last one, and what a tile costs per K slice and beside its slices
+// (whole one, last one).  The same for every number of K splits.
+struct TileHeight { int cols, full, tail; float slice, fixed, tail_slice, tail_fixed; };
+__host__ __device__ inline TileHeight tile_height(const PlanArgs &a, int M, int shape, int mi) {
   const bool l = shape == PLAN_L, x = shape == PLAN_X;
   const int cols = l ? a.tiles_l : x ? a.tiles_x : a.tiles_w, unit = l || x ? 32 : 64, bm = mi * unit;
-  const bool raw = a.split_free || sk > 1;
-  bool ok = cols != 0 && bm <= 256;
-  if (sk > 1) ok = ok && a.split_ok && a.K / PLAN_BK >= PLAN_MIN_SLICES * sk && (long)sk * M * a.N <= a.part_elems;
   const int full = M / bm, tail = M - full * bm;
-  const float fx = (float)((full * cols * sk + PLAN_XCD - 1) / PLAN_XCD), px = tail ? (float)((cols * sk + PLAN_XCD - 1) / PLAN_XCD) : 0.0f;
-  const float rounds = ceilf(fx * a.inv_cus - 1e-4f), more = fmaxf(ceilf((px - (rounds * a.cus - fx)) * a.inv_cus - 1e-4f), 0.0f);
-  const float slices = (float)a.K * (1.0f / PLAN_BK) / (float)sk;
-  auto tile_us = [&](float m) -> float {
-    const float s = l ? 0.261f + 0.0488f * m : x ? fmaxf(0.532f + 0.0557f * m, 0.287f + 0.1124f * m) : fmaxf(0.429f + 0.104f * m, 0.196f + 0.195f * m);
-    const float o = l ? 1.96f + 0.50f * m : x ? 1.48f + 0.80f * m : 2.45f + 0.94f * m;
-    return slices * s + o;
+  auto slice = [&](float m) -> float {
+    return l ? 0.261f + 0.0488f * m : x ? fmaxf(0.532f + 0.0557f * m, 0.287f + 0.1124f * m) : fmaxf(0.429f + 0.104f * m, 0.196f + 0.195f * m);
   };
-  const float empty = 1.0f - fminf((fx + px) * a.inv_cus / fmaxf(rounds + more, 1.0f), 1.0f);
-  const float t = (rounds * tile_us((float)mi) + more * tile_us((float)((tail + unit - 1) / unit))) * (1.0f - 0.22f * empty);
-  const float w = (float)a.N * (float)a.w_cols * (float)a.K * 2.0f * (1.0f / 4.03e6f);
-  const float hi = fmaxf(t, w), lo = fminf(t, w);
-  float us = 1.8f + hi + 0.26f * lo * (lo / hi) * (lo / hi);
+  auto fixed = [&](float m) -> float { return l ? 1.96f + 0.50f * m : x ? 1.48f + 0.80f * m : 2.45f + 0.94f * m; };
+  const float m = (float)mi, t = (float)((tail + unit - 1) / unit);
+  return TileHeight{bm <= 256 ? cols : 0, full, tail, slice(m), fixed(m), slice(t), fixed(t)};
+}
+// The weights' stream, and a price with what its raw results and sums add (M rows, sk splits)
+__host__ __device__ inline float weights_us(const PlanArgs &a) {
+  return (float)a.N * (float)a.w_cols * (float)a.K * 2.0f * (1.0f / 4.03e6f);
+}
+__host__ __device__ inline float with_sums(const PlanArgs &a, int M, int sk, float us) {
   const float mn = 1e-6f * (float)M * (float)a.N;
-  if (raw) us += 0.384f * mn * (float)sk;
+  if (a.split_free || sk > 1) us += 0.384f * mn * (float)sk;
   else if (a.w_cols == 1) us *= 1.08f;  // (the down projection's own epilogue: residual and scatter)
   if (a.split_free) us += 1.58f * mn * (float)(sk - 1);
   else if (sk > 1) us += 1.58f * mn * (float)sk + a.sum_us;
-  return ok ? us : 3e30f;
+  return us;
+}
+__host__ __device__ inline float tile_price(const PlanArgs &a, int M, const TileHeight &h, int sk) {
+  const bool ok = h.cols != 0 && can_split(a, M, sk);
+  const float fx = (float)((h.full * h.cols * sk + PLAN_XCD - 1) / PLAN_XCD), px = h.tail ? (float)((h.cols * sk + PLAN_XCD - 1) / PLAN_XCD) : 0.0f;
+  const float rounds = ceilf(fx * a.inv_cus - 1e-4f), more = fmaxf(ceilf((px - (rounds * a.cus - fx)) * a.inv_cus - 1e-4f), 0.0f);
+  const float slices = (float)a.K * (1.0f / PLAN_BK) / (float)sk;
+  const float empty = 1.0f - fminf((fx + px) * a.inv_cus / fmaxf(rounds + more, 1.0f), 1.0f);
+  const float t = (rounds * (slices * h.slice + h.fixed) + more * (slices * h.tail_slice + h.tail_fixed)) * (1.0f - 0.22f * empty);
+  const float w = weights_us(a), hi = fmaxf(t, w), lo = fminf(t, w);
+  const float us = 1.8f + hi + 0.26f * lo * (lo / hi) * (lo / hi);
+  return ok ? with_sums(a, M, sk, us) : 3e30f;
 }
 
 // Candidate c of the second set for one shape: heights of 1 to 8 units x 8 splits
@@ -146,7 +161,7 @@ __host__ __device__ inline int tile_units(int c) { return c / 8 + 1; }
 
 // The first set's choice in tiles of the best height, height h (units - 1)
 __host__ __device__ inline float first_price(const PlanArgs &a, const GemmPlan &p, int M, int h) {
-  const float us = tile_price(a, p.row_hi, p.xl, h + 1, p.sk);
+  const float us = tile_price(a, p.row_hi, tile_height(a, p.row_hi, p.xl, h + 1), p.sk);
   return p.row_hi < M ? us + a.stream_us : us;
 }
 // Whether a candidate of the second set, with sk splits, takes the place of the first set's choice p: by how much it has
@@ -171,28 +186,43 @@ __host__ __device__ inline bool takes_over(const PlanArgs &a, int M, const GemmP
 inline int first_on_host(const PlanArgs &a, int M) {
   int best = 0;
   float best_t = 1e30f;
-  for (int c = 0; c < PLAN_CANDIDATES; ++c) {
-    const float t = plan_price(a, M, c);
-    if (t < best_t) { best_t = t; best = c; }
-  }
+  for (int shape = 0; shape < (can_stream(a, M) ? 4 : 2); ++shape)
+    for (int sk = 1; sk <= PLAN_MAX_SPLIT && can_split(a, M, sk); ++sk) {
+      const int c = shape * PLAN_MAX_SPLIT + sk - 1;
+      const float t = plan_price(a, M, c);
+      if (t < best_t) { best_t = t; best = c; }
+    }
   return best;
 }
 inline GemmPlan plan_on_host(const PlanArgs &a, int M) {
   if (M <= STREAM_ROWS && a.stream_cols) return GemmPlan{0, 1, 0, stream_split(a, M), 256};
   GemmPlan p = plan_of(a, M, first_on_host(a, M));
-  float first = 2e30f, best_t = 1e30f;
+  float first = 2e30f;
   for (int h = 0; h < 8; ++h) {
     const float t = first_price(a, p, M, h);
     if (t < first) { first = t; p.bm = 32 * (h + 1); }
   }
+  // The second set's least price, of those below the first one's (only these can take over).  No price is below the weights'
+  // stream with its sums: with that, heights priced once for all splits and nothing priced that cannot be taken, a step's four
+  // plans take 4 (hidden 512) to 6 us (4096) of host time instead of 18.
   GemmPlan q = p;
+  float best_t = first;
+  const float least = 1.8f + weights_us(a);
   for (int shape = 0; shape < 3; ++shape) {
     if (shape == PLAN_X ? !a.tiles_x : shape == PLAN_W && !a.tiles_w) continue;
-    for (int c = 0; c < TILE_CANDIDATES; ++c) {
-      const int sk = tile_split(c), mi = tile_units(c);
-      if (sk > 1 && !a.split_ok) continue;
-      const float t = tile_price(a, M, shape, mi, sk);
-      if (t < best_t) { best_t = t; q = GemmPlan{shape, sk, M, 1, mi * (shape == PLAN_W ? 64 : 32)}; }
+    const int unit = shape == PLAN_W ? 64 : 32;
+    // (heights that no row needs cost what the lowest height with one row tile costs)
+    for (int mi = 1; mi * unit <= 256 && (mi - 1) * unit < M; ++mi) {
+      const TileHeight h = tile_height(a, M, shape, mi);
+      for (int i = 0; i < 8 && can_split(a, M, tile_split(i)); ++i) {
+        const int sk = tile_split(i);
+        if (with_sums(a, M, sk, least) >= best_t) {
+          if (sk > 1) break;  // (more splits have more sums)
+          continue;
+        }
+        const float t = tile_price(a, M, h, sk);
+        if (t < best_t) { best_t = t; q = GemmPlan{shape, sk, M, 1, mi * unit}; }
+      }
     }
   }
   return takes_over(a, M, p, first, q.sk, best_t) ? q : p;
@@ -291,7 +321,7 @@ __device__ __forceinline__ GemmPlan plan_on_device(const PlanArgs &a, int M, int
     if (lane == 0) { words[0] = k; words[4] = (uint32_t)c; }
   } else {
     const int shape = wave - 1;
-    const uint32_t k = least_of_wave(tile_price(a, M, shape, tile_units(lane), tile_split(lane)), lane);
+    const uint32_t k = least_of_wave(tile_price(a, M, tile_height(a, M, shape, tile_units(lane)), tile_split(lane)), lane);
     if (lane == 0) words[wave] = k;
   }
   __syncthreads();
