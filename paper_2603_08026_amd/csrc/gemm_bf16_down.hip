@@ -46,8 +46,8 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
     const bool known = plan_known(rows), sums = known || down_has_sums(pa, rows.cap, false);
     if (!sums) pa.split_ok = pa.stream_cols = 0;
     if (known) pa.sum_us = 4.0f;
-    GemmPlan pl;
-    run_planned<DownKind>(ga, e, pa, &pl, plan_dev, s);
+    const GemmPlan pl = plan_here(ga, pa);
+    run_planned<DownKind>(ga, e, pa, pl, plan_dev, s);
     if (!sums || (known && pl.sk == 1 && pl.row_hi == rows.cap)) return;
     sp = splits_of(ga, pl, true, plan_dev);
   }

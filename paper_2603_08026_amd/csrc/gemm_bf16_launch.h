@@ -88,15 +88,18 @@ int ring_grid() { return std::max(N_XCD, cu_count() / N_XCD * N_XCD); }
 int cus_of_xcd() { return ring_grid() / N_XCD; }
 bool plan_known(const Rows &rows) { return mm::plan_known(rows.count != nullptr, rows.cap); }
 
-// GEMM of `rows` in 256-row tiles by a plan: made here (returned in *pl), or on the device, which leaves
-// the splits in plan_dev
+// The plan of a GEMM whose row count the host knows; anything else is planned on the device
+GemmPlan plan_here(const GemmArgs &ga, const PlanArgs &pa) {
+  return plan_known(ga.rows) ? plan_on_host(pa, ga.rows.cap) : GemmPlan{0, 1, 0, 1, 256};
+}
+
+// GEMM of `rows` in row tiles by a plan: `pl` of plan_here, or the device's, which leaves the splits in plan_dev
 template <typename Kind>
-void run_planned(const GemmArgs &ga, typename Kind::Epi epi, const PlanArgs &pa, GemmPlan *pl, int32_t *plan_dev,
+void run_planned(const GemmArgs &ga, typename Kind::Epi epi, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev,
                  hipStream_t s) {
   const int known = plan_known(ga.rows);
-  *pl = known ? plan_on_host(pa, ga.rows.cap) : GemmPlan{0, 1, 0, 1, 256};
   set_lds_once_planned<Kind>();
-  k_gemm_planned<Kind><<<ring_grid(), 256, RING_SLOTS * RING_SLOT, s>>>(ga, epi, pa, *pl, known, known ? nullptr : plan_dev);
+  k_gemm_planned<Kind><<<ring_grid(), 256, RING_SLOTS * RING_SLOT, s>>>(ga, epi, pa, pl, known, known ? nullptr : plan_dev);
 }
 
 Splits splits_of(const GemmArgs &ga, const GemmPlan &pl, bool fused, const int32_t *plan_dev) {

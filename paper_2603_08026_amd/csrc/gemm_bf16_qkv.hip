@@ -8,9 +8,9 @@ Splits gemm_bf16_qkv(const GemmArgs &ga, float *part, const DirectCols &direct, 
   e.out = part;
   e.ldo = ga.N;
   e.direct = direct;
-  GemmPlan pl = plan_on_host(pa, ga.rows.cap);
+  const GemmPlan pl = plan_here(ga, pa);
   if (pl.sk > 1) e.direct.lo = INT_MAX;  // sums of a split are finished by the row kernel
-  run_planned<RawKind<EpiStoreDirect>>(ga, e, pa, &pl, nullptr, s);
+  run_planned<RawKind<EpiStoreDirect>>(ga, e, pa, pl, nullptr, s);
   return splits_of(ga, pl, true, nullptr);
 }
 

@@ -22,7 +22,6 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
     else run_tiles<SkinnyS, true>(ga, e, out.n, s);
     return out;
   }
-  GemmPlan pl;
   if (ring) {
     // Dense steps from DIRECT_ROWS rows on: 20480 rows of 12288 columns, GEMM and row kernel together 1835 -> 1735 us.  Lists
     // stay with the raw result: the kernel is another one than the out-projection's, whose instructions the caches
@@ -30,7 +29,8 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
     // rows 2119 -> 2149 us a pass, 410 rows of a list 302 -> 306 us a step; 2064 rows 812 -> 808, 5160 rows 1872 -> 1859,
     // but how many of a list exist is known to the device alone); dense 1024 rows gain nothing (430 us).
     if (direct.out && !rows.idx && !rows.count && rows.cap >= DIRECT_ROWS) return gemm_bf16_qkv(ga, part, direct, pa, s);
-    run_planned<RawKind<EpiStoreF32>>(ga, e, pa, &pl, plan_dev, s);
+    const GemmPlan pl = plan_here(ga, pa);
+    run_planned<RawKind<EpiStoreF32>>(ga, e, pa, pl, plan_dev, s);
     return splits_of(ga, pl, false, plan_dev);
   }
   pa.stream_cols = 0;

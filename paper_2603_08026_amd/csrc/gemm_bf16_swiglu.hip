@@ -43,8 +43,7 @@ void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const vo
     run_tiles<LargeD8, false>(ga, e, 1, s);
   } else {
     const PlanArgs pa = swiglu_plan_args(N, K, cus_of_xcd());
-    GemmPlan pl;
-    run_planned<SwigluKind>(ga, e, pa, &pl, nullptr, s);
+    run_planned<SwigluKind>(ga, e, pa, plan_here(ga, pa), nullptr, s);
   }
 }
 
