@@ -246,10 +246,10 @@ int enqueue_ffn(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, con
   launch_oproj_finalize(dt(ctx), ctx->part_o, splits, x, w->g_ffn, rows,
                         c.hidden, c.rms_eps, ctx->hs, ctx->fs, s);
   prof_mark(ctx, ST_NORM_FFN, s);
-  launch_gemm_swiglu(dt(ctx), GemmA{ctx->fs, nullptr, c.hidden}, rows, c.hidden, c.ffn_dim, w->w_gate,
+  launch_gemm_swiglu(dt(ctx), ctx->fs, rows, c.hidden, c.ffn_dim, w->w_gate,
                      w->w_up, ctx->act, s);
   prof_mark(ctx, ST_GEMM_SWIGLU, s);
-  launch_gemm_down(dt(ctx), GemmA{ctx->act, nullptr, c.ffn_dim}, rows, c.ffn_dim, c.hidden, w->w_down,
+  launch_gemm_down(dt(ctx), ctx->act, rows, c.ffn_dim, c.hidden, w->w_down,
                    ctx->hs, out_cache, ctx->part_o, ctx->part_elems, ctx->plan, s);
   prof_mark(ctx, ST_GEMM_DOWN, s);
   return check_launch(ctx, "salient ffn");

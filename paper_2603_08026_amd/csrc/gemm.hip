@@ -20,14 +20,16 @@ Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part
   return gemm_bf16_raw(A, rows, K, seg, part, part_elems, plan, direct, s);
 }
 
-void launch_gemm_swiglu(DType t, GemmA A, Rows rows, int K, int N, const void *w_gate,
+void launch_gemm_swiglu(DType t, const void *a, Rows rows, int K, int N, const void *w_gate,
                         const void *w_up, void *act, hipStream_t s) {
+  const GemmA A{a, nullptr, K};
   if (t == F32) gemm_f32_swiglu(A, rows, K, N, w_gate, w_up, act, s);
   else gemm_bf16_swiglu(A, rows, K, N, w_gate, w_up, act, s);
 }
 
-void launch_gemm_down(DType t, GemmA A, Rows rows, int K, int N, const void *w_down, const float *h,
+void launch_gemm_down(DType t, const void *a, Rows rows, int K, int N, const void *w_down, const float *h,
                       void *out_cache, float *scratch, size_t scratch_elems, int32_t *plan, hipStream_t s) {
+  const GemmA A{a, nullptr, K};
   if (t == F32) gemm_f32_down(A, rows, K, N, w_down, h, out_cache, s);
   else gemm_bf16_down(A, rows, K, N, w_down, h, out_cache, scratch, scratch_elems, plan, s);
 }

@@ -57,7 +57,7 @@ struct EpiStoreDirect : EpiStoreF32 {
 
 template <typename T> struct EpiSwiGLU {
   static constexpr bool DUAL = true;
-  static constexpr bool GATHER = false;  // the activation rows may be gathered
+  static constexpr bool GATHER = false;  // GemmArgs::gather is not read: these rows are never gathered
   static constexpr int INTERLEAVE = 0;
   static constexpr bool PRELOAD = false;
   T *act;  // [cap, N]
@@ -80,7 +80,7 @@ template <typename T> struct EpiSwiGLU {
 
 template <typename T> struct EpiDown {
   static constexpr bool DUAL = false;
-  static constexpr bool GATHER = false;  // the activation rows may be gathered
+  static constexpr bool GATHER = false;  // GemmArgs::gather is not read: these rows are never gathered
   static constexpr int INTERLEAVE = 0;
   // The residual is read before the result is written.  h and out may alias as far as the compiler
   // knows, so element by element every load would wait for the store before it; the kernel instead
@@ -120,7 +120,7 @@ template <typename T> struct EpiDown {
 
 template <typename T, int HALF> struct EpiSwiGLUHalves {
   static constexpr bool DUAL = false;
-  static constexpr bool GATHER = false;  // the activation rows may be gathered
+  static constexpr bool GATHER = false;  // GemmArgs::gather is not read: these rows are never gathered
   static constexpr int INTERLEAVE = HALF;  // 48 (96-column tiles) or 64 (128-column tiles)
   static constexpr bool PRELOAD = false;
   T *act;  // [cap, F]

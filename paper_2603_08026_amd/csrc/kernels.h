@@ -199,12 +199,12 @@ struct DirectCols {
 // the four words `plan`, when their number is known there alone).
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
                        int32_t *plan, hipStream_t s, DirectCols direct = DirectCols{});
-// up: act[j,:] = silu(A w_gate^T) * (A w_up^T), T-typed out [cap, N]
-void launch_gemm_swiglu(DType t, GemmA A, Rows rows, int K, int N, const void *w_gate,
+// up: act[j,:] = silu(A w_gate^T) * (A w_up^T), T-typed out [cap, N]; here and below A[j,:] = a[j,:], rows of K elements
+void launch_gemm_swiglu(DType t, const void *a, Rows rows, int K, int N, const void *w_gate,
                         const void *w_up, void *act, hipStream_t s);
 // down: out_cache[row_j,:] = h[j,:] + A[j,:] * w_down^T, T-typed scatter into [T, N]; `scratch`
 // holds K-split partials when K is split; plan: as for launch_gemm_raw.
-void launch_gemm_down(DType t, GemmA A, Rows rows, int K, int N, const void *w_down, const float *h,
+void launch_gemm_down(DType t, const void *a, Rows rows, int K, int N, const void *w_down, const float *h,
                       void *out_cache, float *scratch, size_t scratch_elems, int32_t *plan, hipStream_t s);
 
 // row-major [n_out, n_in] (2-byte elements; n_out % 32 == 0, n_in % 64 == 0) -> weight panels of the bf16 GEMMs
