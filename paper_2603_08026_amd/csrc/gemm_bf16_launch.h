@@ -41,8 +41,6 @@ typedef Shape<128, 64, 4, 1, false, 4> SkinnyN64;  // the same with four waves, 
 typedef Shape<128, 96, 4, 1, false, 4> SkinnyW96;
 typedef Shape<128, 128, 4, 1, false, 4> SkinnyH128;
 
-constexpr int DIRECT_ROWS = 4096;  // rows of a dense step from which its values leave the q|k|v GEMM directly
-
 int cu_count() {
   static int n = 0;
   if (n == 0) {
