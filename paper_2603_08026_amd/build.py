@@ -10,6 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdyllm.so")
+TESTS = os.path.join(os.path.dirname(HERE), "tests")
+PROBE = os.path.join(TESTS, "plan_probe.so")  # kernels that only the tests launch
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -47,6 +49,13 @@ def build(jobs: int = 8, verbose: bool = True) -> str:
     if verbose:
         print("built", LIB, "from", len(srcs), "sources")
     return LIB
+
+
+def build_probe() -> str:
+    r = subprocess.run([HIPCC, *FLAGS, "-shared", os.path.join(TESTS, "plan_probe.hip"), "-o", PROBE], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("hipcc failed for plan_probe.hip:\n%s\n%s" % (r.stdout, r.stderr))
+    return PROBE
 
 
 if __name__ == "__main__":

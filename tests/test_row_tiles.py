@@ -1,6 +1,7 @@
 """Row tiles of every height and the 192-column tiles of the planned GEMMs: the plans (gemm_plan.h, compiled for the
 host), and the layer against the oracle at row counts where each of them runs, with a last tile that is lower than the
-others and one that ends inside a block of 16 rows."""
+others and one that ends inside a block of 16 rows.  Lists are planned on the device (test_gpu_device_plans.py: as the host
+does); a dense step of as many rows runs the host's plan itself."""
 import ctypes as C
 import subprocess
 
@@ -11,6 +12,7 @@ from synth import workload as W
 
 SMALL = W.LayerShape(hidden=1024, n_heads=8, n_kv_heads=8, head_dim=128, ffn=1536, dtype="bf16")
 WIDE = W.LayerShape(hidden=4096, n_heads=32, n_kv_heads=32, head_dim=128, ffn=12288, dtype="bf16")
+FFN = W.LayerShape(hidden=512, n_heads=4, n_kv_heads=4, head_dim=128, ffn=6144, dtype="bf16")
 # (layer, rows, {GEMM: (columns, K splits, rows of a tile)})
 CASES = [
     (SMALL, 129, {"qkv": (128, 2, 32), "gate_up": (128, 1, 32), "down": (128, 3, 32), "oproj": (128, 2, 32)}),
@@ -27,6 +29,19 @@ CASES = [
     (WIDE, 330, {"gate_up": (192, 1, 192), "down": (128, 4, 192)}),
     (WIDE, 511, {"gate_up": (192, 1, 256)}),
     (WIDE, 757, {"gate_up": (192, 1, 192)}),
+    (FFN, 387, {"gate_up": (256, 1, 96)}),
+    (FFN, 417, {"gate_up": (256, 1, 96)}),
+    (FFN, 483, {"gate_up": (192, 1, 128)}),
+    (FFN, 1026, {"gate_up": (256, 1, 224)}),
+    (FFN, 1122, {"gate_up": (256, 1, 256)}),
+    (FFN, 2562, {"down": (128, 5, 224)}),
+    (SMALL, 2244, {"gate_up": (128, 1, 256)}),
+    (SMALL, 2724, {"qkv": (256, 1, 160), "gate_up": (192, 1, 192)}),
+    (SMALL, 4099, {"qkv": (256, 1, 224), "down": (128, 1, 160)}),
+    (SMALL, 4899, {"qkv": (256, 1, 256)}),
+    (WIDE, 258, {"down": (256, 8, 160)}),
+    (WIDE, 579, {"down": (256, 5, 224)}),
+    (WIDE, 675, {"qkv": (192, 1, 192), "down": (256, 5, 256)}),
 ]
 
 SOURCE = r"""
@@ -37,7 +52,7 @@ extern "C" void plan(int kind, int N, int K, long part_elems, int count, int *ou
                                                                                      : down_plan_args(N, K, part_elems, true, 32);
   const GemmPlan p = plan_on_host(a, count);
   out[0] = p.xl == PLAN_X ? 256 : p.xl == PLAN_W ? 192 : 128;
-  out[1] = p.sk; out[2] = p.bm;
+  out[1] = p.sk; out[2] = p.bm; out[3] = p.row_hi;
 }
 """
 
@@ -54,7 +69,7 @@ def test_cases_run_the_tiles_they_name(tmp_path):
                         "-fPIC", src, "-o", so], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     lib = C.CDLL(so)
-    seen = set()
+    seen, blocks = set(), set()
     for s, count, plans in CASES:
         gemms = {"qkv": (0, s.dq + 2 * s.dkv, s.hidden), "oproj": (0, s.hidden, s.dq), "gate_up": (1, s.ffn, s.hidden),
                  "down": (2, s.hidden, s.ffn)}
@@ -62,11 +77,23 @@ def test_cases_run_the_tiles_they_name(tmp_path):
         part = max(16 * min(t, 2048) * s.dq, t * max(s.dq + 2 * s.dkv, s.hidden))  # the context's fp32 scratch
         for name, want in plans.items():
             kind, n, k = gemms[name]
-            out = (C.c_int * 3)()
+            out = (C.c_int * 4)()
             lib.plan(kind, n, k, C.c_long(part), count, out)
-            assert tuple(out) == want, (count, name, tuple(out))
+            assert tuple(out[:3]) == want, (count, name, tuple(out))
             seen.add((out[0], out[2]))
+        for name, (kind, n, k) in gemms.items():  # 16-row blocks of a wave in the whole tiles and in the last one
+            out = (C.c_int * 4)()
+            lib.plan(kind, n, k, C.c_long(part), count, out)
+            if out[3] == count:
+                unit = 64 if out[0] == 192 else 32
+                form = {0: "raw", 1: "swiglu", 2: "down" if out[1] == 1 else "raw sums"}[kind]
+                blocks |= {(form, out[0], -(-r // unit)) for r in (min(out[2], count), count % out[2]) if r}
     assert {(128, 32 * i) for i in range(1, 9)} <= seen and {c for c, _ in seen} == {128, 192, 256}
+    # every form of result, column width and number of blocks that plans of these layers come to (192 columns: heights of 64 rows)
+    for form, cols, heights in (("raw", 128, range(1, 9)), ("raw", 192, range(2, 5)), ("raw", 256, range(1, 9)),
+                                ("swiglu", 128, range(1, 9)), ("swiglu", 192, range(1, 5)), ("swiglu", 256, range(1, 9)),
+                                ("raw sums", 128, range(1, 9)), ("raw sums", 256, range(4, 9)), ("down", 128, range(1, 6))):
+        assert {(form, cols, h) for h in heights} <= blocks, (form, cols, sorted(blocks))
 
 
 @pytest.mark.gpu
@@ -82,4 +109,31 @@ def test_layer_in_tiles_of_this_height(case):
     w = rand_weights(shape, 57, bias=True)
     lay.set_weights(w)
     _check(lay, w, shape, B, 1400, count, count)
+    lay.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_dense_step_of_as_many_rows(case):
+    """The host's plans: keys, values and output rows of a dense step against those of the list of all its tokens."""
+    import torch
+    from paper_2603_08026_amd import binding as Bd
+    from paper_2603_08026_amd.layer import Layer
+    from tests.helpers import TOL, rand_weights
+    shape, count, _ = CASES[case]
+    print("dense rows", case, count, flush=True)
+    lay = Layer.from_shape(shape, 1, count)
+    lay.set_weights(rand_weights(shape, 58, bias=True))
+    x = torch.randn(1, count, shape.hidden, generator=torch.Generator().manual_seed(59)).to(torch.bfloat16).cuda()
+    lay.full_step(x)
+    dense = [t.float().clone() for t in (lay.k, lay.v, lay.out)]
+    every = Bd.IndexList(torch.arange(count, dtype=torch.int32, device="cuda"), torch.tensor([0, count], dtype=torch.int32, device="cuda"))
+    for t in (lay.k, lay.v, lay.out):
+        t.fill_(float("nan"))
+    q = torch.zeros(count, shape.dq, dtype=torch.bfloat16, device="cuda")
+    lay.ctx.qkv_refresh(lay.w, x, every, 1, count, lay.cache, q)
+    lay.ctx.salient_ffn(lay.w, x, lay.c, every, 1, count, lay.out)
+    for name, a, b in zip(("k", "v", "out"), dense, (lay.k, lay.v, lay.out)):
+        err = float((a - b.float()).abs().max() / a.abs().max())
+        assert err <= TOL["bf16"], (name, err)
     lay.close()
