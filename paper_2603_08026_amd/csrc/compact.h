@@ -19,15 +19,12 @@ __device__ __forceinline__ int seq_of(int row, int B, int L) {
   return s < (unsigned)B ? (int)s : B - 1;
 }
 
-// One workgroup of NT threads sweeps the flags [lo, hi) in chunks of NT: wave64 ballot + popcount give
-// each flagged lane its rank inside the wave, the per-wave totals are combined through LDS.  `base`
-// flagged entries precede lo.  The output keeps the input order, so it is ascending.  Per-sequence
-// offsets: the first entry of every sequence writes its own exclusive rank for all sequences that
-// start at or before it.  `coherent` makes the flag reads bypass the per-CU cache (flags written by
-// other workgroups of the same launch).  wave_cnt: LDS scratch of NT/64 ints.  Returns base + the
-// number of flagged entries in [lo, hi).
-// One sweep: entry j = start + thread (j < hi) with its flag f, its token `row` and the sequence sprev of the entry before it
-// (-1: none).  Returns the flagged entries of the sweep.
+// One sweep of a workgroup of NT threads over an entry per thread (`exists`: there is one) with its flag f, its token
+// `row` and the sequence sprev of the entry before it (-1: none): wave64 ballot + popcount give each flagged lane its
+// rank inside the wave, the per-wave totals are combined through LDS.  `base` flagged entries precede the sweep.  The
+// output keeps the input order, so it is ascending.  Per-sequence offsets: the first entry of every sequence writes its
+// own exclusive rank for all sequences that start at or before it.  wave_cnt: LDS scratch of NT/64 ints.  Returns the
+// flagged entries of the sweep.
 template <int NT>
 __device__ __forceinline__ int compact_sweep(bool f, int row, int sprev, bool exists, int base, int B, int L, int32_t *out_idx,
                                              int32_t *out_off, int out_cap, int *wave_cnt) {
@@ -53,6 +50,8 @@ __device__ __forceinline__ int compact_sweep(bool f, int row, int sprev, bool ex
   return tot;
 }
 
+// The flags [lo, hi) in sweeps of NT.  `coherent` makes the flag reads bypass the per-CU cache (flags written by
+// other workgroups of the same launch).  Returns base + the number of flagged entries in [lo, hi).
 template <int NT>
 __device__ __forceinline__ int compact_range(const uint8_t *flag, const Rows &rows, int lo, int hi, int base,
                                              int B, int L, int32_t *out_idx, int32_t *out_off, int out_cap,

@@ -15,9 +15,9 @@
 // every lane names its own 16-byte global source, the hardware writes lane i's data to
 // LDS[M0 + 16*i].  One such instruction therefore fills 8 tile rows x 128 bytes.  No register is
 // used for staging, so NS-1 slices can be in flight per workgroup while the MFMAs of the current
-// slice run; the only synchronisation is one s_waitcnt vmcnt + one barrier per slice.  The 256-row
-// tiles of the large regime use the same copies through buffer descriptors and keep five half
-// slices in flight in a ring of LDS slots (gemm_bf16_ring.h).
+// slice run; the only synchronisation is one s_waitcnt vmcnt + one barrier per slice.  The row
+// tiles of the ring loop (up to 256 rows) use the same copies through buffer descriptors and keep three to five
+// whole slices or five halves of them in LDS (gemm_bf16_ring.h).
 //
 // LDS layout.  Rows are 128 bytes, unpadded (the copy engine writes lanes back to back), with an
 // XOR swizzle instead: the 16-byte chunk c of tile row r lives at chunk position c ^ ((r/2) % 8).
@@ -30,7 +30,7 @@
 // MFMA.  v_mfma_f32_32x32x16_bf16: lane l supplies 8 consecutive k of row (l%32) for A and of
 // column (l%32) for B at k offset 8*(l/32); the accumulator block holds
 //   row = 8*(r/4) + 4*(l/32) + (r%4),  col = l%32   in register r of lane l.
-// The 256-row tiles of the ring loop use v_mfma_f32_16x16x32_bf16 with a permuted order of the weight rows,
+// The row tiles of the ring loop use v_mfma_f32_16x16x32_bf16 with a permuted order of the weight rows,
 // so that neighbouring lanes hold neighbouring runs of columns of one row (gemm_bf16_ring.h).
 //
 // Tile walk.  The row count lives on the device; the grid is one workgroup per CU (k_gemm_planned) or sized
@@ -39,7 +39,7 @@
 // covers a window of list rows [row_lo, row_hi), so that a short last row tile can go to another tile
 // shape.
 //
-// Epilogues.  A wave's loads and stores complete in order, and a wave of the 256-row shapes is alone
+// Epilogues.  A wave's loads and stores complete in order, and a wave of the ring loop is alone
 // on its SIMD: a load issued behind stores (a residual, a register reloaded from scratch memory)
 // returns only after all of them.  The epilogues therefore issue what they read ahead of the stores
 // it could wait for, and the raw fp32 store of a K split is a compile-time form of the kernel (SPLIT)
@@ -138,12 +138,6 @@ __device__ __forceinline__ Walk walk_of(unsigned char *smem) {
 // Rows of a list that exist
 __device__ __forceinline__ int rows_that_exist(const Rows &rows) { return rows.count ? min(*rows.count, rows.cap) : rows.cap; }
 
-// The tiles of rows [row_lo, min(M_all, row_hi)) of a list of M_all rows (row_lo is a multiple of BM) with `splitk` K splits,
-// those that `walk` names.  Ring shapes: tiles of `ring_rows` rows (a multiple of RING_ROWS, at most BM), row_lo = 0.  Splits are cut in whole K slices and may differ by one.
-// SPLIT: the tile goes to the raw fp32 result part[z][j][n] instead of through the
-// fused epilogue.  A compile-time switch: with both forms behind a run-time branch the compiler
-// moves the accumulators out of the accumulation registers ahead of the branch, where they do not
-// fit, and the epilogue's stores each wait for a reload from scratch memory.
 // f(MI) for the number of 16-row blocks per wave of a tile, of at most MAX: every count has a path of its own
 template <int MAX, typename F> __device__ __forceinline__ bool with_blocks(int mi, F &&f) {
   if constexpr (MAX > 4) {
@@ -158,6 +152,13 @@ template <int MAX, typename F> __device__ __forceinline__ bool with_blocks(int m
   return f(std::integral_constant<int, 1>{});
 }
 
+// The tiles of rows [row_lo, min(M_all, row_hi)) of a list of M_all rows (row_lo is a multiple of BM) with `splitk` K splits,
+// those that `walk` names.  Ring shapes: tiles of `ring_rows` rows (a multiple of RING_ROWS, at most BM), row_lo = 0.
+// Splits are cut in whole K slices and may differ by one.
+// SPLIT: the tile goes to the raw fp32 result part[z][j][n] instead of through the
+// fused epilogue.  A compile-time switch: with both forms behind a run-time branch the compiler
+// moves the accumulators out of the accumulation registers ahead of the branch, where they do not
+// fit, and the epilogue's stores each wait for a reload from scratch memory.
 template <typename SH, typename Epi, bool SPLIT>
 __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, int M_all, int row_lo, int row_hi, int splitk,
                                            const Walk &walk, int ring_rows = SH::BM) {
@@ -908,10 +909,10 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(GemmArgs ga, Epi epi, int 
   gemm_tiles<SH, Epi, SPLIT>(ga, epi, rows_that_exist(ga.rows), 0, 0x7fffffff, splitk, walk_of(smem_raw));
 }
 
-// The 256-row tiles (and the weight-streaming tiles of a short last row tile, or of a list with few
+// Row tiles of the ring loop (and the weight-streaming tiles of a short last row tile, or of a list with few
 // rows), by the plan that fits the rows that exist (gemm_plan.h).  One workgroup per CU.
-//   Kind::Epi      fused epilogue of the 256-row tiles; Kind::FUSED / RAW: which of its forms exist
-//   Kind::X, L     tile shapes; Kind::stream(...) runs the weight-streaming tiles
+//   Kind::Epi      fused epilogue of the row tiles; Kind::FUSED / RAW: which of its forms exist
+//   Kind::X, L, W  tile shapes (W: void where there is none); Kind::stream(...) runs the weight-streaming tiles
 // planned: the plan was made on the host (the count is known there).  plan_out (optional): the splits,
 // for the row kernels (Splits::dev).
 template <typename Kind>

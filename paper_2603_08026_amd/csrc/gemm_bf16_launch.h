@@ -35,7 +35,7 @@ static_assert(LargeS::BN == 128 && XLargeS::BN == 256 && LargeD::BN == 64 && XLa
 typedef Shape<256, 128, 4, 2, false, 2> LargeS8;  // eight waves, two LDS stages
 typedef Shape<256, 64, 4, 2, true, 2> LargeD8;
 typedef Shape<128, 64, 4, 2, false, 4> SkinnyS;
-typedef Shape<128, 64, 4, 1, false, 4> SkinnyN64;  // the same with four waves, beside the 256-row tiles in one kernel
+typedef Shape<128, 64, 4, 1, false, 4> SkinnyN64;  // the same with four waves, beside the row tiles in one kernel
 // skinny regime, wide column tiles (fewer re-reads of the activation tile): q|k|v raw result, and
 // gate|up with half-interleaved tiles (48 + 48 or 64 + 64 columns) and SwiGLU in registers
 typedef Shape<128, 96, 4, 1, false, 4> SkinnyW96;

@@ -60,6 +60,14 @@ __host__ __device__ inline int stream_split(const PlanArgs &a, int M) {
   return a.split_ok ? s : 1;
 }
 
+// Whether sk K splits may be taken at all (fewer may then as well)
+__host__ __device__ inline bool can_split(const PlanArgs &a, int M, int sk) {
+  return sk == 1 || (a.split_ok && a.K / PLAN_BK >= PLAN_MIN_SLICES * sk && (long)sk * M * a.N <= a.part_elems);
+}
+__host__ __device__ inline bool can_stream(const PlanArgs &a, int M) {
+  return a.stream_cols && M % 256 > 0 && M % 256 <= STREAM_ROWS && M >= 256;
+}
+
 // Price of candidate c in microseconds, or a huge value if it cannot be taken.  The constants are
 // fitted to measured times of seven GEMMs of two layer shapes (hidden 4096 and 3584).  Every candidate was then timed
 // for 23 GEMMs of six layer shapes (hidden 256 to 4096) at 14 row counts from 140 to 5000: the candidate with the least
@@ -72,13 +80,6 @@ __host__ __device__ inline int stream_split(const PlanArgs &a, int M) {
 //     still walk all of K with their copies) and first fill the slots the full tiles leave;
 //   - weights arrive at 4 TB/s whatever the tiles do; in the streaming tiles as with_stream_price says;
 //   - every K split moves its fp32 sums once more, written and read.
-// whether sk K splits may be taken at all (fewer may then as well)
-__host__ __device__ inline bool can_split(const PlanArgs &a, int M, int sk) {
-  return sk == 1 || (a.split_ok && a.K / PLAN_BK >= PLAN_MIN_SLICES * sk && (long)sk * M * a.N <= a.part_elems);
-}
-__host__ __device__ inline bool can_stream(const PlanArgs &a, int M) {
-  return a.stream_cols && M % 256 > 0 && M % 256 <= STREAM_ROWS && M >= 256;
-}
 __host__ __device__ inline float plan_price(const PlanArgs &a, int M, int c) {
   const int sk = c % PLAN_MAX_SPLIT + 1, xl = (c / PLAN_MAX_SPLIT) & 1, streamed = c / (2 * PLAN_MAX_SPLIT);
   const int tail = M % 256;
@@ -105,17 +106,8 @@ __host__ __device__ inline GemmPlan plan_of(const PlanArgs &a, int M, int c) {
   return GemmPlan{(c / PLAN_MAX_SPLIT) & 1, c % PLAN_MAX_SPLIT + 1, streamed ? M - M % 256 : M, streamed ? stream_split(a, M) : 1, 256};
 }
 
-// Price in microseconds of M rows in tiles of `mi` units of 32 (192 columns: 64) rows with sk K splits, or a huge value.
-// Fitted to 8287 times: 16 GEMMs of four layer shapes (hidden 512 to 4096) at 18 row counts from 140 to 5000, every
-// shape, height and up to ten splits, weights of up to 16 copies in turn.  The candidate with the least price is on
-// average 1.0 % slower than the fastest of all (worst 18 %); the least time itself is 2 to 34 % below that of the best
-// 256-row tiles.
-//   - a K slice costs a fixed part (waits, the weight copies) and one per unit of rows; from five (three) units on
-//     256 (192) columns are bound by their products
-//   - tiles at the same time slow each other down: a chip that is half empty is 11 % faster per tile
-//   - the weights' stream and the tiles' own time overlap, not entirely; a raw result is written at 10 TB/s beside it
-// Tiles of one shape and height: whole row tiles, rows of the last one, and what a tile costs per K slice and beside its slices
-// (whole one, last one).  The same for every number of K splits.
+// Tiles of one shape, `mi` units of 32 (192 columns: 64) rows high: whole row tiles, rows of the last one, and what a tile
+// (a whole one, the last one) costs per K slice and beside its slices.  The same for every number of K splits.
 struct TileHeight { int cols, full, tail; float slice, fixed, tail_slice, tail_fixed; };
 __host__ __device__ inline TileHeight tile_height(const PlanArgs &a, int M, int shape, int mi) {
   const bool l = shape == PLAN_L, x = shape == PLAN_X;
@@ -128,6 +120,7 @@ __host__ __device__ inline TileHeight tile_height(const PlanArgs &a, int M, int 
   const float m = (float)mi, t = (float)((tail + unit - 1) / unit);
   return TileHeight{bm <= 256 ? cols : 0, full, tail, slice(m), fixed(m), slice(t), fixed(t)};
 }
+
 // The weights' stream, and a price with what its raw results and sums add (M rows, sk splits)
 __host__ __device__ inline float weights_us(const PlanArgs &a) {
   return (float)a.N * (float)a.w_cols * (float)a.K * 2.0f * (1.0f / 4.03e6f);
@@ -140,6 +133,16 @@ __host__ __device__ inline float with_sums(const PlanArgs &a, int M, int sk, flo
   else if (sk > 1) us += 1.58f * mn * (float)sk + a.sum_us;
   return us;
 }
+
+// Price in microseconds of M rows in tiles of a height h with sk K splits, or a huge value.
+// Fitted to 8287 times: 16 GEMMs of four layer shapes (hidden 512 to 4096) at 18 row counts from 140 to 5000, every
+// shape, height and up to ten splits, weights of up to 16 copies in turn.  The candidate with the least price is on
+// average 1.0 % slower than the fastest of all (worst 18 %); the least time itself is 2 to 34 % below that of the best
+// 256-row tiles.
+//   - a K slice costs a fixed part (waits, the weight copies) and one per unit of rows; from five (three) units on
+//     256 (192) columns are bound by their products
+//   - tiles at the same time slow each other down: a chip that is half empty is 11 % faster per tile
+//   - the weights' stream and the tiles' own time overlap, not entirely; a raw result is written at 10 TB/s beside it
 __host__ __device__ inline float tile_price(const PlanArgs &a, int M, const TileHeight &h, int sk) {
   const bool ok = h.cols != 0 && can_split(a, M, sk);
   const float fx = (float)((h.full * h.cols * sk + PLAN_XCD - 1) / PLAN_XCD), px = h.tail ? (float)((h.cols * sk + PLAN_XCD - 1) / PLAN_XCD) : 0.0f;
@@ -270,7 +273,7 @@ inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int c
   return with_stream_price(a);
 }
 // Is the plan made on the host?  When the count is known here; and for a list of up to 256 entries, one row
-// tile whatever its count: the same shapes serve, and the device's own plan costs 0.5 to 1 us of a GEMM.
+// tile whatever its count: the same shapes serve, and the device's own plan costs 2 us of a GEMM and its row kernel.
 inline bool plan_known(bool count_on_device, int cap) { return !count_on_device || cap <= 256; }
 // Does the down projection get a sum kernel behind it, and so a plan that may split K or stream a last row tile?
 // Always where the plan for the full length wants it.  Where the device may find fewer rows, also if the list is long
