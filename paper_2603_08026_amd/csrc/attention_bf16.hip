@@ -424,7 +424,7 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   int kbase = b * a.L, Lk = a.L, k_chunk = a.chunk;
   bool compact = false;  // uniform: the candidates of this sequence alone, then the sweep over all keys
   if (a.key_offsets) {
-    const int first = min(a.key_offsets[b], a.key_cap), n = min(a.key_offsets[b + 1], a.key_cap) - first;
+    const int first = min(a.key_offsets[b], a.key_cap), n = max(min(a.key_offsets[b + 1], a.key_cap) - first, 0);
     if constexpr (NORM) {
       compact = compact_form(n, a.L);
       if (compact) {  // the splits cut the sweep; each takes its share of the compact keys, perhaps none

@@ -176,13 +176,15 @@ __host__ __device__ inline float first_price(const PlanArgs &a, const GemmPlan &
 //     gains 301 us in all and loses at most 2 in one place
 //   - the down projection, whose splits cost a sum kernel: 0.85 gains 278 us and loses 10; 0.90 would lose 132
 //   - q|k|v, out-projection: below 2.5e6 results a split less is a gain nearly wherever the price says so; with more of
-//     them 0.88 up to 1024 rows, 0.78 beyond (0.85 against a streamed last row tile): gains 603 us, loses 42, at most 5 in one
-//     place.  0.97 up to 1024 rows and 0.85 beyond gained 501 and lost 141 (step of 256 rows at hidden 4096, q|k|v in one
+//     them 0.88 up to 1024 rows; beyond, 0.78 where a row has no more results than K (the out-projection, whose row kernel
+//     adds the splits of a row at little cost), 0.85 for q|k|v and against a streamed last row tile: gains 605 us, loses
+//     45, at most 5 in one place.  0.97 up to 1024 rows and 0.85 beyond gained 501 and lost 141 (step of 256 rows at hidden 4096, q|k|v in one
 //     split against two, 186 against 181 us; 960 rows, the out-projection likewise, 5 us).
 __host__ __device__ inline bool takes_over(const PlanArgs &a, int M, const GemmPlan &p, float first, int sk, float second) {
   const bool same = p.row_hi == M && sk == p.sk, down = a.split_ok && !a.split_free;
   float share = M <= 1024 && !down ? 0.97f : same ? 0.95f : 0.85f;
-  if (a.split_free && !same) share = (float)M * (float)a.N < 2.5e6f ? 0.98f : M <= 1024 ? 0.88f : p.row_hi < M ? 0.85f : 0.78f;
+  if (a.split_free && !same)
+    share = (float)M * (float)a.N < 2.5e6f ? 0.98f : M <= 1024 ? 0.88f : p.row_hi < M || a.N > a.K ? 0.85f : 0.78f;
   return second < share * first;
 }
 

@@ -118,7 +118,7 @@ def test_plans_of_the_many_row_cases(lib, count, cap, cols, streams):
     ((4096, 32, 32, 12288), "oproj", 1024, 128, 2), ((4096, 32, 32, 12288), "oproj", 1500, 256, 2),
     ((3584, 28, 4, 18944), "oproj", 1000, 128, 2), ((3584, 28, 4, 18944), "qkv", 768, 128, 2),
     ((4096, 32, 32, 12288), "qkv", 400, 128, 1), ((4096, 32, 32, 12288), "qkv", 512, 128, 1),
-    ((4096, 32, 32, 12288), "oproj", 1100, 128, 1), ((2048, 16, 16, 5632), "oproj", 640, 128, 2),
+    ((3584, 28, 4, 18944), "qkv", 1200, 128, 1), ((4096, 32, 32, 12288), "oproj", 1100, 128, 1), ((2048, 16, 16, 5632), "oproj", 640, 128, 2),
     ((1024, 8, 8, 2816), "qkv", 512, 128, 1), ((1024, 8, 8, 2816), "oproj", 1700, 128, 1)])
 def test_plans_of_timed_pairs(lib, dims, gemm, count, cols, splits):
     d, h, kv, f = dims
