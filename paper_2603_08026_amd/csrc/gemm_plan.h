@@ -177,14 +177,18 @@ __host__ __device__ inline float first_price(const PlanArgs &a, const GemmPlan &
 //   - the down projection, whose splits cost a sum kernel: 0.85 gains 278 us and loses 10; 0.90 would lose 132
 //   - q|k|v, out-projection: below 2.5e6 results a split less is a gain nearly wherever the price says so; with more of
 //     them 0.88 up to 1024 rows; beyond, 0.78 where a row has no more results than K (the out-projection, whose row kernel
-//     adds the splits of a row at little cost), 0.85 for q|k|v and against a streamed last row tile: gains 605 us, loses
-//     45, at most 5 in one place.  0.97 up to 1024 rows and 0.85 beyond gained 501 and lost 141 (step of 256 rows at hidden 4096, q|k|v in one
-//     split against two, 186 against 181 us; 960 rows, the out-projection likewise, 5 us).
+//     adds the splits of a row at little cost) and there are at most 7e6, 0.85 for q|k|v, against a streamed last row tile
+//     and for more results: gains 605 us, loses 45, at most 5 in one place.  0.97 up to 1024 rows and 0.85 beyond gained 501
+//     and lost 141 (step of 256 rows at hidden 4096, q|k|v in one split against two, 186 against 181 us; 960 rows, the
+//     out-projection likewise, 5 us).  Out-projection and FFN half with 0.85 / 0.78, us: hidden 4096, 1470 rows 436.2 / 433.0, 1610
+//     475.1 / 470.2, 2000 541.7 / 542.1 (the whole step 846.8 / 849.7); hidden 5120, 3670 rows 1443 / 1460, 3940 1480 / 1509;
+//     hidden 6144, 2770 rows 1535 / 1548, 4030 2031 / 2058: the results of two splits are more memory traffic there than
+//     one split's idle CUs are time.
 __host__ __device__ inline bool takes_over(const PlanArgs &a, int M, const GemmPlan &p, float first, int sk, float second) {
   const bool same = p.row_hi == M && sk == p.sk, down = a.split_ok && !a.split_free;
   float share = M <= 1024 && !down ? 0.97f : same ? 0.95f : 0.85f;
-  if (a.split_free && !same)
-    share = (float)M * (float)a.N < 2.5e6f ? 0.98f : M <= 1024 ? 0.88f : p.row_hi < M || a.N > a.K ? 0.85f : 0.78f;
+  const float results = (float)M * (float)a.N;
+  if (a.split_free && !same) share = results < 2.5e6f ? 0.98f : M <= 1024 ? 0.88f : p.row_hi < M || a.N > a.K || results > 7e6f ? 0.85f : 0.78f;
   return second < share * first;
 }
 

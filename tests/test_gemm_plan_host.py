@@ -119,7 +119,9 @@ def test_plans_of_the_many_row_cases(lib, count, cap, cols, streams):
     ((3584, 28, 4, 18944), "oproj", 1000, 128, 2), ((3584, 28, 4, 18944), "qkv", 768, 128, 2),
     ((4096, 32, 32, 12288), "qkv", 400, 128, 1), ((4096, 32, 32, 12288), "qkv", 512, 128, 1),
     ((3584, 28, 4, 18944), "qkv", 1200, 128, 1), ((4096, 32, 32, 12288), "oproj", 1100, 128, 1), ((2048, 16, 16, 5632), "oproj", 640, 128, 2),
-    ((1024, 8, 8, 2816), "qkv", 512, 128, 1), ((1024, 8, 8, 2816), "oproj", 1700, 128, 1)])
+    ((1024, 8, 8, 2816), "qkv", 512, 128, 1), ((1024, 8, 8, 2816), "oproj", 1700, 128, 1),
+    ((4096, 32, 32, 12288), "oproj", 2000, 128, 1), ((5120, 40, 8, 13824), "oproj", 3670, 256, 1),
+    ((6144, 48, 8, 16384), "oproj", 3310, 256, 1), ((6144, 48, 8, 16384), "oproj", 4030, 256, 1)])
 def test_plans_of_timed_pairs(lib, dims, gemm, count, cols, splits):
     d, h, kv, f = dims
     p = Plan(lib, W.LayerShape(hidden=d, n_heads=h, n_kv_heads=kv, head_dim=128, ffn=f, dtype="bf16"), gemm, count, 6144, 6144)
