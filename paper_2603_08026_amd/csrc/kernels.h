@@ -61,7 +61,7 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
 // the caches at row_j.
 // rope_tab: [max_seq, dh/2, 2] fp32 (cos, sin).  dh is 64 or 128.
 // What the approximate step keeps of its candidates beside the caches (a kernel of its own: with these in the kernel of
-// every step, q of 8192 rows took 55 instead of 49 us):
+// every step, q of 8192 rows took 55 instead of 42 us):
 //   dv        v - v_cache of the rows before the merge, at row_j (DV_BY_TOKEN), at j (DV_BY_ENTRY) or at their candidate_row
 //             by `offsets` (DV_BY_SEQUENCE; not for the rows at positions below entry_lo)
 //   k         nullptr, or a copy of the rotated k rows at the same places (DV_BY_SEQUENCE: in the compact form only)
