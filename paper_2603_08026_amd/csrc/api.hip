@@ -192,7 +192,7 @@ void prof_mark(dyllm_ctx *ctx, int stage, hipStream_t s) {
 }
 
 // gather + norm, q/k/v projection, rotation, K/V merge  [Alg. 3: norm / q_proj / k_proj / v_proj lines]
-int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Rows rows, int L,
+int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Rows rows, int B, int L,
                 dyllm_layer_cache *cache, void *q_out, hipStream_t s) {
   const dyllm_layer_cfg &c = ctx->cfg;
   launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, s);
@@ -200,13 +200,11 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
   WSeg seg;
   seg.w[0] = w->wq; seg.w[1] = w->wk; seg.w[2] = w->wv;
   seg.n_end[0] = ctx->dq; seg.n_end[1] = ctx->dq + ctx->dkv; seg.n_end[2] = ctx->dq + 2 * ctx->dkv;
-  const DirectCols values{cache->v, w->bv, ctx->dq + ctx->dkv, ctx->dkv};
+  const QkvOut out{q_out, cache->k, cache->v, w->bq, w->bk, w->bv, ctx->rope, c.n_heads, c.n_kv_heads, c.head_dim, L, 0, (size_t)B * L};
   const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
-                                     ctx->part_o, ctx->part_elems, ctx->plan, s, values);
+                                     ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
   prof_mark(ctx, ST_GEMM_QKV, s);
-  launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rows, L,
-                      c.n_heads, c.n_kv_heads, c.head_dim, w->bq, w->bk, w->bv, q_out, cache->k,
-                      cache->v, 0, nullptr, s);
+  launch_qkv_finalize(dt(ctx), ctx->part_o, splits, rows, out, nullptr, s);
   prof_mark(ctx, ST_ROPE_SCATTER, s);
   return check_launch(ctx, "qkv refresh");
 }
@@ -297,7 +295,7 @@ int enqueue_sparse_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   int rc;
   const Rows rin = rows_of(idx_in, B);
   prof_begin_call(ctx, s);
-  if ((rc = enqueue_qkv(ctx, w, x, rin, L, cache, ctx->qs, s))) return rc;
+  if ((rc = enqueue_qkv(ctx, w, x, rin, B, L, cache, ctx->qs, s))) return rc;
   {
     AttnArgs a = attn_args(ctx, ctx->qs, cache->k, cache->v, rin, idx_in->offsets, B, L, nullptr, 1);
     a.lse_out = (float *)cache->lse;  // optional fifth cache: log-normalisers of the exact rows
@@ -358,10 +356,10 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   // norm and q projection (+ rotation) of EVERY token of the step  [Alg. 3: Q <- q_proj(x)]
   launch_gather_rmsnorm(dt(ctx), x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, s);
   {
+    const QkvOut out{ctx->qs, nullptr, nullptr, w->bq, nullptr, nullptr, ctx->rope, c.n_heads, 0, c.head_dim, L, by_token, (size_t)B * L};
     const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, all, c.hidden,
-                                       wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s);
-    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, all, L, c.n_heads,
-                        0, c.head_dim, w->bq, nullptr, nullptr, ctx->qs, nullptr, nullptr, by_token, nullptr, s);
+                                       wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
+    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, all, out, nullptr, s);
   }
   // k, v of the salient tokens: norm, projection, rotation, value residual, merge into the caches
   launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, s);
@@ -376,8 +374,8 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     const CandidateOut cand{cached_norm ? ctx->dc : ctx->dv_full, cached_norm || by_sequence ? ctx->ksal : nullptr,
                             cached_norm ? DV_BY_ENTRY : by_sequence ? DV_BY_SEQUENCE : DV_BY_TOKEN, idx_in->offsets,
                             ctx->pos, win.lo};
-    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, ctx->rope, rin, L, 0, c.n_kv_heads, c.head_dim, nullptr, w->bk, w->bv,
-                        nullptr, cache->k, cache->v, 0, &cand, s);
+    const QkvOut out{nullptr, cache->k, cache->v, nullptr, w->bk, w->bv, ctx->rope, 0, c.n_kv_heads, c.head_dim, L, 0, (size_t)B * L};
+    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, rin, out, &cand, s);
   }
   if ((rc = check_launch(ctx, "approx: projections"))) return rc;
   // exact rows of the salient tokens  [Alg. 3: C_sal]; q is stored by token here.  With a cache of
@@ -455,7 +453,7 @@ int enqueue_dense_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_laye
   int rc;
   const Rows all{nullptr, nullptr, B * L};
   prof_begin_call(ctx, s);
-  if ((rc = enqueue_qkv(ctx, w, x, all, L, cache, ctx->qs, s))) return rc;
+  if ((rc = enqueue_qkv(ctx, w, x, all, B, L, cache, ctx->qs, s))) return rc;
   // every row is a query: the context cache is written directly
   if (cache->lse) {  // ... through the merge kernel when the log-normalisers are kept as well
     AttnArgs a = attn_args(ctx, ctx->qs, cache->k, cache->v, all, nullptr, B, L, cache->c, 1);
@@ -693,7 +691,7 @@ int dyllm_qkv_refresh(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *
   if (!x || !q_sal_out || !cache || !cache->k || !cache->v) return fail(ctx, DYLLM_ERR_INVALID_ARG, "NULL tensor");
   if ((rc = check_bl(ctx, B, L))) return rc;
   if ((rc = check_list(ctx, rows, "rows"))) return rc;
-  return enqueue_qkv(ctx, w, x, rows_of(rows, B), L, cache, q_sal_out, (hipStream_t)stream);
+  return enqueue_qkv(ctx, w, x, rows_of(rows, B), B, L, cache, q_sal_out, (hipStream_t)stream);
 }
 
 int dyllm_partial_attention(dyllm_ctx *ctx, const void *q_sal, const void *k_cache,

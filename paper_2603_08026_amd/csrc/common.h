@@ -98,6 +98,10 @@ __device__ __forceinline__ void block_sum3(float &a, float &b, float &c, float *
   for (int i = 0; i < NT / WAVE; ++i) { a += red[3 * i]; b += red[3 * i + 1]; c += red[3 * i + 2]; }
 }
 
+// One element of a rotated pair: own * cos plus (second half of the head) or minus (first half) partner * sin.  Written out, so
+// that every kernel rounds it alike.
+__device__ __forceinline__ float rotated(float own, float c, float partner_sin) { return fmaf(own, c, partner_sin); }
+
 // Asynchronous global -> LDS copy: lane i moves the 16 bytes at its own global address g to
 // LDS[lds_base + 16*i]; lds_base is wave-uniform.  Completion is tracked by vmcnt.
 __device__ __forceinline__ void dma16(const void *g, uint32_t lds_base) {

@@ -7,17 +7,17 @@ void gemm_f32_raw(GemmA, Rows, int, WSeg, float *, hipStream_t);
 void gemm_f32_swiglu(GemmA, Rows, int, int, const void *, const void *, void *, hipStream_t);
 void gemm_f32_down(GemmA, Rows, int, int, const void *, const float *, void *, hipStream_t);
 
-Splits gemm_bf16_raw(GemmA, Rows, int, WSeg, float *, size_t, int32_t *, DirectCols, hipStream_t);
+Splits gemm_bf16_raw(GemmA, Rows, int, WSeg, float *, size_t, int32_t *, const QkvOut *, hipStream_t);
 void gemm_bf16_swiglu(GemmA, Rows, int, int, const void *, const void *, void *, hipStream_t);
 void gemm_bf16_down(GemmA, Rows, int, int, const void *, const float *, void *, float *, size_t, int32_t *, hipStream_t);
 
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
-                       int32_t *plan, hipStream_t s, DirectCols direct) {
+                       int32_t *plan, hipStream_t s, const QkvOut *qkv) {
   if (t == F32) {
     gemm_f32_raw(A, rows, K, seg, part, s);
     return Splits{};
   }
-  return gemm_bf16_raw(A, rows, K, seg, part, part_elems, plan, direct, s);
+  return gemm_bf16_raw(A, rows, K, seg, part, part_elems, plan, qkv, s);
 }
 
 void launch_gemm_swiglu(DType t, const void *a, Rows rows, int K, int N, const void *w_gate,

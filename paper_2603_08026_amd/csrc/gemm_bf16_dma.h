@@ -125,11 +125,13 @@ __device__ __forceinline__ int own_lane() {
 }
 
 // How a workgroup walks the tiles: the first one's number and the distance to the next; the wave's number (scalar)
-// and the LDS.  (Read off the thread's number once per kernel: a later shape's use of it would keep a register across
+// and the LDS; whole: K is not split, and the epilogue finishes rows.  (Read off the thread's number once per kernel:
+// a later shape's use of it would keep a register across
 // the loop of an earlier one.)
 struct Walk {
   int first, step, wave;
   unsigned char *smem;
+  bool whole = false;
 };
 __device__ __forceinline__ Walk walk_of(unsigned char *smem) {
   return Walk{(int)blockIdx.x, (int)gridDim.x, (int)__builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), smem};
@@ -429,6 +431,145 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     // row: what lies past it is neither read nor written, without a branch per row (a branch around a load makes
     // the compiler wait for the load where the paths meet: 38000 instead of 14000 cycles for the down epilogue).
     constexpr int G = RingFull::G, NQ = 2 * NB / G;
+    // Rows of q|k|v finished here: bias, rotation, rounding, and each value to where it belongs, where the raw result is
+    // written, read and written again by a row kernel.  A head's column p turns with column p + HEAD / 2:
+    //   SAME   a wave has whole heads of 128 columns: the partner is in the same lane, 64 columns on, and both use one table entry
+    //   else   the weight rows of a run of 64 columns are those of 32 columns and of their partners (ring_sources): the
+    //          partner is eight lanes on in the row of 16
+    // What is read comes ahead of what it could wait for (a wave's memory operations complete in order): the list's entries
+    // first, the table entries of row block i + AHEAD - 1 before block i is written.  Bound by the stores and the table's
+    // loads, 16 cycles each of the CU's one path.  hidden 4096, GEMM and row kernel, us: dense 20480 rows 1466 + 211 -> 1469; lists of 2064
+    // and 5160 rows 163 + 29 -> 170 + 5, 379 + 80 -> 392 + 5 (the row kernel is launched where the list's length may ask for a split).
+    constexpr bool PAIRS = Epi::QKV == 128 && NQ != 2;  // the weight rows' order differs from the columns'
+    constexpr bool SAME = Epi::QKV == 128 && NQ == 2;
+    constexpr int NP = PAIRS && NQ > 1 ? 2 : 1;  // table entries of a row: one for all runs, or one for every second run
+    constexpr int AHEAD = NP == 1 ? 3 : 2;       // row blocks whose table entries are in flight or in use
+    auto qkv_rows = [&](auto &row, int rbase) {  // this lane's rows (tokens) of every row block
+      constexpr int MI = sizeof(row) / sizeof(row[0]);
+      const int lq = own_lane() / 16;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int n = __builtin_amdgcn_readfirstlane(min(max(M - rbase - RR * i, 0), 16));
+        const auto list = make_srd(rows.idx + (rows.idx ? rbase + RR * i : 0), rows.idx ? n * 4u : 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) row[i][e] = rows.idx ? __builtin_amdgcn_raw_buffer_load_b32(list, lq * 16 + e * 4, 0, 0) : rbase + RR * i + 4 * lq + e;
+      }
+    };
+    auto qkv_table = [&](auto &row, auto &tab, int cbase, int i) {  // the table entries of row block i
+      if constexpr (Epi::QKV > 0) {
+        const QkvOut &o = epi.o;
+        const int l16 = own_lane() % 16;
+        const bool any = (PAIRS ? cbase & ~127 : cbase) < (o.H + o.Hkv) * Epi::QKV;
+        const auto table = make_srd(o.tab, any ? 0xfffffff0u : 0u);  // (values alone: nothing is read)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t pos = epi.position((uint32_t)row[i][e]);
+#pragma unroll
+          for (int u = 0; u < NP; ++u) {
+            const int half = PAIRS ? ((cbase >> 6) + u) & 1 : 0;
+            const uint32_t at = pos * (Epi::QKV * 4u) + (uint32_t)(32 * half + (SAME ? 4 * l16 : 4 * (l16 % 8))) * 8u;
+            tab[i % AHEAD][e][u][0] = load_buf(table, at);
+            tab[i % AHEAD][e][u][1] = load_buf(table, at + 16u);
+          }
+        }
+      }
+    };
+    auto qkv_epilogue = [&](auto &acc, int rbase, int cbase) {
+      if constexpr (Epi::QKV > 0) {
+        constexpr int MI = sizeof(acc[0]) / sizeof(acc[0][0]), HEAD = Epi::QKV;
+        const QkvOut &o = epi.o;
+        const int ln = own_lane(), l16 = ln % 16, lq = ln / 16;
+        const bool upper = (l16 & 8) != 0;  // !SAME: this lane has the second half's columns
+        const int dq = o.H * HEAD, dkv = o.Hkv * HEAD;
+        // (fetched together and selected from, as the weights' addresses in ring_sources)
+        void *to_q = o.q, *to_k = o.k, *to_v = o.v;
+        const void *bq = o.bq, *bk = o.bk, *bv = o.bv;
+        asm volatile("" : "+s"(to_q), "+s"(to_k), "+s"(to_v), "+s"(bq), "+s"(bk), "+s"(bv));
+        int row[MI][4];
+        floatx4 tab[AHEAD][4][NP][2];
+        qkv_rows(row, rbase);
+#pragma unroll
+        for (int i = 0; i < AHEAD - 1 && i < MI; ++i) qkv_table(row, tab, cbase, i);
+        // where a run's columns go, wave-uniform but for the lane's own columns
+        char *out[NQ];
+        int row_bytes[NQ];
+        bool turns[NQ], by_token[NQ];
+        floatx4 bias[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          const int run = cbase + 64 * q, head = PAIRS ? run & ~127 : run, half = PAIRS ? (run >> 6) & 1 : 0;
+          const bool in_q = head < dq, in_k = !in_q && head < dq + dkv;
+          const int start = in_q ? 0 : in_k ? dq : dq + dkv;
+          const int col = head - start + 32 * half + (PAIRS ? (upper ? 64 : 0) + 4 * (l16 % 8) : 4 * l16);
+          out[q] = (char *)(in_q ? to_q : in_k ? to_k : to_v) + (size_t)col * 2;
+          row_bytes[q] = (in_q ? dq : dkv) * 2;
+          turns[q] = in_q || in_k;
+          by_token[q] = !in_q || o.q_by_token;
+          const void *b = in_q ? bq : in_k ? bk : bv;
+          uint2 w = {0u, 0u};
+          if (b) w = *reinterpret_cast<const uint2 *>((const bf16_t *)b + col);
+          bias[q] = floatx4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
+                            __uint_as_float(w.y & 0xffff0000u)};
+        }
+        // TURN: the wave's columns are queries or keys (else values alone), wave-uniform.
+        auto finish = [&](auto turn_c) {
+          constexpr bool TURN = decltype(turn_c)::value;
+#pragma unroll
+          for (int i = 0; i < MI; ++i) {
+            if (TURN && i + AHEAD - 1 < MI) qkv_table(row, tab, cbase, i + AHEAD - 1);
+            const int n = __builtin_amdgcn_readfirstlane(min(max(M - rbase - RR * i, 0), 16));
+            // (the accumulators are still where they were: without this the compiler moves them out of the second register
+            // file ahead of the branch that led here, into scratch memory)
+#pragma unroll
+            for (int c = 0; c < 2 * NB; ++c) asm volatile("" : "+a"(acc[0][i][c]));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              floatx4 x[NQ], y[NQ];
+#pragma unroll
+              for (int q = 0; q < NQ; ++q) {
+                x[q] = floatx4{acc[0][i][G * q][e], acc[0][i][G * q + 1][e], acc[0][i][G * q + 2][e], acc[0][i][G * q + 3][e]} + bias[q];
+              }
+#pragma unroll
+              for (int q = 0; q < NQ; ++q) {
+                const floatx4 *t = tab[i % AHEAD][e][q % NP];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                  float turned = x[q][h];
+                  if constexpr (TURN) {
+                    const float co = t[h / 2][2 * (h % 2)], si = t[h / 2][2 * (h % 2) + 1];
+                    if constexpr (SAME) {
+                      const float ps = x[1 - q][h] * si;
+                      turned = rotated(x[q][h], co, q == 0 ? -ps : ps);
+                    } else {
+                      const float partner = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x[q][h]), 0x128, 0xf, 0xf, false));
+                      const float ps = partner * si;
+                      turned = rotated(x[q][h], co, upper ? ps : -ps);
+                    }
+                  }
+                  y[q][h] = !SAME && NQ > 1 && !turns[q] ? x[q][h] : turned;  // (a wave's runs may be on both sides of the last key column)
+                }
+              }
+              if (4 * lq + e < n) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                  const size_t r = (size_t)(uint32_t)(by_token[q] ? row[i][e] : rbase + RR * i + 4 * lq + e);
+                  *reinterpret_cast<uint2 *>(out[q] + r * (uint32_t)row_bytes[q]) = uint2{pack_bf16(y[q][0], y[q][1]), pack_bf16(y[q][2], y[q][3])};
+                }
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);  // (a row block at a time: more of them at once spill)
+          }
+        };
+        bool any = false;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) any |= turns[q];
+        if (any) {
+          finish(std::true_type{});
+        } else {
+          finish(std::false_type{});
+        }
+      }
+    };
     auto ring_epilogue = [&](auto &acc, int rbase, int cbase, int z) {
       constexpr int MI = sizeof(acc[0]) / sizeof(acc[0][0]);  // 16-row blocks
       const int ln = own_lane(), l16 = ln % 16, lq = ln / 16;
@@ -442,53 +583,16 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
       for (int e = 0; e < 4; ++e) lane_row[e] = (uint32_t)(4 * lq + e) * N + G * l16;
       if constexpr (SPLIT) {
         static_assert(!SPLIT || G == 4, "16-byte raw stores");
+        if constexpr (Epi::QKV > 0) {
+          if (walk.whole) {  // wave-uniform
+            qkv_epilogue(acc, rbase, cbase);
+            return;
+          }
+        }
         const float *pz = split.part + (size_t)z * split.split_stride;
         auto at = [&](int i, int q, int e) {
           return floatx4{acc[0][i][G * q][e], acc[0][i][G * q + 1][e], acc[0][i][G * q + 2][e], acc[0][i][G * q + 3][e]};
         };
-        if constexpr (Epi::DIRECT) {
-          // Direct columns (values): a bias and the rounding are all they need, so they skip the raw result: 2 bytes
-          // written per element where 4 were written, read and 2 written by the row kernel.  A run of 64 columns
-          // (16 lanes) is on one side of direct.lo; a tile may be on both.
-          const DirectCols &dc = epi.direct;
-          if (cbase + 64 * NQ > dc.lo) {  // wave-uniform
-            floatx4 bias[NQ];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-              uint2 w = {0u, 0u};
-              const int c = cbase + 64 * q - dc.lo;
-              if (dc.bias && c >= 0) w = *reinterpret_cast<const uint2 *>((const bf16_t *)dc.bias + c + 4 * l16);
-              bias[q] = floatx4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
-                                __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
-            }
-#pragma unroll
-            for (int i = 0; i < MI; ++i) {
-              // (the accumulators are still where they were: without this the compiler moves them out of the second register
-              // file ahead of the branch above, into scratch memory for 58 registers)
-#pragma unroll
-              for (int c = 0; c < 2 * NB; ++c) asm volatile("" : "+a"(acc[0][i][c]));
-#pragma unroll
-              for (int q = 0; q < NQ; ++q) {
-                const int c = cbase + 64 * q - dc.lo;
-                if (c >= 0) {
-                  const auto out = make_srd((const bf16_t *)dc.out + (size_t)(rbase + RR * i) * dc.ld + c, left(i) ? (uint32_t)(left(i) * dc.ld - c) * 2u : 0);
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) {
-                    const floatx4 v = at(i, q, e) + bias[q];
-                    const float o[4] = {v[0], v[1], v[2], v[3]};
-                    store_buf(o, out, ((uint32_t)(4 * lq + e) * dc.ld + 4 * l16) * 2u);
-                  }
-                } else {
-                  const auto part = block(pz, i, 4);
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) store_buf(at(i, q, e), part, lane_row[e] * 4u + 64 * G * q);
-                }
-              }
-              __builtin_amdgcn_sched_barrier(0);  // (a row block at a time: more of them at once spill)
-            }
-            return;
-          }
-        }
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
           const auto part = block(pz, i, 4);
@@ -585,7 +689,11 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
         const int c = d * (NWC / RingFull::ND), t = c / SH::B_LD, i = c % SH::B_LD;
         // the copy's 8 tile rows hold every G-th weight row from nu on (wave-uniform): rows of one panel, and
         // so of one matrix, whose ends are multiples of 16 G (ring_groups_ok)
-        const int nu = n0 + RingFull::weight_row(i, wave);
+        int nu = n0 + RingFull::weight_row(i, wave);
+        if constexpr (PAIRS) {
+          // a run of 64 holds the 32 columns of half a head's half and their partners: panels 0 and 2, or 1 and 3, of the head
+          if (walk.whole) nu += ((wave & 1) - ((n0 / 64 + i / 2) & 1)) * WPANEL;
+        }
         const bool in1 = nu >= n_end[0], in2 = nu >= n_end[1];
         const void *base = t == 1 ? w[3] : in2 ? w[2] : in1 ? w[1] : w[0];
         const int nl = nu - (t == 1 ? 0 : in2 ? n_end[1] : in1 ? n_end[0] : 0);  // row in its matrix
@@ -919,17 +1027,19 @@ template <typename Kind>
 __global__ __launch_bounds__(256) void k_gemm_planned(GemmArgs ga, typename Kind::Epi epi, PlanArgs pa, GemmPlan pl,
                                                       int planned, int32_t *plan_out) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
-  const Walk walk = walk_of(smem_raw);
+  Walk walk = walk_of(smem_raw);
   const int M = rows_that_exist(ga.rows);
   if (!planned) {
     pl = plan_on_device(pa, M, walk.wave, (uint32_t *)smem_raw);
     __syncthreads();  // (the words are read before anything is copied over them)
   }
+  if constexpr (Kind::Epi::QKV > 0) walk.whole = pl.sk == 1 && epi.o.tab;
   if (plan_out && blockIdx.x == 0 && threadIdx.x == 0) {
     plan_out[0] = pl.sk;
     plan_out[1] = pl.row_hi;
     plan_out[2] = pl.sk_tail;
-    plan_out[3] = (Kind::FUSED && pl.sk == 1) ? pl.row_hi : 0;  // rows whose results are in place
+    // rows whose results are in place
+    plan_out[3] = (walk.whole || Kind::FUSED) && pl.sk == 1 ? pl.row_hi : 0;
   }
   if (pl.row_hi > 0) {
     if (Kind::RAW && (!Kind::FUSED || pl.sk > 1)) {

@@ -100,6 +100,7 @@ void run_planned(const GemmArgs &ga, typename Kind::Epi epi, const PlanArgs &pa,
   k_gemm_planned<Kind><<<ring_grid(), 256, RING_SLOTS * RING_SLOT, s>>>(ga, epi, pa, pl, known, known ? nullptr : plan_dev);
 }
 
+// fused: row tiles finish their rows where K is not split
 Splits splits_of(const GemmArgs &ga, const GemmPlan &pl, bool fused, const int32_t *plan_dev) {
   Splits sp;
   sp.n = pl.sk;

@@ -1,0 +1,10 @@
+// bf16 q|k|v projection with heads of 64 columns: bias, rotary embedding and the merge into the caches in its epilogue.
+#include "gemm_bf16_qkv.h"
+
+namespace dy {
+
+Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, int32_t *plan_dev, hipStream_t s) {
+  return run_qkv<64>(ga, part, out, pa, plan_dev, s);
+}
+
+}  // namespace dy

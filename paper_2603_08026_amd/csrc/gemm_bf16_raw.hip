@@ -3,42 +3,46 @@
 
 namespace dy {
 
-// q|k|v of a dense step of many rows, the values straight into their cache (gemm_bf16_qkv.hip)
-Splits gemm_bf16_qkv(const GemmArgs &ga, float *part, const DirectCols &direct, const PlanArgs &pa, hipStream_t s);
+// q|k|v (gemm_bf16_qkv.hip, gemm_bf16_qkv64.hip: heads of 128 and 64 columns), or with an empty QkvOut any raw result
+Splits gemm_bf16_qkv128(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, int32_t *plan_dev, hipStream_t s);
+Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, int32_t *plan_dev, hipStream_t s);
 
-// raw result part[z][j][n]; returns the numbers of K splits (on the device if the count is there)
-Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, DirectCols direct,
+// raw result part[z][j][n], or rows finished as `qkv` says; returns the numbers of K splits (on the device if the count is there)
+Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, const QkvOut *qkv,
                      hipStream_t s) {
   Splits out;
   if (rows.cap <= 0) return out;
   const int N = seg.n_end[2];
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
-  const EpiStoreF32 e{part, N};
-  const bool w96 = N % SkinnyW96::BN == 0, ring = ring_ok(A, K, seg, N);
+  const bool ring = ring_ok(A, K, seg, N);
+  // A list with room for most of the tokens is a carried one that holds a few percent of them: K of its GEMMs is split, and they
+  // keep to the raw result in a kernel that knows nothing else (8 x 1024 tokens with 330 listed rows, two layers, four
+  // steps: 2075 us; in the kernel that can finish rows, which is three times as long, 2091).  All other raw results
+  // of planned GEMMs share that one, of which the instruction caches then still hold a part from GEMM to GEMM (five sparse
+  // steps of 410 to 5160 rows 0.1 to 1.7 % faster than with the out-projection in a kernel of its own).
+  const bool few = rows.count && (size_t)rows.cap * 2 > (qkv ? qkv->tokens : A.a_rows);
+  // (positions come from a division by at least two, rotary table entries from 32-bit offsets)
+  if (qkv && (qkv->L < 2 || (size_t)qkv->L * qkv->dh * 4 >= ((size_t)1 << 31))) qkv = nullptr;
+  const auto qkv_gemm = qkv && qkv->dh == 64 ? gemm_bf16_qkv64 : gemm_bf16_qkv128;
   PlanArgs pa = raw_plan_args(N, K, part_elems, ring, cus_of_xcd());
   if (rows.cap <= STREAM_ROWS) {
+    const EpiStoreF32 e{part, N};
     out.n = stream_split(pa, rows.cap);
-    if (w96) run_tiles<SkinnyW96, true>(ga, e, out.n, s);
+    if (N % SkinnyW96::BN == 0) run_tiles<SkinnyW96, true>(ga, e, out.n, s);
     else run_tiles<SkinnyS, true>(ga, e, out.n, s);
     return out;
   }
   if (ring) {
-    // Dense steps from DIRECT_ROWS rows on: 20480 rows of 12288 columns, GEMM and row kernel together 1835 -> 1735 us.  The line
-    // is the smallest measured count from which no layer loses (dense steps without / with, us: hidden 4096, 2048 rows 756 /
-    // 751, 4096 rows 1410 / 1390, 8192 rows 2780 / 2741; hidden 3584 with four KV heads 799 / 801, 1511 / 1501, 2932 / 2937;
-    // hidden 2048 258 / 254, 453 / 448, 837 / 808; hidden 1024 115 / 116, 183 / 180, 336 / 327, and 82 / 85 at 1024 rows).  Lists
-    // stay with the raw result: the kernel is another one than the out-projection's, whose instructions the caches
-    // still hold from layer to layer, and few rows lose more by that than they gain (loop of 8 x 1024 tokens with 330 listed
-    // rows 2119 -> 2149 us a pass, 410 rows of a list 302 -> 306 us a step; 2064 rows 812 -> 808, 5160 rows 1872 -> 1859,
-    // but how many of a list exist is known to the device alone).
-    if (direct.out && !rows.idx && !rows.count && rows.cap >= DIRECT_ROWS) return gemm_bf16_qkv(ga, part, direct, pa, s);
-    const GemmPlan pl = plan_here(ga, pa);
-    run_planned<RawKind<EpiStoreF32>>(ga, e, pa, pl, plan_dev, s);
-    return splits_of(ga, pl, false, plan_dev);
+    if (few) {
+      const GemmPlan pl = plan_here(ga, pa);
+      run_planned<RawKind<EpiStoreF32>>(ga, EpiStoreF32{part, N}, pa, pl, plan_dev, s);
+      return splits_of(ga, pl, false, plan_dev);
+    }
+    return qkv ? qkv_gemm(ga, part, *qkv, pa, plan_dev, s) : gemm_bf16_qkv128(ga, part, QkvOut{}, pa, plan_dev, s);
   }
   pa.stream_cols = 0;
   out.n = plan_of(pa, rows.cap, first_on_host(pa, rows.cap)).sk;
-  run_tiles<LargeS8, true>(ga, e, out.n, s);
+  run_tiles<LargeS8, true>(ga, EpiStoreF32{part, N}, out.n, s);
   return out;
 }
 

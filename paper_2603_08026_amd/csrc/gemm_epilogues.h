@@ -34,7 +34,7 @@ struct EpiStoreF32 {
   static constexpr bool GATHER = true;  // the activation rows may be gathered
   static constexpr int INTERLEAVE = 0;
   static constexpr bool PRELOAD = false;
-  static constexpr bool DIRECT = false;
+  static constexpr int QKV = 0;
   float *out;
   int ldo;
   __device__ __forceinline__ void operator()(int j, int row, int n, float acc, float) const {
@@ -48,11 +48,12 @@ struct EpiStoreF32 {
   }
 };
 
-// The same; columns from direct.lo on leave ring tiles as final bf16 rows of direct.out, bias added (gemm_bf16_dma.h).
-// lo is a multiple of 64, or past the last column where there are none; for rows without a list.
-struct EpiStoreDirect : EpiStoreF32 {
-  static constexpr bool DIRECT = true;
-  DirectCols direct;
+// The same for q|k|v with heads of DH columns; where K is not split, ring tiles finish the rows themselves (gemm_bf16_dma.h).
+template <int DH> struct EpiQkv : EpiStoreF32 {
+  static constexpr int QKV = DH;
+  QkvOut o;
+  uint32_t l_mul, l_shift;  // r / L = (r * l_mul) >> (32 + l_shift) for r below 2^31
+  __device__ __forceinline__ uint32_t position(uint32_t r) const { return r - (__umulhi(r, l_mul) >> l_shift) * (uint32_t)o.L; }
 };
 
 template <typename T> struct EpiSwiGLU {
@@ -60,6 +61,7 @@ template <typename T> struct EpiSwiGLU {
   static constexpr bool GATHER = false;  // GemmArgs::gather is not read: these rows are never gathered
   static constexpr int INTERLEAVE = 0;
   static constexpr bool PRELOAD = false;
+  static constexpr int QKV = 0;
   T *act;  // [cap, N]
   int N;
   __device__ __forceinline__ void operator()(int j, int row, int n, float gate, float up) const {
@@ -86,7 +88,7 @@ template <typename T> struct EpiDown {
   // knows, so element by element every load would wait for the store before it; the kernel instead
   // loads a block's residuals (load) and then stores the block (store).
   static constexpr bool PRELOAD = true;
-  static constexpr bool DIRECT = false;
+  static constexpr int QKV = 0;
   const float *h;  // [cap, N]
   T *out;          // [T, N]
   int N;
@@ -123,6 +125,7 @@ template <typename T, int HALF> struct EpiSwiGLUHalves {
   static constexpr bool GATHER = false;  // GemmArgs::gather is not read: these rows are never gathered
   static constexpr int INTERLEAVE = HALF;  // 48 (96-column tiles) or 64 (128-column tiles)
   static constexpr bool PRELOAD = false;
+  static constexpr int QKV = 0;
   T *act;  // [cap, F]
   int F;
   // f = output column of the FFN's hidden layer

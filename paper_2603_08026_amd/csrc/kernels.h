@@ -21,7 +21,7 @@ struct Rows {
 // {n, tail_from, n_tail, done_to} there; the members are then ignored.
 struct Splits {
   int n = 1, tail_from = 0x7fffffff, n_tail = 1;
-  int done_to = 0;  // rows below it were finished by the GEMM's own epilogue: down projection, and the direct columns of q|k|v
+  int done_to = 0;  // rows below it (never more than the list holds) were finished by the GEMM's own epilogue: down projection, q|k|v
   const int32_t *dev = nullptr;
   __device__ Splits resolved() const {
     Splits r = *this;
@@ -49,6 +49,17 @@ __device__ __forceinline__ CandidateRow candidate_row(const int32_t *offsets, in
 }
 enum DvLayout { DV_NONE, DV_BY_TOKEN, DV_BY_ENTRY, DV_BY_SEQUENCE };
 
+// Where q|k|v (or q alone: no key-value heads) of a row go once they are finished: bias, rotary embedding of q and k by the
+// table entry of position (row_j mod L), q at q[j] (q[row_j] when q_by_token), k and v at row_j of the caches.
+// rope_tab: [max_seq, dh/2, 2] fp32 (cos, sin).  dh is 64 or 128.
+struct QkvOut {
+  void *q = nullptr, *k = nullptr, *v = nullptr;
+  const void *bq = nullptr, *bk = nullptr, *bv = nullptr;
+  const float *tab = nullptr;
+  int H = 0, Hkv = 0, dh = 0, L = 0, q_by_token = 0;
+  size_t tokens = 0;  // of all sequences
+};
+
 // ---- row kernels (HBM-bound) ------------------------------------------------------------------
 // out[j,:] = RMSNorm(x[row_j,:]) * gain            x: [T,d] T-typed, out: [cap,d] T-typed
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
@@ -56,10 +67,6 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
 // The GEMMs leave fp32 "raw" results part[z][j][n] (z = K split, j = position in the row list); the
 // finalize kernels below sum the splits and apply the fused tail of the step, one workgroup per row.
 //
-// q/k/v: sum of splits + bias, rotary embedding of q and k by the table entry of position
-// (row mod L), q_out[j] (T-typed [cap,dq]; q_out[row_j] when q_by_token), k and v rows scattered into
-// the caches at row_j.
-// rope_tab: [max_seq, dh/2, 2] fp32 (cos, sin).  dh is 64 or 128.
 // What the approximate step keeps of its candidates beside the caches (a kernel of its own: with these in the kernel of
 // every step, q of 8192 rows took 55 instead of 42 us):
 //   dv        v - v_cache of the rows before the merge, at row_j (DV_BY_TOKEN), at j (DV_BY_ENTRY) or at their candidate_row
@@ -74,10 +81,9 @@ struct CandidateOut {
   int32_t *entry_of;
   int entry_lo;
 };
-void launch_qkv_finalize(DType t, const float *part, Splits splits,
-                         const float *rope_tab, Rows rows, int L, int H, int Hkv, int dh,
-                         const void *bq, const void *bk, const void *bv, void *q_out, void *k_cache,
-                         void *v_cache, int q_by_token, const CandidateOut *cand, hipStream_t s);
+// q/k/v: sum of splits, then as QkvOut says, for the rows from splits.done_to on
+void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, const QkvOut &out, const CandidateOut *cand,
+                         hipStream_t s);
 // out-projection: h[j] = x[row_j] + sum of splits (fp32 [cap,d]); f[j] = RMSNorm(h[j]) * gain (T-typed)
 void launch_oproj_finalize(DType t, const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
@@ -186,19 +192,13 @@ inline WSeg wseg_one(const void *w, int N) {
   s.n_end[0] = s.n_end[1] = s.n_end[2] = N;
   return s;
 }
-// Columns of a raw GEMM that need nothing but a bias (the values among q|k|v): column n >= lo of row j is out[row_j, n - lo]
-// (bf16, row length ld).  The returned Splits::done_to says for which rows the GEMM wrote them (it may be none); the
-// row kernel finishes the others from their raw results.
-struct DirectCols {
-  void *out = nullptr;
-  const void *bias = nullptr;
-  int lo = 0x7fffffff, ld = 0;
-};
 // raw GEMM: part[z][j][n] = sum over K split z of A[j,:] * W[n,:] (fp32, split stride rows*N);
 // returns the numbers of splits used (>= 1), chosen from the rows that exist, N and K (on the device, in
 // the four words `plan`, when their number is known there alone).
+// qkv: where the results go in the end.  The GEMM may finish rows itself (those below Splits::done_to, which have no raw
+// result then); the row kernel finishes the others.
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
-                       int32_t *plan, hipStream_t s, DirectCols direct = DirectCols{});
+                       int32_t *plan, hipStream_t s, const QkvOut *qkv = nullptr);
 // up: act[j,:] = silu(A w_gate^T) * (A w_up^T), T-typed out [cap, N]; here and below A[j,:] = a[j,:], rows of K elements
 void launch_gemm_swiglu(DType t, const void *a, Rows rows, int K, int N, const void *w_gate,
                         const void *w_up, void *act, hipStream_t s);

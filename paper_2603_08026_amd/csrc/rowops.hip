@@ -154,7 +154,7 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
   const int qk_items = (H + Hkv) * per_head, v_items = dkv / 4;
   const Splits sp = splits_of.resolved();
   const size_t split_stride = (size_t)n * ld;
-  for (int j = blockIdx.x; j < n; j += gridDim.x) {
+  for (int j = sp.done_to + blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
     const int splits = sp.of(j);
     const int pos = r % L;
@@ -170,8 +170,7 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
     }
     const float *src = part + (size_t)j * ld;
     const float *t = tab + (size_t)pos * half * 2;
-    const int items = qk_items + (j < sp.done_to ? 0 : v_items);  // (values that the GEMM has written itself are left out)
-    for (int it = threadIdx.x; it < items; it += RB) {
+    for (int it = threadIdx.x; it < qk_items + v_items; it += RB) {
       if (it < qk_items) {
         const int head = it / per_head, p4 = (it % per_head) * 4;
         const bool isq = head < H;
@@ -195,10 +194,14 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
         const float4 t0 = *reinterpret_cast<const float4 *>(t + 2 * p4);      // cos0 sin0 cos1 sin1
         const float4 t1 = *reinterpret_cast<const float4 *>(t + 2 * p4 + 4);  // cos2 sin2 cos3 sin3
         T *dst = isq ? q_out + (size_t)(q_by_token ? r : j) * dq : kc + (size_t)r * dkv;
-        const T lo4[4] = {from_f<T>(x1.x * t0.x - x2.x * t0.y), from_f<T>(x1.y * t0.z - x2.y * t0.w),
-                          from_f<T>(x1.z * t1.x - x2.z * t1.y), from_f<T>(x1.w * t1.z - x2.w * t1.w)};
-        const T hi4[4] = {from_f<T>(x2.x * t0.x + x1.x * t0.y), from_f<T>(x2.y * t0.z + x1.y * t0.w),
-                          from_f<T>(x2.z * t1.x + x1.z * t1.y), from_f<T>(x2.w * t1.z + x1.w * t1.w)};
+        const float a1[4] = {x1.x, x1.y, x1.z, x1.w}, a2[4] = {x2.x, x2.y, x2.z, x2.w};
+        const float co[4] = {t0.x, t0.z, t1.x, t1.z}, si[4] = {t0.y, t0.w, t1.y, t1.w};
+        T lo4[4], hi4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          lo4[u] = from_f<T>(rotated(a1[u], co[u], -(a2[u] * si[u])));
+          hi4[u] = from_f<T>(rotated(a2[u], co[u], a1[u] * si[u]));
+        }
         T *ks = (k_here && !isq) ? k_out + (size_t)cand_row * dkv : nullptr;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -495,16 +498,15 @@ void launch_down_finalize(DType t, const float *part, Splits splits, const float
     k_down_finalize<bf16_t><<<g, RB, 0, s>>>(part, splits, h, rows, d, (bf16_t *)out_cache);
 }
 
-void launch_qkv_finalize(DType t, const float *part, Splits splits,
-                         const float *rope_tab, Rows rows, int L, int H, int Hkv, int dh,
-                         const void *bq, const void *bk, const void *bv, void *q_out, void *k_cache,
-                         void *v_cache, int q_by_token, const CandidateOut *cand, hipStream_t s) {
-  if (rows.cap <= 0) return;
+void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, const QkvOut &o, const CandidateOut *cand,
+                         hipStream_t s) {
+  const int done = splits.dev ? 0 : splits.done_to;
+  if (rows.cap <= 0 || done >= rows.cap) return;
   const CandidateOut c = cand ? *cand : CandidateOut{};
 #define DY_QKV_FIN(TT, C)                                                                               \
-  k_qkv_finalize<TT, C><<<row_grid(rows), RB, 0, s>>>(                                                 \
-      part, splits, rope_tab, rows, L, H, Hkv, dh, (const TT *)bq, (const TT *)bk, (const TT *)bv,     \
-      (TT *)q_out, (TT *)k_cache, (TT *)v_cache, q_by_token, (TT *)c.dv, (TT *)c.k, c.offsets, c.entry_of, c.entry_lo)
+  k_qkv_finalize<TT, C><<<row_grid(rows, rows.cap - done), RB, 0, s>>>(                                 \
+      part, splits, o.tab, rows, o.L, o.H, o.Hkv, o.dh, (const TT *)o.bq, (const TT *)o.bk, (const TT *)o.bv, \
+      (TT *)o.q, (TT *)o.k, (TT *)o.v, o.q_by_token, (TT *)c.dv, (TT *)c.k, c.offsets, c.entry_of, c.entry_lo)
   if (t == F32) {
     if (c.layout == DV_NONE) DY_QKV_FIN(float, DV_NONE);
     else if (c.layout == DV_BY_TOKEN) DY_QKV_FIN(float, DV_BY_TOKEN);
