@@ -195,12 +195,19 @@ void prof_mark(dyllm_ctx *ctx, int stage, hipStream_t s) {
 int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Rows rows, int B, int L,
                 dyllm_layer_cache *cache, void *q_out, hipStream_t s) {
   const dyllm_layer_cfg &c = ctx->cfg;
-  launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, s);
-  prof_mark(ctx, ST_GATHER_NORM, s);
   WSeg seg;
   seg.w[0] = w->wq; seg.w[1] = w->wk; seg.w[2] = w->wv;
   seg.n_end[0] = ctx->dq; seg.n_end[1] = ctx->dq + ctx->dkv; seg.n_end[2] = ctx->dq + 2 * ctx->dkv;
   const QkvOut out{q_out, cache->k, cache->v, w->bq, w->bk, w->bv, ctx->rope, c.n_heads, c.n_kv_heads, c.head_dim, L, 0, (size_t)B * L};
+  if (dt(ctx) == F32) {
+    prof_mark(ctx, ST_GATHER_NORM, s);
+    launch_qkv_f32(x, w->g_attn, c.rms_eps, rows, c.hidden, seg, out, s);
+    prof_mark(ctx, ST_GEMM_QKV, s);
+    prof_mark(ctx, ST_ROPE_SCATTER, s);
+    return check_launch(ctx, "qkv refresh");
+  }
+  launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, s);
+  prof_mark(ctx, ST_GATHER_NORM, s);
   const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
                                      ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
   prof_mark(ctx, ST_GEMM_QKV, s);
@@ -238,14 +245,19 @@ int enqueue_attention(dyllm_ctx *ctx, const void *q, const void *k, const void *
 int enqueue_ffn(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, const void *c_all,
                 Rows rows, void *out_cache, size_t n_tokens, hipStream_t s) {
   const dyllm_layer_cfg &c = ctx->cfg;
-  const Splits splits = launch_gemm_raw(dt(ctx), GemmA{c_all, rows.idx, ctx->dq, n_tokens}, rows, ctx->dq,
-                                     wseg_one(w->wo, c.hidden), ctx->part_o, ctx->part_elems, ctx->plan, s);
-  prof_mark(ctx, ST_GEMM_OPROJ, s);
-  launch_oproj_finalize(dt(ctx), ctx->part_o, splits, x, w->g_ffn, rows,
-                        c.hidden, c.rms_eps, ctx->hs, ctx->fs, s);
-  prof_mark(ctx, ST_NORM_FFN, s);
-  launch_gemm_swiglu(dt(ctx), ctx->fs, rows, c.hidden, c.ffn_dim, w->w_gate,
-                     w->w_up, ctx->act, s);
+  const GemmA A{c_all, rows.idx, ctx->dq, n_tokens};
+  if (dt(ctx) == F32) {
+    launch_oproj_f32(A, rows, ctx->dq, c.hidden, w->wo, x, ctx->hs, s);
+    prof_mark(ctx, ST_GEMM_OPROJ, s);
+    prof_mark(ctx, ST_NORM_FFN, s);
+    launch_swiglu_f32(ctx->hs, w->g_ffn, c.rms_eps, rows, c.hidden, c.ffn_dim, w->w_gate, w->w_up, ctx->act, s);
+  } else {
+    const Splits splits = launch_gemm_raw(BF16, A, rows, ctx->dq, wseg_one(w->wo, c.hidden), ctx->part_o, ctx->part_elems, ctx->plan, s);
+    prof_mark(ctx, ST_GEMM_OPROJ, s);
+    launch_oproj_finalize(ctx->part_o, splits, x, w->g_ffn, rows, c.hidden, c.rms_eps, ctx->hs, ctx->fs, s);
+    prof_mark(ctx, ST_NORM_FFN, s);
+    launch_gemm_swiglu(ctx->fs, rows, c.hidden, c.ffn_dim, w->w_gate, w->w_up, ctx->act, s);
+  }
   prof_mark(ctx, ST_GEMM_SWIGLU, s);
   launch_gemm_down(dt(ctx), ctx->act, rows, c.ffn_dim, c.hidden, w->w_down,
                    ctx->hs, out_cache, ctx->part_o, ctx->part_elems, ctx->plan, s);
@@ -354,12 +366,16 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   int rc;
   ctx->prof_cur = nullptr;  // no per-stage timing on this path
   // norm and q projection (+ rotation) of EVERY token of the step  [Alg. 3: Q <- q_proj(x)]
-  launch_gather_rmsnorm(dt(ctx), x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, s);
   {
     const QkvOut out{ctx->qs, nullptr, nullptr, w->bq, nullptr, nullptr, ctx->rope, c.n_heads, 0, c.head_dim, L, by_token, (size_t)B * L};
-    const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, all, c.hidden,
-                                       wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
-    launch_qkv_finalize(dt(ctx), ctx->part_o, splits, all, out, nullptr, s);
+    if (dt(ctx) == F32) {
+      launch_qkv_f32(x, w->g_attn, c.rms_eps, all, c.hidden, wseg_one(w->wq, ctx->dq), out, s);
+    } else {
+      launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, s);
+      const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, nullptr, c.hidden}, all, c.hidden,
+                                            wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
+      launch_qkv_finalize(BF16, ctx->part_o, splits, all, out, nullptr, s);
+    }
   }
   // k, v of the salient tokens: norm, projection, rotation, value residual, merge into the caches
   launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, s);

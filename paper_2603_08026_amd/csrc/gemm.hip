@@ -1,10 +1,9 @@
-// Dispatch of the salient-row GEMMs by storage type: fp32 -> FMA kernels, bf16 -> MFMA kernels.
+// Dispatch of the salient-row GEMMs by storage type: gemm_f32.hip, gemm_bf16_*.hip.
 #include "kernels.h"
 
 namespace dy {
 
 void gemm_f32_raw(GemmA, Rows, int, WSeg, float *, hipStream_t);
-void gemm_f32_swiglu(GemmA, Rows, int, int, const void *, const void *, void *, hipStream_t);
 void gemm_f32_down(GemmA, Rows, int, int, const void *, const float *, void *, hipStream_t);
 
 Splits gemm_bf16_raw(GemmA, Rows, int, WSeg, float *, size_t, int32_t *, const QkvOut *, hipStream_t);
@@ -20,11 +19,9 @@ Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part
   return gemm_bf16_raw(A, rows, K, seg, part, part_elems, plan, qkv, s);
 }
 
-void launch_gemm_swiglu(DType t, const void *a, Rows rows, int K, int N, const void *w_gate,
+void launch_gemm_swiglu(const void *a, Rows rows, int K, int N, const void *w_gate,
                         const void *w_up, void *act, hipStream_t s) {
-  const GemmA A{a, nullptr, K};
-  if (t == F32) gemm_f32_swiglu(A, rows, K, N, w_gate, w_up, act, s);
-  else gemm_bf16_swiglu(A, rows, K, N, w_gate, w_up, act, s);
+  gemm_bf16_swiglu(GemmA{a, nullptr, K}, rows, K, N, w_gate, w_up, act, s);
 }
 
 void launch_gemm_down(DType t, const void *a, Rows rows, int K, int N, const void *w_down, const float *h,

@@ -51,7 +51,7 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
     if (!sums || (known && pl.sk == 1 && pl.row_hi == rows.cap)) return;
     sp = splits_of(ga, pl, true, plan_dev);
   }
-  launch_down_finalize(BF16, part, sp, h, rows, N, out, s);
+  launch_down_finalize(part, sp, h, rows, N, out, s);
 }
 
 }  // namespace dy

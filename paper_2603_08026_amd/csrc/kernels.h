@@ -84,13 +84,13 @@ struct CandidateOut {
 // q/k/v: sum of splits, then as QkvOut says, for the rows from splits.done_to on
 void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, const QkvOut &out, const CandidateOut *cand,
                          hipStream_t s);
-// out-projection: h[j] = x[row_j] + sum of splits (fp32 [cap,d]); f[j] = RMSNorm(h[j]) * gain (T-typed)
-void launch_oproj_finalize(DType t, const float *part, Splits splits, const void *x,
+// out-projection (bf16): h[j] = x[row_j] + sum of splits (fp32 [cap,d]); f[j] = RMSNorm(h[j]) * gain
+void launch_oproj_finalize(const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
                            hipStream_t s);
-// down projection after a K split: out_cache[row_j] = h[j] + sum of splits, for the rows from
+// down projection (bf16) after a K split: out_cache[row_j] = h[j] + sum of splits, for the rows from
 // splits.done_to on (the rows below it were written by the GEMM's own epilogue)
-void launch_down_finalize(DType t, const float *part, Splits splits, const float *h,
+void launch_down_finalize(const float *part, Splits splits, const float *h,
                           Rows rows, int d, void *out_cache, hipStream_t s);
 // cosine of c_new[j] vs c_cache[row_j], flag = cos < tau, optional commit of the new row.
 void launch_saliency(DType t, const void *c_new, void *c_cache, Rows rows, int D, float tau,
@@ -199,13 +199,23 @@ inline WSeg wseg_one(const void *w, int N) {
 // result then); the row kernel finishes the others.
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
                        int32_t *plan, hipStream_t s, const QkvOut *qkv = nullptr);
-// up: act[j,:] = silu(A w_gate^T) * (A w_up^T), T-typed out [cap, N]; here and below A[j,:] = a[j,:], rows of K elements
-void launch_gemm_swiglu(DType t, const void *a, Rows rows, int K, int N, const void *w_gate,
+// up (bf16): act[j,:] = silu(A w_gate^T) * (A w_up^T), out [cap, N]; here and below A[j,:] = a[j,:], rows of K elements
+void launch_gemm_swiglu(const void *a, Rows rows, int K, int N, const void *w_gate,
                         const void *w_up, void *act, hipStream_t s);
 // down: out_cache[row_j,:] = h[j,:] + A[j,:] * w_down^T, T-typed scatter into [T, N]; `scratch`
 // holds K-split partials when K is split; plan: as for launch_gemm_raw.
 void launch_gemm_down(DType t, const void *a, Rows rows, int K, int N, const void *w_down, const float *h,
                       void *out_cache, float *scratch, size_t scratch_elems, int32_t *plan, hipStream_t s);
+
+// fp32: the same steps without row kernels between them.  K is never split, so a GEMM finishes its rows, and each takes its
+// operand's RMSNorm along.
+// q|k|v of RMSNorm(x[row_j,:]) * gain, finished as QkvOut says
+void launch_qkv_f32(const void *x, const void *gain, float eps, Rows rows, int K, WSeg seg, const QkvOut &out, hipStream_t s);
+// h[j,:] = x[row_j,:] + A[j,:] * wo^T
+void launch_oproj_f32(GemmA A, Rows rows, int K, int N, const void *wo, const void *x, float *h, hipStream_t s);
+// act[j,:] = silu(n w_gate^T) * (n w_up^T) of n = RMSNorm(h[j,:]) * gain
+void launch_swiglu_f32(const float *h, const void *gain, float eps, Rows rows, int K, int N, const void *w_gate,
+                       const void *w_up, void *act, hipStream_t s);
 
 // row-major [n_out, n_in] (2-byte elements; n_out % 32 == 0, n_in % 64 == 0) -> weight panels of the bf16 GEMMs
 void launch_pack_weight(const void *src, int n_out, int n_in, void *dst, hipStream_t s);

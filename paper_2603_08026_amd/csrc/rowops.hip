@@ -474,28 +474,19 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
   }
 }
 
-void launch_oproj_finalize(DType t, const float *part, Splits splits, const void *x,
+void launch_oproj_finalize(const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
                            hipStream_t s) {
   if (rows.cap <= 0) return;
-  if (t == F32)
-    k_oproj_finalize<float><<<row_grid(rows), RB, 0, s>>>(part, splits, (const float *)x,
-                                                              (const float *)gain, rows, d, eps, h, (float *)f);
-  else
-    k_oproj_finalize<bf16_t><<<row_grid(rows), RB, 0, s>>>(part, splits, (const bf16_t *)x,
-                                                               (const bf16_t *)gain, rows, d, eps, h,
-                                                               (bf16_t *)f);
+  k_oproj_finalize<bf16_t><<<row_grid(rows), RB, 0, s>>>(part, splits, (const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, h,
+                                                         (bf16_t *)f);
 }
 
-void launch_down_finalize(DType t, const float *part, Splits splits, const float *h,
+void launch_down_finalize(const float *part, Splits splits, const float *h,
                           Rows rows, int d, void *out_cache, hipStream_t s) {
   const int done = splits.dev ? 0 : splits.done_to;
   if (rows.cap <= 0 || done >= rows.cap) return;
-  const int g = row_grid(rows, rows.cap - done);
-  if (t == F32)
-    k_down_finalize<float><<<g, RB, 0, s>>>(part, splits, h, rows, d, (float *)out_cache);
-  else
-    k_down_finalize<bf16_t><<<g, RB, 0, s>>>(part, splits, h, rows, d, (bf16_t *)out_cache);
+  k_down_finalize<bf16_t><<<row_grid(rows, rows.cap - done), RB, 0, s>>>(part, splits, h, rows, d, (bf16_t *)out_cache);
 }
 
 void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, const QkvOut &o, const CandidateOut *cand,
@@ -508,8 +499,7 @@ void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, c
       part, splits, o.tab, rows, o.L, o.H, o.Hkv, o.dh, (const TT *)o.bq, (const TT *)o.bk, (const TT *)o.bv, \
       (TT *)o.q, (TT *)o.k, (TT *)o.v, o.q_by_token, (TT *)c.dv, (TT *)c.k, c.offsets, c.entry_of, c.entry_lo)
   if (t == F32) {
-    if (c.layout == DV_NONE) DY_QKV_FIN(float, DV_NONE);
-    else if (c.layout == DV_BY_TOKEN) DY_QKV_FIN(float, DV_BY_TOKEN);
+    if (c.layout == DV_BY_TOKEN) DY_QKV_FIN(float, DV_BY_TOKEN);  // (candidates alone: launch_qkv_f32 finishes all others)
     else DY_QKV_FIN(float, DV_BY_ENTRY);
   } else {
     if (c.layout == DV_NONE) DY_QKV_FIN(bf16_t, DV_NONE);

@@ -1,0 +1,75 @@
+"""fp32 projections that normalise their rows on the way and finish them (q|k|v with bias, rotation and merge; the FFN half with
+residual and norm), against the same steps in 64 bits: rows at the edges of 16- and 32-row tiles, one and two 16-column
+blocks a tile (few and many tiles), heads of 64 and 128 columns, grouped heads, bias, sequence lengths that are no power of two,
+widths with fewer K steps than waves.  fp32 sums of at most 1536 products of order one: 1e-5 of the result's norm."""
+import pytest
+import torch
+
+from paper_2603_08026_amd import binding as Bd
+from synth import workload as W
+from tests.helpers import rand_weights
+
+SHAPES = {
+    "dh64": W.LayerShape(hidden=256, n_heads=4, n_kv_heads=4, head_dim=64, ffn=768, dtype="f32"),
+    "dh64-gqa": W.LayerShape(hidden=320, n_heads=6, n_kv_heads=2, head_dim=64, ffn=448, dtype="f32"),
+    "dh128": W.LayerShape(hidden=64, n_heads=6, n_kv_heads=3, head_dim=128, ffn=1536, dtype="f32"),
+}
+
+
+def _norm(x, g, eps):
+    return x / torch.sqrt((x * x).mean(-1, keepdim=True) + eps) * g
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 300, 777])
+@pytest.mark.parametrize("bias", [False, True])
+def test_qkv_and_ffn_rows(shape, n, bias):
+    from paper_2603_08026_amd.layer import Layer
+    s, B, L = SHAPES[shape], 3, 277
+    print("fp32 rows", shape, n, bias, flush=True)
+    g = torch.Generator().manual_seed(n)
+    ids = torch.sort(torch.randperm(B * L, generator=g)[:n])[0]
+    off = torch.tensor([int((ids < b * L).sum()) for b in range(B + 1)], dtype=torch.int32).cuda()
+    x = torch.randn(B, L, s.hidden, generator=g)
+    c = torch.randn(B * L, s.dq, generator=g)
+    lay = Layer.from_shape(s, B, L)
+    w = rand_weights(s, 81, bias=bias)
+    lay.set_weights(w)
+    lst = Bd.IndexList(ids.to(torch.int32).cuda(), off)
+    q = torch.zeros(n, s.dq, device="cuda")
+    lay.k.fill_(5.0)
+    lay.v.fill_(-7.0)
+    lay.out.fill_(2.0)
+    xd = x.cuda()
+    lay.ctx.qkv_refresh(lay.w, xd, lst, B, L, lay.cache, q)
+    lay.ctx.salient_ffn(lay.w, xd, c.cuda(), lst, B, L, lay.out)
+    k, v, out = lay.k.view(B * L, -1).cpu(), lay.v.view(B * L, -1).cpu(), lay.out.view(B * L, -1).cpu()
+    lay.close()
+    w = {a: torch.as_tensor(b).double() for a, b in w.items() if b is not None}
+    rows = x.view(B * L, -1)[ids].double()
+    nrm = _norm(rows, w["g_attn"], s.rms_eps)
+
+    def heads(m, b, turn):
+        y = nrm @ w[m].t() + (w[b] if bias else 0)
+        if not turn:
+            return y
+        y = y.view(n, -1, s.head_dim)
+        half = s.head_dim // 2
+        a = ((ids % L).double()[:, None] * s.rope_theta ** (-2.0 * torch.arange(half, dtype=torch.float64) / s.head_dim))[:, None, :]
+        lo, hi = y[..., :half], y[..., half:]
+        return torch.cat([lo * a.cos() - hi * a.sin(), hi * a.cos() + lo * a.sin()], -1).reshape(n, -1)
+
+    def close(got, want, what):
+        err = ((got.double() - want).norm() / want.norm()).item()
+        assert err <= 1e-5, (what, err)
+
+    close(q.cpu(), heads("wq", "bq", True), "q")
+    close(k[ids], heads("wk", "bk", True), "k")
+    close(v[ids], heads("wv", "bv", False), "v")
+    h = rows + c[ids].double() @ w["wo"].t()
+    f = _norm(h, w["g_ffn"], s.rms_eps)
+    close(out[ids], h + (torch.nn.functional.silu(f @ w["w_gate"].t()) * (f @ w["w_up"].t())) @ w["w_down"].t(), "out")
+    rest = torch.ones(B * L, dtype=torch.bool)
+    rest[ids] = False
+    assert (k[rest] == 5.0).all() and (v[rest] == -7.0).all() and (out[rest] == 2.0).all()
