@@ -396,14 +396,14 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   if ((rc = check_launch(ctx, "approx: projections"))) return rc;
   // exact rows of the salient tokens  [Alg. 3: C_sal]; q is stored by token here.  With a cache of
   // log-normalisers the rows go through the merge kernel, which stores theirs.
-  {
-    const int keep_lse = cache->lse != nullptr;
-    AttnArgs a = attn_args(ctx, ctx->qs, cache->k, cache->v, rin, idx_in->offsets, B, L, ctx->csal, keep_lse);
-    a.q_by_token = 1;
-    a.lse_out = (float *)cache->lse;
-    launch_attention(dt(ctx), a, s);
-    if (keep_lse) launch_attn_combine(dt(ctx), a, s);
-  }
+  const int keep_lse = cache->lse != nullptr;
+  AttnArgs exact = attn_args(ctx, ctx->qs, cache->k, cache->v, rin, idx_in->offsets, B, L, ctx->csal, keep_lse);
+  exact.q_by_token = 1;
+  exact.lse_out = (float *)cache->lse;
+  auto exact_rows = [&]() {
+    launch_attention(dt(ctx), exact, s);
+    if (keep_lse) launch_attn_combine(dt(ctx), exact, s);
+  };
   if (!cached_norm) {
     // approximate residual of every token of the step: the full softmax against the merged keys times
     // the value residual, which is zero outside the salient rows  [Alg. 4]
@@ -414,7 +414,10 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
       a.key_cap = rin.cap;
       a.norm_k = cache->k;
     }
-    launch_attention(dt(ctx), a, s);
+    if (!by_sequence || !launch_attention_both(exact, a, s)) {
+      exact_rows();
+      launch_attention(dt(ctx), a, s);
+    }
     if ((rc = check_launch(ctx, "approx: attention"))) return rc;
     // new contexts of the step's tokens, cosine test, commit; the scratch maps and the residual buffer go back to zero
     Residuals residuals;
@@ -423,6 +426,7 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
                            nullptr, nullptr, L, residuals, s);
     if (!by_sequence) launch_clear_rows(dt(ctx), rin, ctx->dv_full, ctx->dkv, s);
   } else {
+    exact_rows();
     // Reused normalisers (Sec. 3.3's O(N |A| d) form): every token of the step is scored against the
     // candidates' keys only -- compact rows, sequence b's at [offsets[b], offsets[b+1]) -- and the
     // un-normalised partial sums are scaled by the log-normaliser cached at the token's last exact

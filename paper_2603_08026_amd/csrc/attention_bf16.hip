@@ -395,7 +395,7 @@ template <int WQ, int WK_> struct DTile {
 // and reads, half the products.  8 x 1024 tokens, 32 heads, 330 candidates, against all keys meeting the zero-padded
 // residual: whole sequences and response windows on average 74 -> 63 us a pass (one tile a step of the sweep: 68).
 template <int WQ, int WK_, bool NORM>
-__global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, int q_tiles) {  // two waves per SIMD: 256 registers, no AGPR shuffling
+__device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int item) {
   using T = DTile<WQ, WK_>;
   constexpr int DH = T::DH, NW = T::NW, WK = T::WK, BQ = T::BQ, TK = T::TK, ROWB = T::ROWB, NS = T::NS,
                 DB = T::DB, KK = T::KK, LPW = T::LPW;
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   const int l32 = lane % 32, lhi = lane / 32;
   const int wq = wave / WK, wk = wave % WK;
   int kvh = 0, split = 0, tile_info[4];
-  attn_work_item_grouped(a, BQ, q_tiles, &kvh, &split, tile_info);
+  attn_work_item_grouped(a, BQ, q_tiles, item, &kvh, &split, tile_info);
   const int b = tile_info[0];
   if (b < 0) return;  // uniform: no such tile
   const int nq = tile_info[3];  // (row, head of the group) pairs in this tile
@@ -960,6 +960,35 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
   }
 }
 
+// (two waves per SIMD: 256 registers, no AGPR shuffling)
+template <int WQ, int WK_, bool NORM>
+__global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, int q_tiles) {
+  attn_dma<WQ, WK_, NORM>(a, q_tiles, blockIdx.x);
+}
+
+// The context update of Alg. 4 (b, the first `grid_b` workgroups) and exact rows (a), which need nothing of each other, in one launch: a
+// few hundred exact rows are 256 items that wait for their keys on half of the chip's places, and the update's last round
+// leaves places idle as well.  8 x 1024 tokens, 32 heads, 330 exact rows, us: update of a window of 2048 tokens 39 + exact rows 35 ->
+// 68, of all tokens 130 + 40 -> 143; a loop of such steps 3520 -> 3440.
+template <int WQ, int WK_>
+__global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_both(AttnArgs a, int tiles_a, AttnArgs b, int tiles_b, int grid_b) {
+  if ((int)blockIdx.x < grid_b) attn_dma<WQ, WK_, true>(b, tiles_b, blockIdx.x);
+  else attn_dma<WQ, WK_, false>(a, tiles_a, blockIdx.x - grid_b);
+}
+
+template <int WQ, int WK> void launch_both(const AttnArgs &a, const AttnArgs &b, hipStream_t s) {
+  using T = DTile<WQ, WK>;
+  static bool done = false;
+  if (!done) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16_both<WQ, WK>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
+    done = true;
+  }
+  const int tiles_a = max_q_tiles_grouped(a, T::BQ), tiles_b = max_q_tiles_grouped(b, T::BQ);
+  const int grid_b = attn_grid_grouped(b, tiles_b);  // (a multiple of the XCDs, so that both keep their order on them)
+  k_attn_bf16_both<WQ, WK><<<grid_b + attn_grid_grouped(a, tiles_a), T::NT, T::LDS_BYTES, s>>>(a, tiles_a, b, tiles_b, grid_b);
+}
+
 template <int WQ, int WK, bool NORM> void launch_dma(const AttnArgs &a, hipStream_t s) {
   using T = DTile<WQ, WK>;
   static bool done = false;
@@ -985,6 +1014,13 @@ template <int DH, int WQ, int NW, int QB> void launch_cfg(const AttnArgs &a, hip
 }
 
 }  // namespace
+
+bool launch_attention_both(const AttnArgs &a, const AttnArgs &b, hipStream_t s) {
+  if (a.dh != 128 || !b.norm_k || a.norm_k || a.bq != b.bq || a.rows.cap <= 0 || b.rows.cap <= 0) return false;
+  if (a.splits > 1 || b.splits > 1 || a.partial || b.partial) return false;  // (partial results of both would share a buffer)
+  if (a.bq == 128) launch_both<4, 1>(a, b, s); else launch_both<2, 2>(a, b, s);
+  return true;
+}
 
 void launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
   const bool wide = a.bq == 128;  // 128 or 64 query rows per workgroup

@@ -104,7 +104,7 @@ __device__ __forceinline__ int wave_scan(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // last lane of row 1 -> rows 2 and 3
   return x;
 }
-// Work item of a workgroup of a 1-D launch over (key split, KV head, tile of packed rows), XCD-aware as above.
+// Work item of workgroup `item` of a 1-D launch over (key split, KV head, tile of packed rows), XCD-aware as above.
 // info[0] = sequence (or -1: no item), info[1] = index of the sequence's first row in the row list, info[2] = first packed
 // row of the tile, info[3] = packed rows in the tile.  Called by every wave with all its lanes; the results are
 // uniform.  The items are those of the tiles that exist, not of the q_tiles that the list's capacity allows: each XCD takes
@@ -113,7 +113,7 @@ __device__ __forceinline__ int wave_scan(int x) {
 // for 8 sequences of 1024 tokens, 32 heads.)
 // A lane counts the tiles of one sequence (64 at a time): one round of loads, where a walk over the sequences waits for each
 // of them in turn.
-__device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ, int q_tiles, int *kvh, int *split,
+__device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ, int q_tiles, int item, int *kvh, int *split,
                                                        int (&info)[4]) {
   const int g = a.H / a.Hkv, lane = threadIdx.x % WAVE;
   info[0] = -1;
@@ -135,7 +135,7 @@ __device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ
     for (int b0 = 0; b0 < a.B; b0 += WAVE) tiles += tiles_of(b0);
   }
   const int items = tiles * a.Hkv * a.splits, per_xcd = (items + ATTN_XCD - 1) / ATTN_XCD;
-  const int p = blockIdx.x, w = (p % ATTN_XCD) * per_xcd + p / ATTN_XCD;
+  const int p = item, w = (p % ATTN_XCD) * per_xcd + p / ATTN_XCD;
   if (p / ATTN_XCD >= per_xcd || w >= items) return;
   int t = w % tiles;
   const int rest = w / tiles;

@@ -156,6 +156,9 @@ struct AttnArgs {
 };
 // attention rows; merges the splits into a.out unless a.partial is set
 void launch_attention(DType t, const AttnArgs &a, hipStream_t s);
+// exact rows (a) and the context update of Alg. 4 (b: norm_k) in one launch, where both are bf16 with head_dim 128, one key split
+// and the same query tile: returns whether they were launched
+bool launch_attention_both(const AttnArgs &a, const AttnArgs &b, hipStream_t s);
 // merge of the attention partials of a call that left them (a.partial) into a.out (and a.lse_out)
 void launch_attn_combine(DType t, const AttnArgs &a, hipStream_t s);
 // merge of the attention partials fused with the saliency test and the context commit:
