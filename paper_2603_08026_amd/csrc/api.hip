@@ -206,7 +206,7 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
     prof_mark(ctx, ST_ROPE_SCATTER, s);
     return check_launch(ctx, "qkv refresh");
   }
-  launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, s);
+  launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, s);
   prof_mark(ctx, ST_GATHER_NORM, s);
   const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
                                      ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
@@ -350,14 +350,18 @@ Window make_window(dyllm_ctx *ctx, int B, int L, int row_lo, hipStream_t s) {
   return Window{Rows{ctx->win_idx, nullptr, B * (L - row_lo)}, ctx->win_off, row_lo};
 }
 
-// one layer of the sparse step with both attention paths, arguments already checked
+// one layer of the sparse step with both attention paths, arguments already checked; inside: every candidate is a token of the step
 // [Alg. 3 layer body; Sec. 3.3: exact rows for the salient tokens, approximate update for the others]
 int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_layer_cache *cache,
-                         const void *x, const dyllm_index_list *idx_in, int B, int L, Window win, float tau,
+                         const void *x, const dyllm_index_list *idx_in, int B, int L, Window win, bool inside, float tau,
                          int cached_norm, dyllm_index_list *idx_out, float *cos_out, hipStream_t s) {
   const dyllm_layer_cfg &c = ctx->cfg;
   const Rows all = win.rows;
   const Rows rin = rows_of(idx_in, B);
+  const size_t T = (size_t)B * L;
+  // shared (bf16): the candidates are tokens of the step, whose normalised rows lie by token, for q of all and k, v of the candidates.
+  // (A gathered operand of 4 GiB would miss the row tiles' 32-bit offsets.)
+  const bool shared = dt(ctx) == BF16 && inside && T * c.hidden * 2 < ((size_t)1 << 31);
   // by_sequence: the candidates' new keys (ksal) and value residuals lie in the form that the share of a sequence's tokens
   // asks for (compact_form); else the residual lies by token in a buffer that is zero elsewhere, which every key meets
   const bool by_sequence = !cached_norm && dt(ctx) == BF16 && c.head_dim == 128;
@@ -371,19 +375,20 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     if (dt(ctx) == F32) {
       launch_qkv_f32(x, w->g_attn, c.rms_eps, all, c.hidden, wseg_one(w->wq, ctx->dq), out, s);
     } else {
-      launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, s);
-      const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, nullptr, c.hidden}, all, c.hidden,
+      launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, shared, s);
+      const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, shared ? all.idx : nullptr, c.hidden, T}, all, c.hidden,
                                             wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
       launch_qkv_finalize(BF16, ctx->part_o, splits, all, out, nullptr, s);
     }
   }
   // k, v of the salient tokens: norm, projection, rotation, value residual, merge into the caches
-  launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, s);
+  if (!shared) launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, 0, s);
   {
     WSeg seg;
     seg.w[0] = w->wk; seg.w[1] = w->wv; seg.w[2] = w->wv;
     seg.n_end[0] = ctx->dkv; seg.n_end[1] = 2 * ctx->dkv; seg.n_end[2] = 2 * ctx->dkv;
-    const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->fs, nullptr, c.hidden}, rin, c.hidden, seg,
+    const GemmA A = shared ? GemmA{ctx->ns, rin.idx, c.hidden, T} : GemmA{ctx->fs, nullptr, c.hidden, T};
+    const Splits splits = launch_gemm_raw(dt(ctx), A, rin, c.hidden, seg,
                                        ctx->part_o, ctx->part_elems, ctx->plan, s);
     // value residual: by token or by sequence into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
     // entry; the last two next to a compact copy of the new keys; and the step's candidates in the token -> entry map
@@ -772,14 +777,15 @@ int dyllm_layer_step_approx(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_
   if ((rc = check_sparse_layer(ctx, w, cache, x, idx_in, idx_out))) return rc;
   if ((rc = check_cached_norm(ctx, cached_norm, cache))) return rc;
   const Window win = make_window(ctx, B, L, row_lo, (hipStream_t)stream);
-  return enqueue_approx_layer(ctx, w, cache, x, idx_in, B, L, win, tau, cached_norm != 0, idx_out, cos_out,
+  return enqueue_approx_layer(ctx, w, cache, x, idx_in, B, L, win, row_lo == 0, tau, cached_norm != 0, idx_out, cos_out,
                               (hipStream_t)stream);
 }
 
-int dyllm_stack_step_approx(dyllm_ctx *ctx, int32_t n_layers, const dyllm_layer_weights *w,
-                            dyllm_layer_cache *caches, const void *x, const dyllm_index_list *idx_in,
-                            int32_t B, int32_t L, int32_t row_lo, float tau, int32_t cached_norm,
-                            dyllm_index_list *idx_out, float *cos_out, void *stream) {
+// (inside: the first layer's candidates are known to be tokens of the step; the other layers' are selected from them)
+static int stack_step_approx(dyllm_ctx *ctx, int32_t n_layers, const dyllm_layer_weights *w,
+                             dyllm_layer_cache *caches, const void *x, const dyllm_index_list *idx_in,
+                             int32_t B, int32_t L, int32_t row_lo, bool inside, float tau, int32_t cached_norm,
+                             dyllm_index_list *idx_out, float *cos_out, void *stream) {
   if (!ctx) return DYLLM_ERR_INVALID_ARG;
   if (n_layers <= 0 || !w || !caches || !idx_out) return fail(ctx, DYLLM_ERR_INVALID_ARG, "empty stack or NULL array");
   int rc;
@@ -795,12 +801,19 @@ int dyllm_stack_step_approx(dyllm_ctx *ctx, int32_t n_layers, const dyllm_layer_
   const dyllm_index_list *in = idx_in;
   for (int l = 0; l < n_layers; ++l) {
     float *cos_l = cos_out ? cos_out + (size_t)l * B * L : nullptr;
-    if ((rc = enqueue_approx_layer(ctx, &w[l], &caches[l], l ? caches[l - 1].out : x, in, B, L, win, tau,
+    if ((rc = enqueue_approx_layer(ctx, &w[l], &caches[l], l ? caches[l - 1].out : x, in, B, L, win, inside || l > 0, tau,
                                    cached_norm != 0, &idx_out[l], cos_l, (hipStream_t)stream)))
       return rc;
     in = &idx_out[l];
   }
   return DYLLM_OK;
+}
+
+int dyllm_stack_step_approx(dyllm_ctx *ctx, int32_t n_layers, const dyllm_layer_weights *w,
+                            dyllm_layer_cache *caches, const void *x, const dyllm_index_list *idx_in,
+                            int32_t B, int32_t L, int32_t row_lo, float tau, int32_t cached_norm,
+                            dyllm_index_list *idx_out, float *cos_out, void *stream) {
+  return stack_step_approx(ctx, n_layers, w, caches, x, idx_in, B, L, row_lo, row_lo == 0, tau, cached_norm, idx_out, cos_out, stream);
 }
 
 int dyllm_merge_lists(dyllm_ctx *ctx, const dyllm_index_list *a, const dyllm_index_list *b, int32_t B,
@@ -847,8 +860,7 @@ int dyllm_denoise_step(dyllm_ctx *ctx, const dyllm_schedule *sched, int32_t t, i
   int rc;
   if ((rc = dyllm_merge_lists(ctx, carry, decoded, B, L, row_lo, cand, stream))) return rc;
   if (sched->approx)
-    return dyllm_stack_step_approx(ctx, n_layers, w, caches, x, cand, B, L, row_lo, sched->tau,
-                                   sched->approx == 2, idx_out, nullptr, stream);
+    return stack_step_approx(ctx, n_layers, w, caches, x, cand, B, L, row_lo, true, sched->tau, sched->approx == 2, idx_out, nullptr, stream);
   return dyllm_stack_step(ctx, n_layers, w, caches, x, cand, B, L, sched->tau, idx_out, nullptr, stream);
 }
 

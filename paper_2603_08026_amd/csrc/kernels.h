@@ -61,9 +61,9 @@ struct QkvOut {
 };
 
 // ---- row kernels (HBM-bound) ------------------------------------------------------------------
-// out[j,:] = RMSNorm(x[row_j,:]) * gain            x: [T,d] T-typed, out: [cap,d] T-typed
+// out[j,:] (by_token: out[row_j,:]) = RMSNorm(x[row_j,:]) * gain            x: [T,d] T-typed, out: [cap,d] ([T,d]) T-typed
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
-                           void *out, hipStream_t s);
+                           void *out, int by_token, hipStream_t s);
 // The GEMMs leave fp32 "raw" results part[z][j][n] (z = K split, j = position in the row list); the
 // finalize kernels below sum the splits and apply the fused tail of the step, one workgroup per row.
 //

@@ -22,7 +22,7 @@ __device__ __forceinline__ int row_count(const Rows &rows) {
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
                                                         const T *__restrict__ gain, Rows rows, int d,
-                                                        float eps, T *__restrict__ out) {
+                                                        float eps, T *__restrict__ out, int by_token) {
   __shared__ float red[NT / WAVE];
   constexpr int N = Vec16<T>::N;
   const int n = row_count(rows), nv = d / N;
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
     }
     ss = block_sum<NT>(ss, red);
     const float sc = 1.0f / sqrtf(ss / (float)d + eps);
-    T *orow = out + (size_t)j * d;
+    T *orow = out + (size_t)(by_token ? r : j) * d;
 #pragma unroll
     for (int it = 0; it < KEEP; ++it) {
       const int v = threadIdx.x + it * NT;
@@ -457,20 +457,20 @@ inline int row_grid(const Rows &rows) { return row_grid(rows, rows.cap); }
 }  // namespace
 
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
-                           void *out, hipStream_t s) {
+                           void *out, int by_token, hipStream_t s) {
   if (rows.cap <= 0) return;
   const int most = rows.count ? 4 * GRID_LISTED : 32768;  // (a quarter of the threads per workgroup)
   const int grid = rows.cap > most ? most : rows.cap;
   if (t == F32) {
     if (d / 4 <= 256 * KEEP)
-      k_gather_rmsnorm<float, 256><<<grid, 256, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out);
+      k_gather_rmsnorm<float, 256><<<grid, 256, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out, by_token);
     else
-      k_gather_rmsnorm<float, RB><<<row_grid(rows), RB, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out);
+      k_gather_rmsnorm<float, RB><<<row_grid(rows), RB, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out, by_token);
   } else {
     if (d / 8 <= 256 * KEEP)
-      k_gather_rmsnorm<bf16_t, 256><<<grid, 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out);
+      k_gather_rmsnorm<bf16_t, 256><<<grid, 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out, by_token);
     else
-      k_gather_rmsnorm<bf16_t, RB><<<row_grid(rows), RB, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out);
+      k_gather_rmsnorm<bf16_t, RB><<<row_grid(rows), RB, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out, by_token);
   }
 }
 
