@@ -60,6 +60,12 @@ template <typename T> __device__ __forceinline__ void st16(T *p, const Vec16<T> 
   *reinterpret_cast<decltype(v.raw) *>(p) = v.raw;
 }
 
+// the same of data that nobody reads again soon: it takes no place in the L2 from what others need
+template <typename T> __device__ __forceinline__ Vec16<T> ld16_once(const T *p) {
+  typedef __attribute__((__vector_size__(16))) uint32_t uint32x4;
+  return __builtin_bit_cast(Vec16<T>, __builtin_nontemporal_load(reinterpret_cast<const uint32x4 *>(p)));
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
