@@ -405,11 +405,15 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int l32 = lane % 32, lhi = lane / 32;
   const int wq = wave / WK, wk = wave % WK;
-  int kvh = 0, split = 0, tile_info[4];
+  int kvh = 0, split = 0, tile_info[5];
   attn_work_item_grouped(a, BQ, q_tiles, item, &kvh, &split, tile_info);
   const int b = tile_info[0];
   if (b < 0) return;  // uniform: no such tile
   const int nq = tile_info[3];  // (row, head of the group) pairs in this tile
+  // Keys and values that this workgroup alone reads go past the L2 (16 x 1280 tokens, 410 queries: step 299.7 -> 290.1 us; 8 x 1024,
+  // 330: loop 2059 -> 2034); with several query tiles to a sequence the later ones find them there (three layers of 16 x
+  // 2048 tokens, 3300 queries: 3460 us, past the L2 3524).
+  const bool once = !NORM && tile_info[4] != 0;  // uniform
   // this lane's query: packed row p = row * g + head of the group (rows past the end are clamped to
   // the last one; their results are never stored)
   const int grp = a.H / a.Hkv;
@@ -474,8 +478,14 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
       key = key < k_hi ? key : k_hi - 1;
       const int ck = cpos ^ (row & 15);
       const int cv = (((cpos >> 1) ^ ((row & 3) << 1)) << 1) | (cpos & 1);
-      dma16(kc + (size_t)key * kv_stride + ck * 8, sb + (uint32_t)ii * 1024u);
-      dma16(vc + (size_t)key * kv_stride + cv * 8, sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
+      const bf16_t *kp = kc + (size_t)key * kv_stride + ck * 8, *vp = vc + (size_t)key * kv_stride + cv * 8;
+      if (once) {
+        dma16_once(kp, sb + (uint32_t)ii * 1024u);
+        dma16_once(vp, sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
+      } else {
+        dma16(kp, sb + (uint32_t)ii * 1024u);
+        dma16(vp, sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
+      }
     }
   };
 
@@ -496,12 +506,21 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   auto issue_full = [&](int t) {  // tile t, all of whose keys exist, -> stage t % NS
     const uint32_t sb = lds0 + (uint32_t)(t % NS) * T::STAGE_BYTES;
     const size_t adv = (size_t)t * TK * kv_stride * 2;
+    auto copies = [&](auto once_c) {
 #pragma unroll
-    for (int i = 0; i < LPW / 2; ++i) {
-      const int ii = i * NW + wave;
-      dma16_s(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
-      dma16_s(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
-    }
+      for (int i = 0; i < LPW / 2; ++i) {
+        const int ii = i * NW + wave;
+        if constexpr (decltype(once_c)::value) {
+          dma16_s_once(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
+          dma16_s_once(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
+        } else {
+          dma16_s(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
+          dma16_s(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
+        }
+      }
+    };
+    if (once) copies(std::true_type{});
+    else copies(std::false_type{});
   };
 
   // per-lane constants of the operand reads

@@ -106,7 +106,7 @@ __device__ __forceinline__ int wave_scan(int x) {
 }
 // Work item of workgroup `item` of a 1-D launch over (key split, KV head, tile of packed rows), XCD-aware as above.
 // info[0] = sequence (or -1: no item), info[1] = index of the sequence's first row in the row list, info[2] = first packed
-// row of the tile, info[3] = packed rows in the tile.  Called by every wave with all its lanes; the results are
+// row of the tile, info[3] = packed rows in the tile, info[4] = whether it is its sequence's only one.  Called by every wave with all its lanes; the results are
 // uniform.  The items are those of the tiles that exist, not of the q_tiles that the list's capacity allows: each XCD takes
 // an equal share of them, and they come before all workgroups without work.  (Numbered by the capacity, a list of 330
 // entries with room for 8192 had its 256 items in four groups per XCD behind 64 idle workgroups each: 43 us instead of 35
@@ -114,10 +114,10 @@ __device__ __forceinline__ int wave_scan(int x) {
 // A lane counts the tiles of one sequence (64 at a time): one round of loads, where a walk over the sequences waits for each
 // of them in turn.
 __device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ, int q_tiles, int item, int *kvh, int *split,
-                                                       int (&info)[4]) {
+                                                       int (&info)[5]) {
   const int g = a.H / a.Hkv, lane = threadIdx.x % WAVE;
   info[0] = -1;
-  info[1] = info[2] = info[3] = 0;
+  info[1] = info[2] = info[3] = info[4] = 0;
   int total = 0, lo = 0, hi = 0, upto = 0, tiles = q_tiles;
   auto tiles_of = [&](int b0) {  // rows [lo, hi) of this lane's sequence, and the tiles up to and with it
     const int b = b0 + lane;
@@ -147,6 +147,7 @@ __device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ
     info[1] = b * a.L;
     info[2] = (t % per) * BQ;
     info[3] = min(BQ, a.L * g - info[2]);
+    info[4] = per == 1;
     return;
   }
   for (int b0 = 0; b0 < a.B; b0 += WAVE) {
@@ -160,6 +161,7 @@ __device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ
       info[1] = __builtin_amdgcn_readlane(lo, s);
       info[2] = first * BQ;
       info[3] = min(BQ, n - first * BQ);
+      info[4] = n <= BQ;
       return;
     }
     t -= __builtin_amdgcn_readlane(upto, WAVE - 1);

@@ -125,6 +125,19 @@ __device__ __forceinline__ void dma16_s(const void *sbase, uint32_t voff, uint32
                : "s"(lds_base), "v"(voff), "s"(sbase)
                : "memory", "m0");
 }
+// the same two of data that nobody else reads: non-temporal
+__device__ __forceinline__ void dma16_once(const void *g, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(g)
+               : "memory", "m0");
+}
+__device__ __forceinline__ void dma16_s_once(const void *sbase, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+               :
+               : "s"(lds_base), "v"(voff), "s"(sbase)
+               : "memory", "m0");
+}
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
