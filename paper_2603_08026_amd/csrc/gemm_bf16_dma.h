@@ -812,7 +812,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
 #pragma unroll
       for (int t = 0; t < NMAT; ++t)
 #pragma unroll
-        for (int i = 0; i < SH::B_LD; ++i) dma16(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
+        for (int i = 0; i < SH::B_LD; ++i) {
+          if constexpr (SH::PIPE) dma16_once(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
+          else dma16(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
+        }
     };
 
     __syncthreads();  // LDS free: the previous tile of this workgroup is fully consumed
