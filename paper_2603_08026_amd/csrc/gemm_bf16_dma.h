@@ -713,9 +713,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     // from one path to another (the first tile of a path fills the ring anew: only a last row tile changes the path).
     // Where the paths shared a loop, the sources of the copies, and where they met before the epilogue the
     // accumulators, went through other registers and scratch memory at the end of every tile.
-    auto run_tiles_of = [&](auto mi_c) -> bool {
+    auto run_tiles_of = [&](auto mi_c, auto once_c) -> bool {
       constexpr int MI = decltype(mi_c)::value;
-      using R = Ring<NMAT, NB, BN, WR, MI>;
+      using R = Ring<NMAT, NB, BN, WR, MI, decltype(once_c)::value>;
       uint32_t lds_at = lds0;
       asm volatile("" : "+s"(lds_at));  // (what follows from it is computed here, not once for all paths and kept)
       RingSrc src;
@@ -742,7 +742,22 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
       }
     };
     bool more = find();
-    while (more) more = with_blocks<MAX_MI>(blocks_of(tm), run_tiles_of);
+    // One row tile of more than half the height, which is what 129 to 256 rows in one come to: the weights go past the L2, where they
+    // would displace the activations that all workgroups share.  With more row tiles they are found there.  (hidden 4096,
+    // 143 rows: step 184.5 -> 169.8 us; with 573 rows, past the L2 as well, 340 -> 362.)
+    constexpr auto each = std::false_type{};
+    if (tiles_m == 1 && blocks_of(0) > MAX_MI / 2) {
+      const int mi = blocks_of(0);
+      auto once = [&](auto mi_c) -> bool { return run_tiles_of(mi_c, std::true_type{}); };
+      if constexpr (MAX_MI > 4) {
+        while (more) more = mi == 8 ? once(std::integral_constant<int, 8>{}) : mi == 7 ? once(std::integral_constant<int, 7>{})
+                            : mi == 6 ? once(std::integral_constant<int, 6>{}) : once(std::integral_constant<int, 5>{});
+      } else {
+        while (more) more = mi == 4 ? once(std::integral_constant<int, 4>{}) : once(std::integral_constant<int, 3>{});
+      }
+      return;
+    }
+    while (more) more = with_blocks<MAX_MI>(blocks_of(tm), [&](auto mi_c) -> bool { return run_tiles_of(mi_c, each); });
     return;
   }
 

@@ -31,9 +31,11 @@ namespace mm {
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // lane i's 16 bytes at (descriptor base + voff + soff) -> LDS[lds_addr + 16 i]; lds_addr and soff
-// are wave-uniform.  Completion is tracked by vmcnt, in issue order.
+// are wave-uniform.  Completion is tracked by vmcnt, in issue order.  ONCE: of data that nobody else reads: non-temporal (bit 1 of
+// the cache policy).
+template <bool ONCE = false>
 __device__ __forceinline__ void dma16_buf(__amdgpu_buffer_rsrc_t srd, uint32_t voff, uint32_t soff, uint32_t lds_addr) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(srd, (lds_void_t *)(uintptr_t)lds_addr, 16, voff, soff, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(srd, (lds_void_t *)(uintptr_t)lds_addr, 16, voff, soff, 0, ONCE ? 2 : 0);
 }
 
 // descriptor of a raw byte buffer (no stride, no swizzle, 32-bit data format) that covers `bytes`
@@ -97,7 +99,8 @@ struct RingSrc {
 // weight rows); wave grid 4 x 1: six groups, all 192 weight rows of the tile.  The halves of a slice fill as much of
 // their slots as they need.
 
-template <int NMAT, int NB, int BN, int WR, int MI> struct Ring {
+// ONCE: the matrix has one row tile, so that every weight is read by one workgroup once (gemm_bf16_dma.h).
+template <int NMAT, int NB, int BN, int WR, int MI, bool ONCE = false> struct Ring {
   static constexpr int NCB = NMAT * NB;  // column groups per wave
   static constexpr int NC = 2 * NCB;     // 16-column blocks per wave
   static constexpr int AC = WR * MI / 2;        // activation copies per wave and slice (32 tile rows each)
@@ -121,7 +124,7 @@ template <int NMAT, int NB, int BN, int WR, int MI> struct Ring {
   static constexpr int ND = G == 4 ? NWC / 2 : NWC;  // descriptors
   static_assert(ND <= RING_MAX_WSRC, "descriptors of the weight copies");
   static __device__ __forceinline__ void copy_w(const RingSrc &src, int c, uint32_t kt, uint32_t lds_addr) {
-    dma16_buf(src.srd_w[c * ND / NWC], src.vw, kt * W_STEP + (G == 4 && c % 2 ? 2 * ROW : 0), lds_addr);
+    dma16_buf<ONCE>(src.srd_w[c * ND / NWC], src.vw, kt * W_STEP + (G == 4 && c % 2 ? 2 * ROW : 0), lds_addr);
   }
 
   static __device__ __forceinline__ int w_row(int c) { return (((c / 2) / NB) * BN + ((c / 2) % NB) * 32 + (c % 2) * 16) * ROW; }
