@@ -867,8 +867,9 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   // merge the WK wave columns of each query block through LDS
   float *mg = reinterpret_cast<float *>(smem_raw);
   constexpr int PER_WAVE = T::PER_WAVE;
+  static_assert(WK <= 2, "one other wave column");
   if (WK > 1 && wk > 0) {
-    float *dst = mg + (size_t)((wk - 1) * WQ + wq) * PER_WAVE + lane;
+    float *dst = mg + (size_t)wq * PER_WAVE + lane;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -879,28 +880,18 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   if (WK > 1) __syncthreads();
   if (wk != 0) return;
   if (WK > 1) {
-    float M = m_run;
-#pragma unroll
-    for (int w = 1; w < WK; ++w) M = fmaxf(M, mg[(size_t)((w - 1) * WQ + wq) * PER_WAVE + (DB * 16) * 64 + lane]);
+    // (the multiply-adds are written out: left to the compiler, either product may be the rounded one, and kernels that inline
+    // this function differ in the last place)
+    const float *src = mg + (size_t)wq * PER_WAVE + lane;
+    const float M = fmaxf(m_run, src[(DB * 16) * 64]);
     const float Ms = (M == -INFINITY) ? 0.f : M;
-    const float c0 = __builtin_amdgcn_exp2f(m_run - Ms);
-    float lsum = l_run * c0;
+    const float c0 = __builtin_amdgcn_exp2f(m_run - Ms), c1 = __builtin_amdgcn_exp2f(src[(DB * 16) * 64] - Ms);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc_o[db][e] *= c0;
-#pragma unroll
-    for (int w = 1; w < WK; ++w) {
-      const float *src = mg + (size_t)((w - 1) * WQ + wq) * PER_WAVE + lane;
-      const float cw = __builtin_amdgcn_exp2f(src[(DB * 16) * 64] - Ms);
-      lsum += src[(DB * 16 + 1) * 64] * cw;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc_o[db][e] += src[(db * 16 + e) * 64] * cw;
-    }
+      for (int e = 0; e < 16; ++e) acc_o[db][e] = fmaf(src[(db * 16 + e) * 64], c1, acc_o[db][e] * c0);
+    l_run = fmaf(l_run, c0, src[(DB * 16 + 1) * 64] * c1);
     m_run = M;
-    l_run = lsum;
   }
 
   const int r = wq * 32 + l32;

@@ -38,3 +38,46 @@ def test_f32_attention(dh, L, counts, spare):
     print("f32 attention", dh, L, counts, spare, flush=True)
     s = W.LayerShape(hidden=128, n_heads=4, n_kv_heads=2, head_dim=dh, ffn=192, dtype="f32")
     _partial(s, len(counts), L, counts, 1e-5, len(counts) * L if spare else sum(counts))
+
+
+# bf16, 64-row tiles: two wave columns share the keys of a tile of 64 and their sums are merged as fma(other, c1, own * c0), the
+# first column's product rounded.  Scores are equal within a column, so that every weight is 1 and the columns' sums are whole
+# numbers A and -S; c1 is 1 and S the whole part of A c0, so that what is left is what the rounding of A c0 decides: in units
+# of the row sum, fl(A c0) - S against fl(A c0 - S) differ by up to 1/16.  c0 = 2^d is taken from the neighbours of the
+# rounded power (the hardware's has an error of one unit).
+def test_merge_of_wave_columns_rounds_the_first_product():
+    s = W.LayerShape(hidden=128, n_heads=1, n_kv_heads=1, head_dim=128, ffn=128, dtype="bf16")
+    f32 = np.float32
+    sc = np.uint32(0x3e0293ee).view(f32)  # log2(e) / sqrt(128)
+    q0, k0, k1 = 8.0, -2.0, 1.5
+    d = f32(f32(q0 * k0) * sc) - f32(f32(q0 * k1) * sc)
+    c0s = [np.exp2(np.float64(d)).astype(f32)]
+    c0s = [np.nextafter(c0s[0], f32(0)), c0s[0], np.nextafter(c0s[0], f32(1))]
+    rng = np.random.Generator(np.random.Philox(5))
+    parts = np.concatenate([rng.integers(128, 256, (1, 128)), rng.integers(0, 256, (2, 128))])
+    unit = np.array([[65536.0], [256.0], [1.0]])
+    A = (parts * unit).sum(0)
+    S = np.floor(A * np.float64(c0s[1]))
+    s_parts = np.stack([S // 65536, S // 256 % 256, S % 256])
+    v = np.zeros((64, 128))
+    v[0:3] = parts * unit
+    v[32:35] = -s_parts * unit
+    k, q = np.zeros((64, 128)), np.zeros((1, 128))
+    k[:32, 0], k[32:, 0], q[0, 0] = k0, k1, q0
+    lay = Layer.from_shape(s, 1, 64)
+    rows = lay.make_list(np.array([5], np.int32), np.array([0, 1], np.int32))
+    out = torch.zeros(1, 128, dtype=torch.bfloat16, device="cuda")
+    dev = [torch.tensor(a, dtype=torch.bfloat16, device="cuda") for a in (q, k, v)]
+    for a, t in zip((q, k, v), dev):
+        assert (t.double().cpu().numpy() == a).all()
+    lay.ctx.partial_attention(dev[0], dev[1], dev[2], rows, 1, 64, out)
+    got = out.double().cpu().numpy()[0]
+    lay.close()
+
+    def miss(c0):  # (largest error, columns that tell the two roundings apart)
+        two = (A * np.float64(c0)).astype(f32).astype(np.float64) - S
+        one = (A * np.float64(c0) - S).astype(f32).astype(np.float64)
+        err = np.abs(got * (32.0 * np.float64(c0) + 32.0) - two)
+        return err.max(), int((np.abs(two - one) > 0.03).sum())
+    err, telling = min(miss(c) for c in c0s)
+    assert telling >= 20 and err < 0.01, (err, telling)  # (bf16 rounds results of at most 2 by 2^-8)
