@@ -394,8 +394,9 @@ template <int WQ, int WK_> struct DTile {
 // the sequence (norm_k).  After the loop over the candidates a second one sweeps all keys for the sum alone: no V copies
 // and reads, half the products.  8 x 1024 tokens, 32 heads, 330 candidates, against all keys meeting the zero-padded
 // residual: whole sequences and response windows on average 74 -> 63 us a pass (one tile a step of the sweep: 68).
-template <int WQ, int WK_, bool NORM>
-__device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int item) {
+// ONCE: keys and values are copied past the L2 (Once).
+template <int WQ, int WK_, bool NORM, bool ONCE>
+__device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item) {
   using T = DTile<WQ, WK_>;
   constexpr int DH = T::DH, NW = T::NW, WK = T::WK, BQ = T::BQ, TK = T::TK, ROWB = T::ROWB, NS = T::NS,
                 DB = T::DB, KK = T::KK, LPW = T::LPW;
@@ -405,15 +406,9 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int l32 = lane % 32, lhi = lane / 32;
   const int wq = wave / WK, wk = wave % WK;
-  int kvh = 0, split = 0, tile_info[5];
-  attn_work_item_grouped(a, BQ, q_tiles, item, &kvh, &split, tile_info);
-  const int b = tile_info[0];
+  const int b = item.seq, kvh = item.kv_head, split = item.split;
   if (b < 0) return;  // uniform: no such tile
-  const int nq = tile_info[3];  // (row, head of the group) pairs in this tile
-  // Keys and values that this workgroup alone reads go past the L2 (16 x 1280 tokens, 410 queries: step 299.7 -> 290.1 us; 8 x 1024,
-  // 330: loop 2059 -> 2034); with several query tiles to a sequence the later ones find them there (three layers of 16 x
-  // 2048 tokens, 3300 queries: 3460 us, past the L2 3524).
-  const bool once = !NORM && tile_info[4] != 0;  // uniform
+  const int nq = item.n;  // (row, head of the group) pairs in this tile
   // this lane's query: packed row p = row * g + head of the group (rows past the end are clamped to
   // the last one; their results are never stored)
   const int grp = a.H / a.Hkv;
@@ -421,8 +416,8 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   {
     int r = wq * 32 + l32;
     r = r < nq ? r : nq - 1;
-    const int p = tile_info[2] + r;
-    jq = tile_info[1] + p / grp;
+    const int p = item.packed + r;
+    jq = item.row + p / grp;
     hq = kvh * grp + p % grp;
   }
   int kbase = b * a.L, Lk = a.L, k_chunk = a.chunk;
@@ -479,7 +474,7 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
       const int ck = cpos ^ (row & 15);
       const int cv = (((cpos >> 1) ^ ((row & 3) << 1)) << 1) | (cpos & 1);
       const bf16_t *kp = kc + (size_t)key * kv_stride + ck * 8, *vp = vc + (size_t)key * kv_stride + cv * 8;
-      if (once) {
+      if constexpr (ONCE) {
         dma16_once(kp, sb + (uint32_t)ii * 1024u);
         dma16_once(vp, sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
       } else {
@@ -506,21 +501,17 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   auto issue_full = [&](int t) {  // tile t, all of whose keys exist, -> stage t % NS
     const uint32_t sb = lds0 + (uint32_t)(t % NS) * T::STAGE_BYTES;
     const size_t adv = (size_t)t * TK * kv_stride * 2;
-    auto copies = [&](auto once_c) {
 #pragma unroll
-      for (int i = 0; i < LPW / 2; ++i) {
-        const int ii = i * NW + wave;
-        if constexpr (decltype(once_c)::value) {
-          dma16_s_once(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
-          dma16_s_once(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
-        } else {
-          dma16_s(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
-          dma16_s(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
-        }
+    for (int i = 0; i < LPW / 2; ++i) {
+      const int ii = i * NW + wave;
+      if constexpr (ONCE) {
+        dma16_s_once(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
+        dma16_s_once(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
+      } else {
+        dma16_s(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
+        dma16_s(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
       }
-    };
-    if (once) copies(std::true_type{});
-    else copies(std::false_type{});
+    }
   };
 
   // per-lane constants of the operand reads
@@ -970,20 +961,37 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, int q_tiles, int ite
   }
 }
 
+// Which keys and values are copied past the L2: those of a sequence's only query tile, since no other workgroup reads them again and
+// they would displace what others read (16 x 1280 tokens, 410 queries: step 299.7 -> 290.1 us; 8 x 1024, 330: attention 34.7 ->
+// 29.9 us); with several query tiles to a sequence the later ones find them in the L2 (three layers of 16 x 2048 tokens,
+// 3300 queries: 3460 us, past the L2 3524).  The form is chosen outside the loops: with a branch at every tile's copies all launches
+// lost, us: 20480 rows dense 489 -> 503, 4 x 900 dense (28 over 4 heads) 71.2 -> 73.9, 360 listed rows of these 20.0 -> 21.0.
+//   BY_TILE  128-row tiles of a list, whose lengths the device knows: both forms in one kernel
+//   ALL      64-row tiles (2 x 2 waves, whose registers two forms exceed) of a list with room for one tile a sequence
+enum class Once { NONE, ALL, BY_TILE };
+
 // (two waves per SIMD: 256 registers, no AGPR shuffling)
-template <int WQ, int WK_, bool NORM>
+template <int WQ, int WK_, bool NORM, Once ONCE>
 __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, int q_tiles) {
-  attn_dma<WQ, WK_, NORM>(a, q_tiles, blockIdx.x);
+  const AttnItem item = attn_work_item_grouped(a, DTile<WQ, WK_>::BQ, q_tiles, blockIdx.x);
+  if constexpr (ONCE == Once::BY_TILE) {
+    if (item.only) attn_dma<WQ, WK_, NORM, true>(a, item);  // uniform
+    else attn_dma<WQ, WK_, NORM, false>(a, item);
+  } else {
+    attn_dma<WQ, WK_, NORM, ONCE == Once::ALL>(a, item);
+  }
 }
 
 // The context update of Alg. 4 (b, the first `grid_b` workgroups) and exact rows (a), which need nothing of each other, in one launch: a
 // few hundred exact rows are 256 items that wait for their keys on half of the chip's places, and the update's last round
 // leaves places idle as well.  8 x 1024 tokens, 32 heads, 330 exact rows, us: update of a window of 2048 tokens 39 + exact rows 35 ->
-// 68, of all tokens 130 + 40 -> 143; a loop of such steps 3520 -> 3440.
+// 68, of all tokens 130 + 40 -> 143; a loop of such steps 3520 -> 3440.  The exact rows read through the L2, where the update sweeps
+// the same keys (past it the same within 0.6 %).
 template <int WQ, int WK_>
 __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_both(AttnArgs a, int tiles_a, AttnArgs b, int tiles_b, int grid_b) {
-  if ((int)blockIdx.x < grid_b) attn_dma<WQ, WK_, true>(b, tiles_b, blockIdx.x);
-  else attn_dma<WQ, WK_, false>(a, tiles_a, blockIdx.x - grid_b);
+  constexpr int BQ = DTile<WQ, WK_>::BQ;
+  if ((int)blockIdx.x < grid_b) attn_dma<WQ, WK_, true, false>(b, attn_work_item_grouped(b, BQ, tiles_b, blockIdx.x));
+  else attn_dma<WQ, WK_, false, false>(a, attn_work_item_grouped(a, BQ, tiles_a, blockIdx.x - grid_b));
 }
 
 template <int WQ, int WK> void launch_both(const AttnArgs &a, const AttnArgs &b, hipStream_t s) {
@@ -999,16 +1007,16 @@ template <int WQ, int WK> void launch_both(const AttnArgs &a, const AttnArgs &b,
   k_attn_bf16_both<WQ, WK><<<grid_b + attn_grid_grouped(a, tiles_a), T::NT, T::LDS_BYTES, s>>>(a, tiles_a, b, tiles_b, grid_b);
 }
 
-template <int WQ, int WK, bool NORM> void launch_dma(const AttnArgs &a, hipStream_t s) {
+template <int WQ, int WK, bool NORM, Once ONCE> void launch_dma(const AttnArgs &a, hipStream_t s) {
   using T = DTile<WQ, WK>;
   static bool done = false;
   if (!done) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16_dma<WQ, WK, NORM>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16_dma<WQ, WK, NORM, ONCE>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS_BYTES);
     done = true;
   }
   const int q_tiles = max_q_tiles_grouped(a, T::BQ);
-  k_attn_bf16_dma<WQ, WK, NORM><<<attn_grid_grouped(a, q_tiles), T::NT, T::LDS_BYTES, s>>>(a, q_tiles);
+  k_attn_bf16_dma<WQ, WK, NORM, ONCE><<<attn_grid_grouped(a, q_tiles), T::NT, T::LDS_BYTES, s>>>(a, q_tiles);
 }
 
 template <int DH, int WQ, int NW, int QB> void launch_cfg(const AttnArgs &a, hipStream_t s) {
@@ -1038,9 +1046,13 @@ void launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
     // 128 query rows: four waves, each with all keys of a 32-key tile (64 KB of LDS: two workgroups
     // per CU, which drift apart and fill each other's stalls); 64 rows: 2 x 2 waves over 64-key tiles
     if (a.norm_k) {
-      if (wide) launch_dma<4, 1, true>(a, s); else launch_dma<2, 2, true>(a, s);
+      if (wide) launch_dma<4, 1, true, Once::NONE>(a, s); else launch_dma<2, 2, true, Once::NONE>(a, s);
+    } else if (wide) {
+      if (a.offsets) launch_dma<4, 1, false, Once::BY_TILE>(a, s); else launch_dma<4, 1, false, Once::NONE>(a, s);
+    } else if ((long)a.rows.cap * (a.H / a.Hkv) <= (long)a.B * a.bq) {
+      launch_dma<2, 2, false, Once::ALL>(a, s);
     } else {
-      if (wide) launch_dma<4, 1, false>(a, s); else launch_dma<2, 2, false>(a, s);
+      launch_dma<2, 2, false, Once::NONE>(a, s);
     }
   } else {
     if (wide) launch_cfg<64, 2, 4, 2>(a, s); else launch_cfg<64, 1, 4, 2>(a, s);

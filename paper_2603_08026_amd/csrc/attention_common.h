@@ -104,20 +104,19 @@ __device__ __forceinline__ int wave_scan(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // last lane of row 1 -> rows 2 and 3
   return x;
 }
-// Work item of workgroup `item` of a 1-D launch over (key split, KV head, tile of packed rows), XCD-aware as above.
-// info[0] = sequence (or -1: no item), info[1] = index of the sequence's first row in the row list, info[2] = first packed
-// row of the tile, info[3] = packed rows in the tile, info[4] = whether it is its sequence's only one.  Called by every wave with all its lanes; the results are
-// uniform.  The items are those of the tiles that exist, not of the q_tiles that the list's capacity allows: each XCD takes
+// Work item of a workgroup: sequence (or -1: no item), index of its first row in the row list, first packed row of the tile,
+// packed rows in it, whether the tile is its sequence's only one.
+struct AttnItem { int seq = -1, row = 0, packed = 0, n = 0, only = 0, kv_head = 0, split = 0; };
+// The item of workgroup p of a 1-D launch over (key split, KV head, tile of packed rows), XCD-aware as above.  Called by every wave with
+// all its lanes; the results are uniform.  The items are those of the tiles that exist, not of the q_tiles that the list's capacity allows: each XCD takes
 // an equal share of them, and they come before all workgroups without work.  (Numbered by the capacity, a list of 330
 // entries with room for 8192 had its 256 items in four groups per XCD behind 64 idle workgroups each: 43 us instead of 35
 // for 8 sequences of 1024 tokens, 32 heads.)
 // A lane counts the tiles of one sequence (64 at a time): one round of loads, where a walk over the sequences waits for each
 // of them in turn.
-__device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ, int q_tiles, int item, int *kvh, int *split,
-                                                       int (&info)[5]) {
+__device__ __forceinline__ AttnItem attn_work_item_grouped(const AttnArgs &a, int BQ, int q_tiles, int p) {
   const int g = a.H / a.Hkv, lane = threadIdx.x % WAVE;
-  info[0] = -1;
-  info[1] = info[2] = info[3] = info[4] = 0;
+  AttnItem it;
   int total = 0, lo = 0, hi = 0, upto = 0, tiles = q_tiles;
   auto tiles_of = [&](int b0) {  // rows [lo, hi) of this lane's sequence, and the tiles up to and with it
     const int b = b0 + lane;
@@ -135,20 +134,20 @@ __device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ
     for (int b0 = 0; b0 < a.B; b0 += WAVE) tiles += tiles_of(b0);
   }
   const int items = tiles * a.Hkv * a.splits, per_xcd = (items + ATTN_XCD - 1) / ATTN_XCD;
-  const int p = item, w = (p % ATTN_XCD) * per_xcd + p / ATTN_XCD;
-  if (p / ATTN_XCD >= per_xcd || w >= items) return;
+  const int w = (p % ATTN_XCD) * per_xcd + p / ATTN_XCD;
+  if (p / ATTN_XCD >= per_xcd || w >= items) return it;
   int t = w % tiles;
   const int rest = w / tiles;
-  *kvh = rest % a.Hkv;
-  *split = rest / a.Hkv;
+  it.kv_head = rest % a.Hkv;
+  it.split = rest / a.Hkv;
   if (!a.offsets) {
     const int per = (a.L * g + BQ - 1) / BQ, b = t / per;
-    info[0] = b;
-    info[1] = b * a.L;
-    info[2] = (t % per) * BQ;
-    info[3] = min(BQ, a.L * g - info[2]);
-    info[4] = per == 1;
-    return;
+    it.seq = b;
+    it.row = b * a.L;
+    it.packed = (t % per) * BQ;
+    it.n = min(BQ, a.L * g - it.packed);
+    it.only = per == 1;
+    return it;
   }
   for (int b0 = 0; b0 < a.B; b0 += WAVE) {
     if (a.B > WAVE) tiles_of(b0);  // (else still in the registers)
@@ -157,15 +156,16 @@ __device__ __forceinline__ void attn_work_item_grouped(const AttnArgs &a, int BQ
       const int s = __ffsll((unsigned long long)past) - 1;
       const int n = __builtin_amdgcn_readlane((hi - lo) * g, s);
       const int first = t - (__builtin_amdgcn_readlane(upto, s) - (n + BQ - 1) / BQ);
-      info[0] = b0 + s;
-      info[1] = __builtin_amdgcn_readlane(lo, s);
-      info[2] = first * BQ;
-      info[3] = min(BQ, n - first * BQ);
-      info[4] = n <= BQ;
-      return;
+      it.seq = b0 + s;
+      it.row = __builtin_amdgcn_readlane(lo, s);
+      it.packed = first * BQ;
+      it.n = min(BQ, n - first * BQ);
+      it.only = n <= BQ;
+      return it;
     }
     t -= __builtin_amdgcn_readlane(upto, WAVE - 1);
   }
+  return it;
 }
 
 void launch_attention_f32(const AttnArgs &a, hipStream_t s);

@@ -125,7 +125,7 @@ __device__ __forceinline__ void dma16_s(const void *sbase, uint32_t voff, uint32
                : "s"(lds_base), "v"(voff), "s"(sbase)
                : "memory", "m0");
 }
-// the same two of data that nobody else reads: non-temporal
+// the same two of data that is not read again soon enough to be found in the L2: non-temporal
 __device__ __forceinline__ void dma16_once(const void *g, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
                :

@@ -81,3 +81,31 @@ def test_merge_of_wave_columns_rounds_the_first_product():
         return err.max(), int((np.abs(two - one) > 0.03).sum())
     err, telling = min(miss(c) for c in c0s)
     assert telling >= 20 and err < 0.01, (err, telling)  # (bf16 rounds results of at most 2 by 2^-8)
+
+
+# bf16, head_dim 128: which keys are copied past the L2 is decided by the list's room (64-row tiles) or by each sequence's rows
+# (128-row tiles).  Sequences of no, one, one full and several query tiles; key counts that leave stages and tiles of
+# the pipeline partly filled.
+@pytest.mark.parametrize("heads,kv", [(4, 4), (8, 2), (64, 32)])
+@pytest.mark.parametrize("L,counts", [(70, [0, 1, 70]), (300, [16, 64, 65]), (600, [128, 0, 300])])
+def test_copies_past_the_l2(heads, kv, L, counts):
+    print("attention past the L2", heads, kv, L, counts, flush=True)
+    s = W.LayerShape(hidden=128, n_heads=heads, n_kv_heads=kv, head_dim=128, ffn=128, dtype="bf16")
+    B = len(counts)
+    g = torch.Generator().manual_seed(L + heads)
+    k, v = (torch.randn(B, L, kv * 128, generator=g).bfloat16().cuda() for _ in range(2))
+    full = torch.randn(B * L, s.dq, generator=g).bfloat16().cuda()  # a query for every token
+    idx, off = rand_rows(73, B, L, counts)
+    lay = Layer.from_shape(s, B, L)
+    outs = []
+    for cap in (idx.size, B * L):
+        rows = lay.make_list(idx, off, cap=cap)
+        q, out = torch.zeros(cap, s.dq, dtype=torch.bfloat16, device="cuda"), torch.zeros(cap, s.dq, dtype=torch.bfloat16, device="cuda")
+        q[:idx.size] = full[torch.from_numpy(idx).long().cuda()]
+        lay.ctx.partial_attention(q, k, v, rows, B, L, out)
+        outs.append(out[:idx.size].float().cpu().numpy())
+    lay.close()
+    # (lists of other room may have other tiles and key splits: sums in another order, each rounded to 8 bits once)
+    for got in outs:
+        ref = O.partial_attention(to_host(full).reshape(B * L, heads, 128)[idx], to_host(k).reshape(B, L, kv, 128), to_host(v).reshape(B, L, kv, 128), idx, B, L)
+        assert_close(got, ref.reshape(idx.size, -1), 2e-2, "context rows")
