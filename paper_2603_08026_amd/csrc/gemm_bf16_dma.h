@@ -742,22 +742,24 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
       }
     };
     bool more = find();
-    // One row tile of more than half the height, which is what 129 to 256 rows in one come to: the weights go past the L2, where they
-    // would displace the activations that all workgroups share.  With more row tiles they are found there.  (hidden 4096,
-    // 143 rows: step 184.5 -> 169.8 us; with 573 rows, past the L2 as well, 340 -> 362.)
-    constexpr auto each = std::false_type{};
-    if (tiles_m == 1 && blocks_of(0) > MAX_MI / 2) {
-      const int mi = blocks_of(0);
-      auto once = [&](auto mi_c) -> bool { return run_tiles_of(mi_c, std::true_type{}); };
-      if constexpr (MAX_MI > 4) {
+    // All rows in one row tile of more than half the height, which is what 129 to 256 rows in one come to: the weights go past the L2,
+    // where they would displace the activations that all workgroups share.  With more row tiles they are found there.  (hidden
+    // 4096, 143 rows: step 184.5 -> 169.8 us; with 573 rows, past the L2 as well, 340 -> 362.)
+    // The loops exist for the shapes that plans take for so few rows: 128 columns, K split where it may be, and 256 for gate|up (no
+    // other for eight layer shapes of hidden 512 to 8192).  In the others they made the kernels longer for all rows: 330 rows, down
+    // projection 35.9 -> 36.6 us; a loop of 8 x 1024 tokens 2013 -> 2035.
+    constexpr bool ONCE_LOOPS = BN * NMAT == 128 ? (NMAT == 2 || SPLIT) : BN * NMAT == 256 && NMAT == 2;
+    if constexpr (ONCE_LOOPS) {
+      static_assert(MAX_MI == 8, "row blocks of these shapes");
+      if (M_all <= bm && blocks_of(0) > MAX_MI / 2) {
+        const int mi = blocks_of(0);
+        auto once = [&](auto mi_c) -> bool { return run_tiles_of(mi_c, std::true_type{}); };
         while (more) more = mi == 8 ? once(std::integral_constant<int, 8>{}) : mi == 7 ? once(std::integral_constant<int, 7>{})
                             : mi == 6 ? once(std::integral_constant<int, 6>{}) : once(std::integral_constant<int, 5>{});
-      } else {
-        while (more) more = mi == 4 ? once(std::integral_constant<int, 4>{}) : once(std::integral_constant<int, 3>{});
+        return;
       }
-      return;
     }
-    while (more) more = with_blocks<MAX_MI>(blocks_of(tm), [&](auto mi_c) -> bool { return run_tiles_of(mi_c, each); });
+    while (more) more = with_blocks<MAX_MI>(blocks_of(tm), [&](auto mi_c) -> bool { return run_tiles_of(mi_c, std::false_type{}); });
     return;
   }
 
@@ -828,6 +830,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
       for (int t = 0; t < NMAT; ++t)
 #pragma unroll
         for (int i = 0; i < SH::B_LD; ++i) {
+          // (every weight is read by one workgroup; the row tiles that read them too where only a last row tile streams are long
+          // done: dense 1300 rows of hidden 4096 589 -> 581 us, lists of as many equal)
           if constexpr (SH::PIPE) dma16_once(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
           else dma16(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
         }

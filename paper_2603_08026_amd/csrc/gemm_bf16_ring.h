@@ -31,7 +31,7 @@ namespace mm {
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // lane i's 16 bytes at (descriptor base + voff + soff) -> LDS[lds_addr + 16 i]; lds_addr and soff
-// are wave-uniform.  Completion is tracked by vmcnt, in issue order.  ONCE: of data that nobody else reads: non-temporal (bit 1 of
+// are wave-uniform.  Completion is tracked by vmcnt, in issue order.  ONCE: of data that is read once: non-temporal (bit 1 of
 // the cache policy).
 template <bool ONCE = false>
 __device__ __forceinline__ void dma16_buf(__amdgpu_buffer_rsrc_t srd, uint32_t voff, uint32_t soff, uint32_t lds_addr) {
@@ -99,7 +99,7 @@ struct RingSrc {
 // weight rows); wave grid 4 x 1: six groups, all 192 weight rows of the tile.  The halves of a slice fill as much of
 // their slots as they need.
 
-// ONCE: the matrix has one row tile, so that every weight is read by one workgroup once (gemm_bf16_dma.h).
+// ONCE: all rows are in one row tile, so that every weight is read by one workgroup once (gemm_bf16_dma.h).
 template <int NMAT, int NB, int BN, int WR, int MI, bool ONCE = false> struct Ring {
   static constexpr int NCB = NMAT * NB;  // column groups per wave
   static constexpr int NC = 2 * NCB;     // 16-column blocks per wave

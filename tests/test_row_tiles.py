@@ -137,3 +137,57 @@ def test_dense_step_of_as_many_rows(case):
         err = float((a - b.float()).abs().max() / a.abs().max())
         assert err <= TOL["bf16"], (name, err)
     lay.close()
+
+
+# Rows that all lie in one row tile of more than half the height: weights copied past the L2, in loops that exist for some of the
+# tiles' shapes only.
+ONE_TILE = {"wide": (WIDE, [143, 161, 224, 245]), "grouped": (W.DREAM, [129, 192, 200, 256])}
+
+
+def _one_tile_plans(lib, s, count):
+    """{GEMM: (columns, K splits, rows of a tile)} of the GEMMs that have `count` rows in one such tile"""
+    part = 16 * 2048 * s.dq
+    plans = {}
+    for name, (kind, n, k) in {"qkv": (0, s.dq + 2 * s.dkv, s.hidden), "oproj": (0, s.hidden, s.dq), "gate_up": (1, s.ffn, s.hidden),
+                               "down": (2, s.hidden, s.ffn)}.items():
+        out = (C.c_int * 4)()
+        lib.plan(kind, n, k, C.c_long(part), count, out)
+        if count <= out[2] and -(-count // (64 if out[0] == 192 else 32)) > (2 if out[0] == 192 else 4):
+            plans[name] = tuple(out[:3])
+    return plans
+
+
+def test_few_rows_take_the_shapes_that_have_loops_for_them(tmp_path):
+    src, so = str(tmp_path / "plan.cpp"), str(tmp_path / "plan.so")
+    with open(src, "w") as f:
+        f.write(SOURCE % build.CSRC)
+    r = subprocess.run([build.HIPCC, "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-shared",
+                        "-fPIC", src, "-o", so], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    lib = C.CDLL(so)
+    for dims in ((4096, 32, 32, 12288), (3584, 28, 4, 18944), (512, 4, 1, 1536), (1024, 8, 8, 3072), (2048, 16, 4, 5632),
+                 (5120, 40, 8, 25600), (8192, 64, 8, 28672), (4096, 32, 8, 14336)):
+        s = W.LayerShape(hidden=dims[0], n_heads=dims[1], n_kv_heads=dims[2], head_dim=128, ffn=dims[3], dtype="bf16")
+        for count in range(1, 513):
+            for name, (cols, splits, _) in _one_tile_plans(lib, s, count).items():
+                assert cols == 128 and (splits > 1 or name != "down") or (cols, name) == (256, "gate_up"), (dims, count, name)
+    # the counts of the test below run every such loop
+    seen = {(name, p[0], p[2]) for s, counts in ONE_TILE.values() for n in counts for name, p in _one_tile_plans(lib, s, n).items()}
+    assert {(name, cols, h) for name, cols in (("qkv", 128), ("gate_up", 128), ("gate_up", 256), ("down", 128)) for h in (160, 192, 224, 256)} <= seen
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", sorted(ONE_TILE))
+def test_layer_of_rows_in_one_tile(case):
+    from paper_2603_08026_amd.layer import Layer
+    from tests.helpers import rand_weights
+    from tests.test_gpu_planned_gemm import _check
+    shape, counts = ONE_TILE[case]
+    lay = Layer.from_shape(shape, 1, 600)
+    w = rand_weights(shape, 60, bias=True)
+    lay.set_weights(w)
+    for count in counts:
+        for cap in (count, 600) if count == counts[0] else (count,):
+            print("rows in one tile", case, count, cap, flush=True)
+            _check(lay, w, shape, 1, 600, count, cap)
+    lay.close()
