@@ -31,8 +31,9 @@ constexpr int PLAN_L = 0, PLAN_X = 1, PLAN_W = 2;  // GemmPlan::xl
 //   w_cols             weight rows per output column (2 for gate|up)
 //   stream_cols        columns of the weight-streaming tiles; 0: not to be used
 //   split_ok           K splits (and a streamed tail that is split) may be used: a row kernel sums them
-//   split_free         a raw result is written and read back whatever the split (q|k|v, out-projection);
-//                      otherwise a split or a streamed tail costs a sum kernel
+//   split_free         a row kernel follows whatever the split (q|k|v, out-projection); otherwise a split or a streamed
+//                      tail costs a sum kernel.  The prices charge an unsplit result's way through memory, also where
+//                      q|k|v rows leave the GEMM finished (their fit and takes_over's shares are older than that)
 //   part_elems         fp32 elements of the buffer of raw results
 //   cus, inv_cus       CUs of an XCD
 //   stream_us          price of a streamed last row tile
@@ -295,6 +296,18 @@ inline bool down_has_sums(const PlanArgs &a, int cap, bool known) {
   const GemmPlan full = plan_of(a, cap, first_on_host(a, cap));
   return full.sk > 1 || full.row_hi < cap || (!known && (cap > SUM_CAP || loop_us(a.K) >= SUM_LOOP_US));
 }
+
+// Two kernels make raw results in row tiles: one that can finish q|k|v rows where K is not split, and one that knows nothing else and is
+// a third as long.  Few rows pay for a long kernel with instructions that the caches no longer hold, so the first is taken only where
+// it has rows to finish: where the plan of a full list (full) does not split K, and unless the list is a carried one.
+//   - known rows whose K is split, us with the short kernel / the long one: response windows of 768 and 1024 rows in a loop of hidden
+//     4096 1891 / 1914 and 2249 / 2273, dense 560 rows of 28 over 4 heads 317 / 321; from 1150 to 4000 rows equal
+//   - lists whose K is split even when they are full: 307 rows of hidden 4096 240.6 / 243.2, 360 of 28 over 4 heads 273.9 / 274.7
+//   - a list with room for more than half of the tokens (few_of_room) is a carried one, which holds a few percent of them: K is
+//     then split on the device.  4 % of 8 x 1024 tokens: step 248 / 252, loop 1961 / 1993.  With more of them the long kernel
+//     would finish rows: 10 and 25 % of 16 x 1280 tokens 802 / 782 and 1878 / 1805, which the host cannot know.
+inline bool few_of_room(bool count_on_device, int cap, size_t tokens) { return count_on_device && (size_t)cap * 2 > tokens; }
+inline bool finishing_kernel(bool few, const GemmPlan &full) { return !few && full.sk == 1; }
 
 // The ring loop's weight copies have one lane offset for all of a tile: the rows they gather lie in one group of
 // RING_GROUP weight rows, and so must lie in one matrix.  (Ends of the stacked matrices; every head size the library

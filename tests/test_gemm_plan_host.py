@@ -14,6 +14,10 @@ SOURCE = r"""
 #include "%s/gemm_plan.h"
 using namespace dy::mm;
 extern "C" int groups_ok(int end0, int end1) { return ring_groups_ok(end0, end1); }
+// raw result of `cap` rows (listed: of a list, whose count is on the device) of `tokens`: in the kernel that can finish rows?
+extern "C" int finishes(int N, int K, long part_elems, int listed, int cap, long tokens) {
+  return finishing_kernel(few_of_room(listed, cap, tokens), plan_on_host(raw_plan_args(N, K, part_elems, true, 32), cap));
+}
 // kind 0: raw result, 1: gate|up, 2: down; the plan of a list with `count` of `cap` entries (cap < 0: count known on
 // the host) -> columns of the row tiles (0: weight-streaming tiles alone), splits, rows in row tiles, splits behind them,
 // planned on the device, sum kernel
@@ -126,3 +130,19 @@ def test_plans_of_timed_pairs(lib, dims, gemm, count, cols, splits):
     d, h, kv, f = dims
     p = Plan(lib, W.LayerShape(hidden=d, n_heads=h, n_kv_heads=kv, head_dim=128, ffn=f, dtype="bf16"), gemm, count, 6144, 6144)
     assert (p.cols, p.splits, p.tiled_rows) == (cols, splits, count)
+
+
+# layer (hidden, query heads, KV heads), rows (capacity of the list), tokens, list -> q|k|v in the kernel that can finish rows
+@pytest.mark.parametrize("dims,cap,tokens,listed,finishes", [
+    ((4096, 32, 32), 20480, 20480, False, True), ((4096, 32, 32), 1100, 1100, False, True),
+    ((4096, 32, 32), 200, 200, False, False),                                     # known rows whose K is split
+    ((3584, 28, 4), 560, 560, False, False), ((3584, 28, 4), 1600, 1600, False, True),
+    ((4096, 32, 0), 768, 3072, False, False), ((4096, 32, 0), 1024, 4096, False, False),  # q of response windows
+    ((4096, 32, 32), 2064, 20480, True, True), ((4096, 32, 32), 5160, 20480, True, True),
+    ((4096, 32, 32), 2064, 4128, True, True), ((4096, 32, 32), 2064, 4127, True, False),  # room for more than half of the tokens
+    ((4096, 32, 32), 8192, 8192, True, False),
+    ((3584, 28, 4), 360, 3600, True, False)])                                     # lists whose K is split when they are full
+def test_kernel_of_the_projections(lib, dims, cap, tokens, listed, finishes):
+    d, h, kv = dims
+    part = C.c_long(max(16 * min(tokens, 2048) * h * 128, tokens * max(128 * (h + 2 * kv), d)))
+    assert lib.finishes(128 * (h + 2 * kv), d, part, int(listed), cap, C.c_long(tokens)) == int(finishes)
