@@ -8,7 +8,7 @@ import pytest
 
 from paper_2603_08026_amd import build
 from synth import workload as W
-from tests.test_gpu_planned_gemm import NO_SUMS_CAP, REGIMES, SHAPE
+from tests.test_gpu_planned_gemm import HALF, NO_SUMS_CAP, REGIMES, SHAPE
 
 SOURCE = r"""
 #include "%s/gemm_plan.h"
@@ -146,3 +146,18 @@ def test_kernel_of_the_projections(lib, dims, cap, tokens, listed, finishes):
     d, h, kv = dims
     part = C.c_long(max(16 * min(tokens, 2048) * h * 128, tokens * max(128 * (h + 2 * kv), d)))
     assert lib.finishes(128 * (h + 2 * kv), d, part, int(listed), cap, C.c_long(tokens)) == int(finishes)
+
+
+def test_regimes_of_lists_of_half_the_tokens(lib):
+    """Each of them is in the kernel that finishes rows, among them one whose streamed rows the row kernel finishes."""
+    streamed = 0
+    for case in HALF:
+        shape, count, cap, plans = REGIMES[case]
+        tokens = 4 * ((cap + 1) // 2)
+        part = C.c_long(max(16 * min(tokens, 2048) * shape.dq, tokens * max(shape.dq + 2 * shape.dkv, shape.hidden)))
+        assert lib.finishes(shape.dq + 2 * shape.dkv, shape.hidden, part, 1, cap, C.c_long(tokens)) == 1, case
+        for gemm, want in plans.items():
+            p = Plan(lib, shape, gemm, count, cap, tokens)
+            assert (p.cols, p.splits, p.tiled_rows, p.tail_splits) == want, (case, gemm)
+            streamed += gemm == "qkv" and p.splits == 1 and p.streams_tail
+    assert HALF and streamed

@@ -102,3 +102,19 @@ def test_plan_regimes(case):
     lay.set_weights(w)
     _check(lay, w, shape, B, L, count, cap)
     lay.close()
+
+
+# the same in a list with room for half of the tokens at most, whose q|k|v the GEMM may finish (test_gemm_plan_host.py)
+HALF = [c for c, (shape, _, cap, _) in enumerate(REGIMES) if cap <= 2100 and shape.hidden == 4096]
+
+
+@pytest.mark.parametrize("case", HALF)
+def test_plan_regimes_of_a_list_of_half_the_tokens(case):
+    shape, count, cap, _ = REGIMES[case]
+    print("plan regime, half", case, count, cap, flush=True)
+    B, L = 4, (cap + 1) // 2
+    lay = Layer.from_shape(shape, B, L)
+    w = rand_weights(shape, 56, bias=True)
+    lay.set_weights(w)
+    _check(lay, w, shape, B, L, count, cap)
+    lay.close()
