@@ -47,7 +47,6 @@ struct PlanArgs {
 
 constexpr int PLAN_BK = 64, PLAN_XCD = 8;
 constexpr int STREAM_ROWS = 128;     // rows that one weight-streaming tile holds
-constexpr int DIRECT_ROWS = 4096;    // rows from which a dense step and a list of all tokens have one plan in common, and so the same bits, in the tests
 constexpr int PLAN_MIN_SLICES = 8;   // K slices every split keeps (the ring loop needs 3)
 constexpr int PLAN_MAX_SPLIT = 16;
 constexpr int PLAN_CANDIDATES = 4 * PLAN_MAX_SPLIT;  // {128, 256 columns} x {last row tile padded, streamed} x splits

@@ -1,6 +1,5 @@
-"""Values that the q|k|v GEMM of a dense step of many rows writes itself, against the same tokens given as a list, whose
-values go through the row kernel: the same sums, bias and rounding, so the same bits.  Row counts at the edge of that
-rule and with a last tile of one row and of part of a 16-row block; value columns that start at a column tile, at a wave's
+"""Keys and values that the q|k|v GEMM of a dense step writes itself, against the same tokens given as a list, which go through
+the row kernel: the same sums, bias, rotation and rounding, so the same bits.  Few and many rows, row counts with a last tile of one row and of part of a 16-row block; value columns that start at a column tile, at a wave's
 columns, and inside them (192- and 256-column tiles); a last row tile that goes to the weight-streaming tiles, whose values the
 row kernel finishes; NaN and infinities.  The plans that the cases name are checked on the CPU."""
 import ctypes as C
@@ -21,7 +20,7 @@ SHAPES = {
     "inside": W.LayerShape(hidden=512, n_heads=46, n_kv_heads=1, head_dim=64, ffn=512, dtype="bf16"),
     "streamed": W.LayerShape(hidden=1024, n_heads=62, n_kv_heads=1, head_dim=64, ffn=512, dtype="bf16"),
 }
-# shape, B, L -> columns of a tile, rows in row tiles (one K split in all: values are direct)
+# shape, B, L -> columns of a tile, rows in row tiles (one K split in all: rows are finished)
 PLANS = {
     ("mha", 2, 2048): (192, 4096), ("mha", 1, 4097): (256, 4097), ("mha", 3, 1367): (256, 4101), ("mha", 5, 1024): (256, 5120),
     ("gqa", 2, 2048): (128, 4096), ("gqa", 1, 4097): (128, 4097), ("gqa", 3, 1367): (128, 4101), ("gqa", 5, 1024): (128, 5120),
@@ -29,11 +28,16 @@ PLANS = {
     # first value column 3008: in the last 64 of a wave's 192, and 64 into a wave's 128
     ("inside", 2, 2048): (192, 4096), ("inside", 1, 4097): (256, 4097), ("inside", 3, 1367): (256, 4101),
     ("streamed", 1, 4097): (256, 4096), ("streamed", 3, 1400): (256, 4096),
+    # few rows, in tiles of 32 rows and more; a last row tile of one row in the streaming tiles
+    ("mha", 1, 129): (128, 129), ("mha", 1, 300): (128, 300), ("mha", 2, 512): (128, 1024), ("mha", 3, 683): (128, 2049),
+    ("gqa", 1, 129): (128, 129), ("gqa", 3, 683): (128, 2049), ("dh64", 1, 300): (128, 300), ("dh64", 2, 512): (128, 1024),
+    ("inside", 1, 257): (128, 257), ("inside", 2, 1500): (256, 3000), ("streamed", 3, 683): (128, 2048),
 }
 CASES = [(s, b, *bl) for s, b in (("mha", False), ("mha", True), ("gqa", True), ("dh64", True))
          for bl in ((2, 2048), (1, 4097), (3, 1367), (5, 1024))]
 CASES += [("inside", True, 2, 2048), ("inside", True, 1, 4097), ("inside", True, 3, 1367), ("streamed", True, 1, 4097),
           ("streamed", True, 3, 1400)]
+CASES += [(s, True, B, L) for s, B, L in PLANS if B * L < 4096]
 
 SOURCE = r"""
 #include "%s/gemm_plan.h"
@@ -41,7 +45,7 @@ using namespace dy::mm;
 extern "C" void plan(int N, int K, long part_elems, int M, int *out) {
   const GemmPlan p = plan_on_host(raw_plan_args(N, K, part_elems, true, 32), M);
   out[0] = p.xl == PLAN_X ? 256 : p.xl == PLAN_W ? 192 : 128;
-  out[1] = p.row_hi; out[2] = p.sk; out[3] = M >= DIRECT_ROWS;
+  out[1] = p.row_hi; out[2] = p.sk; out[3] = finishing_kernel(false, p);
 }
 """
 
