@@ -191,6 +191,11 @@ void prof_mark(dyllm_ctx *ctx, int stage, hipStream_t s) {
   if (ctx->prof_cur) (void)hipEventRecord(ctx->prof_cur[stage + 1], s);
 }
 
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+  const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+  return pa < pb + b_bytes && pb < pa + a_bytes;
+}
+
 // gather + norm, q/k/v projection, rotation, K/V merge  [Alg. 3: norm / q_proj / k_proj / v_proj lines]
 int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Rows rows, int B, int L,
                 dyllm_layer_cache *cache, void *q_out, hipStream_t s) {
@@ -200,15 +205,19 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
   seg.n_end[0] = ctx->dq; seg.n_end[1] = ctx->dq + ctx->dkv; seg.n_end[2] = ctx->dq + 2 * ctx->dkv;
   const QkvOut out{q_out, cache->k, cache->v, w->bq, w->bk, w->bv, ctx->rope, c.n_heads, c.n_kv_heads, c.head_dim, L, 0, (size_t)B * L};
   if (dt(ctx) == F32) {
+    // (a caller may hand over x for a result: its rows are then normalised first, in a launch of their own)
+    const size_t T = (size_t)B * L, xb = T * c.hidden * 4, kvb = T * ctx->dkv * 4;
+    const bool over_x = overlap(x, xb, q_out, (size_t)rows.cap * ctx->dq * 4) || overlap(x, xb, cache->k, kvb) || overlap(x, xb, cache->v, kvb);
+    if (over_x) launch_gather_rmsnorm(F32, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, s);
     prof_mark(ctx, ST_GATHER_NORM, s);
-    launch_qkv_f32(x, w->g_attn, c.rms_eps, rows, c.hidden, seg, out, s);
+    launch_qkv_f32(over_x ? ctx->ns : x, over_x ? nullptr : w->g_attn, c.rms_eps, rows, c.hidden, seg, out, s);
     prof_mark(ctx, ST_GEMM_QKV, s);
     prof_mark(ctx, ST_ROPE_SCATTER, s);
     return check_launch(ctx, "qkv refresh");
   }
-  launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, s);
+  launch_gather_rmsnorm(BF16, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, s);
   prof_mark(ctx, ST_GATHER_NORM, s);
-  const Splits splits = launch_gemm_raw(dt(ctx), GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
+  const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
                                      ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
   prof_mark(ctx, ST_GEMM_QKV, s);
   launch_qkv_finalize(dt(ctx), ctx->part_o, splits, rows, out, nullptr, s);

@@ -258,6 +258,10 @@ void gemm_f32_down(GemmA A, Rows rows, int K, int N, const void *w_down, const f
 }
 
 void launch_qkv_f32(const void *x, const void *gain, float eps, Rows rows, int K, WSeg seg, const QkvOut &out, hipStream_t s) {
+  if (!gain) {
+    run<false>(GemmA{x, nullptr, K}, rows, K, seg.n_end[2], seg, nullptr, NormIn{}, EpiQkvF32{out}, s);
+    return;
+  }
   run<true>(GemmA{x, rows.idx, K}, rows, K, seg.n_end[2], seg, nullptr, NormIn{(const float *)gain, eps}, EpiQkvF32{out}, s);
 }
 

@@ -212,7 +212,8 @@ void launch_gemm_down(DType t, const void *a, Rows rows, int K, int N, const voi
 
 // fp32: the same steps without row kernels between them.  K is never split, so a GEMM finishes its rows, and each takes its
 // operand's RMSNorm along.
-// q|k|v of RMSNorm(x[row_j,:]) * gain, finished as QkvOut says
+// q|k|v of RMSNorm(x[row_j,:]) * gain, or without a gain of x[j,:], finished as QkvOut says.  x is read while results are written:
+// none of them may lie in its rows.
 void launch_qkv_f32(const void *x, const void *gain, float eps, Rows rows, int K, WSeg seg, const QkvOut &out, hipStream_t s);
 // h[j,:] = x[row_j,:] + A[j,:] * wo^T
 void launch_oproj_f32(GemmA A, Rows rows, int K, int N, const void *wo, const void *x, float *h, hipStream_t s);

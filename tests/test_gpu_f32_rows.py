@@ -73,3 +73,33 @@ def test_qkv_and_ffn_rows(shape, n, bias):
     rest = torch.ones(B * L, dtype=torch.bool)
     rest[ids] = False
     assert (k[rest] == 5.0).all() and (v[rest] == -7.0).all() and (out[rest] == 2.0).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("result", ["q", "k", "v"])
+@pytest.mark.parametrize("n", [17, 300, 777])
+def test_results_in_the_place_of_x(result, n):
+    """x may be handed over for one of the results: its rows are read before any is written."""
+    from paper_2603_08026_amd.layer import Layer
+    s, B, L = SHAPES["dh64"], 3, 277
+    print("fp32 rows over x", result, n, flush=True)
+    g = torch.Generator().manual_seed(n)
+    ids = torch.sort(torch.randperm(B * L, generator=g)[:n])[0]
+    off = torch.tensor([int((ids < b * L).sum()) for b in range(B + 1)], dtype=torch.int32).cuda()
+    lst = Bd.IndexList(ids.to(torch.int32).cuda(), off)
+    x = torch.randn(B, L, s.hidden, generator=g).cuda()
+    lay = Layer.from_shape(s, B, L)
+    lay.set_weights(rand_weights(s, 82, bias=True))
+    outs = []
+    for shared in (False, True):
+        t = {r: torch.full((B * L, s.dq), 3.0, device="cuda") for r in "qkv"}
+        xd = x.clone()
+        if shared:
+            t[result] = xd.view(B * L, -1)
+        cache = Bd.LayerCache(t["k"].data_ptr(), t["v"].data_ptr(), lay.c.data_ptr(), lay.out.data_ptr())
+        lay.ctx.qkv_refresh(lay.w, xd, lst, B, L, cache, t["q"])
+        at = ids.cuda()
+        outs.append([t["q"][:n].clone(), t["k"][at].clone(), t["v"][at].clone()])
+    lay.close()
+    for name, a, b in zip("qkv", *outs):
+        assert ((a - b).norm() / a.norm()).item() <= 1e-6, name  # (the norm's factor before the products and after them)
