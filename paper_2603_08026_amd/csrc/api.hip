@@ -22,7 +22,7 @@ struct dyllm_ctx {
   char *ws;  // one device allocation, carved below
   size_t ws_bytes;
   // carved buffers
-  void *ns;        // [R, d]        normalised salient rows
+  void *ns;        // [R, d]        normalised salient rows (fp32: where the GEMM may not read x itself, enqueue_qkv)
   void *qs;        // [R, dq]       rotated queries
   float *part_o;   // fp32 scratch shared by consecutive stages: raw GEMM results / attention partials
   float *part_ml;

@@ -82,14 +82,16 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, c
       const int j = min(m0 + 16 * i + l16, M - 1);  // rows past the end are clamped; their results are never stored
       ap[i] = A + (size_t)(gather ? gather[j] : j) * lda + 4 * lq;
     }
-#pragma unroll
-    for (int c = 0; c < NT; ++c) {
-      const int n = column(tn, 16 * c + l16);  // looked up in the stacked weight matrices
+    auto weight_row = [&](int t, int x) -> const float * {  // of column x of the tile, looked up in the stacked weight matrices
+      const int n = column(tn, x);
       const bool in1 = n >= seg.n_end[0], in2 = n >= seg.n_end[1];
       const int start = in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0;
-      wp[0][c] = (const float *)(in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0]) + (size_t)(n - start) * K + 4 * lq;
-      if (NMAT == 2) wp[NMAT - 1][c] = W2 + (size_t)n * K + 4 * lq;
-    }
+      return t == 1 ? W2 + (size_t)n * K : (const float *)(in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0]) + (size_t)(n - start) * K;
+    };
+#pragma unroll
+    for (int c = 0; c < NT; ++c)
+#pragma unroll
+      for (int t = 0; t < NMAT; ++t) wp[t][c] = weight_row(t, 16 * c + l16) + 4 * lq;
     floatx4 acc[NMAT][MT][NT];
 #pragma unroll
     for (int t = 0; t < NMAT; ++t)
@@ -173,6 +175,27 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, c
             for (int q = 0; q < 3; ++q) v[t][c] += part[q][(t * MT + i) * NT + c][lane];
             if (NORM) v[t][c] *= scale;
           }
+        if constexpr (NORM) {
+          // Squares whose sum overflows make the factor 0, and their products may have overflowed as well: those of the
+          // normalised elements, 0 or NaN, are taken instead.
+          if (scale == 0.0f) {
+            const float *xr = ap[i] - 4 * lq;
+            for (int c = 0; c < NT; ++c)
+              for (int t = 0; t < NMAT; ++t)
+                for (int e = 0; e < 4; ++e) {
+                  const float *wr = weight_row(t, 16 * c + 4 * lq) + (size_t)e * K;
+                  float sum = 0.f;
+                  for (int k = 0; k < K; ++k) sum += xr[k] * scale * norm.gain[k] * wr[k];
+#pragma unroll
+                  for (int cc = 0; cc < NT; ++cc)
+#pragma unroll
+                    for (int tt = 0; tt < NMAT; ++tt)
+#pragma unroll
+                      for (int ee = 0; ee < 4; ++ee)
+                        if (cc == c && tt == t && ee == e) v[tt][cc][ee] = sum;
+                }
+          }
+        }
         if constexpr (Epi::PAIRS) {
           // this lane's columns of each block, four in a row: first ones or (16 columns, lanes from 32 on; second block) partners
           const QkvOut &o = epi.o;

@@ -103,3 +103,39 @@ def test_results_in_the_place_of_x(result, n):
     lay.close()
     for name, a, b in zip("qkv", *outs):
         assert ((a - b).norm() / a.norm()).item() <= 1e-6, name  # (the norm's factor before the products and after them)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+@pytest.mark.parametrize("n", [16, 400])
+def test_rows_that_are_not_finite_or_overflow(shape, n):
+    """The factor of a row's norm comes after the products: a row of NaN, of one infinity, of values whose squares overflow (the factor
+    is 0) and of values whose products would as well, as if each element were normalised first; the other rows keep their bits."""
+    from paper_2603_08026_amd.layer import Layer
+    s, B, L = SHAPES[shape], 1, 401
+    print("fp32 rows, not finite", shape, n, flush=True)
+    g = torch.Generator().manual_seed(5)
+    x = torch.randn(L, s.hidden, generator=g)
+    odd = x.clone()
+    odd[1, 3], odd[4, 7], odd[6], odd[8] = float("nan"), float("inf"), 1e20 * torch.sign(x[6]), 3e38 * torch.sign(x[8])
+    odd[10] = 3e38
+    lst = Bd.IndexList(torch.arange(n, dtype=torch.int32, device="cuda"), torch.tensor([0, n], dtype=torch.int32, device="cuda"))
+    lay = Layer.from_shape(s, B, L)
+    lay.set_weights(rand_weights(s, 83, std=0.5))
+    c = torch.zeros(L, s.dq, device="cuda")  # (the residual rows are x)
+    outs = []
+    for rows in (x, odd):
+        q = torch.zeros(n, s.dq, device="cuda")
+        xd = rows.cuda()
+        lay.ctx.qkv_refresh(lay.w, xd, lst, B, L, lay.cache, q)
+        lay.ctx.salient_ffn(lay.w, xd, c, lst, B, L, lay.out)
+        outs.append([t.clone() for t in (q, lay.k.view(L, -1)[:n], lay.v.view(L, -1)[:n], lay.out.view(L, -1)[:n])])
+    lay.close()
+    same = [r for r in range(n) if r not in (1, 4, 6, 8, 10)]
+    for name, a, b in zip(("q", "k", "v", "out"), *outs):
+        assert torch.equal(a[same], b[same]), name
+        assert torch.isnan(b[[1, 4]]).all(), name
+        if name == "out":  # nothing is added to rows whose norm is 0
+            assert torch.equal(b[[6, 8, 10]].cpu(), odd[[6, 8, 10]]), name
+        else:
+            assert (b[[6, 8, 10]] == 0).all(), name
