@@ -34,19 +34,23 @@ RIDGE = MFMA_BF16_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)  # flop per byte
 
 
 def stage_work(shape, B, L, M_in, M_out, esz):
-    """Algorithmic flops and HBM bytes of each stage for one step (M_in candidates, M_out salient)."""
+    """Algorithmic flops and HBM bytes of each stage for one step (M_in candidates, M_out salient).  Bias, rotation and merge
+    belong to the q|k|v GEMM, cosine and commit to the attention, in whose epilogues they are, and in fp32 the norms to the GEMMs that
+    take them along; where a K split or a key split leaves them to a kernel behind it, that stage has no work of its own, and
+    no rate."""
     d, dq, dkv, F = shape.hidden, shape.dq, shape.dkv, shape.ffn
     nq = dq + 2 * dkv
     w = {}
-    w["gather_rmsnorm"] = (4.0 * M_in * d, M_in * d * esz * 2 + d * esz)
-    w["gemm_qkv"] = (2.0 * M_in * d * nq, nq * d * esz + M_in * d * esz + M_in * nq * 4)
-    w["rope_scatter"] = (6.0 * M_in * nq, M_in * nq * 4 + M_in * nq * esz)
-    w["partial_attention"] = (4.0 * M_in * L * dq, 2 * B * L * dkv * esz + 2 * M_in * dq * esz)
-    w["saliency_compact"] = (6.0 * M_in * dq, 3 * M_in * dq * esz + M_in + 4 * M_out)
+    f32 = esz == 4
+    w["gather_rmsnorm"] = (0.0, 0.0) if f32 else (4.0 * M_in * d, M_in * d * esz * 2 + d * esz)
+    w["gemm_qkv"] = (2.0 * M_in * d * nq + 6.0 * M_in * nq + (4.0 * M_in * d if f32 else 0.0), nq * d * esz + M_in * d * esz + M_in * nq * esz)
+    w["rope_scatter"] = (0.0, 0.0)
+    w["partial_attention"] = (4.0 * M_in * L * dq + 6.0 * M_in * dq, 2 * B * L * dkv * esz + 3 * M_in * dq * esz)  # (q, old and new context)
+    w["saliency_compact"] = (0.0, 5.0 * M_in + 4 * M_out)  # cosine and flag of a candidate, index of a selected one
     w["marker_overhead"] = (0.0, 0.0)  # two stream events with no work between them
     w["gemm_oproj"] = (2.0 * M_out * dq * d, d * dq * esz + M_out * dq * esz + M_out * d * (esz + 4))
-    w["rmsnorm_ffn"] = (4.0 * M_out * d, M_out * d * (4 + esz))
-    w["gemm_swiglu"] = (4.0 * M_out * d * F, 2 * F * d * esz + M_out * d * esz + M_out * F * esz)
+    w["rmsnorm_ffn"] = (0.0, 0.0) if f32 else (4.0 * M_out * d, M_out * d * (4 + esz))
+    w["gemm_swiglu"] = (4.0 * M_out * d * F + (4.0 * M_out * d if f32 else 0.0), 2 * F * d * esz + M_out * d * esz + M_out * F * esz)
     w["gemm_down"] = (2.0 * M_out * F * d, d * F * esz + M_out * F * esz + M_out * d * (4 + esz))
     return w
 
@@ -235,7 +239,7 @@ def torch_dense_layer_ms(s, B, L, torch, iters=3, seed=5):
 
 def roofline_of(stage_ms, work, dtype):
     """The stage with the largest time against the roof that bounds it."""
-    dom = max((n for n in stage_ms if n != "marker_overhead"), key=lambda n: stage_ms[n])
+    dom = max((n for n in stage_ms if work[n][1]), key=lambda n: stage_ms[n])
     fl, by = work[dom]
     ms = stage_ms[dom]
     is_gemm_or_attn = dom.startswith("gemm") or dom == "partial_attention"

@@ -359,7 +359,8 @@ Window make_window(dyllm_ctx *ctx, int B, int L, int row_lo, hipStream_t s) {
   return Window{Rows{ctx->win_idx, nullptr, B * (L - row_lo)}, ctx->win_off, row_lo};
 }
 
-// one layer of the sparse step with both attention paths, arguments already checked; inside: every candidate is a token of the step
+// one layer of the sparse step with both attention paths, arguments already checked; inside: every candidate is known to be a token of
+// the step (a caller's list for a window is not looked at on the host; keys and values of whatever it names are refreshed)
 // [Alg. 3 layer body; Sec. 3.3: exact rows for the salient tokens, approximate update for the others]
 int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_layer_cache *cache,
                          const void *x, const dyllm_index_list *idx_in, int B, int L, Window win, bool inside, float tau,
