@@ -21,7 +21,7 @@ struct Rows {
 // {n, tail_from, n_tail, done_to} there; the members are then ignored.
 struct Splits {
   int n = 1, tail_from = 0x7fffffff, n_tail = 1;
-  int done_to = 0;  // rows below it (never more than the list holds) were finished by the GEMM's own epilogue: down projection, q|k|v
+  int done_to = 0;  // rows below it were finished by the GEMM's own epilogue (down projection, q|k|v); at most the list's capacity
   const int32_t *dev = nullptr;
   __device__ Splits resolved() const {
     Splits r = *this;

@@ -58,12 +58,11 @@ __global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
 
 // ---- out-projection tail  [Alg. 3: x <- layernorm(out_proj(C)), with the residual] ---------------
 // h[j] = x[row_j] + sum_z part[z][j] (kept in fp32 for the second residual), f[j] = RMSNorm(h[j]) * gain
-template <typename T>
 __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__ part, Splits splits_of,
-                                                        const T *__restrict__ x,
-                                                        const T *__restrict__ gain, Rows rows, int d,
+                                                        const bf16_t *__restrict__ x,
+                                                        const bf16_t *__restrict__ gain, Rows rows, int d,
                                                         float eps, float *__restrict__ h,
-                                                        T *__restrict__ f) {
+                                                        bf16_t *__restrict__ f) {
   __shared__ float red[RB / WAVE];
   const int n = row_count(rows), nv = d / 4;
   const Splits sp = splits_of.resolved();
@@ -71,7 +70,7 @@ __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__
   for (int j = blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
     const int splits = sp.of(j);
-    const T *xr = x + (size_t)r * d;
+    const bf16_t *xr = x + (size_t)r * d;
     float *hr = h + (size_t)j * d;
     float ss = 0.f;
     float4 keep[KEEP];
@@ -84,8 +83,8 @@ __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__
           const float4 b = *reinterpret_cast<const float4 *>(part + z * split_stride + (size_t)j * d + v * 4);
           a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
         }
-        a.x += to_f<T>(xr[v * 4 + 0]); a.y += to_f<T>(xr[v * 4 + 1]);
-        a.z += to_f<T>(xr[v * 4 + 2]); a.w += to_f<T>(xr[v * 4 + 3]);
+        a.x += to_f<bf16_t>(xr[v * 4 + 0]); a.y += to_f<bf16_t>(xr[v * 4 + 1]);
+        a.z += to_f<bf16_t>(xr[v * 4 + 2]); a.w += to_f<bf16_t>(xr[v * 4 + 3]);
         *reinterpret_cast<float4 *>(hr + v * 4) = a;
         ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
         keep[it] = a;
@@ -93,42 +92,41 @@ __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__
     }
     ss = block_sum<RB>(ss, red);
     const float sc = 1.0f / sqrtf(ss / (float)d + eps);
-    T *fr = f + (size_t)j * d;
+    bf16_t *fr = f + (size_t)j * d;
 #pragma unroll
     for (int it = 0; it < KEEP; ++it) {
       const int v = threadIdx.x + it * RB;
       if (v < nv) {
         const float4 a = keep[it];
-        const T *g = gain + v * 4;
-        fr[v * 4 + 0] = from_f<T>(a.x * sc * to_f<T>(g[0]));
-        fr[v * 4 + 1] = from_f<T>(a.y * sc * to_f<T>(g[1]));
-        fr[v * 4 + 2] = from_f<T>(a.z * sc * to_f<T>(g[2]));
-        fr[v * 4 + 3] = from_f<T>(a.w * sc * to_f<T>(g[3]));
+        const bf16_t *g = gain + v * 4;
+        fr[v * 4 + 0] = from_f<bf16_t>(a.x * sc * to_f<bf16_t>(g[0]));
+        fr[v * 4 + 1] = from_f<bf16_t>(a.y * sc * to_f<bf16_t>(g[1]));
+        fr[v * 4 + 2] = from_f<bf16_t>(a.z * sc * to_f<bf16_t>(g[2]));
+        fr[v * 4 + 3] = from_f<bf16_t>(a.w * sc * to_f<bf16_t>(g[3]));
       }
     }
   }
 }
 
 // ---- down-projection tail after a K split  [Alg. 3: FFN second half + cache commit] ---------------
-template <typename T>
 __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ part, Splits splits_of,
                                                        const float *__restrict__ h,
-                                                       Rows rows, int d, T *__restrict__ out) {
+                                                       Rows rows, int d, bf16_t *__restrict__ out) {
   const int n = row_count(rows), nv = d / 4;
   const Splits sp = splits_of.resolved();
   const size_t split_stride = (size_t)n * d;
   for (int j = sp.done_to + blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
     const int splits = sp.of(j);
-    T *orow = out + (size_t)r * d;
+    bf16_t *orow = out + (size_t)r * d;
     for (int v = threadIdx.x; v < nv; v += RB) {
       float4 a = *reinterpret_cast<const float4 *>(h + (size_t)j * d + v * 4);
       for (int z = 0; z < splits; ++z) {
         const float4 b = *reinterpret_cast<const float4 *>(part + z * split_stride + (size_t)j * d + v * 4);
         a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
       }
-      orow[v * 4 + 0] = from_f<T>(a.x); orow[v * 4 + 1] = from_f<T>(a.y);
-      orow[v * 4 + 2] = from_f<T>(a.z); orow[v * 4 + 3] = from_f<T>(a.w);
+      orow[v * 4 + 0] = from_f<bf16_t>(a.x); orow[v * 4 + 1] = from_f<bf16_t>(a.y);
+      orow[v * 4 + 2] = from_f<bf16_t>(a.z); orow[v * 4 + 3] = from_f<bf16_t>(a.w);
     }
   }
 }
@@ -238,9 +236,9 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
 // ---- temporal cosine similarity + salient test (+ commit)  [Sec. 3.1, Sec. 3.2] ----------------
 // s = <a,b> / (max(|a|,1e-8) max(|b|,1e-8)), flag = s < tau.  The old cache row b is read before
 // the same thread overwrites the same elements with a.
-// A row per workgroup: many small workgroups keep the loads of a CU in flight, a thread's all at once.  HBM-bound where the rows are
-// many: 32768 rows of 4096 bf16 columns (537 MB), compaction included, 96.5 -> 84.7 us, most of it by loads that leave the L2 alone;
-// 7500 rows of 3584 24.3 -> 22.5; up to 30 MB equal.
+// A row per workgroup: many small workgroups keep the loads of a CU in flight, a thread's four at a time (all of them up to 4096 bf16 or
+// 2048 fp32 columns).  HBM-bound where the rows are many: 32768 rows of 4096 bf16 columns (537 MB), compaction included, 96.5 -> 84.7
+// us, most of it by loads that leave the L2 alone; 7500 rows of 3584 24.3 -> 22.5; up to 30 MB equal.
 constexpr int SAL_NT = 256;
 
 template <typename T>
@@ -491,7 +489,7 @@ void launch_oproj_finalize(const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
                            hipStream_t s) {
   if (rows.cap <= 0) return;
-  k_oproj_finalize<bf16_t><<<row_grid(rows), RB, 0, s>>>(part, splits, (const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, h,
+  k_oproj_finalize<<<row_grid(rows), RB, 0, s>>>(part, splits, (const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, h,
                                                          (bf16_t *)f);
 }
 
@@ -499,7 +497,7 @@ void launch_down_finalize(const float *part, Splits splits, const float *h,
                           Rows rows, int d, void *out_cache, hipStream_t s) {
   const int done = splits.dev ? 0 : splits.done_to;
   if (rows.cap <= 0 || done >= rows.cap) return;
-  k_down_finalize<bf16_t><<<row_grid(rows, rows.cap - done), RB, 0, s>>>(part, splits, h, rows, d, (bf16_t *)out_cache);
+  k_down_finalize<<<row_grid(rows, rows.cap - done), RB, 0, s>>>(part, splits, h, rows, d, (bf16_t *)out_cache);
 }
 
 void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, const QkvOut &o, const CandidateOut *cand,
