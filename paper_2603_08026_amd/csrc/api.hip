@@ -218,7 +218,7 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
   launch_gather_rmsnorm(BF16, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, s);
   prof_mark(ctx, ST_GATHER_NORM, s);
   const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
-                                     ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
+                                     ctx->part_o, ctx->part_elems, ctx->plan, out, s);
   prof_mark(ctx, ST_GEMM_QKV, s);
   launch_qkv_finalize(dt(ctx), ctx->part_o, splits, rows, out, nullptr, s);
   prof_mark(ctx, ST_ROPE_SCATTER, s);
@@ -261,7 +261,8 @@ int enqueue_ffn(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, con
     prof_mark(ctx, ST_NORM_FFN, s);
     launch_swiglu_f32(ctx->hs, w->g_ffn, c.rms_eps, rows, c.hidden, c.ffn_dim, w->w_gate, w->w_up, ctx->act, s);
   } else {
-    const Splits splits = launch_gemm_raw(BF16, A, rows, ctx->dq, wseg_one(w->wo, c.hidden), ctx->part_o, ctx->part_elems, ctx->plan, s);
+    const Splits splits = launch_gemm_raw(BF16, A, rows, ctx->dq, wseg_one(w->wo, c.hidden), ctx->part_o, ctx->part_elems, ctx->plan,
+                                          raw_beside(c.n_heads, c.n_kv_heads, c.head_dim, n_tokens), s);
     prof_mark(ctx, ST_GEMM_OPROJ, s);
     launch_oproj_finalize(ctx->part_o, splits, x, w->g_ffn, rows, c.hidden, c.rms_eps, ctx->hs, ctx->fs, s);
     prof_mark(ctx, ST_NORM_FFN, s);
@@ -387,7 +388,7 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     } else {
       launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, shared, s);
       const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, shared ? all.idx : nullptr, c.hidden, T}, all, c.hidden,
-                                            wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, s, &out);
+                                            wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, out, s);
       launch_qkv_finalize(BF16, ctx->part_o, splits, all, out, nullptr, s);
     }
   }
@@ -399,7 +400,7 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     seg.n_end[0] = ctx->dkv; seg.n_end[1] = 2 * ctx->dkv; seg.n_end[2] = 2 * ctx->dkv;
     const GemmA A = shared ? GemmA{ctx->ns, rin.idx, c.hidden, T} : GemmA{ctx->fs, nullptr, c.hidden, T};
     const Splits splits = launch_gemm_raw(dt(ctx), A, rin, c.hidden, seg,
-                                       ctx->part_o, ctx->part_elems, ctx->plan, s);
+                                       ctx->part_o, ctx->part_elems, ctx->plan, raw_beside(c.n_heads, c.n_kv_heads, c.head_dim, T), s);
     // value residual: by token or by sequence into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
     // entry; the last two next to a compact copy of the new keys; and the step's candidates in the token -> entry map
     const CandidateOut cand{cached_norm ? ctx->dc : ctx->dv_full, cached_norm || by_sequence ? ctx->ksal : nullptr,

@@ -398,7 +398,7 @@ template <int WQ, int WK_> struct DTile {
 template <int WQ, int WK_, bool NORM, bool ONCE>
 __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item) {
   using T = DTile<WQ, WK_>;
-  constexpr int DH = T::DH, NW = T::NW, WK = T::WK, BQ = T::BQ, TK = T::TK, ROWB = T::ROWB, NS = T::NS,
+  constexpr int DH = T::DH, NW = T::NW, WK = T::WK, TK = T::TK, ROWB = T::ROWB, NS = T::NS,
                 DB = T::DB, KK = T::KK, LPW = T::LPW;
   extern __shared__ __align__(1024) unsigned char smem_raw[];
 

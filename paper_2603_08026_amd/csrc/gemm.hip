@@ -6,12 +6,12 @@ namespace dy {
 void gemm_f32_raw(GemmA, Rows, int, WSeg, float *, hipStream_t);
 void gemm_f32_down(GemmA, Rows, int, int, const void *, const float *, void *, hipStream_t);
 
-Splits gemm_bf16_raw(GemmA, Rows, int, WSeg, float *, size_t, int32_t *, const QkvOut *, hipStream_t);
+Splits gemm_bf16_raw(GemmA, Rows, int, WSeg, float *, size_t, int32_t *, const QkvOut &, hipStream_t);
 void gemm_bf16_swiglu(GemmA, Rows, int, int, const void *, const void *, void *, hipStream_t);
 void gemm_bf16_down(GemmA, Rows, int, int, const void *, const float *, void *, float *, size_t, int32_t *, hipStream_t);
 
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
-                       int32_t *plan, hipStream_t s, const QkvOut *qkv) {
+                       int32_t *plan, const QkvOut &qkv, hipStream_t s) {
   if (t == F32) {
     gemm_f32_raw(A, rows, K, seg, part, s);
     return Splits{};

@@ -7,18 +7,16 @@ namespace dy {
 Splits gemm_bf16_qkv128(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, hipStream_t s);
 Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, hipStream_t s);
 
-// raw result part[z][j][n], or rows finished as `qkv` says; returns the numbers of K splits (on the device if the count is there)
-Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, const QkvOut *qkv,
+// raw result part[z][j][n], or rows finished as `qkv` says where it has a table; returns the numbers of K splits (on the device if the count is there)
+Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, const QkvOut &qkv,
                      hipStream_t s) {
   Splits out;
   if (rows.cap <= 0) return out;
   const int N = seg.n_end[2];
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
   const bool ring = ring_ok(A, K, seg, N);
-  const size_t tokens = qkv ? qkv->tokens : A.a_rows;
   // (positions come from a division by at least two, rotary table entries from 32-bit offsets)
-  if (qkv && (qkv->L < 2 || (size_t)qkv->L * qkv->dh * 4 >= ((size_t)1 << 31))) qkv = nullptr;
-  const auto qkv_gemm = qkv && qkv->dh == 64 ? gemm_bf16_qkv64 : gemm_bf16_qkv128;
+  const bool finishes = qkv.tab && qkv.L >= 2 && (size_t)qkv.L * qkv.dh * 4 < ((size_t)1 << 31);
   PlanArgs pa = raw_plan_args(N, K, part_elems, ring, cus_of_xcd());
   if (rows.cap <= STREAM_ROWS) {
     const EpiStoreF32 e{part, N};
@@ -28,13 +26,16 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
     return out;
   }
   if (ring) {
-    const bool known = plan_known(rows), few = few_of_room(rows.count != nullptr, rows.cap, tokens);
+    const bool known = plan_known(rows);
+    const bool few = few_of_room(rows.count != nullptr, rows.cap, qkv.tokens) || few_results(known, rows.cap, (qkv.H + 2 * qkv.Hkv) * qkv.dh) ||
+                     (!finishes && qkv.dh == 64);
     const GemmPlan full = known || !few ? plan_on_host(pa, rows.cap) : GemmPlan{0, 1, 0, 1, 256};
     if (!finishing_kernel(few, full)) {
       run_planned<RawKind<EpiStoreF32>>(ga, EpiStoreF32{part, N}, pa, full, plan_dev, s);
       return splits_of(ga, full, false, plan_dev);
     }
-    return qkv ? qkv_gemm(ga, part, *qkv, pa, full, plan_dev, s) : gemm_bf16_qkv128(ga, part, QkvOut{}, pa, full, plan_dev, s);
+    if (finishes && qkv.dh == 64) return gemm_bf16_qkv64(ga, part, qkv, pa, full, plan_dev, s);
+    return gemm_bf16_qkv128(ga, part, finishes ? qkv : QkvOut{}, pa, full, plan_dev, s);
   }
   pa.stream_cols = 0;
   out.n = plan_of(pa, rows.cap, first_on_host(pa, rows.cap)).sk;

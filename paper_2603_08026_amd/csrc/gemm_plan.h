@@ -305,7 +305,19 @@ inline bool down_has_sums(const PlanArgs &a, int cap, bool known) {
 //   - a list with room for more than half of the tokens (few_of_room) is a carried one, which holds a few percent of them: K is
 //     then split on the device.  4 % of 8 x 1024 tokens: step 248 / 252, loop 1961 / 1993.  With more of them the long kernel
 //     would finish rows: 10 and 25 % of 16 x 1280 tokens 802 / 782 and 1878 / 1805, which the host cannot know.
+//   - few results of a list planned on the device: the row kernel is launched all the same and had little to do.  Steps, q|k|v columns x
+//     rows: 768 x 310 / 740 / 990 / 1230 / 3080 77.4 / 81.0, 92.9 / 94.9, 99.2 / 100.6, 125.7 / 125.2, 191.8 / 189.8; 1536 x 490 / 990 /
+//     1540 78.6 / 80.3, 102.3 / 101.0, 101.6 / 99.4; 3072 x 370 / 620 / 1080 / 1540 92.3 / 93.5, 104.4 / 104.8, 116.1 / 117.0, 137.9 /
+//     137.2 (hidden 2048: 1080 rows 186.0 / 189.2); 4608 x 720 / 1030 / 1340 400.7 / 402.9, 521.7 / 527.0, 670.6 / 667.1; but 6144 x
+//     310 / 650 / 1000 133.8 / 132.6, 169.0 / 167.2, 211.2 / 209.6; 12288 x 570 / 970 398 / 393, 513 / 504
+// Known rows lose nothing there, since their row kernel is not launched (768 columns x 140 rows 55.3 / 54.5).
+// The out-projection and other raw results of a layer take the same of the two kernels, which then follow each other closely enough for
+// their instructions to be in the caches (16 x 1280 tokens, 2064 rows, out-projection in the short one: 837 -> 845) - with heads of
+// 128 columns: the long kernel for heads of 64 is another one, and raw results beside it take the short kernel (hidden 512,
+// short / long: 140 rows 54.5 / 55.9, 1230 rows 120.1 / 121.6, dense 3072 rows 95.1 / 96.8; hidden 1024 and 2048 equal to 0.8 % faster).
+constexpr int FINISH_ROWS = 1100, FINISH_COLS = 6144;
 inline bool few_of_room(bool count_on_device, int cap, size_t tokens) { return count_on_device && (size_t)cap * 2 > tokens; }
+inline bool few_results(bool known, int cap, int qkv_cols) { return !known && cap < FINISH_ROWS && qkv_cols < FINISH_COLS; }
 inline bool finishing_kernel(bool few, const GemmPlan &full) { return !few && full.sk == 1; }
 
 // The ring loop's weight copies have one lane offset for all of a tile: the rows they gather lie in one group of

@@ -199,9 +199,10 @@ inline WSeg wseg_one(const void *w, int N) {
 // returns the numbers of splits used (>= 1), chosen from the rows that exist, N and K (on the device, in
 // the four words `plan`, when their number is known there alone).
 // qkv: where the results go in the end.  The GEMM may finish rows itself (those below Splits::done_to, which have no raw
-// result then); the row kernel finishes the others.
+// result then); the row kernel finishes the others.  Without a table (raw_beside) it only says which q|k|v the result goes with.
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
-                       int32_t *plan, hipStream_t s, const QkvOut *qkv = nullptr);
+                       int32_t *plan, const QkvOut &qkv, hipStream_t s);
+inline QkvOut raw_beside(int H, int Hkv, int dh, size_t tokens) { return QkvOut{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, H, Hkv, dh, 0, 0, tokens}; }
 // up (bf16): act[j,:] = silu(A w_gate^T) * (A w_up^T), out [cap, N]; here and below A[j,:] = a[j,:], rows of K elements
 void launch_gemm_swiglu(const void *a, Rows rows, int K, int N, const void *w_gate,
                         const void *w_up, void *act, hipStream_t s);

@@ -16,7 +16,8 @@ using namespace dy::mm;
 extern "C" int groups_ok(int end0, int end1) { return ring_groups_ok(end0, end1); }
 // raw result of `cap` rows (listed: of a list, whose count is on the device) of `tokens`: in the kernel that can finish rows?
 extern "C" int finishes(int N, int K, long part_elems, int listed, int cap, long tokens) {
-  return finishing_kernel(few_of_room(listed, cap, tokens), plan_on_host(raw_plan_args(N, K, part_elems, true, 32), cap));
+  const bool few = few_of_room(listed, cap, tokens) || few_results(plan_known(listed, cap), cap, N);
+  return finishing_kernel(few, plan_on_host(raw_plan_args(N, K, part_elems, true, 32), cap));
 }
 // kind 0: raw result, 1: gate|up, 2: down; the plan of a list with `count` of `cap` entries (cap < 0: count known on
 // the host) -> columns of the row tiles (0: weight-streaming tiles alone), splits, rows in row tiles, splits behind them,
@@ -141,7 +142,10 @@ def test_plans_of_timed_pairs(lib, dims, gemm, count, cols, splits):
     ((4096, 32, 32), 2064, 20480, True, True), ((4096, 32, 32), 5160, 20480, True, True),
     ((4096, 32, 32), 2064, 4128, True, True), ((4096, 32, 32), 2064, 4127, True, False),  # room for more than half of the tokens
     ((4096, 32, 32), 8192, 8192, True, False),
-    ((3584, 28, 4), 360, 3600, True, False)])                                     # lists whose K is split when they are full
+    ((3584, 28, 4), 360, 3600, True, False),                                      # lists whose K is split when they are full
+    ((512, 4, 4), 256, 16384, True, True), ((512, 4, 4), 257, 16384, True, False),  # few results of a plan on the device
+    ((1024, 8, 8), 1099, 16384, True, False), ((1024, 8, 8), 1100, 16384, True, True), ((1024, 8, 8), 400, 400, False, True),
+    ((2048, 16, 15), 1099, 16384, True, False), ((2048, 16, 16), 1099, 16384, True, True), ((2048, 16, 16), 310, 16384, True, True)])
 def test_kernel_of_the_projections(lib, dims, cap, tokens, listed, finishes):
     d, h, kv = dims
     part = C.c_long(max(16 * min(tokens, 2048) * h * 128, tokens * max(128 * (h + 2 * kv), d)))
