@@ -969,6 +969,11 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
 //   BY_TILE  128-row tiles of a list, whose lengths the device knows: both forms in one kernel
 //   ALL      64-row tiles (2 x 2 waves, whose registers two forms exceed) of a list with room for one tile a sequence
 enum class Once { NONE, ALL, BY_TILE };
+// Fewer bytes of keys and values than these stay in the caches from step to step, past them they would be fetched again.  Steps, past
+// the L2 / through it, us: 33 MB 86.9 / 84.3 (hidden 2048, 182 rows), 1280 / 1260 (hidden 4096, loop of 2 x 1024 tokens, 80
+// rows), 738 / 725 (hidden 1024, loop); 50 MB 85.0 / 80.4 (hidden 1024, 303 rows); 67 MB 233.8 / 236.2 (hidden 4096, 274 rows), 1039 / 1106
+// (hidden 2048, loop), but 93.5 / 91.8 (hidden 1024, 493 rows); 134 MB 1991 / 2053 (loop); 168 MB 139.7 / 147.4; 268 MB 164 / 190.
+inline bool past_l2(const AttnArgs &a) { return (size_t)a.B * a.L * a.Hkv * a.dh * 4 >= (size_t)64 << 20; }
 
 // (two waves per SIMD: 256 registers, no AGPR shuffling)
 template <int WQ, int WK_, bool NORM, Once ONCE>
@@ -1048,8 +1053,8 @@ void launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
     if (a.norm_k) {
       if (wide) launch_dma<4, 1, true, Once::NONE>(a, s); else launch_dma<2, 2, true, Once::NONE>(a, s);
     } else if (wide) {
-      if (a.offsets) launch_dma<4, 1, false, Once::BY_TILE>(a, s); else launch_dma<4, 1, false, Once::NONE>(a, s);
-    } else if ((long)a.rows.cap * (a.H / a.Hkv) <= (long)a.B * a.bq) {
+      if (a.offsets && past_l2(a)) launch_dma<4, 1, false, Once::BY_TILE>(a, s); else launch_dma<4, 1, false, Once::NONE>(a, s);
+    } else if (past_l2(a) && (long)a.rows.cap * (a.H / a.Hkv) <= (long)a.B * a.bq) {
       launch_dma<2, 2, false, Once::ALL>(a, s);
     } else {
       launch_dma<2, 2, false, Once::NONE>(a, s);

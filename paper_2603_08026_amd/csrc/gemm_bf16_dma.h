@@ -68,10 +68,10 @@ namespace dy {
 namespace mm {
 
 // Tile shape: BM x BN output tile, WAVES_M x WAVES_N waves, DUAL = two weight matrices per tile (fused
-// gate/up), NS LDS stages of one K slice each.
-template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, bool DUAL_, int NS_> struct Shape {
+// gate/up), NS LDS stages of one K slice each.  ONCE: weights that one workgroup alone reads go past the L2.
+template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, bool DUAL_, int NS_, bool ONCE_ = false> struct Shape {
   static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, NS = NS_;
-  static constexpr bool DUAL = DUAL_;
+  static constexpr bool DUAL = DUAL_, ONCE = ONCE_;
   static constexpr int NMAT = DUAL ? 2 : 1;
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   static constexpr int MB = WM / 32, NB = WN / 32;
@@ -748,7 +748,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
     // The loops exist for the shapes that plans take for so few rows: 128 columns, K split where it may be, and 256 for gate|up (no
     // other for eight layer shapes of hidden 512 to 8192).  In the others they made the kernels longer for all rows: 330 rows, down
     // projection 35.9 -> 36.6 us; a loop of 8 x 1024 tokens 2013 -> 2035.
-    constexpr bool ONCE_LOOPS = BN * NMAT == 128 ? (NMAT == 2 || SPLIT) : BN * NMAT == 256 && NMAT == 2;
+    constexpr bool ONCE_LOOPS = SH::ONCE && (BN * NMAT == 128 ? (NMAT == 2 || SPLIT) : BN * NMAT == 256 && NMAT == 2);
     if constexpr (ONCE_LOOPS) {
       static_assert(MAX_MI == 8, "row blocks of these shapes");
       if (M_all <= bm && blocks_of(0) > MAX_MI / 2) {
@@ -832,7 +832,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &ga, const Epi &epi, i
         for (int i = 0; i < SH::B_LD; ++i) {
           // (every weight is read by one workgroup; the row tiles that read them too where only a last row tile streams are long
           // done: dense 1300 rows of hidden 4096 589 -> 581 us, lists of as many equal)
-          if constexpr (SH::PIPE) dma16_once(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
+          if constexpr (SH::ONCE) dma16_once(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
           else dma16(wp[t][i] + ko, sb + (uint32_t)(t * BN) * ROWB + i * (NW * 1024u));
         }
     };

@@ -5,14 +5,14 @@ namespace dy {
 
 namespace {
 
-struct DownKind {  // residual + scatter in the epilogue, or fp32 sums of a K split
+template <bool ONCE> struct DownKind {  // residual + scatter in the epilogue, or fp32 sums of a K split
   typedef EpiDown<bf16_t> Epi;
   typedef XLargeS X;
-  typedef LargeS L;
+  typedef LargeS<ONCE> L;
   typedef void W;
   static constexpr bool FUSED = true, RAW = true;
   static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
-    gemm_tiles<SkinnyN64, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
+    gemm_tiles<SkinnyN64<ONCE>, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
   }
 };
 
@@ -26,14 +26,15 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
   const bool ring = ring_ok(A, K, seg, N);
   PlanArgs pa = down_plan_args(N, K, part_elems, ring, cus_of_xcd());
+  const bool once = past_l2(N, K);
   Splits sp;
   if (rows.cap <= STREAM_ROWS) {
     sp.n = stream_split(pa, rows.cap);
-    if (sp.n == 1) {
-      run_tiles<SkinnyS, false>(ga, e, 1, s);
-      return;
-    }
-    run_tiles<SkinnyS, true>(ga, e, sp.n, s);
+    with_once(once, [&](auto o) {
+      if (sp.n == 1) run_tiles<SkinnyS<decltype(o)::value>, false>(ga, e, 1, s);
+      else run_tiles<SkinnyS<decltype(o)::value>, true>(ga, e, sp.n, s);
+    });
+    if (sp.n == 1) return;
   } else if (!ring) {
     pa.stream_cols = 0;
     sp.n = plan_of(pa, rows.cap, first_on_host(pa, rows.cap)).sk;
@@ -47,7 +48,7 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
     if (!sums) pa.split_ok = pa.stream_cols = 0;
     if (known) pa.sum_us = 4.0f;
     const GemmPlan pl = plan_here(ga, pa);
-    run_planned<DownKind>(ga, e, pa, pl, plan_dev, s);
+    with_once(once, [&](auto o) { run_planned<DownKind<decltype(o)::value>>(ga, e, pa, pl, plan_dev, s); });
     if (!sums || (known && pl.sk == 1 && pl.row_hi == rows.cap)) return;
     sp = splits_of(ga, pl, true, plan_dev);
   }

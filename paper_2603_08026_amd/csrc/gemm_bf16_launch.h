@@ -25,21 +25,25 @@ namespace {
 //          goes to the streaming tiles: gemm_plan.h
 //  skinny  all rows in one 128-row tile, 64-column tiles, 4 stages in flight and a K split so that
 //          about one workgroup per CU streams weights (weight-streaming-bound regime)
+//  ONCE: the matrix goes past the L2 where one workgroup alone reads a weight (past_l2)
 typedef Shape<256, 256, 2, 2, false, 2> XLargeS;
-typedef Shape<256, 128, 2, 2, true, 2> XLargeD;
-typedef Shape<256, 128, 2, 2, false, 2> LargeS;
-typedef Shape<256, 64, 2, 2, true, 2> LargeD;
+template <bool ONCE> using XLargeD = Shape<256, 128, 2, 2, true, 2, ONCE>;
+template <bool ONCE> using LargeS = Shape<256, 128, 2, 2, false, 2, ONCE>;
+template <bool ONCE> using LargeD = Shape<256, 64, 2, 2, true, 2, ONCE>;
 typedef Shape<256, 192, 4, 1, false, 2> WideS;
 typedef Shape<256, 96, 4, 1, true, 2> WideD;
-static_assert(LargeS::BN == 128 && XLargeS::BN == 256 && LargeD::BN == 64 && XLargeD::BN == 128, "columns that the plans count in");
+static_assert(LargeS<false>::BN == 128 && XLargeS::BN == 256 && LargeD<false>::BN == 64 && XLargeD<false>::BN == 128, "columns that the plans count in");
 typedef Shape<256, 128, 4, 2, false, 2> LargeS8;  // eight waves, two LDS stages
 typedef Shape<256, 64, 4, 2, true, 2> LargeD8;
-typedef Shape<128, 64, 4, 2, false, 4> SkinnyS;
-typedef Shape<128, 64, 4, 1, false, 4> SkinnyN64;  // the same with four waves, beside the row tiles in one kernel
+template <bool ONCE> using SkinnyS = Shape<128, 64, 4, 2, false, 4, ONCE>;
+template <bool ONCE> using SkinnyN64 = Shape<128, 64, 4, 1, false, 4, ONCE>;  // the same with four waves, beside the row tiles in one kernel
 // skinny regime, wide column tiles (fewer re-reads of the activation tile): q|k|v raw result, and
 // gate|up with half-interleaved tiles (48 + 48 or 64 + 64 columns) and SwiGLU in registers
-typedef Shape<128, 96, 4, 1, false, 4> SkinnyW96;
-typedef Shape<128, 128, 4, 1, false, 4> SkinnyH128;
+template <bool ONCE> using SkinnyW96 = Shape<128, 96, 4, 1, false, 4, ONCE>;
+template <bool ONCE> using SkinnyH128 = Shape<128, 128, 4, 1, false, 4, ONCE>;
+
+// f(std::true_type or std::false_type)
+template <typename F> auto with_once(bool once, F f) { return once ? f(std::true_type{}) : f(std::false_type{}); }
 
 int cu_count() {
   static int n = 0;
@@ -112,15 +116,15 @@ Splits splits_of(const GemmArgs &ga, const GemmPlan &pl, bool fused, const int32
 }
 
 // q|k|v, out-projection: fp32 result, a row kernel follows
-template <typename E> struct RawKind {
+template <typename E, bool ONCE> struct RawKind {
   typedef E Epi;
   typedef XLargeS X;
-  typedef LargeS L;
+  typedef LargeS<ONCE> L;
   typedef WideS W;
   static constexpr bool FUSED = false, RAW = true;
   static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
-    if (ga.N % SkinnyW96::BN == 0) gemm_tiles<SkinnyW96, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);
-    else gemm_tiles<SkinnyN64, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);
+    if (ga.N % SkinnyW96<ONCE>::BN == 0) gemm_tiles<SkinnyW96<ONCE>, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);
+    else gemm_tiles<SkinnyN64<ONCE>, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);
   }
 };
 

@@ -24,7 +24,7 @@ Splits run_qkv(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArg
   e.o = out;
   e.l_mul = e.l_shift = 0;
   if (out.tab) division_by((uint32_t)out.L, &e.l_mul, &e.l_shift);
-  run_planned<RawKind<EpiQkv<DH>>>(ga, e, pa, pl, plan_dev, s);
+  with_once(past_l2(ga.N, ga.K), [&](auto once) { run_planned<RawKind<EpiQkv<DH>, decltype(once)::value>>(ga, e, pa, pl, plan_dev, s); });
   return splits_of(ga, pl, out.tab != nullptr, plan_dev);
 }
 

@@ -18,11 +18,15 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
   // (positions come from a division by at least two, rotary table entries from 32-bit offsets)
   const bool finishes = qkv.tab && qkv.L >= 2 && (size_t)qkv.L * qkv.dh * 4 < ((size_t)1 << 31);
   PlanArgs pa = raw_plan_args(N, K, part_elems, ring, cus_of_xcd());
+  const bool once = past_l2(N, K);
   if (rows.cap <= STREAM_ROWS) {
     const EpiStoreF32 e{part, N};
     out.n = stream_split(pa, rows.cap);
-    if (N % SkinnyW96::BN == 0) run_tiles<SkinnyW96, true>(ga, e, out.n, s);
-    else run_tiles<SkinnyS, true>(ga, e, out.n, s);
+    with_once(once, [&](auto o) {
+      constexpr bool ONCE = decltype(o)::value;
+      if (N % SkinnyW96<ONCE>::BN == 0) run_tiles<SkinnyW96<ONCE>, true>(ga, e, out.n, s);
+      else run_tiles<SkinnyS<ONCE>, true>(ga, e, out.n, s);
+    });
     return out;
   }
   if (ring) {
@@ -31,7 +35,7 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
                      (!finishes && qkv.dh == 64);
     const GemmPlan full = known || !few ? plan_on_host(pa, rows.cap) : GemmPlan{0, 1, 0, 1, 256};
     if (!finishing_kernel(few, full)) {
-      run_planned<RawKind<EpiStoreF32>>(ga, EpiStoreF32{part, N}, pa, full, plan_dev, s);
+      with_once(once, [&](auto o) { run_planned<RawKind<EpiStoreF32, decltype(o)::value>>(ga, EpiStoreF32{part, N}, pa, full, plan_dev, s); });
       return splits_of(ga, full, false, plan_dev);
     }
     if (finishes && qkv.dh == 64) return gemm_bf16_qkv64(ga, part, qkv, pa, full, plan_dev, s);

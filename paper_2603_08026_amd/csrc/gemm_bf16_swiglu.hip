@@ -15,16 +15,16 @@ __host__ __device__ __forceinline__ GemmArgs halves_args(const GemmArgs &ga) {
   h.N = 2 * ga.N;
   return h;
 }
-struct SwigluKind {
+template <bool ONCE> struct SwigluKind {
   typedef EpiSwiGLU<bf16_t> Epi;
-  typedef XLargeD X;
-  typedef LargeD L;
+  typedef XLargeD<ONCE> X;
+  typedef LargeD<ONCE> L;
   typedef WideD W;
   static constexpr bool FUSED = true, RAW = false;
   static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int, const Walk &w) {
     const GemmArgs h = halves_args(ga);
-    if (ga.N % 48 == 0) gemm_tiles<SkinnyW96, EpiSwiGLUHalves<bf16_t, 48>, false>(h, EpiSwiGLUHalves<bf16_t, 48>{e.act, ga.N}, M, row_lo, INT_MAX, 1, w);
-    else gemm_tiles<SkinnyH128, EpiSwiGLUHalves<bf16_t, 64>, false>(h, EpiSwiGLUHalves<bf16_t, 64>{e.act, ga.N}, M, row_lo, INT_MAX, 1, w);
+    if (ga.N % 48 == 0) gemm_tiles<SkinnyW96<ONCE>, EpiSwiGLUHalves<bf16_t, 48>, false>(h, EpiSwiGLUHalves<bf16_t, 48>{e.act, ga.N}, M, row_lo, INT_MAX, 1, w);
+    else gemm_tiles<SkinnyH128<ONCE>, EpiSwiGLUHalves<bf16_t, 64>, false>(h, EpiSwiGLUHalves<bf16_t, 64>{e.act, ga.N}, M, row_lo, INT_MAX, 1, w);
   }
 };
 
@@ -35,15 +35,19 @@ void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const vo
   const EpiSwiGLU<bf16_t> e{(bf16_t *)act, N};
   const WSeg seg = wseg_one(wg, N);
   const GemmArgs ga = gemm_args(A, rows, K, seg, wu, nullptr);
+  const bool once = past_l2(2 * N, K);
   const bool streamable = N % 48 == 0 || N % 64 == 0;
   if (rows.cap <= STREAM_ROWS && streamable) {
-    if (N % 48 == 0) run_tiles<SkinnyW96, false>(halves_args(ga), EpiSwiGLUHalves<bf16_t, 48>{(bf16_t *)act, N}, 1, s);
-    else run_tiles<SkinnyH128, false>(halves_args(ga), EpiSwiGLUHalves<bf16_t, 64>{(bf16_t *)act, N}, 1, s);
+    with_once(once, [&](auto o) {
+      constexpr bool ONCE = decltype(o)::value;
+      if (N % 48 == 0) run_tiles<SkinnyW96<ONCE>, false>(halves_args(ga), EpiSwiGLUHalves<bf16_t, 48>{(bf16_t *)act, N}, 1, s);
+      else run_tiles<SkinnyH128<ONCE>, false>(halves_args(ga), EpiSwiGLUHalves<bf16_t, 64>{(bf16_t *)act, N}, 1, s);
+    });
   } else if (!ring_ok(A, K, seg, N)) {
     run_tiles<LargeD8, false>(ga, e, 1, s);
   } else {
     const PlanArgs pa = swiglu_plan_args(N, K, cus_of_xcd());
-    run_planned<SwigluKind>(ga, e, pa, plan_here(ga, pa), nullptr, s);
+    with_once(once, [&](auto o) { run_planned<SwigluKind<decltype(o)::value>>(ga, e, pa, plan_here(ga, pa), nullptr, s); });
   }
 }
 

@@ -320,6 +320,14 @@ inline bool few_of_room(bool count_on_device, int cap, size_t tokens) { return c
 inline bool few_results(bool known, int cap, int qkv_cols) { return !known && cap < FINISH_ROWS && qkv_cols < FINISH_COLS; }
 inline bool finishing_kernel(bool few, const GemmPlan &full) { return !few && full.sk == 1; }
 
+// Matrices of 16 MiB and more go past the L2 where one workgroup alone reads a weight.  The caches keep a layer of smaller ones until the
+// next step, and its kernels do without the loops for it, which make them longer for all rows.  Steps with three layers' weights in
+// turn, us, past the L2 / through it: hidden 1024 (layer of 25 MB, largest matrix 11 MB) 100 rows 70.2 / 68.4, 112 rows 68.9 / 66.0, 232
+// rows 69.2 / 67.5; hidden 2048 (100 MB, matrices of 22, 25 and 45 MB) 20 rows 76.8 / 80.7, 100 rows 93.0 / 96.9, 140 rows
+// 94.0 / 96.4; 28 over 4 heads (466 MB) 100 rows 180.6 / 188.6.  (One layer of hidden 2048 called again and again, as no
+// model does, finds its weights in the last-level cache: 100 rows 93.0 / 87.6.)
+inline bool past_l2(int n_rows_w, int K) { return (size_t)n_rows_w * (size_t)K * 2 >= ((size_t)16 << 20); }
+
 // The ring loop's weight copies have one lane offset for all of a tile: the rows they gather lie in one group of
 // RING_GROUP weight rows, and so must lie in one matrix.  (Ends of the stacked matrices; every head size the library
 // accepts is a multiple of 64.)

@@ -84,10 +84,11 @@ def test_merge_of_wave_columns_rounds_the_first_product():
 
 
 # bf16, head_dim 128: which keys are copied past the L2 is decided by the list's room (64-row tiles) or by each sequence's rows
-# (128-row tiles).  Sequences of no, one, one full and several query tiles; key counts that leave stages and tiles of
-# the pipeline partly filled.
-@pytest.mark.parametrize("heads,kv", [(4, 4), (8, 2), (64, 32)])
-@pytest.mark.parametrize("L,counts", [(70, [0, 1, 70]), (300, [16, 64, 65]), (600, [128, 0, 300])])
+# (128-row tiles), for keys and values of 64 MiB and more: the lengths of 1409 tokens, the first in 64-row tiles.  Sequences of
+# no, one, one full and several query tiles; key counts that leave stages and tiles of the pipeline partly filled.
+@pytest.mark.parametrize("heads,kv,L,counts", [(h, kv, L, c) for h, kv in ((4, 4), (8, 2), (64, 32))
+                                               for L, c in ((70, [0, 1, 70]), (300, [16, 64, 65]), (600, [128, 0, 300]))]
+                         + [(64, 32, 1409, c) for c in ([20, 0, 32], [1, 64, 31], [128, 0, 300], [64, 65, 63])])
 def test_copies_past_the_l2(heads, kv, L, counts):
     print("attention past the L2", heads, kv, L, counts, flush=True)
     s = W.LayerShape(hidden=128, n_heads=heads, n_kv_heads=kv, head_dim=128, ffn=128, dtype="bf16")

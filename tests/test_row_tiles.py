@@ -53,6 +53,7 @@ extern "C" void plan(int kind, int N, int K, long part_elems, int count, int *ou
   const GemmPlan p = plan_on_host(a, count);
   out[0] = p.xl == PLAN_X ? 256 : p.xl == PLAN_W ? 192 : 128;
   out[1] = p.sk; out[2] = p.bm; out[3] = p.row_hi;
+  out[4] = past_l2((kind == 1 ? 2 : 1) * N, K);
 }
 """
 
@@ -77,12 +78,12 @@ def test_cases_run_the_tiles_they_name(tmp_path):
         part = max(16 * min(t, 2048) * s.dq, t * max(s.dq + 2 * s.dkv, s.hidden))  # the context's fp32 scratch
         for name, want in plans.items():
             kind, n, k = gemms[name]
-            out = (C.c_int * 4)()
+            out = (C.c_int * 5)()
             lib.plan(kind, n, k, C.c_long(part), count, out)
             assert tuple(out[:3]) == want, (count, name, tuple(out))
             seen.add((out[0], out[2]))
         for name, (kind, n, k) in gemms.items():  # 16-row blocks of a wave in the whole tiles and in the last one
-            out = (C.c_int * 4)()
+            out = (C.c_int * 5)()
             lib.plan(kind, n, k, C.c_long(part), count, out)
             if out[3] == count:
                 unit = 64 if out[0] == 192 else 32
@@ -141,7 +142,9 @@ def test_dense_step_of_as_many_rows(case):
 
 # Rows that all lie in one row tile of more than half the height: weights copied past the L2, in loops that exist for some of the
 # tiles' shapes only.
+# (matrices of 16 MiB and more; the same loops copy those of "small" through the L2)
 ONE_TILE = {"wide": (WIDE, [143, 161, 224, 245]), "grouped": (W.DREAM, [129, 192, 200, 256])}
+SMALL_TILE = {"small": (SMALL, [129, 161, 224, 256])}
 
 
 def _one_tile_plans(lib, s, count):
@@ -150,9 +153,9 @@ def _one_tile_plans(lib, s, count):
     plans = {}
     for name, (kind, n, k) in {"qkv": (0, s.dq + 2 * s.dkv, s.hidden), "oproj": (0, s.hidden, s.dq), "gate_up": (1, s.ffn, s.hidden),
                                "down": (2, s.hidden, s.ffn)}.items():
-        out = (C.c_int * 4)()
+        out = (C.c_int * 5)()
         lib.plan(kind, n, k, C.c_long(part), count, out)
-        if count <= out[2] and -(-count // (64 if out[0] == 192 else 32)) > (2 if out[0] == 192 else 4):
+        if out[4] and count <= out[2] and -(-count // (64 if out[0] == 192 else 32)) > (2 if out[0] == 192 else 4):
             plans[name] = tuple(out[:3])
     return plans
 
@@ -177,12 +180,12 @@ def test_few_rows_take_the_shapes_that_have_loops_for_them(tmp_path):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("case", sorted(ONE_TILE))
+@pytest.mark.parametrize("case", sorted(ONE_TILE) + sorted(SMALL_TILE))
 def test_layer_of_rows_in_one_tile(case):
     from paper_2603_08026_amd.layer import Layer
     from tests.helpers import rand_weights
     from tests.test_gpu_planned_gemm import _check
-    shape, counts = ONE_TILE[case]
+    shape, counts = {**ONE_TILE, **SMALL_TILE}[case]
     lay = Layer.from_shape(shape, 1, 600)
     w = rand_weights(shape, 60, bias=True)
     lay.set_weights(w)
