@@ -50,8 +50,12 @@ struct NormIn {
 // and what a row is divided by goes out of its products: no launch and no pass of its own.
 // PAIRS (q|k|v): the columns of a tile are those of TN / 2 pairs (p, p + dh / 2) of heads: 16 columns hold eight pairs, partners
 // 32 lanes apart; of two blocks of 16 the second holds the partners of the first.
+// Waves per SIMD: left to itself the compiler orders the norm's loop for fewer registers as soon as anything is added behind it, with a
+// wait for all loads every few products; for at most three waves it asks for half a step's operands at once.  With the rows that overflow
+// (below) looked after, us: hidden 4096, 90 / 186 / 458 rows 792 -> 682, 1258 -> 1132, 2996 -> 2768; hidden 2048, 821 rows 1226 -> 1140; hidden
+// 1024, 913 rows 465 -> 457; hidden 256 equal.
 template <typename Epi, int MT, int NT, bool NORM>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, const int32_t *gather,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NORM ? 2 : 1, NORM ? 3 : 8))) void k_gemm_f32(const float *__restrict__ A, const int32_t *gather,
                                                    int lda, Rows rows, int K, int N, WSeg seg,
                                                    const float *__restrict__ W2, NormIn norm, Epi epi) {
   constexpr int TM = 16 * MT, TN = 16 * NT, NMAT = Epi::DUAL ? 2 : 1;
@@ -82,16 +86,14 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, c
       const int j = min(m0 + 16 * i + l16, M - 1);  // rows past the end are clamped; their results are never stored
       ap[i] = A + (size_t)(gather ? gather[j] : j) * lda + 4 * lq;
     }
-    auto weight_row = [&](int t, int x) -> const float * {  // of column x of the tile, looked up in the stacked weight matrices
-      const int n = column(tn, x);
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+      const int n = column(tn, 16 * c + l16);  // looked up in the stacked weight matrices
       const bool in1 = n >= seg.n_end[0], in2 = n >= seg.n_end[1];
       const int start = in2 ? seg.n_end[1] : in1 ? seg.n_end[0] : 0;
-      return t == 1 ? W2 + (size_t)n * K : (const float *)(in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0]) + (size_t)(n - start) * K;
-    };
-#pragma unroll
-    for (int c = 0; c < NT; ++c)
-#pragma unroll
-      for (int t = 0; t < NMAT; ++t) wp[t][c] = weight_row(t, 16 * c + l16) + 4 * lq;
+      wp[0][c] = (const float *)(in2 ? seg.w[2] : in1 ? seg.w[1] : seg.w[0]) + (size_t)(n - start) * K + 4 * lq;
+      if (NMAT == 2) wp[NMAT - 1][c] = W2 + (size_t)n * K + 4 * lq;
+    }
     floatx4 acc[NMAT][MT][NT];
 #pragma unroll
     for (int t = 0; t < NMAT; ++t)
@@ -177,13 +179,17 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, c
           }
         if constexpr (NORM) {
           // Squares whose sum overflows make the factor 0, and their products may have overflowed as well: those of the
-          // normalised elements, 0 or NaN, are taken instead.
+          // normalised elements, 0 or NaN, are taken instead.  (Addresses computed anew, not kept across the loop over K.)
           if (scale == 0.0f) {
-            const float *xr = ap[i] - 4 * lq;
+            int jr = min(m0 + 16 * i + l16, M - 1), tile_n = tn;
+            asm volatile("" : "+v"(jr), "+s"(tile_n));
+            const float *xr = A + (size_t)(gather ? gather[jr] : jr) * lda;
             for (int c = 0; c < NT; ++c)
               for (int t = 0; t < NMAT; ++t)
                 for (int e = 0; e < 4; ++e) {
-                  const float *wr = weight_row(t, 16 * c + 4 * lq) + (size_t)e * K;
+                  const int n = column(tile_n, 16 * c + 4 * lq) + e;
+                  const int in = n >= seg.n_end[1] ? 2 : n >= seg.n_end[0] ? 1 : 0;
+                  const float *wr = t == 1 ? W2 + (size_t)n * K : (const float *)(in == 2 ? seg.w[2] : in == 1 ? seg.w[1] : seg.w[0]) + (size_t)(n - (in ? seg.n_end[in - 1] : 0)) * K;
                   float sum = 0.f;
                   for (int k = 0; k < K; ++k) sum += xr[k] * scale * norm.gain[k] * wr[k];
 #pragma unroll

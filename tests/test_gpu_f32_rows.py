@@ -1,7 +1,7 @@
 """fp32 projections that normalise their rows on the way and finish them (q|k|v with bias, rotation and merge; the FFN half with
 residual and norm), against the same steps in 64 bits: rows at the edges of 16- and 32-row tiles, one and two 16-column
 blocks a tile (few and many tiles), heads of 64 and 128 columns, grouped heads, bias, sequence lengths that are no power of two,
-widths with fewer K steps than waves.  fp32 sums of at most 1536 products of order one: 1e-5 of the result's norm."""
+widths with fewer K steps than waves.  fp32 sums of at most 2816 products of order one: 1e-5 of the result's norm."""
 import pytest
 import torch
 
@@ -13,6 +13,8 @@ SHAPES = {
     "dh64": W.LayerShape(hidden=256, n_heads=4, n_kv_heads=4, head_dim=64, ffn=768, dtype="f32"),
     "dh64-gqa": W.LayerShape(hidden=320, n_heads=6, n_kv_heads=2, head_dim=64, ffn=448, dtype="f32"),
     "dh128": W.LayerShape(hidden=64, n_heads=6, n_kv_heads=3, head_dim=128, ffn=1536, dtype="f32"),
+    # every wave with several steps of K
+    "wide": W.LayerShape(hidden=1024, n_heads=16, n_kv_heads=16, head_dim=64, ffn=2816, dtype="f32"),
 }
 
 
