@@ -214,7 +214,8 @@ int dyllm_layer_step(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_layer_c
  *   The step's tokens are the positions [row_lo, L) of every sequence: row_lo = 0 is a whole-sequence
  *   step, row_lo = L_P a response-only step (Sec. 3.5), in which the tokens below row_lo keep every
  *   cache row and take no part in the test, while keys and values still cover the whole sequence
- *   (App. C.4).  idx_in must hold tokens of the step only.
+ *   (App. C.4).  idx_in must hold tokens of the step only.  (Not looked at: of another token keys and
+ *   values would be refreshed, its context would stay and its log-normaliser become undefined.)
  *   q of ALL tokens of the step is recomputed from x; K, V of the tokens in idx_in are recomputed and
  *   merged into the caches, dV = V_new - V_cache of those tokens taken before the merge;
  *   C[idx_in]  = softmax(q K^T / sqrt(dh)) V            (against the merged caches),
