@@ -39,7 +39,8 @@ struct dyllm_ctx {
   void *fs;        // [R, d]        RMSNorm(h)
   void *act;       // [R, F]        silu(gate)*up
   int32_t *status; // device status word
-  int32_t *plan;   // four words of the last GEMM's plan, for the row kernel behind it
+  // words of the GEMMs' plans that are made on the device, for the GEMMs and the row kernels behind them: raw results, gate|up, down projection
+  int32_t *plan, *plan_up, *plan_down;
   int32_t *scan;   // words of the chained compaction kernel; all zero between calls
   float *rope;     // [max_seq, dh/2, 2]
   // optional per-stage timing (dyllm_profile_begin / _end)
@@ -208,17 +209,18 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
     // (a caller may hand over x for a result: its rows are then normalised first, in a launch of their own)
     const size_t T = (size_t)B * L, xb = T * c.hidden * 4, kvb = T * ctx->dkv * 4;
     const bool over_x = overlap(x, xb, q_out, (size_t)rows.cap * ctx->dq * 4) || overlap(x, xb, cache->k, kvb) || overlap(x, xb, cache->v, kvb);
-    if (over_x) launch_gather_rmsnorm(F32, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, s);
+    if (over_x) launch_gather_rmsnorm(F32, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, PlanJob{}, s);
     prof_mark(ctx, ST_GATHER_NORM, s);
     launch_qkv_f32(over_x ? ctx->ns : x, over_x ? nullptr : w->g_attn, c.rms_eps, rows, c.hidden, seg, out, s);
     prof_mark(ctx, ST_GEMM_QKV, s);
     prof_mark(ctx, ST_ROPE_SCATTER, s);
     return check_launch(ctx, "qkv refresh");
   }
-  launch_gather_rmsnorm(BF16, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, s);
+  const GemmA A{ctx->ns, nullptr, c.hidden};
+  const PlanJob job = plan_gemm_raw(BF16, A, rows, c.hidden, seg, ctx->part_elems, ctx->plan, out);
+  launch_gather_rmsnorm(BF16, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, job, s);
   prof_mark(ctx, ST_GATHER_NORM, s);
-  const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, nullptr, c.hidden}, rows, c.hidden, seg,
-                                     ctx->part_o, ctx->part_elems, ctx->plan, out, s);
+  const Splits splits = launch_gemm_raw(BF16, A, rows, c.hidden, seg, ctx->part_o, ctx->part_elems, ctx->plan, job, out, s);
   prof_mark(ctx, ST_GEMM_QKV, s);
   launch_qkv_finalize(dt(ctx), ctx->part_o, splits, rows, out, nullptr, s);
   prof_mark(ctx, ST_ROPE_SCATTER, s);
@@ -255,6 +257,7 @@ int enqueue_ffn(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, con
                 Rows rows, void *out_cache, size_t n_tokens, hipStream_t s) {
   const dyllm_layer_cfg &c = ctx->cfg;
   const GemmA A{c_all, rows.idx, ctx->dq, n_tokens};
+  PlanJob up{}, down{};
   if (dt(ctx) == F32) {
     launch_oproj_f32(A, rows, ctx->dq, c.hidden, w->wo, x, ctx->hs, s);
     prof_mark(ctx, ST_GEMM_OPROJ, s);
@@ -262,15 +265,17 @@ int enqueue_ffn(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, con
     launch_swiglu_f32(ctx->hs, w->g_ffn, c.rms_eps, rows, c.hidden, c.ffn_dim, w->w_gate, w->w_up, ctx->act, s);
   } else {
     const Splits splits = launch_gemm_raw(BF16, A, rows, ctx->dq, wseg_one(w->wo, c.hidden), ctx->part_o, ctx->part_elems, ctx->plan,
-                                          raw_beside(c.n_heads, c.n_kv_heads, c.head_dim, n_tokens), s);
+                                          PlanJob{}, raw_beside(c.n_heads, c.n_kv_heads, c.head_dim, n_tokens), s);
+    up = plan_gemm_swiglu(rows, c.hidden, c.ffn_dim, ctx->plan_up);
+    down = plan_gemm_down(BF16, rows, c.ffn_dim, c.hidden, ctx->part_elems, ctx->plan_down);
     prof_mark(ctx, ST_GEMM_OPROJ, s);
-    launch_oproj_finalize(ctx->part_o, splits, x, w->g_ffn, rows, c.hidden, c.rms_eps, ctx->hs, ctx->fs, s);
+    launch_oproj_finalize(ctx->part_o, splits, x, w->g_ffn, rows, c.hidden, c.rms_eps, ctx->hs, ctx->fs, up, down, s);
     prof_mark(ctx, ST_NORM_FFN, s);
-    launch_gemm_swiglu(ctx->fs, rows, c.hidden, c.ffn_dim, w->w_gate, w->w_up, ctx->act, s);
+    launch_gemm_swiglu(ctx->fs, rows, c.hidden, c.ffn_dim, w->w_gate, w->w_up, ctx->act, up, s);
   }
   prof_mark(ctx, ST_GEMM_SWIGLU, s);
   launch_gemm_down(dt(ctx), ctx->act, rows, c.ffn_dim, c.hidden, w->w_down,
-                   ctx->hs, out_cache, ctx->part_o, ctx->part_elems, ctx->plan, s);
+                   ctx->hs, out_cache, ctx->part_o, ctx->part_elems, down, s);
   prof_mark(ctx, ST_GEMM_DOWN, s);
   return check_launch(ctx, "salient ffn");
 }
@@ -380,27 +385,29 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
                                             // attention passes find it from a token id
   int rc;
   ctx->prof_cur = nullptr;  // no per-stage timing on this path
+  // k, v of the salient tokens
+  WSeg kv;
+  kv.w[0] = w->wk; kv.w[1] = w->wv; kv.w[2] = w->wv;
+  kv.n_end[0] = ctx->dkv; kv.n_end[1] = 2 * ctx->dkv; kv.n_end[2] = 2 * ctx->dkv;
+  const GemmA kv_a = shared ? GemmA{ctx->ns, rin.idx, c.hidden, T} : GemmA{ctx->fs, nullptr, c.hidden, T};
+  const QkvOut kv_beside = raw_beside(c.n_heads, c.n_kv_heads, c.head_dim, T);
+  const PlanJob kv_job = plan_gemm_raw(dt(ctx), kv_a, rin, c.hidden, kv, ctx->part_elems, ctx->plan, kv_beside);
   // norm and q projection (+ rotation) of EVERY token of the step  [Alg. 3: Q <- q_proj(x)]
   {
     const QkvOut out{ctx->qs, nullptr, nullptr, w->bq, nullptr, nullptr, ctx->rope, c.n_heads, 0, c.head_dim, L, by_token, (size_t)B * L};
     if (dt(ctx) == F32) {
       launch_qkv_f32(x, w->g_attn, c.rms_eps, all, c.hidden, wseg_one(w->wq, ctx->dq), out, s);
     } else {
-      launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, shared, s);
+      launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, shared, shared ? kv_job : PlanJob{}, s);
       const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, shared ? all.idx : nullptr, c.hidden, T}, all, c.hidden,
-                                            wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, out, s);
+                                            wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, PlanJob{}, out, s);
       launch_qkv_finalize(BF16, ctx->part_o, splits, all, out, nullptr, s);
     }
   }
   // k, v of the salient tokens: norm, projection, rotation, value residual, merge into the caches
-  if (!shared) launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, 0, s);
+  if (!shared) launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, 0, kv_job, s);
   {
-    WSeg seg;
-    seg.w[0] = w->wk; seg.w[1] = w->wv; seg.w[2] = w->wv;
-    seg.n_end[0] = ctx->dkv; seg.n_end[1] = 2 * ctx->dkv; seg.n_end[2] = 2 * ctx->dkv;
-    const GemmA A = shared ? GemmA{ctx->ns, rin.idx, c.hidden, T} : GemmA{ctx->fs, nullptr, c.hidden, T};
-    const Splits splits = launch_gemm_raw(dt(ctx), A, rin, c.hidden, seg,
-                                       ctx->part_o, ctx->part_elems, ctx->plan, raw_beside(c.n_heads, c.n_kv_heads, c.head_dim, T), s);
+    const Splits splits = launch_gemm_raw(dt(ctx), kv_a, rin, c.hidden, kv, ctx->part_o, ctx->part_elems, ctx->plan, kv_job, kv_beside, s);
     // value residual: by token or by sequence into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
     // entry; the last two next to a compact copy of the new keys; and the step's candidates in the token -> entry map
     const CandidateOut cand{cached_norm ? ctx->dc : ctx->dv_full, cached_norm || by_sequence ? ctx->ksal : nullptr,
@@ -561,7 +568,7 @@ int dyllm_create(const dyllm_layer_cfg *cfg, dyllm_ctx **out) {
   ctx->part_elems = l.part_elems;
   ctx->cosb = (float *)(b + l.cosb); ctx->flag = (uint8_t *)(b + l.flag);
   ctx->hs = (float *)(b + l.hs); ctx->fs = b + l.fs; ctx->act = b + l.act;
-  ctx->status = (int32_t *)(b + l.status); ctx->plan = ctx->status + 8; ctx->rope = (float *)(b + l.rope);
+  ctx->status = (int32_t *)(b + l.status); ctx->plan = ctx->status + 8; ctx->plan_up = ctx->plan + mm::PLAN_WORDS; ctx->plan_down = ctx->plan_up + mm::PLAN_WORDS; ctx->rope = (float *)(b + l.rope);
   ctx->dv_full = b + l.dv_full; ctx->dc = b + l.dc; ctx->csal = b + l.csal; ctx->pos = (int32_t *)(b + l.pos);
   ctx->win_idx = (int32_t *)(b + l.win_idx); ctx->win_off = (int32_t *)(b + l.win_off);
   ctx->ksal = b + l.ksal; ctx->scan = (int32_t *)(b + l.scan);

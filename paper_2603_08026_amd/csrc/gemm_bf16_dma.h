@@ -1043,25 +1043,26 @@ __global__ __launch_bounds__(SH::NT) void k_gemm_bf16(GemmArgs ga, Epi epi, int 
 // rows), by the plan that fits the rows that exist (gemm_plan.h).  One workgroup per CU.
 //   Kind::Epi      fused epilogue of the row tiles; Kind::FUSED / RAW: which of its forms exist
 //   Kind::X, L, W  tile shapes (W: void where there is none); Kind::stream(...) runs the weight-streaming tiles
-// planned: the plan was made on the host (the count is known there).  plan_out (optional): the splits,
-// for the row kernels (Splits::dev).
+//   Kind::PLANS    the kernel may have to make its plan
+// planned: PLAN_GIVEN: pl (the count is known on the host); PLAN_MADE: words, by the row kernel before; PLAN_HERE: made by every
+// workgroup, the first of which leaves it in words for the row kernels (Splits::dev).
+enum Planned { PLAN_GIVEN, PLAN_MADE, PLAN_HERE };
 template <typename Kind>
 __global__ __launch_bounds__(256) void k_gemm_planned(GemmArgs ga, typename Kind::Epi epi, PlanArgs pa, GemmPlan pl,
-                                                      int planned, int32_t *plan_out) {
+                                                      Planned planned, int32_t *words) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
   Walk walk = walk_of(smem_raw);
   const int M = rows_that_exist(ga.rows);
-  if (!planned) {
-    pl = plan_on_device(pa, M, walk.wave, (uint32_t *)smem_raw);
-    __syncthreads();  // (the words are read before anything is copied over them)
+  if (planned == PLAN_MADE) pl = load_plan(words);
+  if constexpr (Kind::PLANS) {
+    if (planned == PLAN_HERE) {
+      pl = plan_on_device(pa, M, walk.wave, (uint32_t *)smem_raw);
+      __syncthreads();  // (the words are read before anything is copied over them)
+    }
   }
   if constexpr (Kind::Epi::QKV > 0) walk.whole = pl.sk == 1 && epi.o.tab;
-  if (plan_out && blockIdx.x == 0 && threadIdx.x == 0) {
-    plan_out[0] = pl.sk;
-    plan_out[1] = pl.row_hi;
-    plan_out[2] = pl.sk_tail;
-    // rows whose results are in place
-    plan_out[3] = (walk.whole || Kind::FUSED) && pl.sk == 1 ? pl.row_hi : 0;
+  if constexpr (Kind::PLANS) {
+    if (planned == PLAN_HERE && blockIdx.x == 0 && threadIdx.x == 0) store_plan(pl, walk.whole, words);
   }
   if (pl.row_hi > 0) {
     if (Kind::RAW && (!Kind::FUSED || pl.sk > 1)) {

@@ -10,16 +10,42 @@ template <bool ONCE> struct DownKind {  // residual + scatter in the epilogue, o
   typedef XLargeS X;
   typedef LargeS<ONCE> L;
   typedef void W;
-  static constexpr bool FUSED = true, RAW = true;
+  static constexpr bool FUSED = true, RAW = true, PLANS = false;
   static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
     gemm_tiles<SkinnyN64<ONCE>, Epi, true>(ga, e, M, row_lo, INT_MAX, sk, w);
   }
 };
 
+// What the plans of row tiles are made from, and whether a sum kernel follows
+struct DownChoice {
+  PlanArgs pa;
+  bool sums;
+};
+DownChoice choose_down(const Rows &rows, int N, int K, size_t part_elems) {
+  DownChoice c{down_plan_args(N, K, part_elems, true, cus_of_xcd()), true};
+  const bool known = plan_known(rows);
+  c.sums = known || down_has_sums(c.pa, rows.cap, false);
+  if (!c.sums) c.pa.split_ok = c.pa.stream_cols = 0;
+  if (known) c.pa.sum_us = 4.0f;
+  return c;
+}
+
 }  // namespace
 
+PlanJob gemm_bf16_down_plan(Rows rows, int K, int N, size_t part_elems, int32_t *plan_dev) {
+  PlanJob job{};
+  if (rows.cap <= STREAM_ROWS || plan_known(rows) || !ring_ok(GemmA{nullptr, nullptr, K}, K, wseg_one(nullptr, N), N)) return job;
+  const DownChoice c = choose_down(rows, N, K, part_elems);
+  job.args = c.pa;
+  job.rows = rows;
+  job.words = plan_dev;
+  job.sums = c.sums;
+  job.finishes = true;
+  return job;
+}
+
 void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const float *h, void *out,
-                    float *part, size_t part_elems, int32_t *plan_dev, hipStream_t s) {
+                    float *part, size_t part_elems, const PlanJob &job, hipStream_t s) {
   if (rows.cap <= 0) return;
   const EpiDown<bf16_t> e{h, (bf16_t *)out, N};
   const WSeg seg = wseg_one(wd, N);
@@ -44,13 +70,12 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
     }
     run_tiles<LargeS8, true>(ga, e, sp.n, s);
   } else {
-    const bool known = plan_known(rows), sums = known || down_has_sums(pa, rows.cap, false);
-    if (!sums) pa.split_ok = pa.stream_cols = 0;
-    if (known) pa.sum_us = 4.0f;
-    const GemmPlan pl = plan_here(ga, pa);
-    with_once(once, [&](auto o) { run_planned<DownKind<decltype(o)::value>>(ga, e, pa, pl, plan_dev, s); });
-    if (!sums || (known && pl.sk == 1 && pl.row_hi == rows.cap)) return;
-    sp = splits_of(ga, pl, true, plan_dev);
+    const bool known = plan_known(rows);
+    const DownChoice c = known ? choose_down(rows, N, K, part_elems) : DownChoice{job.args, job.sums};
+    const GemmPlan pl = plan_here(ga, c.pa);
+    with_once(once, [&](auto o) { run_planned<DownKind<decltype(o)::value>>(ga, e, c.pa, pl, job.words, true, s); });
+    if (!c.sums || (known && pl.sk == 1 && pl.row_hi == rows.cap)) return;
+    sp = splits_of(ga, pl, true, job.words);
   }
   launch_down_finalize(part, sp, h, rows, N, out, s);
 }

@@ -90,18 +90,18 @@ int ring_grid() { return std::max(N_XCD, cu_count() / N_XCD * N_XCD); }
 int cus_of_xcd() { return ring_grid() / N_XCD; }
 bool plan_known(const Rows &rows) { return mm::plan_known(rows.count != nullptr, rows.cap); }
 
+constexpr GemmPlan NO_PLAN{0, 1, 0, 1, 256};
 // The plan of a GEMM whose row count the host knows; anything else is planned on the device
-GemmPlan plan_here(const GemmArgs &ga, const PlanArgs &pa) {
-  return plan_known(ga.rows) ? plan_on_host(pa, ga.rows.cap) : GemmPlan{0, 1, 0, 1, 256};
-}
+GemmPlan plan_here(const GemmArgs &ga, const PlanArgs &pa) { return plan_known(ga.rows) ? plan_on_host(pa, ga.rows.cap) : NO_PLAN; }
 
-// GEMM of `rows` in row tiles by a plan: `pl` of plan_here, or the device's, which leaves the splits in plan_dev
+// GEMM of `rows` in row tiles by a plan: `pl` of plan_here, or the device's in the words of plan_dev, which a row kernel has
+// left there (made) or this one leaves
 template <typename Kind>
 void run_planned(const GemmArgs &ga, typename Kind::Epi epi, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev,
-                 hipStream_t s) {
-  const int known = plan_known(ga.rows);
+                 bool made, hipStream_t s) {
+  const Planned planned = plan_known(ga.rows) ? PLAN_GIVEN : made ? PLAN_MADE : PLAN_HERE;
   set_lds_once_planned<Kind>();
-  k_gemm_planned<Kind><<<ring_grid(), 256, RING_SLOTS * RING_SLOT, s>>>(ga, epi, pa, pl, known, known ? nullptr : plan_dev);
+  k_gemm_planned<Kind><<<ring_grid(), 256, RING_SLOTS * RING_SLOT, s>>>(ga, epi, pa, pl, planned, planned == PLAN_GIVEN ? nullptr : plan_dev);
 }
 
 // fused: row tiles finish their rows where K is not split
@@ -121,7 +121,7 @@ template <typename E, bool ONCE> struct RawKind {
   typedef XLargeS X;
   typedef LargeS<ONCE> L;
   typedef WideS W;
-  static constexpr bool FUSED = false, RAW = true;
+  static constexpr bool FUSED = false, RAW = true, PLANS = true;
   static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int sk, const Walk &w) {
     if (ga.N % SkinnyW96<ONCE>::BN == 0) gemm_tiles<SkinnyW96<ONCE>, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);
     else gemm_tiles<SkinnyN64<ONCE>, EpiStoreF32, true>(ga, e, M, row_lo, INT_MAX, sk, w);

@@ -17,14 +17,14 @@ inline void division_by(uint32_t d, uint32_t *mul, uint32_t *shift) {
 }
 
 template <int DH>
-Splits run_qkv(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, hipStream_t s) {
+Splits run_qkv(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made, hipStream_t s) {
   EpiQkv<DH> e;
   e.out = part;
   e.ldo = ga.N;
   e.o = out;
   e.l_mul = e.l_shift = 0;
   if (out.tab) division_by((uint32_t)out.L, &e.l_mul, &e.l_shift);
-  with_once(past_l2(ga.N, ga.K), [&](auto once) { run_planned<RawKind<EpiQkv<DH>, decltype(once)::value>>(ga, e, pa, pl, plan_dev, s); });
+  with_once(past_l2(ga.N, ga.K), [&](auto once) { run_planned<RawKind<EpiQkv<DH>, decltype(once)::value>>(ga, e, pa, pl, plan_dev, made, s); });
   return splits_of(ga, pl, out.tab != nullptr, plan_dev);
 }
 

@@ -3,9 +3,9 @@
 
 namespace dy {
 
-Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev,
+Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made,
                         hipStream_t s) {
-  return run_qkv<64>(ga, part, out, pa, pl, plan_dev, s);
+  return run_qkv<64>(ga, part, out, pa, pl, plan_dev, made, s);
 }
 
 }  // namespace dy

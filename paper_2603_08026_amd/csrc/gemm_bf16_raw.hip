@@ -4,19 +4,54 @@
 namespace dy {
 
 // q|k|v (gemm_bf16_qkv.hip, gemm_bf16_qkv64.hip: heads of 128 and 64 columns), or with an empty QkvOut any raw result
-Splits gemm_bf16_qkv128(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, hipStream_t s);
-Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, hipStream_t s);
+Splits gemm_bf16_qkv128(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made, hipStream_t s);
+Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made, hipStream_t s);
+
+namespace {
+
+// What a raw result in row tiles is made from: the plan of a full list, and whether the kernel that can finish rows is taken
+struct RawChoice {
+  PlanArgs pa;
+  GemmPlan full;
+  bool finishing;
+};
+// (positions come from a division by at least two, rotary table entries from 32-bit offsets)
+bool can_finish(const QkvOut &qkv) { return qkv.tab && qkv.L >= 2 && (size_t)qkv.L * qkv.dh * 4 < ((size_t)1 << 31); }
+RawChoice choose_raw(const Rows &rows, int N, int K, size_t part_elems, const QkvOut &qkv) {
+  RawChoice c;
+  c.pa = raw_plan_args(N, K, part_elems, true, cus_of_xcd());
+  const bool known = plan_known(rows);
+  const bool few = few_of_room(rows.count != nullptr, rows.cap, qkv.tokens) || few_results(known, rows.cap, (qkv.H + 2 * qkv.Hkv) * qkv.dh) ||
+                   (!can_finish(qkv) && qkv.dh == 64);
+  c.full = known || !few ? plan_on_host(c.pa, rows.cap) : NO_PLAN;
+  c.finishing = finishing_kernel(few, c.full);
+  return c;
+}
+
+}  // namespace
+
+PlanJob gemm_bf16_raw_plan(GemmA A, Rows rows, int K, WSeg seg, size_t part_elems, int32_t *plan_dev, const QkvOut &qkv) {
+  PlanJob job{};
+  const int N = seg.n_end[2];
+  if (rows.cap <= STREAM_ROWS || plan_known(rows) || !ring_ok(A, K, seg, N)) return job;
+  const RawChoice c = choose_raw(rows, N, K, part_elems, qkv);
+  job.args = c.pa;
+  job.full = c.full;
+  job.rows = rows;
+  job.words = plan_dev;
+  job.finishing = c.finishing;
+  job.finishes = c.finishing && can_finish(qkv);
+  return job;
+}
 
 // raw result part[z][j][n], or rows finished as `qkv` says where it has a table; returns the numbers of K splits (on the device if the count is there)
-Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, const QkvOut &qkv,
-                     hipStream_t s) {
+Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, const PlanJob &job,
+                     const QkvOut &qkv, hipStream_t s) {
   Splits out;
   if (rows.cap <= 0) return out;
   const int N = seg.n_end[2];
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
   const bool ring = ring_ok(A, K, seg, N);
-  // (positions come from a division by at least two, rotary table entries from 32-bit offsets)
-  const bool finishes = qkv.tab && qkv.L >= 2 && (size_t)qkv.L * qkv.dh * 4 < ((size_t)1 << 31);
   PlanArgs pa = raw_plan_args(N, K, part_elems, ring, cus_of_xcd());
   const bool once = past_l2(N, K);
   if (rows.cap <= STREAM_ROWS) {
@@ -30,16 +65,14 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
     return out;
   }
   if (ring) {
-    const bool known = plan_known(rows);
-    const bool few = few_of_room(rows.count != nullptr, rows.cap, qkv.tokens) || few_results(known, rows.cap, (qkv.H + 2 * qkv.Hkv) * qkv.dh) ||
-                     (!finishes && qkv.dh == 64);
-    const GemmPlan full = known || !few ? plan_on_host(pa, rows.cap) : GemmPlan{0, 1, 0, 1, 256};
-    if (!finishing_kernel(few, full)) {
-      with_once(once, [&](auto o) { run_planned<RawKind<EpiStoreF32, decltype(o)::value>>(ga, EpiStoreF32{part, N}, pa, full, plan_dev, s); });
-      return splits_of(ga, full, false, plan_dev);
+    const bool made = job.words != nullptr, finishes = can_finish(qkv);
+    const RawChoice c = made ? RawChoice{job.args, job.full, job.finishing} : choose_raw(rows, N, K, part_elems, qkv);
+    if (!c.finishing) {
+      with_once(once, [&](auto o) { run_planned<RawKind<EpiStoreF32, decltype(o)::value>>(ga, EpiStoreF32{part, N}, c.pa, c.full, plan_dev, made, s); });
+      return splits_of(ga, c.full, false, plan_dev);
     }
-    if (finishes && qkv.dh == 64) return gemm_bf16_qkv64(ga, part, qkv, pa, full, plan_dev, s);
-    return gemm_bf16_qkv128(ga, part, finishes ? qkv : QkvOut{}, pa, full, plan_dev, s);
+    if (finishes && qkv.dh == 64) return gemm_bf16_qkv64(ga, part, qkv, c.pa, c.full, plan_dev, made, s);
+    return gemm_bf16_qkv128(ga, part, finishes ? qkv : QkvOut{}, c.pa, c.full, plan_dev, made, s);
   }
   pa.stream_cols = 0;
   out.n = plan_of(pa, rows.cap, first_on_host(pa, rows.cap)).sk;

@@ -20,7 +20,7 @@ template <bool ONCE> struct SwigluKind {
   typedef XLargeD<ONCE> X;
   typedef LargeD<ONCE> L;
   typedef WideD W;
-  static constexpr bool FUSED = true, RAW = false;
+  static constexpr bool FUSED = true, RAW = false, PLANS = false;
   static __device__ __forceinline__ void stream(const GemmArgs &ga, const Epi &e, int M, int row_lo, int, const Walk &w) {
     const GemmArgs h = halves_args(ga);
     if (ga.N % 48 == 0) gemm_tiles<SkinnyW96<ONCE>, EpiSwiGLUHalves<bf16_t, 48>, false>(h, EpiSwiGLUHalves<bf16_t, 48>{e.act, ga.N}, M, row_lo, INT_MAX, 1, w);
@@ -28,16 +28,26 @@ template <bool ONCE> struct SwigluKind {
   }
 };
 
+bool streams(const Rows &rows, int N) { return rows.cap <= STREAM_ROWS && (N % 48 == 0 || N % 64 == 0); }
+
 }  // namespace
 
-void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const void *wu, void *act, hipStream_t s) {
+PlanJob gemm_bf16_swiglu_plan(Rows rows, int K, int N, int32_t *plan_dev) {
+  PlanJob job{};
+  if (rows.cap <= 0 || streams(rows, N) || plan_known(rows) || !ring_ok(GemmA{nullptr, nullptr, K}, K, wseg_one(nullptr, N), N)) return job;
+  job.args = swiglu_plan_args(N, K, cus_of_xcd());
+  job.rows = rows;
+  job.words = plan_dev;
+  return job;
+}
+
+void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const void *wu, void *act, const PlanJob &job, hipStream_t s) {
   if (rows.cap <= 0) return;
   const EpiSwiGLU<bf16_t> e{(bf16_t *)act, N};
   const WSeg seg = wseg_one(wg, N);
   const GemmArgs ga = gemm_args(A, rows, K, seg, wu, nullptr);
   const bool once = past_l2(2 * N, K);
-  const bool streamable = N % 48 == 0 || N % 64 == 0;
-  if (rows.cap <= STREAM_ROWS && streamable) {
+  if (streams(rows, N)) {
     with_once(once, [&](auto o) {
       constexpr bool ONCE = decltype(o)::value;
       if (N % 48 == 0) run_tiles<SkinnyW96<ONCE>, false>(halves_args(ga), EpiSwiGLUHalves<bf16_t, 48>{(bf16_t *)act, N}, 1, s);
@@ -47,7 +57,7 @@ void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const vo
     run_tiles<LargeD8, false>(ga, e, 1, s);
   } else {
     const PlanArgs pa = swiglu_plan_args(N, K, cus_of_xcd());
-    with_once(once, [&](auto o) { run_planned<SwigluKind<decltype(o)::value>>(ga, e, pa, plan_here(ga, pa), nullptr, s); });
+    with_once(once, [&](auto o) { run_planned<SwigluKind<decltype(o)::value>>(ga, e, pa, plan_here(ga, pa), job.words, true, s); });
   }
 }
 

@@ -5,9 +5,11 @@
 // takes the shapes of a dense step for a few hundred rows (one request batch of 8 x 1024 tokens, 330
 // salient rows: 32 tiles of the down projection on 256 CUs, 201 us against 55 us with a K split; two layers and four
 // steps of that loop 4080 -> 2424 us).
-// So the kernel makes its own plan once it has read the count: every candidate is priced by one lane of
-// a workgroup, the cheapest wins, and the row kernels that follow read the chosen split back from four words
-// of device memory.  Where the host knows the count (dense steps) it evaluates the same functions and
+// So plans are made on the device once the count is there: every candidate is priced by one lane of
+// a workgroup, the cheapest wins, and the row kernels that follow read the chosen split back from words
+// of device memory.  A workgroup of the row kernel ahead of the GEMM does that beside its rows (PlanJob, kernels.h); where there is
+// none that knows the count (the out-projection, behind the compaction) every workgroup of the GEMM does it for itself, which takes 1.7 us
+// before its first copy.  Where the host knows the count (dense steps) it evaluates the same functions and
 // passes the plan in.
 //
 // Two sets of candidates.  The first has tiles of 256 rows (plan_price).  The second has tiles of any height
@@ -380,6 +382,22 @@ __device__ __forceinline__ GemmPlan plan_on_device(const PlanArgs &a, int M, int
   if (takes_over(a, M, p, __uint_as_float(w[0] & ~63u), tile_split(c), __uint_as_float(k & ~63u)))
     p = GemmPlan{shape, tile_split(c), M, 1, tile_units(c) * (shape == PLAN_W ? 64 : 32)};
   return p;
+}
+
+// Words of a plan in device memory: the first four are those of Splits::dev
+enum PlanWord { PW_SK, PW_ROW_HI, PW_SK_TAIL, PW_DONE_TO, PW_XL, PW_BM, PLAN_WORDS = 8 };
+// done: the row tiles finish their rows where K is not split
+__device__ __forceinline__ void store_plan(const GemmPlan &p, bool done, int32_t *words) {
+  words[PW_SK] = p.sk;
+  words[PW_ROW_HI] = p.row_hi;
+  words[PW_SK_TAIL] = p.sk_tail;
+  words[PW_DONE_TO] = done && p.sk == 1 ? p.row_hi : 0;
+  words[PW_XL] = p.xl;
+  words[PW_BM] = p.bm;
+}
+__device__ __forceinline__ GemmPlan load_plan(const int32_t *words) {
+  auto w = [&](PlanWord i) -> int { return __builtin_amdgcn_readfirstlane(words[i]); };
+  return GemmPlan{w(PW_XL), w(PW_SK), w(PW_ROW_HI), w(PW_SK_TAIL), w(PW_BM)};
 }
 
 }  // namespace mm

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "gemm_plan.h"
 
 namespace dy {
 
@@ -18,7 +19,7 @@ struct Rows {
 // K splits of a raw GEMM result: the rows below tail_from hold n partial sums each, the rows from
 // tail_from on (a short last row tile in tiles of another shape) n_tail.  The split stride is the number of
 // rows that exist times the row length.  dev: the plan was made on the device, which left
-// {n, tail_from, n_tail, done_to} there; the members are then ignored.
+// {n, tail_from, n_tail, done_to} there (mm::PlanWord); the members are then ignored.
 struct Splits {
   int n = 1, tail_from = 0x7fffffff, n_tail = 1;
   int done_to = 0;  // rows below it were finished by the GEMM's own epilogue (down projection, q|k|v); at most the list's capacity
@@ -29,6 +30,18 @@ struct Splits {
     return r;
   }
   __host__ __device__ int of(int j) const { return j < tail_from ? n : n_tail; }
+};
+
+// The plan of a GEMM whose rows the device counts, to be made by a row kernel ahead of it (plan_gemm_*): a workgroup of
+// that kernel prices the candidates while the others take their rows, and the GEMM reads words.  words == nullptr: no such job.
+struct PlanJob {
+  mm::PlanArgs args;
+  mm::GemmPlan full;  // raw results: the plan of a full list, where it was looked at
+  Rows rows;
+  int32_t *words = nullptr;
+  bool finishing = false;  // raw results: the kernel that can finish rows is taken
+  bool sums = false;       // down projection: a kernel for split sums follows
+  bool finishes = false;   // the GEMM finishes the rows whose K is not split
 };
 
 // Candidates of the approximate update of a sequence (bf16, head_dim 128): up to a fifth of its tokens their keys and
@@ -63,7 +76,7 @@ struct QkvOut {
 // ---- row kernels (HBM-bound) ------------------------------------------------------------------
 // out[j,:] (by_token: out[row_j,:]) = RMSNorm(x[row_j,:]) * gain            x: [T,d] T-typed, out: [cap,d] ([T,d]) T-typed
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
-                           void *out, int by_token, hipStream_t s);
+                           void *out, int by_token, const PlanJob &job, hipStream_t s);
 // The GEMMs leave fp32 "raw" results part[z][j][n] (z = K split, j = position in the row list); the
 // finalize kernels below sum the splits and apply the fused tail of the step, one workgroup per row.
 //
@@ -87,7 +100,7 @@ void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, c
 // out-projection (bf16): h[j] = x[row_j] + sum of splits (fp32 [cap,d]); f[j] = RMSNorm(h[j]) * gain
 void launch_oproj_finalize(const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
-                           hipStream_t s);
+                           const PlanJob &job0, const PlanJob &job1, hipStream_t s);
 // down projection (bf16) after a K split: out_cache[row_j] = h[j] + sum of splits, for the rows from
 // splits.done_to on (the rows below it were written by the GEMM's own epilogue)
 void launch_down_finalize(const float *part, Splits splits, const float *h,
@@ -197,19 +210,24 @@ inline WSeg wseg_one(const void *w, int N) {
 }
 // raw GEMM: part[z][j][n] = sum over K split z of A[j,:] * W[n,:] (fp32, split stride rows*N);
 // returns the numbers of splits used (>= 1), chosen from the rows that exist, N and K (on the device, in
-// the four words `plan`, when their number is known there alone).
+// the PLAN_WORDS words `plan`, when their number is known there alone).
+// job: made by plan_gemm_raw of the same arguments and done by a row kernel since, or empty (the GEMM plans for itself).
 // qkv: where the results go in the end.  The GEMM may finish rows itself (those below Splits::done_to, which have no raw
 // result then); the row kernel finishes the others.  Without a table (raw_beside) it only says which q|k|v the result goes with.
+PlanJob plan_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, size_t part_elems, int32_t *plan, const QkvOut &qkv);
 Splits launch_gemm_raw(DType t, GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems,
-                       int32_t *plan, const QkvOut &qkv, hipStream_t s);
+                       int32_t *plan, const PlanJob &job, const QkvOut &qkv, hipStream_t s);
 inline QkvOut raw_beside(int H, int Hkv, int dh, size_t tokens) { return QkvOut{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, H, Hkv, dh, 0, 0, tokens}; }
 // up (bf16): act[j,:] = silu(A w_gate^T) * (A w_up^T), out [cap, N]; here and below A[j,:] = a[j,:], rows of K elements
+// job: made by plan_gemm_swiglu of the same rows, K and N and done by a row kernel since
+PlanJob plan_gemm_swiglu(Rows rows, int K, int N, int32_t *plan);
 void launch_gemm_swiglu(const void *a, Rows rows, int K, int N, const void *w_gate,
-                        const void *w_up, void *act, hipStream_t s);
+                        const void *w_up, void *act, const PlanJob &job, hipStream_t s);
 // down: out_cache[row_j,:] = h[j,:] + A[j,:] * w_down^T, T-typed scatter into [T, N]; `scratch`
-// holds K-split partials when K is split; plan: as for launch_gemm_raw.
+// holds K-split partials when K is split; job: as for launch_gemm_swiglu.
+PlanJob plan_gemm_down(DType t, Rows rows, int K, int N, size_t scratch_elems, int32_t *plan);
 void launch_gemm_down(DType t, const void *a, Rows rows, int K, int N, const void *w_down, const float *h,
-                      void *out_cache, float *scratch, size_t scratch_elems, int32_t *plan, hipStream_t s);
+                      void *out_cache, float *scratch, size_t scratch_elems, const PlanJob &job, hipStream_t s);
 
 // fp32: the same steps without row kernels between them.  K is never split, so a GEMM finishes its rows, and each takes its
 // operand's RMSNorm along.

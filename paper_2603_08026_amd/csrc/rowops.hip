@@ -1,6 +1,8 @@
 // Row-wise kernels of the sparse layer step: gather + RMSNorm, rotary embedding + K/V merge,
 // cosine saliency (+ context commit), stream compaction.  All are HBM-bound: one workgroup walks
 // one token row with 16-byte loads, reductions in fp32.
+#include <algorithm>
+#include <type_traits>
 #include "common.h"
 #include "compact.h"
 #include "kernels.h"
@@ -16,17 +18,34 @@ __device__ __forceinline__ int row_count(const Rows &rows) {
   return rows.count ? min(*rows.count, rows.cap) : rows.cap;
 }
 
+// The first workgroups of a row kernel, one for every job, make plans instead of taking rows (all NT threads, a multiple of four waves).  The
+// GEMM behind needs its plan as soon as it starts and would take 1.7 us to make it; here that happens beside the rows.  Hidden 4096: step of 410 listed rows 293 -> 285 us, of 2064 798.5 -> 796.9; loop of 8 x 1024 tokens 2004 -> 1956.
+template <int NT> __device__ __forceinline__ void make_plan(const PlanJob &job) {
+  __shared__ uint32_t lds[2 * NT / WAVE];  // eight words for four waves, which all make the same plan
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const mm::GemmPlan p = mm::plan_on_device(job.args, row_count(job.rows), wave % 4, lds + 8 * (wave / 4));
+  if (threadIdx.x == 0) mm::store_plan(p, job.finishes, job.words);
+}
+
 // ---- gather + RMSNorm  [Alg. 3: layernorm(x) restricted to the salient rows] -------------------
 // NT threads per row: 256 when the row fits KEEP vectors per thread (more rows in flight per CU and a
 // four-wave reduction), else RB.
-template <typename T, int NT>
+// JOB: with a plan to make (in the kernel without, which takes known rows, its code and registers would be for nothing).
+template <typename T, int NT, bool JOB>
 __global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
                                                         const T *__restrict__ gain, Rows rows, int d,
-                                                        float eps, T *__restrict__ out, int by_token) {
+                                                        float eps, T *__restrict__ out, int by_token, PlanJob job) {
   __shared__ float red[NT / WAVE];
   constexpr int N = Vec16<T>::N;
+  constexpr int first = JOB ? 1 : 0;
+  if constexpr (JOB) {
+    if (blockIdx.x == 0) {
+      make_plan<NT>(job);
+      return;
+    }
+  }
   const int n = row_count(rows), nv = d / N;
-  for (int j = blockIdx.x; j < n; j += gridDim.x) {
+  for (int j = blockIdx.x - first; j < n; j += gridDim.x - first) {
     const int r = rows.idx ? rows.idx[j] : j;
     const T *xr = x + (size_t)r * d;
     float ss = 0.f;
@@ -58,16 +77,27 @@ __global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
 
 // ---- out-projection tail  [Alg. 3: x <- layernorm(out_proj(C)), with the residual] ---------------
 // h[j] = x[row_j] + sum_z part[z][j] (kept in fp32 for the second residual), f[j] = RMSNorm(h[j]) * gain
+// JOBS: with plans to make
+template <bool JOBS>
 __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__ part, Splits splits_of,
                                                         const bf16_t *__restrict__ x,
                                                         const bf16_t *__restrict__ gain, Rows rows, int d,
                                                         float eps, float *__restrict__ h,
-                                                        bf16_t *__restrict__ f) {
+                                                        bf16_t *__restrict__ f, PlanJob job0, PlanJob job1) {
   __shared__ float red[RB / WAVE];
+  const int first = JOBS ? (job0.words ? 1 : 0) + (job1.words ? 1 : 0) : 0;
+  if constexpr (JOBS) {
+    if ((int)blockIdx.x < first) {
+      // (a selected job would be copied to scratch memory)
+      if (blockIdx.x == 0 && job0.words) make_plan<RB>(job0);
+      else make_plan<RB>(job1);
+      return;
+    }
+  }
   const int n = row_count(rows), nv = d / 4;
   const Splits sp = splits_of.resolved();
   const size_t split_stride = (size_t)n * d;
-  for (int j = blockIdx.x; j < n; j += gridDim.x) {
+  for (int j = blockIdx.x - first; j < n; j += gridDim.x - first) {
     const int r = rows.idx ? rows.idx[j] : j;
     const int splits = sp.of(j);
     const bf16_t *xr = x + (size_t)r * d;
@@ -468,29 +498,34 @@ inline int row_grid(const Rows &rows) { return row_grid(rows, rows.cap); }
 }  // namespace
 
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
-                           void *out, int by_token, hipStream_t s) {
-  if (rows.cap <= 0) return;
+                           void *out, int by_token, const PlanJob &job, hipStream_t s) {
+  if (rows.cap <= 0 && !job.words) return;
   const int most = rows.count ? 4 * GRID_LISTED : 32768;  // (a quarter of the threads per workgroup)
-  const int grid = rows.cap > most ? most : rows.cap;
-  if (t == F32) {
-    if (d / 4 <= 256 * KEEP)
-      k_gather_rmsnorm<float, 256><<<grid, 256, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out, by_token);
+  const int plans = job.words ? 1 : 0, grid = std::max(std::min(rows.cap, most), 1) + plans, wide_grid = row_grid(rows) + plans;
+  auto go = [&](auto zero, auto job_c) {
+    using T = decltype(zero);
+    constexpr bool JOB = decltype(job_c)::value;
+    if (d / Vec16<T>::N <= 256 * KEEP)
+      k_gather_rmsnorm<T, 256, JOB><<<grid, 256, 0, s>>>((const T *)x, (const T *)gain, rows, d, eps, (T *)out, by_token, job);
     else
-      k_gather_rmsnorm<float, RB><<<row_grid(rows), RB, 0, s>>>((const float *)x, (const float *)gain, rows, d, eps, (float *)out, by_token);
-  } else {
-    if (d / 8 <= 256 * KEEP)
-      k_gather_rmsnorm<bf16_t, 256><<<grid, 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out, by_token);
-    else
-      k_gather_rmsnorm<bf16_t, RB><<<row_grid(rows), RB, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, (bf16_t *)out, by_token);
-  }
+      k_gather_rmsnorm<T, RB, JOB><<<wide_grid, RB, 0, s>>>((const T *)x, (const T *)gain, rows, d, eps, (T *)out, by_token, job);
+  };
+  if (t == F32) go(float{}, std::false_type{});
+  else if (plans) go(bf16_t{}, std::true_type{});
+  else go(bf16_t{}, std::false_type{});
 }
 
 void launch_oproj_finalize(const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
-                           hipStream_t s) {
+                           const PlanJob &job0, const PlanJob &job1, hipStream_t s) {
   if (rows.cap <= 0) return;
-  k_oproj_finalize<<<row_grid(rows), RB, 0, s>>>(part, splits, (const bf16_t *)x, (const bf16_t *)gain, rows, d, eps, h,
-                                                         (bf16_t *)f);
+  const int plans = (job0.words ? 1 : 0) + (job1.words ? 1 : 0);
+  auto go = [&](auto jobs_c) {
+    k_oproj_finalize<decltype(jobs_c)::value><<<row_grid(rows) + plans, RB, 0, s>>>(part, splits, (const bf16_t *)x, (const bf16_t *)gain, rows,
+                                                                                      d, eps, h, (bf16_t *)f, job0, job1);
+  };
+  if (plans) go(std::true_type{});
+  else go(std::false_type{});
 }
 
 void launch_down_finalize(const float *part, Splits splits, const float *h,
