@@ -484,34 +484,26 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
     }
   };
 
-  // full tiles: a scalar base per tile and loop-invariant lane offsets (no vector arithmetic per copy)
-  uint32_t off_k[LPW / 2], off_v[LPW / 2];
-#pragma unroll
-  for (int i = 0; i < LPW / 2; ++i) {
-    const int ii = i * NW + wave, row = ii * 4 + r4;
-    off_k[i] = (uint32_t)(((size_t)row * kv_stride + (cpos ^ (row & 15)) * 8) * 2);
-    off_v[i] = (uint32_t)(((size_t)row * kv_stride + (((((cpos >> 1) ^ ((row & 3) << 1)) << 1) | (cpos & 1)) * 8)) * 2);
-  }
+  // full tiles: a scalar base per copy and loop-invariant lane offsets (no vector arithmetic per copy); the copies of a wave are 16
+  // rows apart, so that they share the swizzle and differ in the base alone
+  static_assert(NW * 4 % 16 == 0, "the rows of a wave's copies agree in their last four bits");
+  const int row0 = wave * 4 + r4;
+  const uint32_t off_k = (uint32_t)(((size_t)row0 * kv_stride + (cpos ^ (row0 & 15)) * 8) * 2);
+  const uint32_t off_v = (uint32_t)(((size_t)row0 * kv_stride + (((((cpos >> 1) ^ ((row0 & 3) << 1)) << 1) | (cpos & 1)) * 8)) * 2);
+  const size_t copy_step = (size_t)NW * 4 * kv_stride * 2;  // bytes between the rows of a wave's copies
   auto uniform_ptr = [](const void *p) {
     const uint64_t u = (uint64_t)p;
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
     return (const unsigned char *)(((uint64_t)hi << 32) | lo);
   };
   const unsigned char *kc_u = uniform_ptr(kc + (size_t)k_lo * kv_stride), *vc_u = uniform_ptr(vc + (size_t)k_lo * kv_stride);
-  auto issue_full = [&](int t) {  // tile t, all of whose keys exist, -> stage t % NS
-    const uint32_t sb = lds0 + (uint32_t)(t % NS) * T::STAGE_BYTES;
-    const size_t adv = (size_t)t * TK * kv_stride * 2;
-#pragma unroll
-    for (int i = 0; i < LPW / 2; ++i) {
-      const int ii = i * NW + wave;
-      if constexpr (ONCE) {
-        dma16_s_once(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
-        dma16_s_once(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
-      } else {
-        dma16_s(kc_u + adv, off_k[i], sb + (uint32_t)ii * 1024u);
-        dma16_s(vc_u + adv, off_v[i], sb + (uint32_t)T::REGION + (uint32_t)ii * 1024u);
-      }
-    }
+  // copy c of this wave's LPW of tile t, all of whose keys exist, -> stage t % NS (K and V rows in turn)
+  auto issue_one = [&](int t, int c) {
+    const uint32_t sb = lds0 + (uint32_t)(t % NS) * T::STAGE_BYTES + (uint32_t)(c & 1) * T::REGION + (uint32_t)((c >> 1) * NW + wave) * 1024u;
+    const unsigned char *base = ((c & 1) ? vc_u : kc_u) + (size_t)t * TK * kv_stride * 2 + (c >> 1) * copy_step;
+    const uint32_t off = (c & 1) ? off_v : off_k;
+    if constexpr (ONCE) dma16_s_once(base, off, sb);
+    else dma16_s(base, off, sb);
   };
 
   // per-lane constants of the operand reads
@@ -570,19 +562,19 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
 #pragma unroll
     for (int db = 0; db < DB; ++db) vf[ks][db] = pf[ks];
   }
-  auto pv = [&]() {  // O^T += V^T P^T of the tile held in vf / pf
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-        acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][db], pf[ks], acc_o[db], 0, 0, 0);
+  auto pv = [&](int ks, int db) {  // O^T += V^T P^T of the tile held in vf / pf
+    acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][db], pf[ks], acc_o[db], 0, 0, 0);
   };
-  // One tile.  Order: (1) the first K fragments of tile t+1 are requested from LDS and the maximum
-  // of tile t's scores is taken (and, rarely, the reference moved); (2) sixteen matrix instructions
-  // follow -- the P V product of tile t-1, then the score product of tile t+1 -- each with its share
-  // of tile t's exponentials behind it; the other K fragments are requested in between and the V
-  // fragments of tile t at the end, into registers the products have released.  No product waits
-  // for an LDS read issued right before it, and the vector ALU works while the matrix pipe does.
+  // One tile: sixteen matrix instructions -- the P V product of tile t-1 (0 .. 7), then the score product of tile t+1 -- with
+  // everything else dealt out between them, because a wave has the matrix pipe and the vector ALU to itself most of the time and
+  // whatever stands in a row is time in which the other waits.  Behind products 0 .. 3: the maximum of tile t's scores, the rest of
+  // the K reads; then, rarely, the reference moves; behind 4 .. 15: tile t's exponentials (one or two to a product), their rounding
+  // and sums, and the V reads of tile t into the registers that the products release, so that they have returned long before
+  // the next barrier.  The tile's copies go out one at a time, not in a burst behind the barrier where no wave multiplies.
+  // The order is pinned with scheduling barriers.  (With groups of instructions named instead, the compiler put the first eight products
+  // back to back and the maximum, the V reads and four copies in a row before the barrier; a tile took a lone wave some 1300 cycles, now
+  // 1170, and two waves of a SIMD 1600 each.  Alone, us: dense 16 x 1280 tokens, 32 heads 486 -> 459, 1 x 1024 36.2 -> 34.1; 5200 listed rows
+  // 169 -> 163.)
   // STEADY: the tile fetched in this iteration is a full one and no key of tile t lies past the end.
   // STAGE: the LDS stage of tile t when the caller knows it at compile time (the loop is unrolled over
   // the stages, so that the operand reads are a loop-invariant lane address plus an immediate), else -1.
@@ -597,19 +589,29 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
       else wait_vmcnt<0>();
     }
     __syncthreads();  // tile t+1 is in LDS (all waves' parts); everyone is done with tile t-1's stage
-    if (STEADY) issue_full(t + NS - 1);
-    else if (t + NS - 1 < n_tiles) issue(t + NS - 1);
+    if (!STEADY && t + NS - 1 < n_tiles) issue(t + NS - 1);
+    auto copy_behind = [&](int product) {
+      constexpr int EVERY = 16 / LPW;
+      if (STEADY && product % EVERY == EVERY / 2) issue_one(t + NS - 1, product / EVERY);
+    };
     const unsigned char *st = smem_raw + (size_t)sidx * T::STAGE_BYTES;
     const unsigned char *st_next = smem_raw + (size_t)((sidx + 1) % NS) * T::STAGE_BYTES;
     const int k0 = k_lo + t * TK;
 
+    constexpr bool LATE_K = WK > 1;  // (these tiles need more address registers: their K fragments arrive in two halves)
     bf16x8 kf[KK];
-    {
-      const unsigned char *skp = st_next + krow * ROWB;
+    auto read_k = [&](int kk) {
+      kf[kk] = *reinterpret_cast<const bf16x8 *>(st_next + krow * ROWB + (((2 * kk + lhi) ^ ksw) * 16));
+    };
+    auto read_v = [&](int ks, int db) {
+      const unsigned char *p = st + T::REGION + vrow * ROWB + 8 * (lane % 4) + ks * 16 * ROWB + (((db * 2 + hb) ^ vsw) * 32);
+      const shortx4 g0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(p));
+      const shortx4 g1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(p + 8 * ROWB));
+      const shortx8 av = __builtin_shufflevector(g0, g1, 0, 1, 2, 3, 4, 5, 6, 7);
+      vf[ks][db] = __builtin_bit_cast(bf16x8, av);
+    };
 #pragma unroll
-      for (int kk = 0; kk < KK / 2; ++kk)
-        kf[kk] = *reinterpret_cast<const bf16x8 *>(skp + (((2 * kk + lhi) ^ ksw) * 16));
-    }
+    for (int kk = 0; kk < KK / 2; ++kk) read_k(kk);
     if (!STEADY) {
       const int key_base = k0 + key_lane;
       if (k0 + TK > k_hi) {  // wave-uniform: only the last tile can hold keys past the end
@@ -618,15 +620,23 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
           if (key_base + 8 * (e / 4) + (e % 4) >= k_hi) s_cur[e] = -INFINITY;
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
     // running maximum of tile t (lazily moved reference)
     float mx = s_cur[0];
 #pragma unroll
-    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s_cur[e]);
+    for (int db = 0; db < DB; ++db) {
+      pv(0, db);
+      if (!LATE_K) read_k(KK / 2 + db);
+      copy_behind(db);
+#pragma unroll
+      for (int e = 4 * db; e < 4 * db + 4; ++e) mx = fmaxf(mx, s_cur[e]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     mx = xhalf_max(mx) * sc;
     const bool need = mx > m_run + 8.0f;
     if (__any(need)) {
-      // (rare after the first tiles) the accumulator changes its reference; the pending probabilities
-      // of tile t-1 belong to the old one and are scaled with it (by 2^-8 at most, or by exactly 1)
+      // (rare after the first tiles) the accumulator changes its reference; the half of tile t-1's probabilities whose
+      // product is still to come belongs to the old one and is scaled with it (by 2^-8 at most, or by exactly 1)
       const float corr = need ? __builtin_amdgcn_exp2f(m_run - mx) : 1.0f;
       m_run = need ? mx : m_run;
       l_run *= corr;
@@ -634,86 +644,47 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc_o[db][e] *= corr;
+      const uint4 w = __builtin_bit_cast(uint4, pf[1]);
+      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+      uint32_t o[4];
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const uint4 w = __builtin_bit_cast(uint4, pf[ks]);
-        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-        uint32_t o[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          o[q] = pack_bf16(__uint_as_float(ww[q] << 16) * corr, __uint_as_float(ww[q] & 0xffff0000u) * corr);
-        pf[ks] = __builtin_bit_cast(bf16x8, uint4{o[0], o[1], o[2], o[3]});
-      }
+      for (int q = 0; q < 4; ++q)
+        o[q] = pack_bf16(__uint_as_float(ww[q] << 16) * corr, __uint_as_float(ww[q] & 0xffff0000u) * corr);
+      pf[1] = __builtin_bit_cast(bf16x8, uint4{o[0], o[1], o[2], o[3]});
     }
     const float neg_ref = (m_run == -INFINITY) ? 0.f : -m_run;
 
-    // Sixteen matrix instructions -- P V of tile t-1, then the scores of tile t+1 -- each followed by
-    // its share of tile t's exponentials; the V fragments of tile t are requested in between, into
-    // the registers the first eight have released.
     // (after the last tile the score product reads a stage that holds no tile: the result is dropped)
-    float arg[16], pe[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) arg[e] = fmaf(s_cur[e], sc, neg_ref);
-    pv();
-#pragma unroll
-    for (int e = 0; e < 8; ++e) pe[e] = __builtin_amdgcn_exp2f(arg[e]);
-    {
-      const unsigned char *skp = st_next + krow * ROWB;
-#pragma unroll
-      for (int kk = KK / 2; kk < KK; ++kk)
-        kf[kk] = *reinterpret_cast<const bf16x8 *>(skp + (((2 * kk + lhi) ^ ksw) * 16));
-    }
+    // the row sum is taken over the rounded probabilities, the values the P V product uses
+    // (one two-element dot product with (1, 1) per register instead of two additions)
+    float pe[16], ps0 = 0.f, ps1 = 0.f;
+    uint32_t pw[8];
+    const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3f803f80u);
     floatx16 s_next;
 #pragma unroll
     for (int e = 0; e < 16; ++e) s_next[e] = 0.f;
+    auto round_pair = [&](int i) {
+      pw[i] = pack_bf16(pe[2 * i], pe[2 * i + 1]);
+      float &ps = (i & 1) ? ps1 : ps0;
+      ps = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pw[i]), ones, ps, false);
+    };
+    auto exps = [](int slot) { return slot < 0 ? 0 : slot < 4 ? slot + 1 : 4 + 3 * (slot - 3) / 2; };  // taken by then
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-      s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], s_next, 0, 0, 0);
+    for (int slot = 0; slot < 4 + KK; ++slot) {
+      if (slot < 4) pv(1, slot);
+      else s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[slot - 4], qf[slot - 4], s_next, 0, 0, 0);
+      if (LATE_K && slot < 4) read_k(KK / 2 + slot);
+      if (LATE_K ? slot >= 4 && slot < 8 : slot < 4) read_v(0, slot % 4);
+      if (slot >= 4 && slot < 8) read_v(1, slot % 4);
+      copy_behind(4 + slot);
 #pragma unroll
-    for (int e = 8; e < 16; ++e) pe[e] = __builtin_amdgcn_exp2f(arg[e]);
-    // the row sum is taken over the rounded probabilities, the values the P V product uses
-    // (one two-element dot product with (1, 1) per register instead of two additions)
-    float ps0 = 0.f, ps1 = 0.f;
-    uint32_t pw[8];
-    const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3f803f80u);
+      for (int e = exps(slot - 1); e < exps(slot); ++e) pe[e] = __builtin_amdgcn_exp2f(fmaf(s_cur[e], sc, neg_ref));
 #pragma unroll
-    for (int e = 0; e < 16; e += 4) {
-      pw[e >> 1] = pack_bf16(pe[e], pe[e + 1]);
-      pw[(e >> 1) + 1] = pack_bf16(pe[e + 2], pe[e + 3]);
-      ps0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pw[e >> 1]), ones, ps0, false);
-      ps1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pw[(e >> 1) + 1]), ones, ps1, false);
+      for (int i = exps(slot - 2) / 2; i < exps(slot - 1) / 2; ++i) round_pair(i);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    float ps = ps0 + ps1;
-    {
-      const unsigned char *svp = st + T::REGION + vrow * ROWB + 8 * (lane % 4);
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const unsigned char *p = svp + ks * 16 * ROWB + (((db * 2 + hb) ^ vsw) * 32);
-          const shortx4 g0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(p));
-          const shortx4 g1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(p + 8 * ROWB));
-          const shortx8 av = __builtin_shufflevector(g0, g1, 0, 1, 2, 3, 4, 5, 6, 7);
-          vf[ks][db] = __builtin_bit_cast(bf16x8, av);
-        }
-    }
-    // instruction order
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // P V product
-      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // scale + shift of two scores
-      __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);  // an exponential
-      if (i == 3) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);  // the other four K reads
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // score product
-      __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);  // an exponential
-      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // rounding and sum
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);   // the V reads of tile t
-    ps = xhalf_sum(ps);
-    l_run += ps;
+    round_pair(7);
+    l_run += ps0 + ps1;  // (this lane's keys; the other half's are added behind the loop)
     {
       const uint4 v0{pw[0], pw[1], pw[2], pw[3]}, v1{pw[4], pw[5], pw[6], pw[7]};
       pf[0] = __builtin_bit_cast(bf16x8, v0);
@@ -735,7 +706,11 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
     for (; t < n_steady; ++t) body(t, std::true_type{}, dyn{});
     for (; t < n_tiles; ++t) body(t, std::false_type{}, dyn{});
   }
-  pv();  // the last tile's
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) pv(ks, db);  // the last tile's
+  l_run = xhalf_sum(l_run);
   }
   if (NORM && compact) {
     if (Lk == 0) {  // uniform: nothing has changed in this sequence, the rows are zero
@@ -755,8 +730,8 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
         if (n_lo + (t + 1) * TN <= n_hi) {  // uniform
 #pragma unroll
           for (int i = 0; i < LPN; ++i) {
-            const unsigned char *base = kn_u + ((size_t)t * TN + (i / (LPN / 2)) * TK) * kv_stride * 2;
-            dma16_s(base, off_k[i % (LPN / 2)], sb + (uint32_t)(i / (LPN / 2)) * T::REGION + (uint32_t)((i % (LPN / 2)) * NW + wave) * 1024u);
+            const unsigned char *base = kn_u + ((size_t)t * TN + (i / (LPN / 2)) * TK) * kv_stride * 2 + (i % (LPN / 2)) * copy_step;
+            dma16_s(base, off_k, sb + (uint32_t)(i / (LPN / 2)) * T::REGION + (uint32_t)((i % (LPN / 2)) * NW + wave) * 1024u);
           }
         } else {  // keys past the end re-read the last one (masked later)
 #pragma unroll

@@ -110,3 +110,36 @@ def test_copies_past_the_l2(heads, kv, L, counts):
     for got in outs:
         ref = O.partial_attention(to_host(full).reshape(B * L, heads, 128)[idx], to_host(k).reshape(B, L, kv, 128), to_host(v).reshape(B, L, kv, 128), idx, B, L)
         assert_close(got, ref.reshape(idx.size, -1), 2e-2, "context rows")
+
+
+# bf16, head_dim 128: the loop is unrolled over four stages and ends in tiles of its own, rows leave 4 * i + sub to an access, and a
+# reference that moves takes the half of the pending probabilities along: key counts around those of one to nine
+# tiles of 32 and of 64, row counts around those of a wave, keys that grow so that the reference moves all along the sweep, also back to
+# back.  Probabilities and results are rounded to bf16 once each (2^-8 of a weighted mean of values within 5): 2e-2.
+@pytest.mark.parametrize("L", [1, 31, 33, 64, 97, 128, 129, 161, 255, 257, 300])
+@pytest.mark.parametrize("heads,kv", [(2, 2), (6, 2)])
+@pytest.mark.parametrize("steep", [0.0, 0.3])
+def test_bf16_attention_sweep(heads, kv, L, steep):
+    print("bf16 attention sweep", heads, kv, L, steep, flush=True)
+    s = W.LayerShape(hidden=128, n_heads=heads, n_kv_heads=kv, head_dim=128, ffn=128, dtype="bf16")
+    counts = [min(L, c) for c in (1, 3, 31, 33, 64, 65, 0, 127, 129)]
+    B = len(counts)
+    g = torch.Generator().manual_seed(17 * L + heads)
+    k, v = (torch.randn(B, L, kv, 128, generator=g) for _ in range(2))
+    q = torch.randn(B * L, heads, 128, generator=g)
+    q[..., 0] = 12.0
+    k[..., 0] += steep * torch.arange(L).view(1, L, 1)  # scores rise by 0.3 * 12 / sqrt(128) a key
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    idx, off = rand_rows(75, B, L, counts)
+    lay = Layer.from_shape(s, B, L)
+    for cap in (idx.size, B * L):
+        rows = lay.make_list(idx, off, cap=cap)
+        qd = torch.zeros(cap, s.dq, dtype=torch.bfloat16, device="cuda")
+        qd[:idx.size] = q.view(B * L, -1)[torch.from_numpy(idx).long()].cuda()
+        out = torch.full((cap, s.dq), -7.0, dtype=torch.bfloat16, device="cuda")
+        lay.ctx.partial_attention(qd, k.cuda(), v.cuda(), rows, B, L, out)
+        torch.cuda.synchronize()
+        ref = O.partial_attention(q.float().numpy()[idx], k.float().numpy(), v.float().numpy(), idx, B, L)
+        assert_close(to_host(out)[:idx.size], ref.reshape(idx.size, -1), 2e-2, "context rows")
+        assert (out[idx.size:] == -7.0).all()
+    lay.close()
