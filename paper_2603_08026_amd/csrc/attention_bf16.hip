@@ -368,6 +368,14 @@ __device__ __forceinline__ float xhalf_sum(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// sum over the 16 lanes of a row of lanes, in all of them (rotations inside the row: no LDS)
+__device__ __forceinline__ float row16_sum(float x) {
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, false));
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false));
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, false));
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false));
+  return x;
+}
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
 template <int WQ, int WK_> struct DTile {
@@ -384,7 +392,9 @@ template <int WQ, int WK_> struct DTile {
   static constexpr int PER_WAVE = (DB * 16 + 2) * 64;    // merge scratch per wave (floats)
   static constexpr size_t LDS_BYTES = (size_t)NS * STAGE_BYTES;
   static_assert(NS >= 3 && (NS - 2) * LPW < 64, "stages (the loop reads two tiles at a time) and vmcnt immediate");
-  static_assert((size_t)(WK - 1) * WQ * PER_WAVE * 4 <= LDS_BYTES, "merge scratch must fit in the tile buffers");
+  // behind the loop the tile buffers hold the merge scratch, then a row region per wave row
+  static constexpr size_t MERGE_BYTES = (size_t)(WK - 1) * WQ * PER_WAVE * 4;
+  static_assert(MERGE_BYTES % 256 == 0 && MERGE_BYTES + (size_t)BQ * ROWB <= LDS_BYTES, "merge scratch and rows must fit in the tile buffers");
   static_assert(LPW >= 2 && LPW % 2 == 0, "every wave copies K and V rows");
 };
 
@@ -828,6 +838,23 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
       l_run = xhalf_sum(l_lane);
     }
   }
+  // Finished rows leave (and cached ones come) as whole rows of 256 bytes, 16 lanes to a row, by way of LDS: lane (sub, cc) holds
+  // 16 bytes of the rows 4 * i + sub.  In the order of the accumulators, two lanes to a query, every access of a wave touched 32
+  // rows by 16 bytes.
+  const bool finish = a.c_commit || (a.splits == 1 && !a.partial);  // uniform
+  const int sub = lane / 16, cc = lane % 16;
+  uint32_t place = 0, row_at[8];  // the query's row of the context cache, or of the output (T * H rows of 256 bytes fit in memory)
+  uint4 old[8];
+  if (finish && wk == 0) {
+    const uint32_t tok = a.c_commit && a.rows.idx ? (uint32_t)a.rows.idx[jq] : (uint32_t)jq;
+    place = tok * (uint32_t)a.H + (uint32_t)hq;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      row_at[i] = (uint32_t)__shfl((int)place, 4 * i + sub, WAVE);
+      old[i] = uint4{0, 0, 0, 0};
+      if (a.c_commit && wq * 32 + 4 * i + sub < nq) old[i] = *(reinterpret_cast<const uint4 *>((const bf16_t *)a.c_commit + (size_t)row_at[i] * DH) + cc);
+    }
+  }
   __syncthreads();  // every wave is done with the last tile: the stages become merge scratch
 
   // merge the WK wave columns of each query block through LDS
@@ -860,55 +887,9 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
     m_run = M;
   }
 
-  const int r = wq * 32 + l32;
-  if (a.c_commit) {
-    // Fused commit  [Alg. 3: cosine line and cache commit]: the row is normalised and rounded to the
-    // storage type; this lane holds 64 of the head's 128 columns of its query.  It reads the same
-    // columns of the cached context of the query's token, adds up <new, old>, |new|^2, |old|^2 over the
-    // stored values, overwrites the cached columns, and the two lanes of a query leave the head's sums.
-    float dot = 0.f, na = 0.f, nb = 0.f;
-    const bool live = r < nq;  // (lanes past the tile's last row take part in the shuffle only)
-    const int j = jq, h = hq;
-    if (live) {
-      const size_t tok = a.rows.idx ? (size_t)a.rows.idx[j] : (size_t)j;
-      bf16_t *crow = (bf16_t *)a.c_commit + (tok * a.H + h) * DH + 4 * lhi;
-      const float inv = 1.0f / l_run;
-      uint2 old[DB][4];
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) old[db][g] = *reinterpret_cast<const uint2 *>(crow + db * 32 + 8 * g);
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 w;
-          w.x = pack_bf16(acc_o[db][4 * g] * inv, acc_o[db][4 * g + 1] * inv);
-          w.y = pack_bf16(acc_o[db][4 * g + 2] * inv, acc_o[db][4 * g + 3] * inv);
-          const uint32_t nw[2] = {w.x, w.y}, ow[2] = {old[db][g].x, old[db][g].y};
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const float f0 = __uint_as_float(nw[q] << 16), f1 = __uint_as_float(nw[q] & 0xffff0000u);
-            const float b0 = __uint_as_float(ow[q] << 16), b1 = __uint_as_float(ow[q] & 0xffff0000u);
-            dot += f0 * b0 + f1 * b1;
-            na += f0 * f0 + f1 * f1;
-            nb += b0 * b0 + b1 * b1;
-          }
-          *reinterpret_cast<uint2 *>(crow + db * 32 + 8 * g) = w;
-        }
-      if (a.lse_out && lhi == 0) a.lse_out[tok * a.H + h] = m_run * LN2 + __logf(l_run);
-    }
-    dot += __shfl_xor(dot, 32, WAVE);
-    na += __shfl_xor(na, 32, WAVE);
-    nb += __shfl_xor(nb, 32, WAVE);
-    if (live && lhi == 0)
-      *reinterpret_cast<float4 *>(a.cos_part + ((size_t)j * a.H + h) * 4) = float4{dot, na, nb, 0.f};
-    return;
-  }
-  if (r >= nq) return;
-  const int j = jq, h = hq;
-  if (a.splits == 1 && !a.partial) {
-    bf16_t *out = (bf16_t *)a.out + ((size_t)j * a.H + h) * DH + 4 * lhi;
+  if (wq * 32 >= nq) return;  // uniform: no query
+  if (finish) {
+    unsigned char *rows_lds = smem_raw + T::MERGE_BYTES + wq * 32 * ROWB;  // this wave's; 16-byte chunk c of row r at c ^ (r % 16)
     const float inv = 1.0f / l_run;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -917,9 +898,47 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
         uint2 w;
         w.x = pack_bf16(acc_o[db][4 * g] * inv, acc_o[db][4 * g + 1] * inv);
         w.y = pack_bf16(acc_o[db][4 * g + 2] * inv, acc_o[db][4 * g + 3] * inv);
-        *reinterpret_cast<uint2 *>(out + db * 32 + 8 * g) = w;
+        *reinterpret_cast<uint2 *>(rows_lds + l32 * ROWB + (((db * 4 + g) ^ (l32 & 15)) * 16) + lhi * 8) = w;
       }
-  } else {
+    asm volatile("" : : : "memory");  // the reads below are of another type (LDS accesses of a wave keep their order)
+    bf16_t *out = (bf16_t *)(a.c_commit ? a.c_commit : a.out);
+    // Fused commit  [Alg. 3: cosine line and cache commit]: the old columns of the query's token were read above; the sums
+    // <new, old>, |new|^2, |old|^2 are taken over the stored values, and the head's go to cos_part.
+    float dot_r = 0.f, na_r = 0.f, nb_r = 0.f;  // of row 4 * cc + sub (lanes with cc < 8)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int rr = 4 * i + sub;
+      const uint4 w = *reinterpret_cast<const uint4 *>(rows_lds + rr * ROWB + ((cc ^ (rr & 15)) * 16));
+      if (wq * 32 + rr < nq) *(reinterpret_cast<uint4 *>(out + (size_t)row_at[i] * DH) + cc) = w;
+      if (a.c_commit) {
+        const uint32_t nw[4] = {w.x, w.y, w.z, w.w}, ow[4] = {old[i].x, old[i].y, old[i].z, old[i].w};
+        float dot = 0.f, na = 0.f, nb = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float f0 = __uint_as_float(nw[q] << 16), f1 = __uint_as_float(nw[q] & 0xffff0000u);
+          const float b0 = __uint_as_float(ow[q] << 16), b1 = __uint_as_float(ow[q] & 0xffff0000u);
+          dot = fmaf(f1, b1, fmaf(f0, b0, dot));
+          na = fmaf(f1, f1, fmaf(f0, f0, na));
+          nb = fmaf(b1, b1, fmaf(b0, b0, nb));
+        }
+        dot = row16_sum(dot);
+        na = row16_sum(na);
+        nb = row16_sum(nb);
+        if (cc == i) { dot_r = dot; na_r = na; nb_r = nb; }
+      }
+    }
+    if (a.c_commit) {
+      if (a.lse_out && lhi == 0 && wq * 32 + l32 < nq) a.lse_out[place] = m_run * LN2 + __logf(l_run);
+      const int rr = 4 * (cc & 7) + sub;
+      const int jh = __shfl(jq * a.H + hq, rr, WAVE);
+      if (cc < 8 && wq * 32 + rr < nq) *reinterpret_cast<float4 *>(a.cos_part + (size_t)jh * 4) = float4{dot_r, na_r, nb_r, 0.f};
+    }
+    return;
+  }
+  const int r = wq * 32 + l32;
+  if (r >= nq) return;
+  const int j = jq, h = hq;
+  {
     float *po = a.part_o + (((size_t)split * a.rows.cap + j) * a.H + h) * DH + 4 * lhi;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
