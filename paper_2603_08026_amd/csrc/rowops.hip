@@ -18,6 +18,47 @@ __device__ __forceinline__ int row_count(const Rows &rows) {
   return rows.count ? min(*rows.count, rows.cap) : rows.cap;
 }
 
+// Four neighbouring elements, loaded and stored as one word
+template <typename T> struct Vec4;
+template <> struct Vec4<float> {
+  float4 raw;
+  __device__ __forceinline__ float get(int i) const { return (&raw.x)[i]; }
+  __device__ __forceinline__ void set(int i, float v) { (&raw.x)[i] = v; }
+};
+template <> struct Vec4<bf16_t> {
+  uint2 raw;
+  __device__ __forceinline__ float get(int i) const {
+    const uint32_t w = (&raw.x)[i >> 1];
+    return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
+  }
+  __device__ __forceinline__ void set(int i, float v) {
+    const uint32_t b = f2bf(v);
+    uint32_t &w = (&raw.x)[i >> 1];
+    w = (i & 1) ? ((w & 0x0000ffffu) | (b << 16)) : ((w & 0xffff0000u) | b);
+  }
+};
+template <typename T> __device__ __forceinline__ Vec4<T> ld4(const T *p) {
+  Vec4<T> v;
+  v.raw = *reinterpret_cast<const decltype(v.raw) *>(p);
+  return v;
+}
+template <typename T> __device__ __forceinline__ void st4(T *p, const Vec4<T> &v) { *reinterpret_cast<decltype(v.raw) *>(p) = v.raw; }
+
+// a += the partial sums z0 .. splits - 1 at p, in their order, two loads in flight (not for the down projection and the out-projection:
+// 330 rows 9.8 -> 11.0 and 6.8 -> 7.3 us)
+__device__ __forceinline__ void add_splits(float4 &a, const float *p, size_t stride, int z0, int splits) {
+  int z = z0;
+  for (; z + 1 < splits; z += 2) {
+    const float4 b = *reinterpret_cast<const float4 *>(p + z * stride), c = *reinterpret_cast<const float4 *>(p + (z + 1) * stride);
+    a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
+  }
+  if (z < splits) {
+    const float4 b = *reinterpret_cast<const float4 *>(p + z * stride);
+    a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+  }
+}
+
 // The first workgroups of a row kernel, one for every job, make plans instead of taking rows (all NT threads, a multiple of four waves).  The
 // GEMM behind needs its plan as soon as it starts and would take 1.7 us to make it; here that happens beside the rows.  Hidden 4096: step of 410 listed rows 293 -> 285 us, of 2064 798.5 -> 796.9; loop of 8 x 1024 tokens 2004 -> 1956.
 template <int NT> __device__ __forceinline__ void make_plan(const PlanJob &job) {
@@ -31,8 +72,9 @@ template <int NT> __device__ __forceinline__ void make_plan(const PlanJob &job) 
 // NT threads per row: 256 when the row fits KEEP vectors per thread (more rows in flight per CU and a
 // four-wave reduction), else RB.
 // JOB: with a plan to make (in the kernel without, which takes known rows, its code and registers would be for nothing).
-template <typename T, int NT, bool JOB>
-__global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
+// NV: vectors a thread keeps, two (rows of up to 4096 bf16 elements) or four.
+template <typename T, int NT, bool JOB, int NV>
+__global__ __launch_bounds__(NT, 8) void k_gather_rmsnorm(const T *__restrict__ x,
                                                         const T *__restrict__ gain, Rows rows, int d,
                                                         float eps, T *__restrict__ out, int by_token, PlanJob job) {
   __shared__ float red[NT / WAVE];
@@ -45,30 +87,40 @@ __global__ __launch_bounds__(NT) void k_gather_rmsnorm(const T *__restrict__ x,
     }
   }
   const int n = row_count(rows), nv = d / N;
+  // A row is a chain of round trips (count, id, row, sum), so what can be asked for ahead is: both of a thread's vectors of the row at once
+  // (an index past the end reads the last vector again; a branch around a load waits for it), and the gain.  Four of each
+  // would not leave the registers for eight waves a SIMD.  Hidden 4096, us: 20480 rows 57 -> 50, 8192 27.6 -> 24.5, 1942 10.6 -> 9.8.
+  constexpr bool AHEAD = NV <= 2;
+  Vec16<T> g[NV];
+#pragma unroll
+  for (int it = 0; it < NV; ++it)
+    if (AHEAD && it * NT < nv) g[it] = ld16(gain + min((int)threadIdx.x + it * NT, nv - 1) * N);  // (uniform branch)
   for (int j = blockIdx.x - first; j < n; j += gridDim.x - first) {
     const int r = rows.idx ? rows.idx[j] : j;
     const T *xr = x + (size_t)r * d;
     float ss = 0.f;
-    Vec16<T> keep[KEEP];
+    Vec16<T> keep[NV];
 #pragma unroll
-    for (int it = 0; it < KEEP; ++it) {
-      const int v = threadIdx.x + it * NT;
-      if (v < nv) {
-        keep[it] = ld16(xr + v * N);
+    for (int it = 0; it < NV; ++it)
+      if (AHEAD && it * NT < nv) keep[it] = ld16(xr + min((int)threadIdx.x + it * NT, nv - 1) * N);
+#pragma unroll
+    for (int it = 0; it < NV; ++it)
+      if ((int)threadIdx.x + it * NT < nv) {
+        if (!AHEAD) keep[it] = ld16(xr + (threadIdx.x + it * NT) * N);
 #pragma unroll
         for (int i = 0; i < N; ++i) ss += keep[it].get(i) * keep[it].get(i);
       }
-    }
     ss = block_sum<NT>(ss, red);
     const float sc = 1.0f / sqrtf(ss / (float)d + eps);
     T *orow = out + (size_t)(by_token ? r : j) * d;
 #pragma unroll
-    for (int it = 0; it < KEEP; ++it) {
+    for (int it = 0; it < NV; ++it) {
       const int v = threadIdx.x + it * NT;
       if (v < nv) {
-        Vec16<T> g = ld16(gain + v * N), o;
+        const Vec16<T> gv = AHEAD ? g[it] : ld16(gain + v * N);
+        Vec16<T> o;
 #pragma unroll
-        for (int i = 0; i < N; ++i) o.set(i, keep[it].get(i) * sc * g.get(i));
+        for (int i = 0; i < N; ++i) o.set(i, keep[it].get(i) * sc * gv.get(i));
         st16(orow + v * N, o);
       }
     }
@@ -164,7 +216,8 @@ __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ 
 // ---- q/k/v tail: bias + rotary embedding + K/V merge  [Alg. 3: K[idx] <- k_proj(x[idx]), same V] --
 // Half-split pairing: element p of a head couples with element p + dh/2, rotated by the angle
 // pos * theta^(-2p/dh); the table holds (cos, sin) per (pos, p).  A thread handles 4 neighbouring
-// pairs of one head (two float4 of the raw result, two float4 of the table).
+// pairs of one head (two float4 of the raw result, two float4 of the table), stored four elements at a time (one at a time,
+// 330 rows of 12288 columns 11.0 -> 9.8 us).
 // DV: with what the approximate step keeps of its candidates (CandidateOut).
 template <typename T, DvLayout DV>
 __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ part, Splits splits_of,
@@ -205,6 +258,8 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
         const int hh = isq ? head : head - H;
         const int c0 = hh * dh + p4;              // column inside q or k
         const int s0 = (isq ? 0 : dq) + c0;       // column inside the raw row
+        const float4 t0 = *reinterpret_cast<const float4 *>(t + 2 * p4);      // cos0 sin0 cos1 sin1
+        const float4 t1 = *reinterpret_cast<const float4 *>(t + 2 * p4 + 4);  // cos2 sin2 cos3 sin3
         float4 x1 = *reinterpret_cast<const float4 *>(src + s0);
         float4 x2 = *reinterpret_cast<const float4 *>(src + s0 + half);
         for (int z = 1; z < splits; ++z) {
@@ -219,45 +274,40 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
           x2.x += to_f<T>(b[c0 + half]); x2.y += to_f<T>(b[c0 + half + 1]);
           x2.z += to_f<T>(b[c0 + half + 2]); x2.w += to_f<T>(b[c0 + half + 3]);
         }
-        const float4 t0 = *reinterpret_cast<const float4 *>(t + 2 * p4);      // cos0 sin0 cos1 sin1
-        const float4 t1 = *reinterpret_cast<const float4 *>(t + 2 * p4 + 4);  // cos2 sin2 cos3 sin3
         T *dst = isq ? q_out + (size_t)(q_by_token ? r : j) * dq : kc + (size_t)r * dkv;
         const float a1[4] = {x1.x, x1.y, x1.z, x1.w}, a2[4] = {x2.x, x2.y, x2.z, x2.w};
         const float co[4] = {t0.x, t0.z, t1.x, t1.z}, si[4] = {t0.y, t0.w, t1.y, t1.w};
-        T lo4[4], hi4[4];
+        Vec4<T> lo4, hi4;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          lo4[u] = from_f<T>(rotated(a1[u], co[u], -(a2[u] * si[u])));
-          hi4[u] = from_f<T>(rotated(a2[u], co[u], a1[u] * si[u]));
+          lo4.set(u, rotated(a1[u], co[u], -(a2[u] * si[u])));
+          hi4.set(u, rotated(a2[u], co[u], a1[u] * si[u]));
         }
-        T *ks = (k_here && !isq) ? k_out + (size_t)cand_row * dkv : nullptr;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          dst[c0 + u] = lo4[u];
-          dst[c0 + half + u] = hi4[u];
-          if (ks) {
-            ks[c0 + u] = lo4[u];
-            ks[c0 + half + u] = hi4[u];
-          }
+        st4(dst + c0, lo4);
+        st4(dst + c0 + half, hi4);
+        if (k_here && !isq) {
+          T *ks = k_out + (size_t)cand_row * dkv;
+          st4(ks + c0, lo4);
+          st4(ks + c0 + half, hi4);
         }
       } else {
         const int c0 = (it - qk_items) * 4;
         float4 x = *reinterpret_cast<const float4 *>(src + dq + dkv + c0);
-        for (int z = 1; z < splits; ++z) {
-          const float4 y = *reinterpret_cast<const float4 *>(src + z * split_stride + dq + dkv + c0);
-          x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
-        }
+        add_splits(x, src + dq + dkv + c0, split_stride, 1, splits);
         if (bv) {
           x.x += to_f<T>(bv[c0]); x.y += to_f<T>(bv[c0 + 1]); x.z += to_f<T>(bv[c0 + 2]); x.w += to_f<T>(bv[c0 + 3]);
         }
         T *vrow = vc + (size_t)r * dkv + c0;
-        const T n0 = from_f<T>(x.x), n1 = from_f<T>(x.y), n2 = from_f<T>(x.z), n3 = from_f<T>(x.w);
+        Vec4<T> v;
+        v.set(0, x.x); v.set(1, x.y); v.set(2, x.z); v.set(3, x.w);
         if (dv_here) {  // residual of the stored values, before the merge overwrites the cached row
-          T *d = dv_out + (size_t)cand_row * dkv + c0;
-          d[0] = from_f<T>(to_f<T>(n0) - to_f<T>(vrow[0])); d[1] = from_f<T>(to_f<T>(n1) - to_f<T>(vrow[1]));
-          d[2] = from_f<T>(to_f<T>(n2) - to_f<T>(vrow[2])); d[3] = from_f<T>(to_f<T>(n3) - to_f<T>(vrow[3]));
+          const Vec4<T> old = ld4(vrow);
+          Vec4<T> dv;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) dv.set(u, v.get(u) - old.get(u));
+          st4(dv_out + (size_t)cand_row * dkv + c0, dv);
         }
-        vrow[0] = n0; vrow[1] = n1; vrow[2] = n2; vrow[3] = n3;
+        st4(vrow, v);
       }
     }
   }
@@ -505,10 +555,12 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
   auto go = [&](auto zero, auto job_c) {
     using T = decltype(zero);
     constexpr bool JOB = decltype(job_c)::value;
-    if (d / Vec16<T>::N <= 256 * KEEP)
-      k_gather_rmsnorm<T, 256, JOB><<<grid, 256, 0, s>>>((const T *)x, (const T *)gain, rows, d, eps, (T *)out, by_token, job);
-    else
-      k_gather_rmsnorm<T, RB, JOB><<<wide_grid, RB, 0, s>>>((const T *)x, (const T *)gain, rows, d, eps, (T *)out, by_token, job);
+    const int nv = d / Vec16<T>::N;
+#define DY_GATHER(NT, NV, G) k_gather_rmsnorm<T, NT, JOB, NV><<<G, NT, 0, s>>>((const T *)x, (const T *)gain, rows, d, eps, (T *)out, by_token, job)
+    if (nv <= 2 * 256) DY_GATHER(256, 2, grid);
+    else if (nv <= 256 * KEEP) DY_GATHER(256, KEEP, grid);
+    else DY_GATHER(RB, KEEP, wide_grid);
+#undef DY_GATHER
   };
   if (t == F32) go(float{}, std::false_type{});
   else if (plans) go(bf16_t{}, std::true_type{});
