@@ -24,11 +24,6 @@ struct Splits {
   int n = 1, tail_from = 0x7fffffff, n_tail = 1;
   int done_to = 0;  // rows below it were finished by the GEMM's own epilogue (down projection, q|k|v); at most the list's capacity
   const int32_t *dev = nullptr;
-  __device__ Splits resolved() const {
-    Splits r = *this;
-    if (dev) { r.n = dev[0]; r.tail_from = dev[1]; r.n_tail = dev[2]; r.done_to = dev[3]; }
-    return r;
-  }
   __host__ __device__ int of(int j) const { return j < tail_from ? n : n_tail; }
 };
 

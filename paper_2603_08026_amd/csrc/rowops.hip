@@ -59,6 +59,28 @@ __device__ __forceinline__ void add_splits(float4 &a, const float *p, size_t str
   }
 }
 
+// How many rows exist and the splits of a GEMM's result.  Where the device has planned, both are read at once (the plan's words with one
+// load: the count is on the device then); one after the other they are up to five round trips at the head of a kernel.  1942 rows of 4096,
+// with row_ahead, us: down projection's sums 19.5 -> 18.8, out-projection's tail 21.3 -> 20.6, norm 9.8 -> 9.5; 1137 of 3584 14.7 -> 14.2.
+struct RowsAndSplits {
+  int n;
+  Splits sp;
+};
+__device__ __forceinline__ RowsAndSplits rows_and_splits(const Rows &rows, const Splits &splits) {
+  RowsAndSplits r{0, splits};
+  if (splits.dev) {
+    const int4 w = *reinterpret_cast<const int4 *>(splits.dev);
+    const int n = *rows.count;
+    r.sp.n = w.x; r.sp.tail_from = w.y; r.sp.n_tail = w.z; r.sp.done_to = w.w;
+    r.n = min(n, rows.cap);
+  } else {
+    r.n = row_count(rows);
+  }
+  return r;
+}
+// Row id of entry j, which need not exist: asked for beside the count
+__device__ __forceinline__ int row_ahead(const Rows &rows, int j) { return rows.idx && j < rows.cap ? rows.idx[j] : j; }
+
 // The first workgroups of a row kernel, one for every job, make plans instead of taking rows (all NT threads, a multiple of four waves).  The
 // GEMM behind needs its plan as soon as it starts and would take 1.7 us to make it; here that happens beside the rows.  Hidden 4096: step of 410 listed rows 293 -> 285 us, of 2064 798.5 -> 796.9; loop of 8 x 1024 tokens 2004 -> 1956.
 template <int NT> __device__ __forceinline__ void make_plan(const PlanJob &job) {
@@ -86,7 +108,9 @@ __global__ __launch_bounds__(NT, 8) void k_gather_rmsnorm(const T *__restrict__ 
       return;
     }
   }
-  const int n = row_count(rows), nv = d / N;
+  const int nv = d / N;
+  int j = blockIdx.x - first, r = row_ahead(rows, j);
+  const int n = row_count(rows);
   // A row is a chain of round trips (count, id, row, sum), so what can be asked for ahead is: both of a thread's vectors of the row at once
   // (an index past the end reads the last vector again; a branch around a load waits for it), and the gain.  Four of each
   // would not leave the registers for eight waves a SIMD.  Hidden 4096, us: 20480 rows 57 -> 50, 8192 27.6 -> 24.5, 1942 10.6 -> 9.8.
@@ -95,8 +119,7 @@ __global__ __launch_bounds__(NT, 8) void k_gather_rmsnorm(const T *__restrict__ 
 #pragma unroll
   for (int it = 0; it < NV; ++it)
     if (AHEAD && it * NT < nv) g[it] = ld16(gain + min((int)threadIdx.x + it * NT, nv - 1) * N);  // (uniform branch)
-  for (int j = blockIdx.x - first; j < n; j += gridDim.x - first) {
-    const int r = rows.idx ? rows.idx[j] : j;
+  for (; j < n; j += gridDim.x - first, r = row_ahead(rows, j)) {
     const T *xr = x + (size_t)r * d;
     float ss = 0.f;
     Vec16<T> keep[NV];
@@ -146,11 +169,11 @@ __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__
       return;
     }
   }
-  const int n = row_count(rows), nv = d / 4;
-  const Splits sp = splits_of.resolved();
+  int j = blockIdx.x - first, r = row_ahead(rows, j);
+  const auto [n, sp] = rows_and_splits(rows, splits_of);
+  const int nv = d / 4;
   const size_t split_stride = (size_t)n * d;
-  for (int j = blockIdx.x - first; j < n; j += gridDim.x - first) {
-    const int r = rows.idx ? rows.idx[j] : j;
+  for (; j < n; j += gridDim.x - first, r = row_ahead(rows, j)) {
     const int splits = sp.of(j);
     const bf16_t *xr = x + (size_t)r * d;
     float *hr = h + (size_t)j * d;
@@ -194,8 +217,8 @@ __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__
 __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ part, Splits splits_of,
                                                        const float *__restrict__ h,
                                                        Rows rows, int d, bf16_t *__restrict__ out) {
-  const int n = row_count(rows), nv = d / 4;
-  const Splits sp = splits_of.resolved();
+  const auto [n, sp] = rows_and_splits(rows, splits_of);
+  const int nv = d / 4;
   const size_t split_stride = (size_t)n * d;
   for (int j = sp.done_to + blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
@@ -229,11 +252,10 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
                                                       int q_by_token, T *__restrict__ dv_out, T *__restrict__ k_out,
                                                       const int32_t *__restrict__ cand_offsets,
                                                       int32_t *__restrict__ entry_of, int entry_lo) {
-  const int n = row_count(rows);
+  const auto [n, sp] = rows_and_splits(rows, splits_of);
   const int half = dh / 2, dq = H * dh, dkv = Hkv * dh, ld = dq + 2 * dkv;
   const int per_head = half / 4;  // items of 4 pairs per head
   const int qk_items = (H + Hkv) * per_head, v_items = dkv / 4;
-  const Splits sp = splits_of.resolved();
   const size_t split_stride = (size_t)n * ld;
   for (int j = sp.done_to + blockIdx.x; j < n; j += gridDim.x) {
     const int r = rows.idx ? rows.idx[j] : j;
