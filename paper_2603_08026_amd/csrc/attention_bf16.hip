@@ -984,7 +984,7 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
 // The context update of Alg. 4 (b, the first `grid_b` workgroups) and exact rows (a), which need nothing of each other, in one launch: a
 // few hundred exact rows are 256 items that wait for their keys on half of the chip's places, and the update's last round
 // leaves places idle as well.  8 x 1024 tokens, 32 heads, 330 exact rows, us: update of a window of 2048 tokens 39 + exact rows 35 ->
-// 68, of all tokens 130 + 40 -> 143; a loop of such steps 3520 -> 3440.  The exact rows read through the L2, where the update sweeps
+// 68, of all tokens 130 + 40 -> 143 (62 and 141 with the order of the loop pinned); a loop of such steps 3520 -> 3440.  The exact rows read through the L2, where the update sweeps
 // the same keys (past it the same within 0.6 %).
 template <int WQ, int WK_>
 __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_both(AttnArgs a, int tiles_a, AttnArgs b, int tiles_b, int grid_b) {
