@@ -44,21 +44,6 @@ template <typename T> __device__ __forceinline__ Vec4<T> ld4(const T *p) {
 }
 template <typename T> __device__ __forceinline__ void st4(T *p, const Vec4<T> &v) { *reinterpret_cast<decltype(v.raw) *>(p) = v.raw; }
 
-// a += the partial sums z0 .. splits - 1 at p, in their order, two loads in flight (not for the down projection and the out-projection:
-// 330 rows 9.8 -> 11.0 and 6.8 -> 7.3 us)
-__device__ __forceinline__ void add_splits(float4 &a, const float *p, size_t stride, int z0, int splits) {
-  int z = z0;
-  for (; z + 1 < splits; z += 2) {
-    const float4 b = *reinterpret_cast<const float4 *>(p + z * stride), c = *reinterpret_cast<const float4 *>(p + (z + 1) * stride);
-    a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-    a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
-  }
-  if (z < splits) {
-    const float4 b = *reinterpret_cast<const float4 *>(p + z * stride);
-    a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-  }
-}
-
 // How many rows exist and the splits of a GEMM's result.  Where the device has planned, both are read at once (the plan's words with one
 // load: the count is on the device then); one after the other they are up to five round trips at the head of a kernel.  1942 rows of 4096,
 // with row_ahead, us: down projection's sums 19.5 -> 18.8, out-projection's tail 21.3 -> 20.6, norm 9.8 -> 9.5; 1137 of 3584 14.7 -> 14.2.
@@ -239,8 +224,13 @@ __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ 
 // ---- q/k/v tail: bias + rotary embedding + K/V merge  [Alg. 3: K[idx] <- k_proj(x[idx]), same V] --
 // Half-split pairing: element p of a head couples with element p + dh/2, rotated by the angle
 // pos * theta^(-2p/dh); the table holds (cos, sin) per (pos, p).  A thread handles 4 neighbouring
-// pairs of one head (two float4 of the raw result, two float4 of the table), stored four elements at a time (one at a time,
-// 330 rows of 12288 columns 11.0 -> 9.8 us).
+// pairs of one head (two float4 of the raw result, two float4 of the table), stored four elements at a time.  Bound by the
+// HBM where the rows are many, by the two workgroups that a CU holds where they are a few hundred: the form without candidates
+// keeps to 96 scalar registers, the most with which a SIMD's 800 hold eight waves.  (The v sums two splits at a
+// time took 106, and with them one workgroup a CU.)  Listed rows, a few percent of the list's room, elements stored one at a time /
+// v sums in pairs, one workgroup a CU / as here, us: 12288 columns 330 rows 10.4 / 9.1 / 8.9, 1024 15.7 / 15.2 / 14.7, 4096 65.5 /
+// 51.6 / 51.2; 4608 columns 512 rows 6.9 / 7.0 / 5.9, 768 8.9 / 9.4 / 7.9, 2048 12.5 / 12.8 / 11.2.  Candidates (330 rows of 8192 columns)
+// 12.3 / 11.8 / 11.1.
 // DV: with what the approximate step keeps of its candidates (CandidateOut).
 template <typename T, DvLayout DV>
 __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ part, Splits splits_of,
@@ -315,7 +305,10 @@ __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ p
       } else {
         const int c0 = (it - qk_items) * 4;
         float4 x = *reinterpret_cast<const float4 *>(src + dq + dkv + c0);
-        add_splits(x, src + dq + dkv + c0, split_stride, 1, splits);
+        for (int z = 1; z < splits; ++z) {
+          const float4 y = *reinterpret_cast<const float4 *>(src + z * split_stride + dq + dkv + c0);
+          x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+        }
         if (bv) {
           x.x += to_f<T>(bv[c0]); x.y += to_f<T>(bv[c0 + 1]); x.z += to_f<T>(bv[c0 + 2]); x.w += to_f<T>(bv[c0 + 3]);
         }
@@ -557,8 +550,8 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int n) {
 
 // Workgroups of a row kernel.  Where the count is on the device the capacity may be far above it, and
 // workgroups without a row are not free (8192 of 1024 threads each for 330 rows: k_qkv_finalize 12.7 us, with
-// 1024 of them 11.3 us).  Of the 1024-thread ones 512 are resident at once (two per CU); they take further rows in
-// turn.  Full lists lose nothing by it: q/k/v stage at hidden 256 / 4096, 20480 listed rows, 96 -> 85 / 1937 -> 1820 us
+// 1024 of them 11.3 us).  Of the 1024-thread ones 512 are resident at once (two per CU; of k_qkv_finalize's forms with
+// candidates, whose scalar registers allow seven waves a SIMD, 256); they take further rows in turn.  Full lists lose nothing by it: q/k/v stage at hidden 256 / 4096, 20480 listed rows, 96 -> 85 / 1937 -> 1820 us
 // together with what the GEMMs gained.
 constexpr int GRID_KNOWN = 8192, GRID_LISTED = 1024;
 inline int row_grid(const Rows &rows, int cap) {
