@@ -39,8 +39,9 @@ struct dyllm_ctx {
   void *fs;        // [R, d]        RMSNorm(h)
   void *act;       // [R, F]        silu(gate)*up
   int32_t *status; // device status word
-  // words of the GEMMs' plans that are made on the device, for the GEMMs and the row kernels behind them: raw results, gate|up, down projection
-  int32_t *plan, *plan_up, *plan_down;
+  // words of the GEMMs' plans that are made on the device, for the GEMMs and the row kernels behind them: raw results, gate|up, down
+  // projection, and k|v of the candidates of the approximate step (made ahead of another raw result)
+  int32_t *plan, *plan_up, *plan_down, *plan_kv;
   int32_t *scan;   // words of the chained compaction kernel; all zero between calls
   float *rope;     // [max_seq, dh/2, 2]
   // optional per-stage timing (dyllm_profile_begin / _end)
@@ -56,6 +57,11 @@ struct Layout {
   size_t ns, qs, part_o, part_ml, cosb, flag, hs, fs, act, status, rope, dv_full, dc, csal, pos, win_idx, win_off, ksal, scan, total;
   size_t part_elems;
 };
+
+// the status word, a counter, and from PLANS_AT on the plans
+constexpr int PLANS_AT = 8;
+constexpr size_t STATUS_BYTES = 256;
+static_assert((PLANS_AT + 4 * mm::PLAN_WORDS) * 4 <= STATUS_BYTES, "room for the plans");
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -79,7 +85,7 @@ Layout make_layout(const dyllm_layer_cfg &c) {
   l.hs = take(R * d * 4);
   l.fs = take(R * d * e);
   l.act = take(R * (size_t)c.ffn_dim * e);
-  l.status = take(256);
+  l.status = take(STATUS_BYTES);
   l.rope = take((size_t)c.max_seq * (c.head_dim / 2) * 2 * 4);
   l.dv_full = take(R * dkv * e);
   l.dc = take(R * dq * e);
@@ -391,7 +397,8 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   kv.n_end[0] = ctx->dkv; kv.n_end[1] = 2 * ctx->dkv; kv.n_end[2] = 2 * ctx->dkv;
   const GemmA kv_a = shared ? GemmA{ctx->ns, rin.idx, c.hidden, T} : GemmA{ctx->fs, nullptr, c.hidden, T};
   const QkvOut kv_beside = raw_beside(c.n_heads, c.n_kv_heads, c.head_dim, T);
-  const PlanJob kv_job = plan_gemm_raw(dt(ctx), kv_a, rin, c.hidden, kv, ctx->part_elems, ctx->plan, kv_beside);
+  // (made in the norm kernel of all tokens, ahead of the GEMM for q, which may plan for itself: words of its own)
+  const PlanJob kv_job = plan_gemm_raw(dt(ctx), kv_a, rin, c.hidden, kv, ctx->part_elems, ctx->plan_kv, kv_beside);
   // norm and q projection (+ rotation) of EVERY token of the step  [Alg. 3: Q <- q_proj(x)]
   {
     const QkvOut out{ctx->qs, nullptr, nullptr, w->bq, nullptr, nullptr, ctx->rope, c.n_heads, 0, c.head_dim, L, by_token, (size_t)B * L};
@@ -407,7 +414,7 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
   // k, v of the salient tokens: norm, projection, rotation, value residual, merge into the caches
   if (!shared) launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, 0, kv_job, s);
   {
-    const Splits splits = launch_gemm_raw(dt(ctx), kv_a, rin, c.hidden, kv, ctx->part_o, ctx->part_elems, ctx->plan, kv_job, kv_beside, s);
+    const Splits splits = launch_gemm_raw(dt(ctx), kv_a, rin, c.hidden, kv, ctx->part_o, ctx->part_elems, ctx->plan_kv, kv_job, kv_beside, s);
     // value residual: by token or by sequence into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list
     // entry; the last two next to a compact copy of the new keys; and the step's candidates in the token -> entry map
     const CandidateOut cand{cached_norm ? ctx->dc : ctx->dv_full, cached_norm || by_sequence ? ctx->ksal : nullptr,
@@ -568,7 +575,9 @@ int dyllm_create(const dyllm_layer_cfg *cfg, dyllm_ctx **out) {
   ctx->part_elems = l.part_elems;
   ctx->cosb = (float *)(b + l.cosb); ctx->flag = (uint8_t *)(b + l.flag);
   ctx->hs = (float *)(b + l.hs); ctx->fs = b + l.fs; ctx->act = b + l.act;
-  ctx->status = (int32_t *)(b + l.status); ctx->plan = ctx->status + 8; ctx->plan_up = ctx->plan + mm::PLAN_WORDS; ctx->plan_down = ctx->plan_up + mm::PLAN_WORDS; ctx->rope = (float *)(b + l.rope);
+  ctx->status = (int32_t *)(b + l.status); ctx->rope = (float *)(b + l.rope);
+  ctx->plan = ctx->status + PLANS_AT;
+  ctx->plan_up = ctx->plan + mm::PLAN_WORDS; ctx->plan_down = ctx->plan_up + mm::PLAN_WORDS; ctx->plan_kv = ctx->plan_down + mm::PLAN_WORDS;
   ctx->dv_full = b + l.dv_full; ctx->dc = b + l.dc; ctx->csal = b + l.csal; ctx->pos = (int32_t *)(b + l.pos);
   ctx->win_idx = (int32_t *)(b + l.win_idx); ctx->win_off = (int32_t *)(b + l.win_off);
   ctx->ksal = b + l.ksal; ctx->scan = (int32_t *)(b + l.scan);
@@ -583,7 +592,7 @@ int dyllm_create(const dyllm_layer_cfg *cfg, dyllm_ctx **out) {
       tab[((size_t)p * half + j) * 2 + 1] = (float)sin(ang);
     }
   hipError_t e = hipMemcpy(ctx->rope, tab.data(), tab.size() * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemset(ctx->status, 0, 256);
+  if (e == hipSuccess) e = hipMemset(ctx->status, 0, STATUS_BYTES);
   if (e == hipSuccess) e = hipMemset(ctx->dv_full, 0, l.dc - l.dv_full);
   if (e == hipSuccess) e = hipMemset(ctx->pos, 0, l.win_idx - l.pos);
   if (e == hipSuccess) e = hipMemset(ctx->scan, 0, (size_t)compact_scan_words() * 4);

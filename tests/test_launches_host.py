@@ -1,0 +1,77 @@
+"""The launches of whole calls, recorded without a GPU (launch_probe.hip): every GEMM and row kernel that reads a plan from device memory finds there
+the plan that was made for it."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2603_08026_amd import binding, build
+
+SHAPES = {  # hidden, query heads, KV heads, head_dim, FFN width
+    "8b": (4096, 32, 32, 128, 12288),
+    "7b": (3584, 28, 4, 128, 18944),
+    "split down": (512, 4, 2, 128, 4096),
+    "no sums": (512, 8, 8, 64, 640),
+}
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    if not os.path.exists(binding.LIB_PATH):
+        build.build(verbose=False)
+    exe = str(tmp_path_factory.mktemp("launch") / "probe")
+    d, so = os.path.split(binding.LIB_PATH)
+    r = subprocess.run([build.HIPCC, *build.FLAGS, "-O1", "-rdynamic", os.path.join(build.TESTS, "launch_probe.hip"), "-o", exe, "-L" + d, "-l:" + so,
+                        "-Wl,-rpath," + d], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return exe
+
+
+def launches(probe, case, cap, shape, B=3, L=900, lo=0, cached=0):
+    r = subprocess.run([probe, case] + [str(v) for v in (cap, *SHAPES[shape], B, L, lo, cached)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr
+    out = []
+    for line in r.stdout.splitlines():
+        name, *words = line.split(" ")
+        out.append((name, [tuple(w.split("=")) for w in words]))
+    return out
+
+
+def check(events):
+    """A plan is made (by a row kernel, or by a GEMM for itself), read by the GEMM it was made for, and by the row kernel behind that GEMM;
+    nothing else is put in its place in between.  Returns how many GEMMs read a plan made ahead."""
+    held, reads, last = {}, 0, None  # words -> (launch that made the plan, GEMM that has run by it)
+    for i, (name, words) in enumerate(events):
+        for what, at in words:
+            assert at not in ("0", "(nil)"), (i, name, what)  # a plan from nowhere
+            if what == "reads":
+                assert at in held and held[at][1] is None, (i, name, "reads a plan that another GEMM has used or nobody has made")
+                held[at] = (held[at][0], i)
+                last = at
+                reads += 1
+            elif what == "splits":
+                assert at == last and held[at][1] is not None, (i, name, "reads the splits of another GEMM")
+            else:
+                assert at not in held or held[at][1] is not None, (i, name, "a plan was made and nobody has read it")
+                gemm = "k_gemm_planned" in name
+                held[at] = (i, i if gemm else None)
+                if gemm:
+                    last = at
+    assert all(gemm is not None for _, gemm in held.values()), "a plan that nobody reads"
+    return reads
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("cap", [100, 200, 300, 1000, 2700])
+@pytest.mark.parametrize("case,lo,cached", [("step", 0, 0), ("ffn", 0, 0), ("approx", 0, 0), ("approx", 700, 0), ("approx", 0, 1), ("approx", 700, 1)])
+def test_plans_reach_their_gemms(probe, shape, cap, case, lo, cached):
+    ahead = check(launches(probe, case, cap, shape, lo=lo, cached=cached))
+    assert ahead == (0 if cap <= 256 else 2 if case == "ffn" else 3)
+
+
+# The norm kernel leaves the plan of the candidates' k and v ahead of the GEMM for q of all tokens: that GEMM makes a plan of its own where
+# the device counts its rows.
+@pytest.mark.parametrize("cached", [0, 1])
+@pytest.mark.parametrize("shape", ["8b", "split down"])
+def test_candidates_plan_outlasts_the_query_projection(probe, shape, cached):
+    assert check(launches(probe, "counted window", 1000, shape, lo=500, cached=cached)) == 3
