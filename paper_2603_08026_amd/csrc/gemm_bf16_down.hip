@@ -30,11 +30,13 @@ DownChoice choose_down(const Rows &rows, int N, int K, size_t part_elems) {
   return c;
 }
 
+Way down_way(const Rows &rows, int K, int N) { return way_of(rows.cap, true, ring_ok(GemmA{nullptr, nullptr, K}, K, wseg_one(nullptr, N), N)); }
+
 }  // namespace
 
 PlanJob gemm_bf16_down_plan(Rows rows, int K, int N, size_t part_elems, int32_t *plan_dev) {
   PlanJob job{};
-  if (rows.cap <= STREAM_ROWS || plan_known(rows) || !ring_ok(GemmA{nullptr, nullptr, K}, K, wseg_one(nullptr, N), N)) return job;
+  if (!wants_plan(down_way(rows, K, N), rows)) return job;
   const DownChoice c = choose_down(rows, N, K, part_elems);
   job.args = c.pa;
   job.rows = rows;
@@ -46,22 +48,22 @@ PlanJob gemm_bf16_down_plan(Rows rows, int K, int N, size_t part_elems, int32_t 
 
 void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const float *h, void *out,
                     float *part, size_t part_elems, const PlanJob &job, hipStream_t s) {
-  if (rows.cap <= 0) return;
+  const Way way = way_with(down_way(rows, K, N), rows, job.words);
+  if (way == Way::NONE) return;
   const EpiDown<bf16_t> e{h, (bf16_t *)out, N};
   const WSeg seg = wseg_one(wd, N);
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
-  const bool ring = ring_ok(A, K, seg, N);
-  PlanArgs pa = down_plan_args(N, K, part_elems, ring, cus_of_xcd());
+  PlanArgs pa = down_plan_args(N, K, part_elems, way != Way::EIGHT, cus_of_xcd());
   const bool once = past_l2(N, K);
   Splits sp;
-  if (rows.cap <= STREAM_ROWS) {
+  if (way == Way::STREAM) {
     sp.n = stream_split(pa, rows.cap);
     with_once(once, [&](auto o) {
       if (sp.n == 1) run_tiles<SkinnyS<decltype(o)::value>, false>(ga, e, 1, s);
       else run_tiles<SkinnyS<decltype(o)::value>, true>(ga, e, sp.n, s);
     });
     if (sp.n == 1) return;
-  } else if (!ring) {
+  } else if (way == Way::EIGHT) {
     pa.stream_cols = 0;
     sp.n = plan_of(pa, rows.cap, first_on_host(pa, rows.cap)).sk;
     if (sp.n == 1) {

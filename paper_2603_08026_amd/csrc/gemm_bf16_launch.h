@@ -89,6 +89,8 @@ int ring_grid() { return std::max(N_XCD, cu_count() / N_XCD * N_XCD); }
 
 int cus_of_xcd() { return ring_grid() / N_XCD; }
 bool plan_known(const Rows &rows) { return mm::plan_known(rows.count != nullptr, rows.cap); }
+bool wants_plan(Way way, const Rows &rows) { return mm::wants_plan(way, rows.count != nullptr, rows.cap); }
+Way way_with(Way way, const Rows &rows, bool made) { return mm::way_with(way, rows.count != nullptr, rows.cap, made); }
 
 constexpr GemmPlan NO_PLAN{0, 1, 0, 1, 256};
 // The plan of a GEMM whose row count the host knows; anything else is planned on the device

@@ -28,12 +28,14 @@ RawChoice choose_raw(const Rows &rows, int N, int K, size_t part_elems, const Qk
   return c;
 }
 
+Way raw_way(const GemmA &A, const Rows &rows, int K, const WSeg &seg) { return way_of(rows.cap, true, ring_ok(A, K, seg, seg.n_end[2])); }
+
 }  // namespace
 
 PlanJob gemm_bf16_raw_plan(GemmA A, Rows rows, int K, WSeg seg, size_t part_elems, int32_t *plan_dev, const QkvOut &qkv) {
   PlanJob job{};
   const int N = seg.n_end[2];
-  if (rows.cap <= STREAM_ROWS || plan_known(rows) || !ring_ok(A, K, seg, N)) return job;
+  if (!wants_plan(raw_way(A, rows, K, seg), rows)) return job;
   const RawChoice c = choose_raw(rows, N, K, part_elems, qkv);
   job.args = c.pa;
   job.full = c.full;
@@ -48,13 +50,13 @@ PlanJob gemm_bf16_raw_plan(GemmA A, Rows rows, int K, WSeg seg, size_t part_elem
 Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t part_elems, int32_t *plan_dev, const PlanJob &job,
                      const QkvOut &qkv, hipStream_t s) {
   Splits out;
-  if (rows.cap <= 0) return out;
+  const Way way = raw_way(A, rows, K, seg);
+  if (way == Way::NONE) return out;
   const int N = seg.n_end[2];
   const GemmArgs ga = gemm_args(A, rows, K, seg, nullptr, part);
-  const bool ring = ring_ok(A, K, seg, N);
-  PlanArgs pa = raw_plan_args(N, K, part_elems, ring, cus_of_xcd());
+  PlanArgs pa = raw_plan_args(N, K, part_elems, way != Way::EIGHT, cus_of_xcd());
   const bool once = past_l2(N, K);
-  if (rows.cap <= STREAM_ROWS) {
+  if (way == Way::STREAM) {
     const EpiStoreF32 e{part, N};
     out.n = stream_split(pa, rows.cap);
     with_once(once, [&](auto o) {
@@ -64,7 +66,7 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
     });
     return out;
   }
-  if (ring) {
+  if (way == Way::TILES) {
     const bool made = job.words != nullptr, finishes = can_finish(qkv);
     const RawChoice c = made ? RawChoice{job.args, job.full, job.finishing} : choose_raw(rows, N, K, part_elems, qkv);
     if (!c.finishing) {

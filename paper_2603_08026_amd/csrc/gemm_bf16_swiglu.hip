@@ -28,13 +28,15 @@ template <bool ONCE> struct SwigluKind {
   }
 };
 
-bool streams(const Rows &rows, int N) { return rows.cap <= STREAM_ROWS && (N % 48 == 0 || N % 64 == 0); }
+Way swiglu_way(const Rows &rows, int K, int N) {
+  return way_of(rows.cap, N % 48 == 0 || N % 64 == 0, ring_ok(GemmA{nullptr, nullptr, K}, K, wseg_one(nullptr, N), N));
+}
 
 }  // namespace
 
 PlanJob gemm_bf16_swiglu_plan(Rows rows, int K, int N, int32_t *plan_dev) {
   PlanJob job{};
-  if (rows.cap <= 0 || streams(rows, N) || plan_known(rows) || !ring_ok(GemmA{nullptr, nullptr, K}, K, wseg_one(nullptr, N), N)) return job;
+  if (!wants_plan(swiglu_way(rows, K, N), rows)) return job;
   job.args = swiglu_plan_args(N, K, cus_of_xcd());
   job.rows = rows;
   job.words = plan_dev;
@@ -42,18 +44,19 @@ PlanJob gemm_bf16_swiglu_plan(Rows rows, int K, int N, int32_t *plan_dev) {
 }
 
 void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const void *wu, void *act, const PlanJob &job, hipStream_t s) {
-  if (rows.cap <= 0) return;
+  const Way way = way_with(swiglu_way(rows, K, N), rows, job.words);
+  if (way == Way::NONE) return;
   const EpiSwiGLU<bf16_t> e{(bf16_t *)act, N};
   const WSeg seg = wseg_one(wg, N);
   const GemmArgs ga = gemm_args(A, rows, K, seg, wu, nullptr);
   const bool once = past_l2(2 * N, K);
-  if (streams(rows, N)) {
+  if (way == Way::STREAM) {
     with_once(once, [&](auto o) {
       constexpr bool ONCE = decltype(o)::value;
       if (N % 48 == 0) run_tiles<SkinnyW96<ONCE>, false>(halves_args(ga), EpiSwiGLUHalves<bf16_t, 48>{(bf16_t *)act, N}, 1, s);
       else run_tiles<SkinnyH128<ONCE>, false>(halves_args(ga), EpiSwiGLUHalves<bf16_t, 64>{(bf16_t *)act, N}, 1, s);
     });
-  } else if (!ring_ok(A, K, seg, N)) {
+  } else if (way == Way::EIGHT) {
     run_tiles<LargeD8, false>(ga, e, 1, s);
   } else {
     const PlanArgs pa = swiglu_plan_args(N, K, cus_of_xcd());

@@ -283,6 +283,16 @@ inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int c
 // Is the plan made on the host?  When the count is known here; and for a list of up to 256 entries, one row
 // tile whatever its count: the same shapes serve, and the device's own plan costs 2 us of a GEMM and its row kernel.
 inline bool plan_known(bool count_on_device, int cap) { return !count_on_device || cap <= 256; }
+// What the rows of a GEMM go through: nothing, weight-streaming tiles alone (streams: up to 128 rows, where the shape has such tiles), row tiles
+// of the ring loop by a plan, or the eight-wave shapes, which need neither
+enum class Way { NONE, STREAM, TILES, EIGHT };
+inline Way way_of(int cap, bool streams, bool ring) {
+  return cap <= 0 ? Way::NONE : streams && cap <= STREAM_ROWS ? Way::STREAM : ring ? Way::TILES : Way::EIGHT;
+}
+// Is a plan to be made on the device?  The launcher of a GEMM and what has its plan made ahead both ask here.
+inline bool wants_plan(Way way, bool count_on_device, int cap) { return way == Way::TILES && !plan_known(count_on_device, cap); }
+// The way of a GEMM whose kernel cannot make its plan: without one (made) the rows take the shapes that need none
+inline Way way_with(Way way, bool count_on_device, int cap, bool made) { return wants_plan(way, count_on_device, cap) && !made ? Way::EIGHT : way; }
 // Does the down projection get a sum kernel behind it, and so a plan that may split K or stream a last row tile?
 // Always where the plan for the full length wants it.  Where the device may find fewer rows, also if the list is long
 // (SUM_CAP) or K is: a few rows without a split take the whole K loop of one row tile, against the sum kernel's

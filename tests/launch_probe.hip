@@ -98,6 +98,10 @@ int main(int argc, char **argv) {
     rc = enqueue_approx_layer(ctx, &w, &cache, x, &in, B, L, win, true, 0.5f, cached, &out, cos, nullptr);
   } else if (what == "ffn") {
     rc = dyllm_salient_ffn(ctx, &w, x, cache.c, &in, B, L, cache.out, nullptr);
+  } else if (what == "down alone") {  // a GEMM whose plan nobody has made
+    launch_gemm_down(BF16, ctx->act, rows_of(&in, B), cfg.ffn_dim, cfg.hidden, w.w_down, ctx->hs, cache.out, ctx->part_o, ctx->part_elems, PlanJob{}, nullptr);
+  } else if (what == "up alone") {
+    launch_gemm_swiglu(ctx->fs, rows_of(&in, B), cfg.hidden, cfg.ffn_dim, w.w_gate, w.w_up, ctx->act, PlanJob{}, nullptr);
   } else {
     rc = 4;
   }

@@ -14,6 +14,9 @@ SOURCE = r"""
 #include "%s/gemm_plan.h"
 using namespace dy::mm;
 extern "C" int groups_ok(int end0, int end1) { return ring_groups_ok(end0, end1); }
+// 0: nothing, 1: weight-streaming tiles, 2: row tiles, 3: eight-wave shapes; for a GEMM whose kernel cannot make its plan
+extern "C" int way(int cap, int streams, int ring, int listed, int made) { return (int)way_with(way_of(cap, streams, ring), listed, cap, made); }
+extern "C" int ahead(int cap, int streams, int ring, int listed) { return wants_plan(way_of(cap, streams, ring), listed, cap); }
 // raw result of `cap` rows (listed: of a list, whose count is on the device) of `tokens`: in the kernel that can finish rows?
 extern "C" int finishes(int N, int K, long part_elems, int listed, int cap, long tokens) {
   const bool few = few_of_room(listed, cap, tokens) || few_results(plan_known(listed, cap), cap, N);
@@ -69,6 +72,18 @@ def test_matrix_ends_inside_a_group_of_permuted_rows_are_not_for_the_ring_loop(l
 def test_ends_of_the_stacked_projections_are(lib, dq, dkv):
     assert lib.groups_ok(dq, dq + dkv)
     assert lib.groups_ok(dkv, 2 * dkv)
+
+
+def test_row_tiles_of_counted_rows_have_a_plan(lib):
+    for cap in (0, 1, 128, 129, 256, 257, 5000):
+        for streams in (0, 1):
+            for ring in (0, 1):
+                for listed in (0, 1):
+                    base = 0 if cap == 0 else 1 if streams and cap <= 128 else 2 if ring else 3
+                    device = base == 2 and listed and cap > 256  # its plan is made on the device
+                    assert lib.ahead(cap, streams, ring, listed) == int(device)
+                    assert lib.way(cap, streams, ring, listed, 1) == base
+                    assert lib.way(cap, streams, ring, listed, 0) == (3 if device else base)
 
 
 @pytest.mark.parametrize("case", range(len(REGIMES)))

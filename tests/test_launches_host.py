@@ -75,3 +75,10 @@ def test_plans_reach_their_gemms(probe, shape, cap, case, lo, cached):
 @pytest.mark.parametrize("shape", ["8b", "split down"])
 def test_candidates_plan_outlasts_the_query_projection(probe, shape, cached):
     assert check(launches(probe, "counted window", 1000, shape, lo=500, cached=cached)) == 3
+
+# A GEMM that cannot plan for itself and gets no plan takes tiles that need none.
+@pytest.mark.parametrize("case", ["down alone", "up alone"])
+@pytest.mark.parametrize("cap", [300, 2700])
+def test_gemm_without_a_plan(probe, case, cap):
+    events = launches(probe, case, cap, "8b")
+    assert events and not any("k_gemm_planned" in name for name, _ in events), events
