@@ -215,7 +215,7 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
     // (a caller may hand over x for a result: its rows are then normalised first, in a launch of their own)
     const size_t T = (size_t)B * L, xb = T * c.hidden * 4, kvb = T * ctx->dkv * 4;
     const bool over_x = overlap(x, xb, q_out, (size_t)rows.cap * ctx->dq * 4) || overlap(x, xb, cache->k, kvb) || overlap(x, xb, cache->v, kvb);
-    if (over_x) launch_gather_rmsnorm(F32, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, PlanJob{}, s);
+    if (over_x) launch_gather_rmsnorm(F32, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, PlanMaker{}, s);
     prof_mark(ctx, ST_GATHER_NORM, s);
     launch_qkv_f32(over_x ? ctx->ns : x, over_x ? nullptr : w->g_attn, c.rms_eps, rows, c.hidden, seg, out, s);
     prof_mark(ctx, ST_GEMM_QKV, s);
@@ -224,7 +224,7 @@ int enqueue_qkv(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, Row
   }
   const GemmA A{ctx->ns, nullptr, c.hidden};
   const PlanJob job = plan_gemm_raw(BF16, A, rows, c.hidden, seg, ctx->part_elems, ctx->plan, out);
-  launch_gather_rmsnorm(BF16, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, job, s);
+  launch_gather_rmsnorm(BF16, x, w->g_attn, rows, c.hidden, c.rms_eps, ctx->ns, 0, job.make, s);
   prof_mark(ctx, ST_GATHER_NORM, s);
   const Splits splits = launch_gemm_raw(BF16, A, rows, c.hidden, seg, ctx->part_o, ctx->part_elems, ctx->plan, job, out, s);
   prof_mark(ctx, ST_GEMM_QKV, s);
@@ -275,7 +275,7 @@ int enqueue_ffn(dyllm_ctx *ctx, const dyllm_layer_weights *w, const void *x, con
     up = plan_gemm_swiglu(rows, c.hidden, c.ffn_dim, ctx->plan_up);
     down = plan_gemm_down(BF16, rows, c.ffn_dim, c.hidden, ctx->part_elems, ctx->plan_down);
     prof_mark(ctx, ST_GEMM_OPROJ, s);
-    launch_oproj_finalize(ctx->part_o, splits, x, w->g_ffn, rows, c.hidden, c.rms_eps, ctx->hs, ctx->fs, up, down, s);
+    launch_oproj_finalize(ctx->part_o, splits, x, w->g_ffn, rows, c.hidden, c.rms_eps, ctx->hs, ctx->fs, up.make, down.make, s);
     prof_mark(ctx, ST_NORM_FFN, s);
     launch_gemm_swiglu(ctx->fs, rows, c.hidden, c.ffn_dim, w->w_gate, w->w_up, ctx->act, up, s);
   }
@@ -405,14 +405,14 @@ int enqueue_approx_layer(dyllm_ctx *ctx, const dyllm_layer_weights *w, dyllm_lay
     if (dt(ctx) == F32) {
       launch_qkv_f32(x, w->g_attn, c.rms_eps, all, c.hidden, wseg_one(w->wq, ctx->dq), out, s);
     } else {
-      launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, shared, shared ? kv_job : PlanJob{}, s);
+      launch_gather_rmsnorm(BF16, x, w->g_attn, all, c.hidden, c.rms_eps, ctx->ns, shared, shared ? kv_job.make : PlanMaker{}, s);
       const Splits splits = launch_gemm_raw(BF16, GemmA{ctx->ns, shared ? all.idx : nullptr, c.hidden, T}, all, c.hidden,
                                             wseg_one(w->wq, ctx->dq), ctx->part_o, ctx->part_elems, ctx->plan, PlanJob{}, out, s);
       launch_qkv_finalize(BF16, ctx->part_o, splits, all, out, nullptr, s);
     }
   }
   // k, v of the salient tokens: norm, projection, rotation, value residual, merge into the caches
-  if (!shared) launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, 0, kv_job, s);
+  if (!shared) launch_gather_rmsnorm(dt(ctx), x, w->g_attn, rin, c.hidden, c.rms_eps, ctx->fs, 0, kv_job.make, s);
   {
     const Splits splits = launch_gemm_raw(dt(ctx), kv_a, rin, c.hidden, kv, ctx->part_o, ctx->part_elems, ctx->plan_kv, kv_job, kv_beside, s);
     // value residual: by token or by sequence into the zero-padded [T, dkv] buffer (Alg. 4 as printed), or by list

@@ -38,17 +38,17 @@ PlanJob gemm_bf16_down_plan(Rows rows, int K, int N, size_t part_elems, int32_t 
   PlanJob job{};
   if (!wants_plan(down_way(rows, K, N), rows)) return job;
   const DownChoice c = choose_down(rows, N, K, part_elems);
-  job.args = c.pa;
-  job.rows = rows;
-  job.words = plan_dev;
+  job.make.args = c.pa;
+  job.make.rows = rows;
+  job.make.words = plan_dev;
   job.sums = c.sums;
-  job.finishes = true;
+  job.make.finishes = true;
   return job;
 }
 
 void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const float *h, void *out,
                     float *part, size_t part_elems, const PlanJob &job, hipStream_t s) {
-  const Way way = way_with(down_way(rows, K, N), rows, job.words);
+  const Way way = way_with(down_way(rows, K, N), rows, job.make.words);
   if (way == Way::NONE) return;
   const EpiDown<bf16_t> e{h, (bf16_t *)out, N};
   const WSeg seg = wseg_one(wd, N);
@@ -73,11 +73,11 @@ void gemm_bf16_down(GemmA A, Rows rows, int K, int N, const void *wd, const floa
     run_tiles<LargeS8, true>(ga, e, sp.n, s);
   } else {
     const bool known = plan_known(rows);
-    const DownChoice c = known ? choose_down(rows, N, K, part_elems) : DownChoice{job.args, job.sums};
+    const DownChoice c = known ? choose_down(rows, N, K, part_elems) : DownChoice{job.make.args, job.sums};
     const GemmPlan pl = plan_here(ga, c.pa);
-    with_once(once, [&](auto o) { run_planned<DownKind<decltype(o)::value>>(ga, e, c.pa, pl, job.words, true, s); });
+    with_once(once, [&](auto o) { run_planned<DownKind<decltype(o)::value>>(ga, e, c.pa, pl, job.make.words, true, s); });
     if (!c.sums || (known && pl.sk == 1 && pl.row_hi == rows.cap)) return;
-    sp = splits_of(ga, pl, true, job.words);
+    sp = splits_of(ga, pl, true, job.make.words);
   }
   launch_down_finalize(part, sp, h, rows, N, out, s);
 }

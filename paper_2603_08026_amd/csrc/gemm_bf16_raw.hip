@@ -37,12 +37,12 @@ PlanJob gemm_bf16_raw_plan(GemmA A, Rows rows, int K, WSeg seg, size_t part_elem
   const int N = seg.n_end[2];
   if (!wants_plan(raw_way(A, rows, K, seg), rows)) return job;
   const RawChoice c = choose_raw(rows, N, K, part_elems, qkv);
-  job.args = c.pa;
+  job.make.args = c.pa;
   job.full = c.full;
-  job.rows = rows;
-  job.words = plan_dev;
+  job.make.rows = rows;
+  job.make.words = plan_dev;
   job.finishing = c.finishing;
-  job.finishes = c.finishing && can_finish(qkv);
+  job.make.finishes = c.finishing && can_finish(qkv);
   return job;
 }
 
@@ -67,8 +67,8 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
     return out;
   }
   if (way == Way::TILES) {
-    const bool made = job.words != nullptr, finishes = can_finish(qkv);
-    const RawChoice c = made ? RawChoice{job.args, job.full, job.finishing} : choose_raw(rows, N, K, part_elems, qkv);
+    const bool made = job.make.words != nullptr, finishes = can_finish(qkv);
+    const RawChoice c = made ? RawChoice{job.make.args, job.full, job.finishing} : choose_raw(rows, N, K, part_elems, qkv);
     if (!c.finishing) {
       with_once(once, [&](auto o) { run_planned<RawKind<EpiStoreF32, decltype(o)::value>>(ga, EpiStoreF32{part, N}, c.pa, c.full, plan_dev, made, s); });
       return splits_of(ga, c.full, false, plan_dev);

@@ -37,14 +37,14 @@ Way swiglu_way(const Rows &rows, int K, int N) {
 PlanJob gemm_bf16_swiglu_plan(Rows rows, int K, int N, int32_t *plan_dev) {
   PlanJob job{};
   if (!wants_plan(swiglu_way(rows, K, N), rows)) return job;
-  job.args = swiglu_plan_args(N, K, cus_of_xcd());
-  job.rows = rows;
-  job.words = plan_dev;
+  job.make.args = swiglu_plan_args(N, K, cus_of_xcd());
+  job.make.rows = rows;
+  job.make.words = plan_dev;
   return job;
 }
 
 void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const void *wu, void *act, const PlanJob &job, hipStream_t s) {
-  const Way way = way_with(swiglu_way(rows, K, N), rows, job.words);
+  const Way way = way_with(swiglu_way(rows, K, N), rows, job.make.words);
   if (way == Way::NONE) return;
   const EpiSwiGLU<bf16_t> e{(bf16_t *)act, N};
   const WSeg seg = wseg_one(wg, N);
@@ -60,7 +60,7 @@ void gemm_bf16_swiglu(GemmA A, Rows rows, int K, int N, const void *wg, const vo
     run_tiles<LargeD8, false>(ga, e, 1, s);
   } else {
     const PlanArgs pa = swiglu_plan_args(N, K, cus_of_xcd());
-    with_once(once, [&](auto o) { run_planned<SwigluKind<decltype(o)::value>>(ga, e, pa, plan_here(ga, pa), job.words, true, s); });
+    with_once(once, [&](auto o) { run_planned<SwigluKind<decltype(o)::value>>(ga, e, pa, plan_here(ga, pa), job.make.words, true, s); });
   }
 }
 

@@ -29,14 +29,18 @@ struct Splits {
 
 // The plan of a GEMM whose rows the device counts, to be made by a row kernel ahead of it (plan_gemm_*): a workgroup of
 // that kernel prices the candidates while the others take their rows, and the GEMM reads words.  words == nullptr: no such job.
-struct PlanJob {
+struct PlanMaker {
   mm::PlanArgs args;
-  mm::GemmPlan full;  // raw results: the plan of a full list, where it was looked at
   Rows rows;
   int32_t *words = nullptr;
+  bool finishes = false;  // the GEMM finishes the rows whose K is not split
+};
+// ... and what the launcher of that GEMM keeps of its choice
+struct PlanJob {
+  PlanMaker make;
+  mm::GemmPlan full;       // raw results: the plan of a full list, where it was looked at
   bool finishing = false;  // raw results: the kernel that can finish rows is taken
   bool sums = false;       // down projection: a kernel for split sums follows
-  bool finishes = false;   // the GEMM finishes the rows whose K is not split
 };
 
 // Candidates of the approximate update of a sequence (bf16, head_dim 128): up to a fifth of its tokens their keys and
@@ -71,7 +75,7 @@ struct QkvOut {
 // ---- row kernels (HBM-bound) ------------------------------------------------------------------
 // out[j,:] (by_token: out[row_j,:]) = RMSNorm(x[row_j,:]) * gain            x: [T,d] T-typed, out: [cap,d] ([T,d]) T-typed
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
-                           void *out, int by_token, const PlanJob &job, hipStream_t s);
+                           void *out, int by_token, const PlanMaker &job, hipStream_t s);
 // The GEMMs leave fp32 "raw" results part[z][j][n] (z = K split, j = position in the row list); the
 // finalize kernels below sum the splits and apply the fused tail of the step, one workgroup per row.
 //
@@ -95,7 +99,7 @@ void launch_qkv_finalize(DType t, const float *part, Splits splits, Rows rows, c
 // out-projection (bf16): h[j] = x[row_j] + sum of splits (fp32 [cap,d]); f[j] = RMSNorm(h[j]) * gain
 void launch_oproj_finalize(const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
-                           const PlanJob &job0, const PlanJob &job1, hipStream_t s);
+                           const PlanMaker &job0, const PlanMaker &job1, hipStream_t s);
 // down projection (bf16) after a K split: out_cache[row_j] = h[j] + sum of splits, for the rows from
 // splits.done_to on (the rows below it were written by the GEMM's own epilogue)
 void launch_down_finalize(const float *part, Splits splits, const float *h,

@@ -68,7 +68,7 @@ __device__ __forceinline__ int row_ahead(const Rows &rows, int j) { return rows.
 
 // The first workgroups of a row kernel, one for every job, make plans instead of taking rows (all NT threads, a multiple of four waves).  The
 // GEMM behind needs its plan as soon as it starts and would take 1.7 us to make it; here that happens beside the rows.  Hidden 4096: step of 410 listed rows 293 -> 285 us, of 2064 798.5 -> 796.9; loop of 8 x 1024 tokens 2004 -> 1956.
-template <int NT> __device__ __forceinline__ void make_plan(const PlanJob &job) {
+template <int NT> __device__ __forceinline__ void make_plan(const PlanMaker &job) {
   __shared__ uint32_t lds[2 * NT / WAVE];  // eight words for four waves, which all make the same plan
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const mm::GemmPlan p = mm::plan_on_device(job.args, row_count(job.rows), wave % 4, lds + 8 * (wave / 4));
@@ -83,7 +83,7 @@ template <int NT> __device__ __forceinline__ void make_plan(const PlanJob &job) 
 template <typename T, int NT, bool JOB, int NV>
 __global__ __launch_bounds__(NT, 8) void k_gather_rmsnorm(const T *__restrict__ x,
                                                         const T *__restrict__ gain, Rows rows, int d,
-                                                        float eps, T *__restrict__ out, int by_token, PlanJob job) {
+                                                        float eps, T *__restrict__ out, int by_token, PlanMaker job) {
   __shared__ float red[NT / WAVE];
   constexpr int N = Vec16<T>::N;
   constexpr int first = JOB ? 1 : 0;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(RB) void k_oproj_finalize(const float *__restrict__
                                                         const bf16_t *__restrict__ x,
                                                         const bf16_t *__restrict__ gain, Rows rows, int d,
                                                         float eps, float *__restrict__ h,
-                                                        bf16_t *__restrict__ f, PlanJob job0, PlanJob job1) {
+                                                        bf16_t *__restrict__ f, PlanMaker job0, PlanMaker job1) {
   __shared__ float red[RB / WAVE];
   const int first = JOBS ? (job0.words ? 1 : 0) + (job1.words ? 1 : 0) : 0;
   if constexpr (JOBS) {
@@ -563,7 +563,7 @@ inline int row_grid(const Rows &rows) { return row_grid(rows, rows.cap); }
 }  // namespace
 
 void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, int d, float eps,
-                           void *out, int by_token, const PlanJob &job, hipStream_t s) {
+                           void *out, int by_token, const PlanMaker &job, hipStream_t s) {
   if (rows.cap <= 0 && !job.words) return;
   const int most = rows.count ? 4 * GRID_LISTED : 32768;  // (a quarter of the threads per workgroup)
   const int plans = job.words ? 1 : 0, grid = std::max(std::min(rows.cap, most), 1) + plans, wide_grid = row_grid(rows) + plans;
@@ -584,7 +584,7 @@ void launch_gather_rmsnorm(DType t, const void *x, const void *gain, Rows rows, 
 
 void launch_oproj_finalize(const float *part, Splits splits, const void *x,
                            const void *gain, Rows rows, int d, float eps, float *h, void *f,
-                           const PlanJob &job0, const PlanJob &job1, hipStream_t s) {
+                           const PlanMaker &job0, const PlanMaker &job1, hipStream_t s) {
   if (rows.cap <= 0) return;
   const int plans = (job0.words ? 1 : 0) + (job1.words ? 1 : 0);
   auto go = [&](auto jobs_c) {

@@ -33,7 +33,7 @@ hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { 
 hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t) {
   const std::string &name = kernels()[f];
   auto is = [&](const char *part) { return name.find(part) != std::string::npos; };
-  auto maker = [&](int i) { return ((const PlanJob *)args[i])->words; };
+  auto maker = [&](int i) { return ((const PlanMaker *)args[i])->words; };
   printf("%s", name.c_str());
   if (is("k_gemm_planned")) {
     const int how = *(const int *)args[4];
