@@ -98,6 +98,9 @@ int main(int argc, char **argv) {
     rc = enqueue_approx_layer(ctx, &w, &cache, x, &in, B, L, win, true, 0.5f, cached, &out, cos, nullptr);
   } else if (what == "ffn") {
     rc = dyllm_salient_ffn(ctx, &w, x, cache.c, &in, B, L, cache.out, nullptr);
+  } else if (what == "attention") {  // rows in a tile, key splits, keys of a split
+    const AttnArgs a = attn_args(ctx, ctx->qs, cache.k, cache.v, rows_of(&in, B), in.offsets, B, L, nullptr, 0);
+    printf("plan bq=%d splits=%d chunk=%d\n", a.bq, a.splits, a.chunk);
   } else if (what == "down alone") {  // a GEMM whose plan nobody has made
     launch_gemm_down(BF16, ctx->act, rows_of(&in, B), cfg.ffn_dim, cfg.hidden, w.w_down, ctx->hs, cache.out, ctx->part_o, ctx->part_elems, PlanJob{}, nullptr);
   } else if (what == "up alone") {

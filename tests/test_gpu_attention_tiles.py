@@ -112,34 +112,48 @@ def test_copies_past_the_l2(heads, kv, L, counts):
         assert_close(got, ref.reshape(idx.size, -1), 2e-2, "context rows")
 
 
-# bf16, head_dim 128: the loop is unrolled over four stages and ends in tiles of its own, rows leave 4 * i + sub to an access, and a
-# reference that moves takes the half of the pending probabilities along: key counts around those of one to nine
-# tiles of 32 and of 64, row counts around those of a wave, keys that grow so that the reference moves all along the sweep, also back to
-# back.  Probabilities and results are rounded to bf16 once each (2^-8 of a weighted mean of values within 5): 2e-2.
-@pytest.mark.parametrize("L", [1, 31, 33, 64, 97, 128, 129, 161, 255, 257, 300])
-@pytest.mark.parametrize("heads,kv", [(2, 2), (6, 2)])
+# bf16, head_dim 128, two kernels: 128-row tiles with key tiles of 32 and 64-row tiles with key tiles of 64.  The loop over the key tiles is
+# unrolled over four stages from eight tiles on, takes the others but the last four one by one and ends in tiles of their own;
+# rows leave 4 * i + sub to an access; a reference that moves takes the half of the pending probabilities along.  So: row
+# counts around those of a wave and a tile, keys that grow so that the reference moves in every tile, and for each kernel, with all keys in one
+# split (rows finished in place), numbers of key tiles from one to ten and above, the last of them full and not.  Few rows are cut over
+# keys as well (2 and 6 heads: partial sums, merged by a kernel of their own).
+SWEEP_COUNTS = {1: (1, 3, 31, 33, 64, 65, 0, 127, 129), 4: (1, 8, 16, 17, 0, 32, 33, 35, 16)}  # by heads of a group
+SWEEP = ([(h, kv, 1, L) for h, kv in ((2, 2), (6, 2)) for L in (1, 31, 33, 64, 97, 128, 129, 161, 255, 257, 300)]
+         + [(16, 16, 1, L) for L in (1, 64, 65, 90, 97, 128, 129, 161, 200, 225, 257, 300, 320, 350, 385, 400, 449, 512, 513, 577, 769)]
+         + [(32, 8, 1, L) for L in (40, 200, 257, 449, 513, 577)] + [(16, 16, 4, L) for L in (1, 33, 64)])
+
+
+def sweep_lists(heads, kv, times, L):
+    """The lists of a case: ids, offsets, and the capacities they are given."""
+    counts = [min(L, c) for c in (SWEEP_COUNTS.get(heads // kv) or SWEEP_COUNTS[1])] * times
+    idx, off = rand_rows(75, len(counts), L, counts)
+    return idx, off, (idx.size, len(counts) * L)
+
+
+# Probabilities and results are rounded to bf16 once each (2^-8 of a weighted mean of values within 5): 2e-2.
+@pytest.mark.parametrize("heads,kv,times,L", SWEEP)
 @pytest.mark.parametrize("steep", [0.0, 0.3])
-def test_bf16_attention_sweep(heads, kv, L, steep):
-    print("bf16 attention sweep", heads, kv, L, steep, flush=True)
+def test_bf16_attention_sweep(heads, kv, times, L, steep):
+    print("bf16 attention sweep", heads, kv, times, L, steep, flush=True)
     s = W.LayerShape(hidden=128, n_heads=heads, n_kv_heads=kv, head_dim=128, ffn=128, dtype="bf16")
-    counts = [min(L, c) for c in (1, 3, 31, 33, 64, 65, 0, 127, 129)]
-    B = len(counts)
+    idx, off, caps = sweep_lists(heads, kv, times, L)
+    B = off.size - 1
     g = torch.Generator().manual_seed(17 * L + heads)
     k, v = (torch.randn(B, L, kv, 128, generator=g) for _ in range(2))
     q = torch.randn(B * L, heads, 128, generator=g)
     q[..., 0] = 12.0
-    k[..., 0] += steep * torch.arange(L).view(1, L, 1)  # scores rise by 0.3 * 12 / sqrt(128) a key
+    k[..., 0] += steep * torch.arange(L).view(1, L, 1)  # scores rise by 0.3 * 12 / sqrt(128) a key: 15 and 29 powers of two a tile
     q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
-    idx, off = rand_rows(75, B, L, counts)
+    ref = O.partial_attention(q.float().numpy()[idx], k.float().numpy(), v.float().numpy(), idx, B, L)
     lay = Layer.from_shape(s, B, L)
-    for cap in (idx.size, B * L):
+    for cap in caps:
         rows = lay.make_list(idx, off, cap=cap)
         qd = torch.zeros(cap, s.dq, dtype=torch.bfloat16, device="cuda")
         qd[:idx.size] = q.view(B * L, -1)[torch.from_numpy(idx).long()].cuda()
         out = torch.full((cap, s.dq), -7.0, dtype=torch.bfloat16, device="cuda")
         lay.ctx.partial_attention(qd, k.cuda(), v.cuda(), rows, B, L, out)
         torch.cuda.synchronize()
-        ref = O.partial_attention(q.float().numpy()[idx], k.float().numpy(), v.float().numpy(), idx, B, L)
         assert_close(to_host(out)[:idx.size], ref.reshape(idx.size, -1), 2e-2, "context rows")
         assert (out[idx.size:] == -7.0).all()
     lay.close()

@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from paper_2603_08026_amd import binding, build
+from tests.test_gpu_attention_tiles import SWEEP, sweep_lists
 
 SHAPES = {  # hidden, query heads, KV heads, head_dim, FFN width
     "8b": (4096, 32, 32, 128, 12288),
@@ -28,7 +29,7 @@ def probe(tmp_path_factory):
 
 
 def launches(probe, case, cap, shape, B=3, L=900, lo=0, cached=0):
-    r = subprocess.run([probe, case] + [str(v) for v in (cap, *SHAPES[shape], B, L, lo, cached)], capture_output=True, text=True, timeout=60)
+    r = subprocess.run([probe, case] + [str(v) for v in (cap, *SHAPES.get(shape, shape), B, L, lo, cached)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr
     out = []
     for line in r.stdout.splitlines():
@@ -82,3 +83,33 @@ def test_candidates_plan_outlasts_the_query_projection(probe, shape, cached):
 def test_gemm_without_a_plan(probe, case, cap):
     events = launches(probe, case, cap, "8b")
     assert events and not any("k_gemm_planned" in name for name, _ in events), events
+
+
+def attention_plan(probe, heads, kv, B, L, cap):
+    """Rows in a query tile, key splits, key tiles of the first split, whether a last tile is not full."""
+    (_, words), = launches(probe, "attention", cap, (128, heads, kv, 128, 128), B=B, L=L)
+    p = {k: int(v) for k, v in words}
+    tile = 32 if p["bq"] == 128 else 64
+    keys = min(L, p["chunk"])
+    return p["bq"], p["splits"], -(-keys // tile), keys % tile > 0
+
+
+def test_attention_sweep_runs_what_it_names(probe):
+    """Key tiles of the cases whose rows are finished in place, for both kernels; a case of several heads to a group in each, with a steady state
+    that is unrolled and a last tile that is not full; and cases that are cut over keys."""
+    seen, grouped, split = {64: {}, 128: {}}, set(), 0
+    for heads, kv, times, L in SWEEP:
+        idx, off, caps = sweep_lists(heads, kv, times, L)
+        for cap in caps:
+            bq, splits, tiles, partial = attention_plan(probe, heads, kv, off.size - 1, L, cap)
+            if splits > 1:
+                split += 1
+                continue
+            seen[bq].setdefault(tiles, set()).add(partial)
+            if heads > kv and tiles > 8 and partial:
+                grouped.add(bq)
+    for bq in (64, 128):
+        assert set(range(1, 11)) <= set(seen[bq]), (bq, sorted(seen[bq]))
+        assert any(n >= 12 for n in seen[bq])
+        assert sum(len(p) == 2 for p in seen[bq].values()) >= 3, seen[bq]
+    assert grouped == {64, 128} and split >= 10
