@@ -9,10 +9,11 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import dyllm_oracle as O
 from paper_2603_08026_amd import binding as Bd
-from paper_2603_08026_amd.layer import Layer
+from paper_2603_08026_amd.layer import Layer, to_host
 from synth import workload as W
-from tests.helpers import TOL, rand_rows, rand_weights
+from tests.helpers import TOL, assert_close, rand_rows, rand_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -75,4 +76,50 @@ def test_step(shape, B, L, n, full_cap):
         ref[j] = torch.einsum("hgl,lhd->hgd", p, v[b]).reshape(s.n_heads, s.head_dim)
     err = (new[at].float().cpu() - ref.view(n, -1)).abs().max() / ref.abs().max()
     assert float(err) <= TOL["bf16"]
+    lay.close()
+
+
+# Rows that the attention kernel commits (one key split), in 64-row tiles where the list is full and in 128-row tiles where it has room for every
+# token: rows per sequence that leave a wave partly filled, waves without a query and a second tile.
+COMMITTED = {"heads": (SHAPE, 200, [1, 33, 65, 100, 0, 129]), "groups": (GROUPED, 70, [1, 9, 17, 33, 0] * 4)}
+
+
+@pytest.mark.parametrize("name", COMMITTED)
+@pytest.mark.parametrize("full_cap", [False, True])
+@pytest.mark.parametrize("keep_lse", [False, True])
+def test_committed_rows(name, full_cap, keep_lse):
+    """Contexts, cosines and log-normalisers of the listed rows, and every bit of the others.  A normaliser is the logarithm of a sum of positive
+    terms that were each rounded once to the 8 bits of bf16, by 2^-8 of the term at most (half of the spacing above a power of two): the sum
+    is off by 2^-8 of itself at most, its logarithm by -log(1 - 2^-8) < 2^-8 + 2^-16; scores and the logarithm in fp32, of values up to 10: 2e-5."""
+    print("committed rows", name, full_cap, keep_lse, flush=True)
+    s, L, counts = COMMITTED[name]
+    B = len(counts)
+    T, n = B * L, sum(counts)
+    lay = Layer.from_shape(s, B, L, keep_lse=keep_lse)
+    lay.set_weights(rand_weights(s, 98, std=0.08))
+    gen = torch.Generator().manual_seed(99)
+    x = torch.randn(B, L, s.hidden, generator=gen).to(torch.bfloat16).cuda()
+    for t in (lay.k, lay.v, lay.c, lay.out) + ((lay.lse,) if keep_lse else ()):
+        t.copy_(torch.randn(t.shape, generator=gen).to(t.dtype))
+    old = [t.clone() for t in (lay.c.view(T, -1), lay.lse.view(T, -1) if keep_lse else lay.c.view(T, -1))]
+    idx, off = rand_rows(100, B, L, counts)
+    rows = lay.make_list(idx, off, cap=T if full_cap else n)
+    out = lay.layer_step(x, rows, 0.5, Bd.IndexList.empty(T, B))
+    assert lay.ctx.poll_status() == 0
+    c, cos = lay.c.view(T, -1).clone(), lay.cos[:n].clone()
+    lse = lay.lse.view(T, -1).clone() if keep_lse else None
+    q = torch.zeros(rows.cap, s.dq, dtype=torch.bfloat16, device="cuda")
+    lay.ctx.qkv_refresh(lay.w, x, rows, B, L, lay.cache, q)
+    qh, kh, vh = to_host(q)[:n].reshape(n, s.n_heads, s.head_dim), to_host(lay.k), to_host(lay.v)
+    at = torch.from_numpy(idx.astype(np.int64)).cuda()
+    assert_close(to_host(c)[idx], O.partial_attention(qh, kh, vh, idx, B, L), TOL["bf16"], "contexts")
+    cos64 = torch.nn.functional.cosine_similarity(c[at].double(), old[0][at].double(), dim=-1)
+    assert float((cos.double() - cos64).abs().max()) < 2e-5
+    assert np.array_equal(lay.read_list(out)[0], idx[cos.cpu().numpy() < np.float32(0.5)])
+    rest = torch.ones(T, dtype=torch.bool, device="cuda")
+    rest[at] = False
+    assert torch.equal(c[rest], old[0][rest])
+    if keep_lse:
+        assert np.abs(lse.cpu().numpy()[idx] - O.partial_lse(qh, kh, idx, B, L)).max() <= 2.0 ** -8 + 2.0 ** -16 + 2e-5
+        assert torch.equal(lse[rest], old[1][rest])
     lay.close()

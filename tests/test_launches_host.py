@@ -7,6 +7,7 @@ import pytest
 
 from paper_2603_08026_amd import binding, build
 from tests.test_gpu_attention_tiles import SWEEP, sweep_lists
+from tests.test_gpu_listed_steps import COMMITTED
 
 SHAPES = {  # hidden, query heads, KV heads, head_dim, FFN width
     "8b": (4096, 32, 32, 128, 12288),
@@ -113,3 +114,11 @@ def test_attention_sweep_runs_what_it_names(probe):
         assert any(n >= 12 for n in seen[bq])
         assert sum(len(p) == 2 for p in seen[bq].values()) >= 3, seen[bq]
     assert grouped == {64, 128} and split >= 10
+
+
+@pytest.mark.parametrize("name", COMMITTED)
+def test_committed_rows_run_what_they_name(probe, name):
+    s, L, counts = COMMITTED[name]
+    B = len(counts)
+    for cap, bq in ((sum(counts), 64), (B * L, 128)):
+        assert attention_plan(probe, s.n_heads, s.n_kv_heads, B, L, cap)[:2] == (bq, 1)
