@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = {
     "split down": W.LayerShape(hidden=512, n_heads=4, n_kv_heads=2, head_dim=128, ffn=4096, dtype="bf16"),
     "no sums": W.LayerShape(hidden=512, n_heads=8, n_kv_heads=8, head_dim=64, ffn=640, dtype="bf16"),
+    "wide": W.LayerShape(hidden=2048, n_heads=16, n_kv_heads=4, head_dim=128, ffn=2816, dtype="bf16"),
 }
 B, L = 3, 900
 COUNTS = [40, 1500, 128, 129, 600, 2700, 330, 0, 260]
@@ -23,7 +24,9 @@ def _caches(lay):
     return [lay.k, lay.v, lay.c, lay.out]
 
 
-@pytest.mark.parametrize("approx", [False, True])
+# approx: the first position of the approximate step (0: whole sequences, else a response window; listed tokens ahead of it get k and v alone),
+# or no such step
+@pytest.mark.parametrize("approx", [None, 0, 500])
 @pytest.mark.parametrize("name", SHAPES)
 def test_other_counts_before(name, approx):
     print("plans ahead", name, approx, flush=True)
@@ -47,8 +50,10 @@ def test_other_counts_before(name, approx):
             for t, t0 in zip(_caches(lay), start):
                 t.copy_(t0)
             rows = lay.make_list(idx, off, cap=T)
-            step = lay.layer_step_approx if approx else lay.layer_step
-            out = step(xs[1], rows, 0.9, Bd.IndexList.empty(T, B))
+            if approx is None:
+                out = lay.layer_step(xs[1], rows, 0.9, Bd.IndexList.empty(T, B))
+            else:
+                out = lay.layer_step_approx(xs[1], rows, 0.9, Bd.IndexList.empty(T, B), row_lo=approx)
             got.append([t.clone() for t in _caches(lay)] + [out.offsets.clone()])
             assert lay.ctx.poll_status() == 0
             if lay is not used:
