@@ -43,3 +43,39 @@ def test_norm_and_projection(hidden, kv, dh, bias):
         assert np.array_equal(kg[others], k0[others].astype(np.float64)) and np.array_equal(vg[others], v0[others].astype(np.float64))
         assert np.all(to_host(q_out)[idx.size:] == 0)
     lay.close()
+
+
+# fp32: the norm kernel runs ahead of the candidates' GEMM of the approximate step and where a result takes the place of x; one or two vectors a thread
+# (2048), up to four (2112, 4096), the wide workgroup (4160).  Sums of up to 4160 products in fp32, 2^-24 * sqrt(4160) = 4e-6 of their size: 1e-4 as
+# everywhere.
+@pytest.mark.parametrize("hidden", [64, 2048, 2112, 4096, 4160])
+@pytest.mark.parametrize("counts", [[3, 1], [90, 61]])
+def test_norm_and_projection_f32(hidden, counts):
+    print("fp32 row width", hidden, counts, flush=True)
+    s = W.LayerShape(hidden=hidden, n_heads=2, n_kv_heads=1, head_dim=64, ffn=128, dtype="f32")
+    cfg = oracle_cfg(s)
+    B, L = 2, 100
+    w = rand_weights(s, 95, bias=True)
+    x = W.philox(96, "x").standard_normal((B, L, hidden), dtype=np.float32)
+    idx, off = rand_rows(97, B, L, counts)
+    q, k, v = O.project_qkv(O.rmsnorm(x.reshape(B * L, -1)[idx], w["g_attn"], cfg.rms_eps), idx % L, w, cfg)
+    lay = Layer.from_shape(s, B, L)
+    lay.set_weights(w)
+    rows = lay.make_list(idx, off)
+    # q in the place of x (whose rows are the wider ones, or hold all of q between them)
+    room = torch.zeros(max(B * L * hidden, idx.size * s.dq), device="cuda")
+    xd = room[:B * L * hidden].view(B, L, hidden)
+    xd.copy_(torch.from_numpy(x))
+    lay.ctx.qkv_refresh(lay.w, xd, rows, B, L, lay.cache, room)
+    torch.cuda.synchronize()
+    assert_close(to_host(room[:idx.size * s.dq]), q.reshape(-1), 1e-4, "q in the place of x")
+    assert_close(to_host(lay.k).reshape(B * L, -1)[idx], k.reshape(idx.size, -1), 1e-4, "k rows")
+    # candidates of the approximate step, which also takes q of all tokens
+    lay.k.zero_()
+    lay.v.zero_()
+    lay.c.copy_(torch.randn(lay.c.shape, generator=torch.Generator().manual_seed(5)))
+    lay.layer_step_approx(lay.upload(x), rows, 0.5)
+    torch.cuda.synchronize()
+    assert_close(to_host(lay.k).reshape(B * L, -1)[idx], k.reshape(idx.size, -1), 1e-4, "candidates' k")
+    assert_close(to_host(lay.v).reshape(B * L, -1)[idx], v.reshape(idx.size, -1), 1e-4, "candidates' v")
+    lay.close()
