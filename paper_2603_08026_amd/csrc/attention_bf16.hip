@@ -849,10 +849,10 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
     const uint32_t tok = a.c_commit && a.rows.idx ? (uint32_t)a.rows.idx[jq] : (uint32_t)jq;
     place = tok * (uint32_t)a.H + (uint32_t)hq;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      row_at[i] = (uint32_t)__shfl((int)place, 4 * i + sub, WAVE);
-      old[i] = uint4{0, 0, 0, 0};
-      if (a.c_commit && wq * 32 + 4 * i + sub < nq) old[i] = *(reinterpret_cast<const uint4 *>((const bf16_t *)a.c_commit + (size_t)row_at[i] * DH) + cc);
+    for (int i = 0; i < 8; ++i) row_at[i] = (uint32_t)__shfl((int)place, 4 * i + sub, WAVE);
+    if (a.c_commit) {  // (rows past the end are the last one again)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) old[i] = *(reinterpret_cast<const uint4 *>((const bf16_t *)a.c_commit + (size_t)row_at[i] * DH) + cc);
     }
   }
   __syncthreads();  // every wave is done with the last tile: the stages become merge scratch
@@ -902,16 +902,23 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
       }
     asm volatile("" : : : "memory");  // the reads below are of another type (LDS accesses of a wave keep their order)
     bf16_t *out = (bf16_t *)(a.c_commit ? a.c_commit : a.out);
-    // Fused commit  [Alg. 3: cosine line and cache commit]: the old columns of the query's token were read above; the sums
-    // <new, old>, |new|^2, |old|^2 are taken over the stored values, and the head's go to cos_part.
-    float dot_r = 0.f, na_r = 0.f, nb_r = 0.f;  // of row 4 * cc + sub (lanes with cc < 8)
+    uint4 row[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int rr = 4 * i + sub;
-      const uint4 w = *reinterpret_cast<const uint4 *>(rows_lds + rr * ROWB + ((cc ^ (rr & 15)) * 16));
-      if (wq * 32 + rr < nq) *(reinterpret_cast<uint4 *>(out + (size_t)row_at[i] * DH) + cc) = w;
-      if (a.c_commit) {
-        const uint32_t nw[4] = {w.x, w.y, w.z, w.w}, ow[4] = {old[i].x, old[i].y, old[i].z, old[i].w};
+      row[i] = *reinterpret_cast<const uint4 *>(rows_lds + rr * ROWB + ((cc ^ (rr & 15)) * 16));
+    }
+    // Fused commit  [Alg. 3: cosine line and cache commit]: the old columns of the query's token were read above; the sums
+    // <new, old>, |new|^2, |old|^2 are taken over the stored values, and the head's go to cos_part.  All sums ahead of all
+    // stores: a wait for a cached row also waits for the stores before it, and with each row's store ahead of its sums eight of them
+    // were waited for in turn.  Rows in the accumulators' order / whole, a store and a wait each / as here, us: 330 rows of 8 x 1024 tokens, 32
+    // heads, one item a CU 34.2 / 35.4 / 34.4; 5200 of 16 x 1280 172 / 168 / 165; 28 over 4 heads at 7 % 52.4 / 50.2 / 49.7; 64-row tiles,
+    // 160 rows of 4 x 1024 26.9 / 27.7 / 27.2.
+    float dot_r = 0.f, na_r = 0.f, nb_r = 0.f;  // of row 4 * cc + sub (lanes with cc < 8)
+    if (a.c_commit) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t nw[4] = {row[i].x, row[i].y, row[i].z, row[i].w}, ow[4] = {old[i].x, old[i].y, old[i].z, old[i].w};
         float dot = 0.f, na = 0.f, nb = 0.f;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -927,6 +934,9 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
         if (cc == i) { dot_r = dot; na_r = na; nb_r = nb; }
       }
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (wq * 32 + 4 * i + sub < nq) *(reinterpret_cast<uint4 *>(out + (size_t)row_at[i] * DH) + cc) = row[i];
     if (a.c_commit) {
       if (a.lse_out && lhi == 0 && wq * 32 + l32 < nq) a.lse_out[place] = m_run * LN2 + __logf(l_run);
       const int rr = 4 * (cc & 7) + sub;
