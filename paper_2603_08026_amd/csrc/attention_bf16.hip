@@ -913,11 +913,13 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
     // stores: a wait for a cached row also waits for the stores before it, and with each row's store ahead of its sums eight of them
     // were waited for in turn.  Rows in the accumulators' order / whole, a store and a wait each / as here, us: 330 rows of 8 x 1024 tokens, 32
     // heads, one item a CU 34.2 / 35.4 / 34.4; 5200 of 16 x 1280 172 / 168 / 165; 28 over 4 heads at 7 % 52.4 / 50.2 / 49.7; 64-row tiles,
-    // 160 rows of 4 x 1024 26.9 / 27.7 / 27.2.
+    // 160 rows of 4 x 1024 26.9 / 27.7 / 27.2.  Short sweeps feel the sums themselves, which end with the wave's last row: 13 rows
+    // in each of 64 x 64 tokens 38.5 / 42 / 39.8, of 32 x 128 33.7 / 35.4 / 32.5 (all eight groups of rows 41.0 and 33.2).
     float dot_r = 0.f, na_r = 0.f, nb_r = 0.f;  // of row 4 * cc + sub (lanes with cc < 8)
     if (a.c_commit) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
+        if (wq * 32 + 4 * i >= nq) break;  // uniform: the wave's other rows do not exist
         const uint32_t nw[4] = {row[i].x, row[i].y, row[i].z, row[i].w}, ow[4] = {old[i].x, old[i].y, old[i].z, old[i].w};
         float dot = 0.f, na = 0.f, nb = 0.f;
 #pragma unroll
