@@ -578,12 +578,12 @@ __device__ __forceinline__ void attn_dma(const AttnArgs &a, const AttnItem &item
   // One tile: sixteen matrix instructions -- the P V product of tile t-1 (0 .. 7), then the score product of tile t+1 -- with
   // everything else dealt out between them, because a wave has the matrix pipe and the vector ALU to itself most of the time and
   // whatever stands in a row is time in which the other waits.  Behind products 0 .. 3: the maximum of tile t's scores, the rest of
-  // the K reads; then, rarely, the reference moves; behind 4 .. 15: tile t's exponentials (one or two to a product), their rounding
-  // and sums, and the V reads of tile t into the registers that the products release, so that they have returned long before
-  // the next barrier.  The tile's copies go out one at a time, not in a burst behind the barrier where no wave multiplies.
+  // the K reads (two wave columns: behind 4 .. 7); then, rarely, the reference moves; behind 4 .. 15: tile t's exponentials (one or
+  // two to a product), their rounding and sums, and the V reads of tile t into the registers that the products release, so that
+  // they have returned long before the next barrier.  The tile's copies go out one at a time, not in a burst behind the barrier where no wave multiplies.
   // The order is pinned with scheduling barriers.  (With groups of instructions named instead, the compiler put the first eight products
-  // back to back and the maximum, the V reads and four copies in a row before the barrier; a tile took a lone wave some 1300 cycles, now
-  // 1170, and two waves of a SIMD 1600 each.  Alone, us: dense 16 x 1280 tokens, 32 heads 486 -> 459, 1 x 1024 36.2 -> 34.1; 5200 listed rows
+  // back to back and the maximum, the V reads and four copies in a row before the barrier.  Cycles of a tile: a lone wave some 1300, now 1140
+  // to 1180; two waves of a SIMD 1600 each, now 1390 (2064 listed rows) to 1500 (dense).  Alone, us: dense 16 x 1280 tokens, 32 heads 486 -> 459, 1 x 1024 36.2 -> 34.1; 5200 listed rows
   // 169 -> 163.)
   // STEADY: the tile fetched in this iteration is a full one and no key of tile t lies past the end.
   // STAGE: the LDS stage of tile t when the caller knows it at compile time (the loop is unrolled over
@@ -996,8 +996,8 @@ __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_dma(AttnArgs a, 
 // The context update of Alg. 4 (b, the first `grid_b` workgroups) and exact rows (a), which need nothing of each other, in one launch: a
 // few hundred exact rows are 256 items that wait for their keys on half of the chip's places, and the update's last round
 // leaves places idle as well.  8 x 1024 tokens, 32 heads, 330 exact rows, us: update of a window of 2048 tokens 39 + exact rows 35 ->
-// 68, of all tokens 130 + 40 -> 143 (62 and 141 with the order of the loop pinned); a loop of such steps 3520 -> 3440.  The exact rows read through the L2, where the update sweeps
-// the same keys (past it the same within 0.6 %).
+// 68, of all tokens 130 + 40 -> 143 (62 and 141 with the order of the loop pinned); a loop of such steps 3520 -> 3440.  The exact rows
+// read through the L2, where the update sweeps the same keys (past it the same within 0.6 %).
 template <int WQ, int WK_>
 __global__ __launch_bounds__(64 * WQ * WK_, 2) void k_attn_bf16_both(AttnArgs a, int tiles_a, AttnArgs b, int tiles_b, int grid_b) {
   constexpr int BQ = DTile<WQ, WK_>::BQ;

@@ -17,7 +17,8 @@ inline void division_by(uint32_t d, uint32_t *mul, uint32_t *shift) {
 }
 
 template <int DH>
-Splits run_qkv(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made, hipStream_t s) {
+Splits run_qkv(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made,
+               hipStream_t s) {
   EpiQkv<DH> e;
   e.out = part;
   e.ldo = ga.N;

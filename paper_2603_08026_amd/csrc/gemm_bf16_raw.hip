@@ -4,8 +4,10 @@
 namespace dy {
 
 // q|k|v (gemm_bf16_qkv.hip, gemm_bf16_qkv64.hip: heads of 128 and 64 columns), or with an empty QkvOut any raw result
-Splits gemm_bf16_qkv128(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made, hipStream_t s);
-Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made, hipStream_t s);
+Splits gemm_bf16_qkv128(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made,
+                        hipStream_t s);
+Splits gemm_bf16_qkv64(const GemmArgs &ga, float *part, const QkvOut &out, const PlanArgs &pa, const GemmPlan &pl, int32_t *plan_dev, bool made,
+                       hipStream_t s);
 
 namespace {
 
@@ -70,7 +72,9 @@ Splits gemm_bf16_raw(GemmA A, Rows rows, int K, WSeg seg, float *part, size_t pa
     const bool made = job.make.words != nullptr, finishes = can_finish(qkv);
     const RawChoice c = made ? RawChoice{job.make.args, job.full, job.finishing} : choose_raw(rows, N, K, part_elems, qkv);
     if (!c.finishing) {
-      with_once(once, [&](auto o) { run_planned<RawKind<EpiStoreF32, decltype(o)::value>>(ga, EpiStoreF32{part, N}, c.pa, c.full, plan_dev, made, s); });
+      with_once(once, [&](auto o) {
+        run_planned<RawKind<EpiStoreF32, decltype(o)::value>>(ga, EpiStoreF32{part, N}, c.pa, c.full, plan_dev, made, s);
+      });
       return splits_of(ga, c.full, false, plan_dev);
     }
     if (finishes && qkv.dh == 64) return gemm_bf16_qkv64(ga, part, qkv, c.pa, c.full, plan_dev, made, s);

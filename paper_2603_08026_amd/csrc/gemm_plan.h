@@ -281,7 +281,10 @@ inline PlanArgs down_plan_args(int N, int K, size_t part_elems, bool ring, int c
   return with_stream_price(a);
 }
 // Is the plan made on the host?  When the count is known here; and for a list of up to 256 entries, one row
-// tile whatever its count: the same shapes serve, and the device's own plan costs 2 us of a GEMM and its row kernel.
+// tile whatever its count: the same shapes serve, and most steps lose by the device's plan.  Steps of one layer, lists of 256
+// entries, full / half full / 20 rows, us, planned here | on the device (ahead, in row kernels): 28 over 4 heads 205 / 176 / 142 |
+// 209 / 188 / 158; hidden 1024 68 / 62 / 54 | 73 / 72 / 64; hidden 4096 192 / 176 / 142 | 195 / 156 / 136, where few rows in much room gain;
+// 140 entries 159 / 154 / 136 | 163 / 176 / 157, 60 / 57 / 53 | 67 / 69 / 64, 161 / 152 / 137 | 164 / 145 / 135.
 inline bool plan_known(bool count_on_device, int cap) { return !count_on_device || cap <= 256; }
 // What the rows of a GEMM go through: nothing, weight-streaming tiles alone (streams: up to 128 rows, where the shape has such tiles), row tiles
 // of the ring loop by a plan, or the eight-wave shapes, which need neither

@@ -67,7 +67,10 @@ __device__ __forceinline__ RowsAndSplits rows_and_splits(const Rows &rows, const
 __device__ __forceinline__ int row_ahead(const Rows &rows, int j) { return rows.idx && j < rows.cap ? rows.idx[j] : j; }
 
 // The first workgroups of a row kernel, one for every job, make plans instead of taking rows (all NT threads, a multiple of four waves).  The
-// GEMM behind needs its plan as soon as it starts and would take 1.7 us to make it; here that happens beside the rows.  Hidden 4096: step of 410 listed rows 293 -> 285 us, of 2064 798.5 -> 796.9; loop of 8 x 1024 tokens 2004 -> 1956.
+// GEMM behind needs its plan as soon as it starts and would take 1.7 us to make it; here that happens beside the rows.  Hidden 4096,
+// steps of 410 listed rows 292.5 -> 287.4 us, of 2064 795 -> 790, loop of 8 x 1024 tokens 1991 -> 1966; 28 over 4 heads, 1137 rows equal.
+// Beside few rows the plans are what ends last: the out-projection's tail 6.8 -> 7.7 at 330 rows and 6.9 -> 8.1 at 410 (14.2 -> 14.7 at 1137,
+// 21.2 -> 20.4 at 2064), which gate|up and the down projection then gain twice over.
 template <int NT> __device__ __forceinline__ void make_plan(const PlanMaker &job) {
   __shared__ uint32_t lds[2 * NT / WAVE];  // eight words for four waves, which all make the same plan
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
@@ -78,7 +81,7 @@ template <int NT> __device__ __forceinline__ void make_plan(const PlanMaker &job
 // ---- gather + RMSNorm  [Alg. 3: layernorm(x) restricted to the salient rows] -------------------
 // NT threads per row: 256 when the row fits KEEP vectors per thread (more rows in flight per CU and a
 // four-wave reduction), else RB.
-// JOB: with a plan to make (in the kernel without, which takes known rows, its code and registers would be for nothing).
+// JOB: with a plan to make (in the kernel without, for rows whose plan is made on the host, its code and registers would be for nothing).
 // NV: vectors a thread keeps, two (rows of up to 4096 bf16 elements) or four.
 template <typename T, int NT, bool JOB, int NV>
 __global__ __launch_bounds__(NT, 8) void k_gather_rmsnorm(const T *__restrict__ x,
@@ -227,10 +230,10 @@ __global__ __launch_bounds__(RB) void k_down_finalize(const float *__restrict__ 
 // pairs of one head (two float4 of the raw result, two float4 of the table), stored four elements at a time.  Bound by the
 // HBM where the rows are many, by the two workgroups that a CU holds where they are a few hundred: the form without candidates
 // keeps to 96 scalar registers, the most with which a SIMD's 800 hold eight waves.  (The v sums two splits at a
-// time took 106, and with them one workgroup a CU.)  Listed rows, a few percent of the list's room, elements stored one at a time /
-// v sums in pairs, one workgroup a CU / as here, us: 12288 columns 330 rows 10.4 / 9.1 / 8.9, 1024 15.7 / 15.2 / 14.7, 4096 65.5 /
-// 51.6 / 51.2; 4608 columns 512 rows 6.9 / 7.0 / 5.9, 768 8.9 / 9.4 / 7.9, 2048 12.5 / 12.8 / 11.2.  Candidates (330 rows of 8192 columns)
-// 12.3 / 11.8 / 11.1.
+// time took 106, and with them one workgroup a CU.)  Rows of a list with room for 8192, elements stored one at a time / v sums in
+// pairs, one workgroup a CU / as here, us: 12288 columns 330 rows 10.4 / 9.1 / 8.9, 1024 15.7 / 15.2 / 14.7, 4096 65.5 / 51.6 / 51.2;
+// 4608 columns 512 rows 6.9 / 7.0 / 5.9, 768 8.9 / 9.4 / 7.9, 2048 12.5 / 12.8 / 11.2.  Candidates (330 rows of 8192 columns) 12.3 /
+// 11.8 / 11.1.
 // DV: with what the approximate step keeps of its candidates (CandidateOut).
 template <typename T, DvLayout DV>
 __global__ __launch_bounds__(RB) void k_qkv_finalize(const float *__restrict__ part, Splits splits_of,
@@ -551,8 +554,8 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int n) {
 // Workgroups of a row kernel.  Where the count is on the device the capacity may be far above it, and
 // workgroups without a row are not free (8192 of 1024 threads each for 330 rows: k_qkv_finalize 12.7 us, with
 // 1024 of them 11.3 us).  Of the 1024-thread ones 512 are resident at once (two per CU; of k_qkv_finalize's forms with
-// candidates, whose scalar registers allow seven waves a SIMD, 256); they take further rows in turn.  Full lists lose nothing by it: q/k/v stage at hidden 256 / 4096, 20480 listed rows, 96 -> 85 / 1937 -> 1820 us
-// together with what the GEMMs gained.
+// candidates, whose scalar registers allow seven waves a SIMD, 256); they take further rows in turn.  Full lists lose nothing by it:
+// q/k/v stage at hidden 256 / 4096, 20480 listed rows, 96 -> 85 / 1937 -> 1820 us together with what the GEMMs gained.
 constexpr int GRID_KNOWN = 8192, GRID_LISTED = 1024;
 inline int row_grid(const Rows &rows, int cap) {
   const int most = rows.count ? GRID_LISTED : GRID_KNOWN;

@@ -102,7 +102,8 @@ int main(int argc, char **argv) {
     const AttnArgs a = attn_args(ctx, ctx->qs, cache.k, cache.v, rows_of(&in, B), in.offsets, B, L, nullptr, 0);
     printf("plan bq=%d splits=%d chunk=%d\n", a.bq, a.splits, a.chunk);
   } else if (what == "down alone") {  // a GEMM whose plan nobody has made
-    launch_gemm_down(BF16, ctx->act, rows_of(&in, B), cfg.ffn_dim, cfg.hidden, w.w_down, ctx->hs, cache.out, ctx->part_o, ctx->part_elems, PlanJob{}, nullptr);
+    launch_gemm_down(BF16, ctx->act, rows_of(&in, B), cfg.ffn_dim, cfg.hidden, w.w_down, ctx->hs, cache.out, ctx->part_o, ctx->part_elems,
+                     PlanJob{}, nullptr);
   } else if (what == "up alone") {
     launch_gemm_swiglu(ctx->fs, rows_of(&in, B), cfg.hidden, cfg.ffn_dim, w.w_gate, w.w_up, ctx->act, PlanJob{}, nullptr);
   } else {

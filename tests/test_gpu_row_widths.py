@@ -45,8 +45,8 @@ def test_norm_and_projection(hidden, kv, dh, bias):
     lay.close()
 
 
-# fp32: the norm kernel runs ahead of the candidates' GEMM of the approximate step and where a result takes the place of x; one or two vectors a thread
-# (2048), up to four (2112, 4096), the wide workgroup (4160).  Sums of up to 4160 products in fp32, 2^-24 * sqrt(4160) = 4e-6 of their size: 1e-4 as
+# fp32: the norm kernel runs ahead of the candidates' GEMM of the approximate step and where a result takes the place of x; one or two
+# vectors a thread (2048), up to four (2112, 4096), the wide workgroup (4160).  Sums of up to 4160 products in fp32, 2^-24 * sqrt(4160) = 4e-6 of their size: 1e-4 as
 # everywhere.
 @pytest.mark.parametrize("hidden", [64, 2048, 2112, 4096, 4160])
 @pytest.mark.parametrize("counts", [[3, 1], [90, 61]])

@@ -30,7 +30,8 @@ def probe(tmp_path_factory):
 
 
 def launches(probe, case, cap, shape, B=3, L=900, lo=0, cached=0):
-    r = subprocess.run([probe, case] + [str(v) for v in (cap, *SHAPES.get(shape, shape), B, L, lo, cached)], capture_output=True, text=True, timeout=60)
+    args = [probe, case] + [str(v) for v in (cap, *SHAPES.get(shape, shape), B, L, lo, cached)]
+    r = subprocess.run(args, capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr
     out = []
     for line in r.stdout.splitlines():
@@ -65,7 +66,8 @@ def check(events):
 
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("cap", [100, 200, 300, 1000, 2700])
-@pytest.mark.parametrize("case,lo,cached", [("step", 0, 0), ("ffn", 0, 0), ("approx", 0, 0), ("approx", 700, 0), ("approx", 0, 1), ("approx", 700, 1)])
+@pytest.mark.parametrize("case,lo,cached", [("step", 0, 0), ("ffn", 0, 0), ("approx", 0, 0), ("approx", 700, 0), ("approx", 0, 1),
+                                            ("approx", 700, 1)])
 def test_plans_reach_their_gemms(probe, shape, cap, case, lo, cached):
     ahead = check(launches(probe, case, cap, shape, lo=lo, cached=cached))
     assert ahead == (0 if cap <= 256 else 2 if case == "ffn" else 3)
